@@ -2,7 +2,7 @@
 // (Algorithm 2, inference part, as a prefix scan over the k table slots).
 //
 // Every thread of the workgroup exponentiates its 4 consecutive slots of the
-// first 1024 (gathering the raw target logits from LDS) and the wavefront scans
+// first 1024 (of the first 4 per thread in larger workgroups; gathering the raw target logits from LDS) and the wavefront scans
 // the partial sums; after a barrier every wavefront adds the totals of the
 // wavefronts before it, compares the inclusive sums of its own slots with
 // delta * Z under the rounding margin and publishes the first slot that does
@@ -75,8 +75,8 @@ struct SlotTerms {
     unsigned skip;   // bit q: slot 4*tid+q is the token itself or beyond k
 };
 
-// All threads, before the barrier that publishes wtot / wbad.
-template <typename LT>
+// All TNT threads, before the barrier that publishes wtot / wbad.
+template <typename LT, int TNT = NT>
 __device__ __forceinline__ SlotTerms slot_terms(const int (&nb)[4], int xt, int k, int V, const int32_t* nrow,
                                                 const unsigned char* s_row, float ct, float* wtot, int* wbad) {
     using L = Lane<LT>;
@@ -99,7 +99,7 @@ __device__ __forceinline__ SlotTerms slot_terms(const int (&nb)[4], int xt, int 
         run += e;
         st.incl[q] = run;
     }
-    for (int j = NT * 4 + tid; j < k; j += NT)     // entries the walk may never reach are range-checked too
+    for (int j = TNT * 4 + tid; j < k; j += TNT)   // entries the walk may never reach are range-checked too
         if ((unsigned)nrow[j] >= (unsigned)V) bad = 1;
     const float incl = wave_scan_incl(run);
     st.excl = wave_prev(incl, 0.f);
@@ -153,9 +153,10 @@ __device__ __forceinline__ void classify_slots(const SlotTerms& st, const SlotTe
     }
 }
 
-// Slots beyond the first 1024, walked by one wavefront 1024 at a time (k > 1024 and no cut among
-// the first 1024).  carry: the sum over the first 1024 slots.  The result has the meaning of the combined per-wavefront results.
-template <typename LT>
+// Slots beyond the first 4 TNT (four per thread), walked by one wavefront 1024 at a time (k > 4 TNT
+// and no cut before).  carry: the sum over the slots before.  The result has the meaning of the
+// combined per-wavefront results.
+template <typename LT, int TNT = NT>
 __device__ __forceinline__ CutResult walk_tail(const SlotTest& test, float carry, int xt, int xs, int k, int V,
                                                const int32_t* knn, const unsigned char* s_row, float ct) {
     using L = Lane<LT>;
@@ -163,7 +164,7 @@ __device__ __forceinline__ CutResult walk_tail(const SlotTest& test, float carry
     const int32_t* nrow = knn + (int64_t)xs * k;
     int first_np = INT_MAX, first_df = INT_MAX, bad = 0;
     float s_cut = 0.f;
-    for (int base = NT * 4; base < k; base += WAVE * SPL) {
+    for (int base = TNT * 4; base < k; base += WAVE * SPL) {
         const int j0 = base + lane * SPL;
         float ev[SPL];
         float run = 0.f;

@@ -13,9 +13,9 @@
 //               (ambiguous comparison, unusable input, a rejected row whose
 //               resampled token is wanted) re-evaluates it: same rule, then
 //               the residual and its inverse CDF.
-// Shapes the fast path does not cover (rows not 16-byte aligned, V not a
-// multiple of the vector width, rows beyond the register budget) run the
-// exact path for every row (kernel verify_exact).
+// The fast path takes any row of 16 bytes up to 128 KiB, at any address: 256, 512 or
+// 1024 threads per row.  Other shapes (and diagnostics of rows that are not 16-byte
+// aligned whole vectors) run the exact path for every row (kernel verify_exact).
 // Three modes (verify_args.h): decisions and resampled tokens; decisions only;
 // the fp64 path for selected verifications in 512-thread workgroups
 // (resample_selected, and tree_finish, which first walks its draft tree).
@@ -37,25 +37,22 @@
 namespace lantern {
 
 // LDS layout of verify_fast after the raw row
+template <int TNW>
 struct FastShared {
-    float wmax_t[NW], wmax_g[NW];   // per-wave maxima over the sampled part of the row
-    float wsum_t[NW], wsum_g[NW];   // per-wave sums of exponentials
-    float wtot[NW];                 // per-wave totals of the neighbour terms (first 1024 slots)
-    int wbad[NW];                   // a table entry outside [0,V)
-    int cut_np[NW];                 // per wavefront: first slot not definitely inside the bound,
-    int cut_df[NW];                 //   first slot definitely outside it,
-    float cut_s[NW];                //   sum before the former
-    int tail[4];                    // k > 1024: the result of the walk beyond slot 1024 (a_size, S, definite, bad)
-    // from here on the memory is reused by the exact path once the fp32 decision is taken
-    float gs[NT * 4];               // inclusive sums of the neighbour terms within their wavefront
-    unsigned gskip[NT];             // bit q: slot 4*tid+q is the token itself or beyond k
-};
-constexpr size_t FAST_SHARED_HEAD = offsetof(FastShared, gs);
-constexpr size_t FAST_SHARED_TAIL = sizeof(FastShared) - FAST_SHARED_HEAD;
-static_assert(FAST_SHARED_HEAD % 16 == 0, "the exact path's LDS region must be 16-byte aligned");
+    float wmax_t[TNW], wmax_g[TNW]; // per-wave maxima over the sampled part of the row
+    float wsum_t[TNW], wsum_g[TNW]; // per-wave sums of exponentials
+    float wtot[TNW];                // per-wave totals of the neighbour terms (first four slots per thread)
+    int wbad[TNW];                  // a table entry outside [0,V)
+    int cut_np[TNW];                // per wavefront: first slot not definitely inside the bound,
+    int cut_df[TNW];                //   first slot definitely outside it,
+    float cut_s[TNW];               //   sum before the former
+    int tail[4];                    // longer table rows: the result of the walk beyond those slots (a_size, S, definite, bad)
+};                                  // followed by the exact path's region
+static_assert(sizeof(FastShared<4>) % 16 == 0 && sizeof(FastShared<8>) % 16 == 0 && sizeof(FastShared<16>) % 16 == 0,
+              "the exact path's LDS region must be 16-byte aligned");
 
 template <typename LT, bool VEC, int TNT = NT>
-__device__ void exact_row(const VerifyArgs& a, int row, unsigned char* ex, const unsigned char* lds_row,
+__device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned char* ex, const unsigned char* lds_row,
                           bool have_max, float max_t, float max_g, const unsigned char* lds_grow = nullptr);
 
 // ---------------------------------------------------------------------------
@@ -93,11 +90,11 @@ struct OnePassLayout {
 // The exponential's table sits at the very start of the workgroup's LDS (before the row): the
 // address of a lookup is then the masked integer itself, with no base to add.
 constexpr int EXP_TABLE_BYTES = 2 * EXP_TABLE_N * (int)sizeof(double);
-__host__ __device__ inline OnePassLayout one_pass_layout(int V) {
+__host__ __device__ inline OnePassLayout one_pass_layout(int V, int threads) {
     OnePassLayout L;
     size_t off = (sizeof(ExactShared) + 15) & ~size_t(15);
     L.mask = off;      off += (((size_t)V + 31) / 32) * 4;  off = (off + 15) & ~size_t(15);
-    L.seg = off;       off += 16 * NW * 2 * sizeof(double);           // up to 16 vector chunks per thread
+    L.seg = off;       off += 8 * (threads / WAVE) * 2 * sizeof(double);   // up to 8 vector chunks per thread
     L.amb = off;       off += AMB_CAP * sizeof(AmbEntry);
     L.amb_count = off; off += 16;
     L.total = off;
@@ -160,22 +157,24 @@ __device__ __forceinline__ void one_pass_token(OnePassAcc& acc, float lt, float 
 // nb: table slots 4*tid .. 4*tid+3.  ref_t, ref_g: the fp32 pass's reference logits; Zt32, Zg32:
 // its sums; a_size: its (definite) cut.
 // tab_lds: where the exponential's table goes in LDS.
-template <typename LT, int NV, bool FULL>
-__device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int lrow,
+// Returns false (the same in every thread) when the row is left to the general path.
+template <typename LT, int TNT, int NV, bool FULL>
+__device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int lrow,
                                                const int (&nb)[4], float ref_t, float ref_g,
                                                float Zt32, float Zg32, int a_size, int xt, float lg_tok, float u_acc32,
                                                unsigned char* tab_lds, unsigned char* ex,
                                                const unsigned char* s_row) {
     using L = Lane<LT>;
     constexpr int EPV = L::EPV;
-    constexpr int NSEG = NV * NW;                            // at most 64: one wavefront scans them
+    constexpr int TNW = TNT / WAVE;
+    constexpr int NSEG = NV * TNW;                           // one wavefront scans them, 64 at a time
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
     const int wave = tid >> 6;
     const int V = a.V;
     const int k = a.k;
-    const int nvec = V / EPV;
-    const OnePassLayout lay = one_pass_layout(V);
+    const int nvec = (V + EPV - 1) / EPV;                    // the last one padded with -inf (in LDS as well)
+    const OnePassLayout lay = one_pass_layout(V, TNT);
     ExactShared& sh = *reinterpret_cast<ExactShared*>(ex);
     uint32_t* mask = reinterpret_cast<uint32_t*>(ex + lay.mask);
     double* seg = reinterpret_cast<double*>(ex + lay.seg);
@@ -186,18 +185,25 @@ __device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int
     const double rt = (double)ref_t, rg = (double)ref_g;
     const float u_res32 = a.uniforms[2 * (int64_t)row + 1];  // in flight during the pass
     // the drafter's row, every load issued now; it arrives while the table and the mask are set up
-    const uint4* gsrc = reinterpret_cast<const uint4*>(reinterpret_cast<const LT*>(a.draft) + (int64_t)lrow * a.stride);
+    const LT* grow = reinterpret_cast<const LT*>(a.draft) + (int64_t)lrow * a.stride;
+    auto draft_vector = [&](int vi) {
+        if (FULL) return reinterpret_cast<const uint4*>(grow)[vi];
+        return row_vector_finish<LT, EPV>(load16_any(row_vector_address<LT, EPV>(grow, vi, V)), vi, V, L::NEG_INF_WORD);
+    };
     uint4 G[NV];
 #pragma unroll
     for (int c = 0; c < NV; ++c) {
-        const int vi = c * NT + tid;
-        G[c] = (FULL || vi < nvec) ? gsrc[vi]
-                                   : make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
+        const int vi = c * TNT + tid;
+        G[c] = FULL ? draft_vector(vi) : load16_any(row_vector_address<LT, EPV>(grow, vi, V));
+    }
+    if (!FULL) {
+#pragma unroll
+        for (int c = 0; c < NV; ++c) G[c] = row_vector_finish<LT, EPV>(G[c], c * TNT + tid, V, L::NEG_INF_WORD);
     }
 
     // ---- table of the exponential, empty mask, empty list ----
-    tab[tid] = EXP_TABLE_HILO[tid];                          // 2 * 128 doubles, one per thread (cache-resident)
-    for (int w = tid; w < nwords; w += NT) mask[w] = 0u;
+    if (tid < 2 * EXP_TABLE_N) tab[tid] = EXP_TABLE_HILO[tid];   // 2 * 128 doubles (cache-resident)
+    for (int w = tid; w < nwords; w += TNT) mask[w] = 0u;
     if (tid == 0) *amb_count = 0;
     __syncthreads();
 
@@ -211,9 +217,9 @@ __device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int
             atomicOr(&mask[n >> 5], 1u << (n & 31));
         }
     }
-    if (a_size > NT * 4) {
+    if (a_size > TNT * 4) {
         const int32_t* nrow = a.knn + (int64_t)xt * k;
-        for (int j = NT * 4 + tid; j < a_size; j += NT) {
+        for (int j = TNT * 4 + tid; j < a_size; j += TNT) {
             const int n = nrow[j];
             if (n != xt) {
                 s_loc += exp_tab((double)L::lds(s_row, n) - rt, tab);
@@ -221,7 +227,7 @@ __device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int
             }
         }
     }
-    const double S = block_sum<NW>(s_loc, sh.red, tid);      // its barriers also publish the mask
+    const double S = block_sum<TNW>(s_loc, sh.red, tid);     // its barriers also publish the mask
     const double e_tx = exp_tab((double)L::lds(s_row, xt) - rt, tab);
     const double e_gx = exp_tab((double)lg_tok - rg, tab);
 
@@ -247,7 +253,7 @@ __device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int
         uint4 gv = G[0];
 #pragma unroll
         for (int i = 0; i + 1 < NV; ++i) G[i] = G[i + 1];
-        const int vi = c * NT + tid;
+        const int vi = c * TNT + tid;
         const bool live = FULL || vi < nvec;
         uint4 tv = live ? reinterpret_cast<const uint4*>(s_row)[vi]
                         : make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
@@ -271,12 +277,12 @@ __device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int
         const double pt = wave_sum_dpp(acc.pt);
         const double pg = wave_sum_dpp(acc.pg);
         if (lane == 0) {
-            seg[2 * (c * NW + wave)] = pt;
-            seg[2 * (c * NW + wave) + 1] = pg;
+            seg[2 * (c * TNW + wave)] = pt;
+            seg[2 * (c * TNW + wave) + 1] = pg;
         }
     }
-    const double zt = block_sum<NW>(acc.zt, sh.red, tid);
-    const double zg = block_sum<NW>(acc.zg, sh.red2, tid);  // its barriers publish seg and the list
+    const double zt = block_sum<TNW>(acc.zt, sh.red, tid);
+    const double zg = block_sum<TNW>(acc.zg, sh.red2, tid); // its barriers publish seg and the list
 
     // ---- decision ----
     const double mass = (e_tx + S) / zt;
@@ -296,32 +302,59 @@ __device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int
             a.out_resample[row] = -1;
         }
     }
-    if (accepted) return;
+    if (accepted) return true;
 
     // ---- rejected: residual mass per segment (segments in token order), the one that holds the draw ----
     const int n_amb = *amb_count;
     const double inv_zt = 1.0 / zt, inv_zg = 1.0 / zg;
     if (wave == 0) {
-        double r = 0.0;
-        if (lane < NSEG) {
-            r = seg[2 * lane] * inv_zt - seg[2 * lane + 1] * inv_zg;
-            r = r > 0.0 ? r : 0.0;
-            for (int i = 0; i < n_amb && i < AMB_CAP; ++i) {
-                const int v = amb[i].x / EPV;               // vector of the token: chunk v / NT, thread v % NT
-                if ((v / NT) * NW + ((v % NT) >> 6) == lane) {
-                    const double d = amb[i].et * inv_zt - amb[i].eg * inv_zg;
-                    r += d > 0.0 ? d : 0.0;
+        constexpr int NB = (NSEG + WAVE - 1) / WAVE;
+        double incl[NB], mass_in[NB], Z = 0.0;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int s = b * WAVE + lane;
+            double r = 0.0;
+            if (s < NSEG) {
+                r = seg[2 * s] * inv_zt - seg[2 * s + 1] * inv_zg;
+                r = r > 0.0 ? r : 0.0;
+                for (int i = 0; i < n_amb && i < AMB_CAP; ++i) {
+                    const int v = amb[i].x / EPV;           // vector of the token: chunk v / TNT, thread v % TNT
+                    if ((v / TNT) * TNW + ((v % TNT) >> 6) == s) {
+                        const double d = amb[i].et * inv_zt - amb[i].eg * inv_zg;
+                        r += d > 0.0 ? d : 0.0;
+                    }
+                }
+            }
+            mass_in[b] = r;
+            incl[b] = Z + wave_scan_incl(r);
+            Z = lane63_d(incl[b]);
+        }
+        const double cthr = (double)u_res32 * Z;
+        int s = -1, last = 0;
+        double before = 0.0;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const unsigned long long cross = __ballot(b * WAVE + lane < NSEG && incl[b] > cthr);
+            const unsigned long long has = __ballot(mass_in[b] > 0.0);
+            if (s < 0 && cross) {
+                const int l = __ffsll((long long)cross) - 1;
+                s = b * WAVE + l;
+                if (l) before = __shfl(incl[b], l - 1, WAVE);
+                else if (b) before = lane63_d(incl[b > 0 ? b - 1 : 0]);
+                else before = 0.0;
+            }
+            if (has) last = b * WAVE + 63 - __clzll((long long)has);
+        }
+        if (s < 0) {   // rounding can leave no crossing: the last segment that holds mass takes the draw
+            s = last;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if (s / WAVE == b) {
+                    const int l = s % WAVE;
+                    before = l ? __shfl(incl[b], l - 1, WAVE) : (b ? lane63_d(incl[b > 0 ? b - 1 : 0]) : 0.0);
                 }
             }
         }
-        const double incl = wave_scan_incl(r);
-        const double Z = __shfl(incl, WAVE - 1, WAVE);
-        const double cthr = (double)u_res32 * Z;
-        const unsigned long long cross = __ballot(lane < NSEG && incl > cthr);
-        const unsigned long long has = __ballot(r > 0.0);
-        // rounding can leave no crossing: the last segment that holds mass takes the draw
-        const int s = cross ? (__ffsll((long long)cross) - 1) : (has ? 63 - __clzll((long long)has) : 0);
-        const double before = s ? __shfl(incl, s - 1, WAVE) : 0.0;
         if (lane == 0) {
             sh.bcast[0] = before;
             sh.bcast[1] = cthr;
@@ -333,18 +366,17 @@ __device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int
     // a list that overflowed, or a residual without mass (by rounding): the general path
     // (uniform over the workgroup)
     if (n_amb > AMB_CAP || !(sh.bcast[2] > 0.0)) {
-        __syncthreads();
-        exact_row<LT, true>(a, row, ex, s_row, false, 0.f, 0.f);
-        return;
+        __syncthreads();   // the general path reuses this LDS
+        return false;
     }
     const int ent = sh.ibcast[0];
-    if (wave == (ent % NW)) {
+    if (wave == (ent % TNW)) {
         const double P = sh.bcast[0], cthr = sh.bcast[1];
-        const int vi = (ent / NW) * NT + tid;
+        const int vi = (ent / TNW) * TNT + tid;
         const int x0 = vi * EPV;
         const bool live = FULL || vi < nvec;
         const uint4 ninf = make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
-        const uint4 gv = live ? gsrc[vi] : ninf;             // this segment of the drafter's row, once more
+        const uint4 gv = draft_vector(vi);                   // this segment of the drafter's row, once more
         const uint4 tv = live ? reinterpret_cast<const uint4*>(s_row)[vi] : ninf;
         const unsigned in_a = live ? (mask[x0 >> 5] >> (x0 & 31)) & ((1u << EPV) - 1u) : 0u;
         double r[EPV];
@@ -380,12 +412,12 @@ __device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int
             // no token of the segment holds mass: its mass was rounding noise of the sums (it takes a
             // draw within ~1e-16 of a segment edge).  The first token after it that holds mass is
             // the one the cumulative sum reaches next; failing that, the last one before it.
-            const int seg_x0 = ((ent / NW) * NT + (ent % NW) * WAVE) * EPV;   // first token of the segment
+            const int seg_x0 = ((ent / TNW) * TNT + (ent % TNW) * WAVE) * EPV;   // first token of the segment
             int before = -1, after = INT_MAX;
             for (int v0 = 0; v0 < nvec; v0 += WAVE) {
                 const int v = v0 + lane;
                 const bool lv = v < nvec;
-                const uint4 gq = lv ? gsrc[v] : ninf;
+                const uint4 gq = draft_vector(lv ? v : nvec - 1);
                 const uint4 tq = lv ? reinterpret_cast<const uint4*>(s_row)[v] : ninf;
                 const unsigned ia = lv ? (mask[(v * EPV) >> 5] >> ((v * EPV) & 31)) & ((1u << EPV) - 1u) : 0u;
                 int first = INT_MAX, last = -1;
@@ -407,6 +439,7 @@ __device__ __forceinline__ void exact_one_pass(const VerifyArgs& a, int row, int
             a.out_resample[row] = found;
         }
     }
+    return true;
 }
 
 // Per-row scalars and table slots, fetched together with the row.
@@ -418,7 +451,9 @@ struct RowMeta {
 };
 
 // fp32 path, one workgroup per row.
-// FULL: the row fills all NV vector slots of every thread (no bounds checks).
+// TNT threads, NV 16-byte vectors per thread and row.
+// FULL: rows are 16-byte aligned and fill all NV vector slots of every thread (no bounds checks);
+// otherwise they may start at any element and have any length of at least one vector.
 // VT: the token's table row can be read with 16-byte loads (k a multiple of four, table 16-byte
 // aligned); the other case is a kernel of its own because a load that only one of two paths
 // issues makes the hardware wait counters, which are placed statically, wait for every load.
@@ -429,22 +464,23 @@ struct RowMeta {
 // rather than the row maximum: any element of the row works, because the sum then holds
 // a term equal to one (Z >= 1) and every term is at most Z; rows whose sum exceeds 2^46
 // (an element more than 32 above the reference) are left to the exact path.
-template <typename LT, int NV, bool FULL, bool VT>
-__global__ __launch_bounds__(NT, (NV <= 8 ? 4 : 2)) void verify_fast(VerifyArgs a) {
+template <typename LT, int TNT, int NV, bool FULL, bool VT>
+__global__ __launch_bounds__(TNT, 4) void verify_fast(VerifyArgs a) {
     using L = Lane<LT>;
     constexpr int EPV = L::EPV;
+    constexpr int TNW = TNT / WAVE;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* s_row = smem + EXP_TABLE_BYTES;           // the fp64 path's table goes in front
     const int row_bytes = (a.V * (int)sizeof(LT) + 15) & ~15;
-    FastShared& sh = *reinterpret_cast<FastShared*>(s_row + row_bytes);
-    unsigned char* ex_lds = reinterpret_cast<unsigned char*>(sh.gs);
+    FastShared<TNW>& sh = *reinterpret_cast<FastShared<TNW>*>(s_row + row_bytes);
+    unsigned char* ex_lds = s_row + row_bytes + sizeof(FastShared<TNW>);
 
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
     const int wave = tid >> 6;
     const int V = a.V;
     const int k = a.k;
-    const int nvec = V / EPV;
+    const int nvec = (V + EPV - 1) / EPV;
     const int row = verification_of_block(blockIdx.x, a.N, a.row_index != nullptr);
     bool row_ok;
     const int lrow = logit_row(a.row_index, a.R, row, &row_ok);
@@ -459,17 +495,17 @@ __global__ __launch_bounds__(NT, (NV <= 8 ? 4 : 2)) void verify_fast(VerifyArgs 
     // stream both rows: NV 16-byte loads per thread and row, coalesced
     uint4 T[NV], G[NV];
     {
-        const uint4* tv = reinterpret_cast<const uint4*>(reinterpret_cast<const LT*>(a.target) + (int64_t)lrow * a.stride);
-        const uint4* gv = reinterpret_cast<const uint4*>(reinterpret_cast<const LT*>(a.draft) + (int64_t)lrow * a.stride);
+        const LT* trow = reinterpret_cast<const LT*>(a.target) + (int64_t)lrow * a.stride;
+        const LT* grow = reinterpret_cast<const LT*>(a.draft) + (int64_t)lrow * a.stride;
 #pragma unroll
         for (int c = 0; c < NV; ++c) {
-            const int vi = c * NT + tid;
-            if (FULL || vi < nvec) {
-                T[c] = load_stream16(tv + vi);
-                G[c] = load_stream16(gv + vi);
+            const int vi = c * TNT + tid;
+            if (FULL) {
+                T[c] = load_stream16(reinterpret_cast<const uint4*>(trow) + vi);
+                G[c] = load_stream16(reinterpret_cast<const uint4*>(grow) + vi);
             } else {
-                T[c] = make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
-                G[c] = T[c];
+                T[c] = load_stream16_any(row_vector_address<LT, EPV>(trow, vi, V));
+                G[c] = load_stream16_any(row_vector_address<LT, EPV>(grow, vi, V));
             }
         }
     }
@@ -486,7 +522,7 @@ __global__ __launch_bounds__(NT, (NV <= 8 ? 4 : 2)) void verify_fast(VerifyArgs 
             m.nb[0] = q.x; m.nb[1] = q.y; m.nb[2] = q.z; m.nb[3] = q.w;
         } else {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) m.nb[q] = (j0 + q < k) ? nrow[j0 + q] : 0;
+            for (int q = 0; q < 4; ++q) m.nb[q] = nrow[min(j0 + q, k - 1)];
         }
         m.lg_tok = L::glob(reinterpret_cast<const LT*>(a.draft) + (int64_t)lrow * a.stride, xs0);
     }
@@ -501,7 +537,11 @@ __global__ __launch_bounds__(NT, (NV <= 8 ? 4 : 2)) void verify_fast(VerifyArgs 
         // ---- raw target row to LDS; reference = maximum over vector slot 0 of every thread ----
 #pragma unroll
         for (int c = 0; c < NV; ++c) {
-            const int vi = c * NT + tid;
+            const int vi = c * TNT + tid;
+            if (!FULL) {
+                T[c] = row_vector_finish<LT, EPV>(T[c], vi, V, L::NEG_INF_WORD);
+                G[c] = row_vector_finish<LT, EPV>(G[c], vi, V, L::NEG_INF_WORD);
+            }
             if (FULL || vi < nvec) reinterpret_cast<uint4*>(s_row)[vi] = T[c];
         }
         float rt = neg_inf_f(), rg = neg_inf_f();
@@ -517,7 +557,7 @@ __global__ __launch_bounds__(NT, (NV <= 8 ? 4 : 2)) void verify_fast(VerifyArgs 
         rt = sh.wmax_t[0];
         rg = sh.wmax_g[0];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) {
+        for (int w = 1; w < TNW; ++w) {
             rt = fmaxf(rt, sh.wmax_t[w]);
             rg = fmaxf(rg, sh.wmax_g[w]);
         }
@@ -531,27 +571,29 @@ __global__ __launch_bounds__(NT, (NV <= 8 ? 4 : 2)) void verify_fast(VerifyArgs 
         float st = 0.f, sg = 0.f;
 #pragma unroll
         for (int c = 0; c < NV; ++c) {
-            float et[EPV], eg[EPV];
+            if (FULL || c * TNT < nvec) {                    // uniform; else nothing of the row in this chunk
+                float et[EPV], eg[EPV];
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) {
-                et[e] = hw_exp2(__builtin_fmaf(L::get(T[c], e), LOG2E_F, -ct));
-                eg[e] = hw_exp2(__builtin_fmaf(L::get(G[c], e), LOG2E_F, -cg));
-            }
-#pragma unroll
-            for (int s = EPV / 2; s > 0; s >>= 1)
-#pragma unroll
-                for (int e = 0; e < s; ++e) {
-                    et[e] += et[e + s];
-                    eg[e] += eg[e + s];
+                for (int e = 0; e < EPV; ++e) {
+                    et[e] = hw_exp2(__builtin_fmaf(L::get(T[c], e), LOG2E_F, -ct));
+                    eg[e] = hw_exp2(__builtin_fmaf(L::get(G[c], e), LOG2E_F, -cg));
                 }
-            st += et[0];
-            sg += eg[0];
+#pragma unroll
+                for (int s = EPV / 2; s > 0; s >>= 1)
+#pragma unroll
+                    for (int e = 0; e < s; ++e) {
+                        et[e] += et[e + s];
+                        eg[e] += eg[e + s];
+                    }
+                st += et[0];
+                sg += eg[0];
+            }
         }
         st = wave_sum(st);
         sg = wave_sum(sg);
 
         // ---- neighbour terms of slots 4*tid .. 4*tid+3, scanned within the wavefront ----
-        const SlotTerms slots = slot_terms<LT>(m.nb, xt, k, V, a.knn + (int64_t)xs * k, s_row, ct, sh.wtot, sh.wbad);
+        const SlotTerms slots = slot_terms<LT, TNT>(m.nb, xt, k, V, a.knn + (int64_t)xs * k, s_row, ct, sh.wtot, sh.wbad);
         if (lane == 0) { sh.wsum_t[wave] = st; sh.wsum_g[wave] = sg; }
         __syncthreads();  // sums and wavefront totals of the neighbour terms are published
 
@@ -559,7 +601,7 @@ __global__ __launch_bounds__(NT, (NV <= 8 ? 4 : 2)) void verify_fast(VerifyArgs 
         float Zt = 0.f, Zg = 0.f, woff = 0.f, run_off = 0.f;
         int bad = (tok_ok && row_ok) ? 0 : 1;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
+        for (int w = 0; w < TNW; ++w) {
             Zt += sh.wsum_t[w];
             Zg += sh.wsum_g[w];
             if (w < wave) woff += sh.wtot[w];
@@ -582,16 +624,16 @@ __global__ __launch_bounds__(NT, (NV <= 8 ? 4 : 2)) void verify_fast(VerifyArgs 
         int first_np = INT_MAX, first_df = INT_MAX;
         float s_cut = 0.f;
 #pragma unroll
-        for (int w = NW - 1; w >= 0; --w) {
+        for (int w = TNW - 1; w >= 0; --w) {
             if (sh.cut_np[w] != INT_MAX) { first_np = sh.cut_np[w]; s_cut = sh.cut_s[w]; }
             first_df = min(first_df, sh.cut_df[w]);
         }
         bool cut_definite = (first_np == INT_MAX) || (first_np == first_df);
         int a_size = (first_np == INT_MAX) ? k : first_np;
         float S = (first_np == INT_MAX) ? run_off : s_cut;
-        if (first_np == INT_MAX && k > NT * 4) {      // uniform: the walk goes on beyond slot 1024
+        if (first_np == INT_MAX && k > TNT * 4) {     // uniform: the walk goes on beyond four slots per thread
             if (wave == 0) {
-                const CutResult tail = walk_tail<LT>(test, run_off, xt, xs, k, V, a.knn, s_row, ct);
+                const CutResult tail = walk_tail<LT, TNT>(test, run_off, xt, xs, k, V, a.knn, s_row, ct);
                 if (lane == 0) {
                     sh.tail[0] = tail.a_size;
                     sh.tail[1] = __float_as_int(tail.S);
@@ -632,12 +674,12 @@ __global__ __launch_bounds__(NT, (NV <= 8 ? 4 : 2)) void verify_fast(VerifyArgs 
             // not settled in fp32: this workgroup evaluates the row in fp64; the raw target row stays in
             // LDS.  With the resampled token wanted, a usable row with a definite cut is finished in one
             // pass from the registers.
-            if (!bad && sums_ok && cut_definite && a.mode == VERIFY_FULL) {
-                exact_one_pass<LT, NV, FULL>(a, row, lrow, m.nb, rt, rg, Zt, Zg, a_size, xt, m.lg_tok, m.u_acc,
-                                             smem, ex_lds, s_row);
-            } else {
-                exact_row<LT, true>(a, row, ex_lds, s_row, false, 0.f, 0.f);
-            }
+            bool done = false;
+            if (!bad && sums_ok && cut_definite && a.mode == VERIFY_FULL)
+                done = exact_one_pass<LT, TNT, NV, FULL>(a, row, lrow, m.nb, rt, rg, Zt, Zg, a_size, xt, m.lg_tok,
+                                                         m.u_acc, smem, ex_lds, s_row);
+            // one call, so that it is inlined: as a function its argument block goes through memory
+            if (!done) exact_row<LT, FULL, TNT>(a, row, ex_lds, s_row, false, 0.f, 0.f);
         }
     }
 }
@@ -682,7 +724,7 @@ __device__ __forceinline__ double resid_term(int x, int xt, int V, float lt, flo
 // wavefront, lane, element) is ascending token order.  Every pass over the row
 // loads the next chunk's vectors before it works on the current one.
 template <typename LT, bool VEC, int TNT>
-__device__ void exact_row(const VerifyArgs& a, int row, unsigned char* ex, const unsigned char* lds_row,
+__device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned char* ex, const unsigned char* lds_row,
                           bool have_max, float max_t, float max_g, const unsigned char* lds_grow) {
     constexpr int TNW = TNT / WAVE;
     const bool selected = a.mode == VERIFY_SELECTED;
@@ -1011,66 +1053,82 @@ __global__ __launch_bounds__(SEL_NT) void tree_finish(VerifyArgs a, const int32_
 // host-side launch
 // ---------------------------------------------------------------------------
 
-// Dynamic LDS of verify_fast: raw row, the head of FastShared, then a region that holds either
-// the neighbour partial sums or the exact path's data.
+// Dynamic LDS of verify_fast: raw row, reductions, then the exact paths' region.
 template <typename LT>
-static size_t fast_lds_bytes(int V) {
+static size_t fast_lds_bytes(int V, int threads) {
     const size_t row_bytes = ((size_t)V * sizeof(LT) + 15) & ~size_t(15);
-    size_t tail = exact_lds_bytes(V) > FAST_SHARED_TAIL ? exact_lds_bytes(V) : FAST_SHARED_TAIL;
-    const size_t one_pass = one_pass_layout(V).total;
-    if (one_pass > tail) tail = one_pass;
-    return EXP_TABLE_BYTES + row_bytes + FAST_SHARED_HEAD + tail;
+    const size_t head = threads == 256 ? sizeof(FastShared<4>) : threads == 512 ? sizeof(FastShared<8>) : sizeof(FastShared<16>);
+    const size_t one_pass = one_pass_layout(V, threads).total;
+    const size_t exact = exact_lds_bytes(V, threads);
+    return EXP_TABLE_BYTES + row_bytes + head + (one_pass > exact ? one_pass : exact);
+}
+
+// Rows of 16-byte aligned whole vectors, stride included.
+template <typename LT>
+static bool whole_vectors(const VerifyArgs& a) {
+    const uintptr_t align = reinterpret_cast<uintptr_t>(a.target) | reinterpret_cast<uintptr_t>(a.draft) |
+                            (uintptr_t)(a.stride * (int64_t)sizeof(LT));
+    return (align & 15) == 0 && a.V % Lane<LT>::EPV == 0;
 }
 
 // launch == false: only the LDS limits are raised (lantern_prepare), nothing is enqueued.
-template <typename LT, int NV>
+template <typename LT, int TNT, int NV>
 static hipError_t launch_fast_nv(const VerifyArgs& a, hipStream_t stream, bool launch) {
-    const size_t lds = fast_lds_bytes<LT>(a.V);
-    const bool full = a.V == NV * NT * Lane<LT>::EPV;
-    // three instantiations: whole rows with a vector-readable table, ragged rows with one, and the rest
+    const size_t lds = fast_lds_bytes<LT>(a.V, TNT);
+    const bool full = a.V == NV * TNT * Lane<LT>::EPV && whole_vectors<LT>(a);
+    // three instantiations: whole rows with a vector-readable table, other rows with one, and the rest
     const bool vt = ((a.k & 3) == 0) && ((reinterpret_cast<uintptr_t>(a.knn) & 15) == 0);
     if (!launch) {   // every one of them may be needed later
-        hipError_t e = allow_lds<&verify_fast<LT, NV, true, true>>(lds);
-        if (e == hipSuccess) e = allow_lds<&verify_fast<LT, NV, false, true>>(lds);
-        if (e == hipSuccess) e = allow_lds<&verify_fast<LT, NV, false, false>>(lds);
+        hipError_t e = allow_lds<&verify_fast<LT, TNT, NV, true, true>>(lds);
+        if (e == hipSuccess) e = allow_lds<&verify_fast<LT, TNT, NV, false, true>>(lds);
+        if (e == hipSuccess) e = allow_lds<&verify_fast<LT, TNT, NV, false, false>>(lds);
         return e;
     }
-    const hipError_t e = (full && vt) ? allow_lds<&verify_fast<LT, NV, true, true>>(lds)
-                         : vt         ? allow_lds<&verify_fast<LT, NV, false, true>>(lds)
-                                      : allow_lds<&verify_fast<LT, NV, false, false>>(lds);
+    const hipError_t e = (full && vt) ? allow_lds<&verify_fast<LT, TNT, NV, true, true>>(lds)
+                         : vt         ? allow_lds<&verify_fast<LT, TNT, NV, false, true>>(lds)
+                                      : allow_lds<&verify_fast<LT, TNT, NV, false, false>>(lds);
     if (e != hipSuccess) return e;
     if (full && vt)
-        hipLaunchKernelGGL((verify_fast<LT, NV, true, true>), dim3(a.N), dim3(NT), lds, stream, a);
+        hipLaunchKernelGGL((verify_fast<LT, TNT, NV, true, true>), dim3(a.N), dim3(TNT), lds, stream, a);
     else if (vt)
-        hipLaunchKernelGGL((verify_fast<LT, NV, false, true>), dim3(a.N), dim3(NT), lds, stream, a);
+        hipLaunchKernelGGL((verify_fast<LT, TNT, NV, false, true>), dim3(a.N), dim3(TNT), lds, stream, a);
     else
-        hipLaunchKernelGGL((verify_fast<LT, NV, false, false>), dim3(a.N), dim3(NT), lds, stream, a);
+        hipLaunchKernelGGL((verify_fast<LT, TNT, NV, false, false>), dim3(a.N), dim3(TNT), lds, stream, a);
     return hipGetLastError();
 }
 
+// Up to 8 vectors per thread and row stay in registers; the number of threads follows from that, so a
+// longer row takes a larger workgroup (V = 65536 bf16, 960 rows of which 45 % are rejected: 230 us with
+// 1024 threads against 527 us on the fp64 path that such rows took before; 960 rows of 8192 bf16 logits
+// at addresses not aligned to 16 bytes: 35 us against 68 us).
 template <typename LT>
 static hipError_t launch_fast(const VerifyArgs& a, hipStream_t stream, bool launch) {
-    const int nvec = a.V / Lane<LT>::EPV;
+    const int nvec = (a.V + Lane<LT>::EPV - 1) / Lane<LT>::EPV;
     const int nv = (nvec + NT - 1) / NT;
-    if (nv <= 1) return launch_fast_nv<LT, 1>(a, stream, launch);
-    if (nv <= 2) return launch_fast_nv<LT, 2>(a, stream, launch);
-    if (nv <= 4) return launch_fast_nv<LT, 4>(a, stream, launch);
-    if (nv <= 8) return launch_fast_nv<LT, 8>(a, stream, launch);
-    return launch_fast_nv<LT, 16>(a, stream, launch);
+    if (nv <= 1) return launch_fast_nv<LT, 256, 1>(a, stream, launch);
+    if (nv <= 2) return launch_fast_nv<LT, 256, 2>(a, stream, launch);
+    if (nv <= 4) return launch_fast_nv<LT, 256, 4>(a, stream, launch);
+    if (nv <= 8) return launch_fast_nv<LT, 256, 8>(a, stream, launch);
+    if (nv <= 16) return launch_fast_nv<LT, 512, 8>(a, stream, launch);
+    return launch_fast_nv<LT, 1024, 8>(a, stream, launch);
 }
 
-// Rows the fp32 pass covers: whole 16-byte vectors, at most 16 per thread, k within the scan's depth.
+// Rows the fp32 pass covers: at least one 16-byte vector, at most 8 vectors for each of 1024 threads,
+// k within the scan's depth.
 template <typename LT>
 static bool fast_shape(int V, int k) {
     constexpr int EPV = Lane<LT>::EPV;
-    return (V % EPV) == 0 && (V / EPV + NT - 1) / NT <= 16 && k <= FAST_MAX_K;
+    return V >= EPV && V <= 8 * 1024 * EPV && k <= FAST_MAX_K;
 }
 
 template <typename LT>
 static hipError_t launch_typed(const VerifyArgs& a, hipStream_t stream) {
-    const uintptr_t align = reinterpret_cast<uintptr_t>(a.target) | reinterpret_cast<uintptr_t>(a.draft) |
-                            (uintptr_t)(a.stride * (int64_t)sizeof(LT));
-    if ((align & 15) == 0 && fast_shape<LT>(a.V, a.k)) return launch_fast<LT>(a, stream, true);
+    // Diagnostics of rows that are no whole vectors, or of more than 64 KiB, come from the fp64 path as
+    // they always have; decisions and tokens are the same either way.
+    const bool diagnostics = a.out_prob || a.out_mass || a.out_gtok;
+    const bool long_row = (a.V + Lane<LT>::EPV - 1) / Lane<LT>::EPV > 16 * NT;
+    if (fast_shape<LT>(a.V, a.k) && !(diagnostics && (long_row || !whole_vectors<LT>(a))))
+        return launch_fast<LT>(a, stream, true);
     const size_t lds = exact_lds_bytes(a.V);
     const hipError_t e = allow_lds<&verify_exact<LT>>(lds);
     if (e != hipSuccess) return e;

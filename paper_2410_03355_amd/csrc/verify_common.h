@@ -69,6 +69,51 @@ __device__ __forceinline__ uint4 load_stream16(const uint4* p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// The same from an address aligned to the element only (one dwordx4 load either way: the hardware
+// takes any address).
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ uint4 load_stream16_any(const void* p) {
+    const u32x4_any v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint4 load16_any(const void* p) {
+    const u32x4_any v = *reinterpret_cast<const u32x4_any*>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// A 16-byte vector moved down by `over` elements of `bits` bits, the freed places at its end filled
+// from `fill` (over * bits in 1 .. 127; all of it from 128 on).
+__device__ __forceinline__ uint4 shift_down_fill(uint4 v, int over, int bits, uint32_t fill) {
+    const int s = over * bits;
+    if (s >= 128) return make_uint4(fill, fill, fill, fill);
+    uint64_t lo = ((uint64_t)v.y << 32) | v.x, hi = ((uint64_t)v.w << 32) | v.z;
+    const uint64_t f = ((uint64_t)fill << 32) | fill;
+    if (s >= 64) {
+        const int r = s - 64;
+        lo = r ? (hi >> r) | (f << (64 - r)) : hi;
+        hi = f;
+    } else {
+        lo = (lo >> s) | (hi << (64 - s));
+        hi = (hi >> s) | (f << (64 - s));
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
+
+// Vector vi (tokens EPV vi .. EPV vi + EPV - 1) of a row of V >= EPV logits that may start at any
+// element and end anywhere.  row_vector_address: where to load 16 bytes that lie inside the row
+// whatever vi is, so the load needs no branch (a load inside a branch makes the statically placed
+// wait counters wait for every load before it); row_vector_finish: what was loaded there, moved
+// into place, with the tokens at and beyond V reading -inf.
+template <typename LT, int EPV>
+__device__ __forceinline__ const LT* row_vector_address(const LT* row, int vi, int V) {
+    return row + min(vi * EPV, V - EPV);
+}
+template <typename LT, int EPV>
+__device__ __forceinline__ uint4 row_vector_finish(uint4 v, int vi, int V, uint32_t neg_inf_word) {
+    const int over = vi * EPV + EPV - V;
+    return over > 0 ? shift_down_fill(v, over, 8 * (int)sizeof(LT), neg_inf_word) : v;
+}
+
 template <typename LT>
 struct Lane;
 
