@@ -175,6 +175,22 @@ def test_exact_ties_and_duplicates(oracle_mod, lantern_gpu):
     np.testing.assert_array_equal(got, want)
 
 
+@pytest.mark.parametrize("V,d,k,dtype", [
+    (1200, 8, 100, torch.float32),     # whole rows, 256 candidate slots
+    (4800, 16, 100, torch.bfloat16),   # candidate lists, 256 slots
+    (8064, 8, 504, torch.float32),     # candidate lists, 1024 slots
+    (4096, 8, 64, torch.float32),      # 63 and 64 equal keys: the most that still counts as not crowded
+])
+def test_rows_of_equal_keys(oracle_mod, lantern_gpu, V, d, k, dtype):
+    """Every code occurs k times: a row's candidates are two sets of equal keys, ordered by index."""
+    g = torch.Generator().manual_seed(V + k)
+    codes = torch.randn(V // k + 1, d, generator=g).repeat_interleave(k, dim=0)[:V]
+    cb = codes[torch.randperm(V, generator=g)].to(dtype).contiguous()
+    got = _gpu_table(lantern_gpu, cb, k)
+    want = oracle_mod.build_knn(cb.float().numpy(), k, threads=16)
+    np.testing.assert_array_equal(got, want)
+
+
 @pytest.mark.parametrize("V,d,k,dtype,metric", [
     (2166, 1, 1475, torch.float32, "cosine"),    # every key is -1, +1 or missing: all rows through the all-pairs pass
     (500, 3, 500, torch.float32, "cosine"),      # direct keys, every token listed
