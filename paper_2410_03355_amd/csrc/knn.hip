@@ -133,11 +133,20 @@ static FilterPlan filter_plan(int V, int d, int k, int cb_dtype) {
     return P;
 }
 
+// The sampled-threshold path reads its operands from copies in the order in which the matrix cores
+// take them: 32 tokens to a tile, and per tile and step (16 bf16 or 8 fp32 coordinates) the 16 bytes of
+// each of the 64 lanes one after the other, so that an operand is one contiguous load of 1 KiB (read from the
+// codebook itself a load touches 32 rows, each a cache line of its own).
+constexpr size_t PACKED_STEP_BYTES = 64 * 16;
+__host__ __device__ inline size_t packed_tiles(int tokens) { return ((size_t)tokens + 31) / 32; }
+__host__ __device__ inline size_t packed_steps(int d, int cb_dtype) { return cb_dtype == 1 ? ((size_t)d + 15) / 16 : ((size_t)d + 7) / 8; }
+
 struct KnnLayout {
     size_t stats, norms, nmax, dist, flags, slow, total;
-    // sampled-threshold path (filter.use): the sample's codes and norms, a row block's keys to the
-    // sample, its thresholds, list lengths and candidate lists; `dist` is then not laid out
-    size_t scb, snorms, skeys, thr, counts, cand;
+    // sampled-threshold path (filter.use): the codebook and the sample as matrix-core operands, what the
+    // contraction folds in per token, the sample's norms, a row block's keys to the sample, its thresholds,
+    // list lengths and candidate lists (or, in their place, bit rows); `dist` is then not laid out
+    size_t packed, spacked, fold, snorms, skeys, thr, counts, cand;
     FilterPlan filter;
     int row_block;   // query rows per pass through the key block
     int slow_wgs;    // workgroups (and fp64 row buffers) of the exact pass
@@ -152,9 +161,12 @@ static KnnLayout knn_layout(int V, int d, int cb_dtype, const FilterPlan& plan, 
     L.stats = off; off = align_up(off + 256, 256);   // int32[0]: rows that took the exact all-pairs pass
     L.norms = off; off = align_up(off + sizeof(float) * (size_t)V, 256);
     L.nmax = off;  off = align_up(off + 256, 256);
-    L.dist = L.scb = L.snorms = L.skeys = L.thr = L.counts = L.cand = off;
+    L.dist = L.packed = L.spacked = L.fold = L.snorms = L.skeys = L.thr = L.counts = L.cand = off;
     if (plan.use) {
-        L.scb = off;    off = align_up(off + (cb_dtype == 1 ? 2 : 4) * (size_t)plan.S * d, 256);
+        const size_t steps = packed_steps(d, cb_dtype);
+        L.packed = off;  off = align_up(off + packed_tiles(V) * steps * PACKED_STEP_BYTES, 256);
+        L.spacked = off; off = align_up(off + packed_tiles(plan.S) * steps * PACKED_STEP_BYTES, 256);
+        L.fold = off;    off = align_up(off + sizeof(float) * 32 * packed_tiles(V), 256);
         L.snorms = off; off = align_up(off + sizeof(float) * (size_t)plan.S, 256);
         L.skeys = off;  off = align_up(off + sizeof(float) * (size_t)L.row_block * plan.S, 256);
         L.thr = off;    off = align_up(off + sizeof(float) * (size_t)L.row_block, 256);
@@ -523,23 +535,92 @@ __device__ __forceinline__ void contract_block(const float* const (&arow)[2], co
     }
 }
 
-// All keys of rows [r0, r0 + rows) of the codebook cb (V tokens, norms `norms`) against the VB
-// tokens of the column operand cbB (norms nb: the codebook itself, or a sample of it) into dist.
-// blockIdx = (column tile, row tile).
+// The same block from packed operands (ap, bp: a lane's 16 bytes of step 0 of the two row strips and the
+// two column strips).  acc holds what the products are added to.
 template <typename CT>
-__global__ __launch_bounds__(NT) void knn_dist_mfma(const CT* cb, const CT* cbB, const float* norms, const float* nb,
-                                                    int V, int VB, int d, int r0, int rows, int metric, float* dist) {
+__device__ __forceinline__ void mfma_step(const uint4& a, const uint4& b, f32x16& acc);
+template <>
+__device__ __forceinline__ void mfma_step<uint16_t>(const uint4& a, const uint4& b, f32x16& acc) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+template <>
+__device__ __forceinline__ void mfma_step<float>(const uint4& a, const uint4& b, f32x16& acc) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+}
+template <typename CT>
+__device__ __forceinline__ void contract_packed(const uint4* const (&ap)[2], const uint4* const (&bp)[2], int steps,
+                                                f32x16 (&acc)[2][2]) {
+    uint4 na[2] = {ap[0][0], ap[1][0]}, nb[2] = {bp[0][0], bp[1][0]};
+    for (int s = 0; s < steps; ++s) {
+        const uint4 fa[2] = {na[0], na[1]}, fb[2] = {nb[0], nb[1]};
+        const int n = min(s + 1, steps - 1) * WAVE;   // the next step's operands are on their way meanwhile
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            na[t] = ap[t][n];
+            nb[t] = bp[t][n];
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) mfma_step<CT>(fa[a], fb[b], acc[a][b]);
+    }
+}
+__device__ __forceinline__ const uint4* packed_operand(const uint4* packed, int tile, int tiles, int steps, int lane) {
+    return packed + ((int64_t)min(tile, tiles - 1) * steps * WAVE + lane);
+}
+
+// Keys of rows [r0, r0 + rows) to the S tokens of the sample, from packed operands; r0 is a multiple of
+// 128.  blockIdx = (column tile, row tile).
+template <typename CT>
+__global__ __launch_bounds__(NT) void knn_sample_keys(const uint4* packed, const uint4* spacked, const float* norms,
+                                                      const float* snorms, int V, int S, int steps, int r0, int rows,
+                                                      int metric, float* skeys) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int wave = threadIdx.x >> 6;
     const int i_base = r0 + blockIdx.y * 128 + (wave >> 1) * 64;
     const int j_base = blockIdx.x * 128 + (wave & 1) * 64;
-    if (i_base >= r0 + rows || j_base >= VB) return;
+    if (i_base >= r0 + rows || j_base >= S) return;
+    const uint4* ap[2];
+    const uint4* bp[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        ap[t] = packed_operand(packed, i_base / 32 + t, (int)packed_tiles(V), steps, lane);
+        bp[t] = packed_operand(spacked, j_base / 32 + t, (int)packed_tiles(S), steps, lane);
+    }
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+    contract_packed<CT>(ap, bp, steps, acc);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+            store_tile(acc[a][b], i_base + a * 32, j_base + b * 32, lane, r0, rows, S, metric, norms, snorms, skeys);
+}
+
+// All keys of rows [r0, r0 + rows) of the codebook cb (V tokens, norms `norms`) against the whole
+// codebook into dist.  blockIdx = (column tile, row tile).
+template <typename CT>
+__global__ __launch_bounds__(NT) void knn_dist_mfma(const CT* cb, const float* norms, int V, int d, int r0, int rows,
+                                                    int metric, float* dist) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wave = threadIdx.x >> 6;
+    const int i_base = r0 + blockIdx.y * 128 + (wave >> 1) * 64;
+    const int j_base = blockIdx.x * 128 + (wave & 1) * 64;
+    if (i_base >= r0 + rows || j_base >= V) return;
     const CT* arow[2];
     const CT* brow[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         arow[t] = cb + (int64_t)min(i_base + t * 32 + (lane & 31), V - 1) * d;
-        brow[t] = cbB + (int64_t)min(j_base + t * 32 + (lane & 31), VB - 1) * d;
+        brow[t] = cb + (int64_t)min(j_base + t * 32 + (lane & 31), V - 1) * d;
     }
     f32x16 acc[2][2];
     contract_block(arow, brow, d, lane, acc);
@@ -547,7 +628,7 @@ __global__ __launch_bounds__(NT) void knn_dist_mfma(const CT* cb, const CT* cbB,
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
-            store_tile(acc[a][b], i_base + a * 32, j_base + b * 32, lane, r0, rows, VB, metric, norms, nb, dist);
+            store_tile(acc[a][b], i_base + a * 32, j_base + b * 32, lane, r0, rows, V, metric, norms, norms, dist);
 }
 
 // Where the filtering contraction leaves a row block's candidates.
@@ -558,71 +639,50 @@ struct FilterOut {
     int cap;
 };
 
-// LDS of the filtering contraction: per row of the workgroup's 128 its threshold, its norm and a
-// counter (pass 1: keys kept; pass 2: next free slot of the row's list).
+// The filtering contraction takes the tokens as rows of its tiles and the query rows as columns: a
+// lane then holds one query's values only, its threshold is one register, and a hit costs a compare.
+// What is compared is not the key but its token-dependent part, larger for nearer tokens:
+//   squared l2   v = G_ij - n_j / 2 (the matrix cores start from - n_j / 2),  key = n_i - 2 v
+//   cosine       v = G_ij / sqrt(n_j),                                        key = - v / sqrt(n_i)
+// fold[j]: - n_j / 2 or 1 / sqrt(n_j); NaN beyond the vocabulary, where v then passes no comparison.
+template <int METRIC>
+__device__ __forceinline__ float fold_of(float n) { return METRIC == 0 ? -0.5f * n : rsqrtf(n); }
+template <int METRIC>
+__device__ __forceinline__ float value_at(float key, float n) { return METRIC == 0 ? 0.5f * (n - key) : -key * sqrtf(n); }
+template <int METRIC>
+__device__ __forceinline__ float key_of_value(float v, float n, float rn) { return METRIC == 0 ? n - 2.f * v : -v * rn; }
+// Element r of a lane's column is token 8*(r/4) + 4*(lane/32) + r%4 of the tile: four loads of four.
+__device__ __forceinline__ void load_fold(const float* fold, int tile, int lane, float (&o)[16]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float4 v = *reinterpret_cast<const float4*>(fold + tile * 32 + 8 * q + 4 * (lane >> 5));
+        o[4 * q] = v.x; o[4 * q + 1] = v.y; o[4 * q + 2] = v.z; o[4 * q + 3] = v.w;
+    }
+}
+
+// LDS of the filtering contraction: per row of the workgroup's 128 the value its threshold stands for,
+// its norm and a counter (first: keys kept; then: next free slot of the row's list).
 struct FilterShared {
-    float thr[128];
+    float val[128];
     float norm[128];
     int slots[128];
 };
-
-// One 32-row strip of a wavefront's 64x64 block in the filtering contraction, columns j0..j0+63
-// (tiles acc0, acc1); l0: the strip's first row within the workgroup's 128, i0 its token.  A key
-// stays if it is at or below its row's threshold (NaN for rows beyond the block) and is not the
-// row's own token.  Element r of lanes 0-31 belongs to one row and of lanes 32-63 to another, so
-// each half of the wavefront adds its number of kept keys to its row's counter with one LDS
-// atomic; WRITE: what the atomic returns is the first of the half's slots in the row's list, and
-// the keys are placed by their lane rank.
-template <bool WRITE, int METRIC>
-__device__ __forceinline__ void filter_strip(const f32x16& acc0, const f32x16& acc1, int l0, int i0, int j0, int lane,
-                                             int il_wg, int V, const float* norms, FilterShared& sh,
-                                             const FilterOut& f) {
-    const int half = lane >> 5;
-    const int hl = lane & 31;
-    const int ja = j0 + hl, jb = j0 + 32 + hl;
-    const bool va = ja < V, vb = jb < V;
-    const float na = norms[va ? ja : V - 1], nb = norms[vb ? jb : V - 1];
-    const uint32_t below = (1u << hl) - 1u;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int l = l0 + 8 * (r >> 2) + 4 * half + (r & 3);
-        const int i = i0 + 8 * (r >> 2) + 4 * half + (r & 3);
-        const float ni = sh.norm[l];
-        const float t = sh.thr[l];
-        const float ka = approx_key(acc0[r], ni, na, METRIC), kb = approx_key(acc1[r], ni, nb, METRIC);
-        const bool pa = va && ja != i && ka <= t;
-        const bool pb = vb && jb != i && kb <= t;
-        const uint64_t ma = __ballot(pa), mb = __ballot(pb);
-        const uint32_t ha = (uint32_t)(half ? ma >> 32 : ma), hb = (uint32_t)(half ? mb >> 32 : mb);
-        const int n = __popc(ha) + __popc(hb);
-        if (!WRITE) {
-            if (hl == 0 && n > 0) atomicAdd(&sh.slots[l], n);
-        } else {
-            int first = 0;
-            if (hl == 0 && n > 0) first = atomicAdd(&sh.slots[l], n);
-            const int b0 = __builtin_amdgcn_readlane(first, 0), b1 = __builtin_amdgcn_readlane(first, 32);
-            first = half ? b1 : b0;
-            uint2* list = f.cand + (int64_t)(il_wg + l) * f.cap;   // only dereferenced for rows of the block
-            const int sa = first + __popc(ha & below);
-            const int sb = first + __popc(ha) + __popc(hb & below);
-            if (pa && sa < f.cap) list[sa] = make_uint2(min(ord_key(ka), 0xFFFFFFFEu), (uint32_t)ja);
-            if (pb && sb < f.cap) list[sb] = make_uint2(min(ord_key(kb), 0xFFFFFFFEu), (uint32_t)jb);
-        }
-        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // four rows in flight: keeps the register count down
-    }
-}
 
 // Filtering contraction: rows [r0, r0 + rows) against the whole codebook, keeping for every row
 // only the (key, token) pairs at or below the row's threshold.  A workgroup owns a tile of 128
 // rows by 128 tokens.  It contracts, counts the kept keys per row in LDS, reserves each row's
 // slots in its list with one atomic add per row, and then places the keys (the accumulators stay
-// in registers meanwhile).
+// in registers meanwhile, which values are kept in a bit mask per lane).
 // Grid: one-dimensional, 8 * ceil(row tiles / 8) * column tiles workgroups, dealt so that all
 // column tiles of a row strip run on one XCD (workgroups go to the eight XCDs in turn) and a
 // row's list and counter stay in that XCD's L2.
+// Bound by the compares and the placing of hits at small d, by the operand loads at large d.  With
+// queries across the lanes and packed operands 278 -> 210 us (V = 16384, d = 8 fp32, k = 1000) and
+// 145 -> 82 us (V = 8192, d = 256 bf16, k = 100) against tiles with queries as rows, whose hits took
+// two ballots and four population counts per element, read from the codebook itself.
 template <typename CT, int METRIC>
-__global__ __launch_bounds__(NT, 2) void knn_filter_mfma(const CT* cb, const float* norms, int V, int d, int r0,
-                                                         int rows, FilterOut f) {
+__global__ __launch_bounds__(NT, 2) void knn_filter_list(const uint4* packed, const float* fold, const float* norms, int V,
+                                                         int steps, int r0, int rows, FilterOut f) {
     __shared__ FilterShared sh;
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
@@ -632,46 +692,95 @@ __global__ __launch_bounds__(NT, 2) void knn_filter_mfma(const CT* cb, const flo
     const int ti = (q / nct) * 8 + xcd;
     const int tj = q % nct;
     if (ti >= nrt) return;   // the whole workgroup
+    const int tiles = (int)packed_tiles(V);
     const int il_wg = ti * 128;        // first row of the workgroup within the block
     const int l_base = (wave >> 1) * 64;
-    const int i_base = r0 + il_wg + l_base;
-    const int j_base = tj * 128 + (wave & 1) * 64;
-    const bool live = j_base < V;      // rows beyond the block are kept out by their thresholds (NaN)
+    const int t_base = tj * 4 + (wave & 1) * 2;   // first token tile
+    const bool live = t_base < tiles;
     if (tid < 128) {
         const bool row_ok = il_wg + tid < rows;
-        // rows beyond the block: no key compares at or below NaN (a threshold of -inf would let the
-        // cosine key -g / sqrt(0 n_j) = -inf through), and the norm is kept away from zero
-        sh.thr[tid] = row_ok ? f.thr[il_wg + tid] : NAN;
-        sh.norm[tid] = row_ok ? norms[r0 + il_wg + tid] : 1.f;
+        const float n = row_ok ? norms[r0 + il_wg + tid] : 1.f;
+        sh.norm[tid] = n;
+        sh.val[tid] = row_ok ? value_at<METRIC>(f.thr[il_wg + tid], n) : NAN;   // beyond the block: nothing is kept
         sh.slots[tid] = 0;
     }
     __syncthreads();
-    f32x16 acc[2][2];
+    f32x16 acc[2][2];   // [token strip][query strip]
+    uint32_t hits[2] = {0u, 0u};
     if (live) {
-        const CT* arow[2];
-        const CT* brow[2];
+        const uint4* ap[2];
+        const uint4* bp[2];
+        float fd[2][16];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            arow[t] = cb + (int64_t)min(i_base + t * 32 + (lane & 31), V - 1) * d;
-            brow[t] = cb + (int64_t)min(j_base + t * 32 + (lane & 31), V - 1) * d;
+            ap[t] = packed_operand(packed, t_base + t, tiles, steps, lane);
+            bp[t] = packed_operand(packed, (r0 + il_wg + l_base) / 32 + t, tiles, steps, lane);
         }
-        contract_block(arow, brow, d, lane, acc);
+        if (METRIC == 0) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a) load_fold(fold, min(t_base + a, tiles - 1), lane, fd[a]);
+        }
 #pragma unroll
         for (int a = 0; a < 2; ++a)
-            filter_strip<false, METRIC>(acc[a][0], acc[a][1], l_base + a * 32, i_base + a * 32, j_base, lane, il_wg, V,
-                                        norms, sh, f);
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[a][b][r] = METRIC == 0 ? fd[a][r] : 0.f;
+        contract_packed<CT>(ap, bp, steps, acc);
+        if (METRIC != 0) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                load_fold(fold, min(t_base + a, tiles - 1), lane, fd[a]);
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[a][b][r] *= fd[a][r];
+            }
+        }
+        const bool second = t_base + 1 < tiles;   // else strip 1 is strip 0 once more
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int l = l_base + b * 32 + (lane & 31);
+            const float least = sh.val[l];
+            uint32_t h = 0;   // bit 16 a + r
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) h |= acc[a][b][r] >= least ? 1u << (16 * a + r) : 0u;
+            if (!second) h &= 0xFFFFu;
+            // the row itself is no candidate
+            const int own = r0 + il_wg + l - t_base * 32;   // within the two strips?
+            if ((unsigned)own < 64u && ((own >> 2) & 1) == (lane >> 5))
+                h &= ~(1u << (16 * (own >> 5) + 4 * ((own & 31) >> 3) + (own & 3)));
+            hits[b] = h;
+            if (h) atomicAdd(&sh.slots[l], __popc(h));
+        }
     }
     __syncthreads();
     if (tid < 128) {
         const int n = sh.slots[tid];   // n > 0 only for rows of the block
-        sh.slots[tid] = (n > 0 && il_wg + tid < rows) ? atomicAdd(f.counts + il_wg + tid, n) : 0;
+        sh.slots[tid] = n > 0 ? atomicAdd(f.counts + il_wg + tid, n) : 0;
     }
     __syncthreads();
     if (live) {
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-            filter_strip<true, METRIC>(acc[a][0], acc[a][1], l_base + a * 32, i_base + a * 32, j_base, lane, il_wg, V,
-                                       norms, sh, f);
+        for (int b = 0; b < 2; ++b) {
+            const int l = l_base + b * 32 + (lane & 31);
+            const uint32_t h = hits[b];
+            const float n = sh.norm[l], rn = METRIC == 0 ? 0.f : rsqrtf(n);
+            int slot = h ? atomicAdd(&sh.slots[l], __popc(h)) : 0;
+            uint2* list = f.cand + (int64_t)(il_wg + l) * f.cap;   // only dereferenced for rows of the block
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if ((h >> (16 * a + r)) & 1u) {
+                        const int j = (t_base + a) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                        const float key = key_of_value<METRIC>(acc[a][b][r], n, rn);
+                        if (slot < f.cap) list[slot] = make_uint2(min(ord_key(key), 0xFFFFFFFEu), (uint32_t)j);
+                        ++slot;
+                    }
+        }
     }
 }
 
@@ -684,15 +793,41 @@ __host__ __device__ inline int sample_token(int s, int S, int V) {
     return j < V ? (int)j : V - 1;
 }
 
-template <typename CT>
-__global__ __launch_bounds__(NT) void knn_gather_sample(const CT* cb, const float* norms, int V, int d, int S,
-                                                        CT* scb, float* snorms) {
+// The packed operands of the codebook (its `tiles` tiles) and, after them, of the sample; one thread per
+// lane of a step.  Also fold[] for every token of those tiles, and the sample's norms.
+template <typename CT, int METRIC>
+__global__ __launch_bounds__(NT) void knn_pack(const CT* cb, const float* norms, int V, int d, int S, int steps,
+                                               uint4* packed, uint4* spacked, float* fold, float* snorms) {
+    const int tiles = (int)packed_tiles(V), stiles = (int)packed_tiles(S);
     const int64_t t = (int64_t)blockIdx.x * NT + threadIdx.x;
-    if (t >= (int64_t)S * d) return;
-    const int s = (int)(t / d), c = (int)(t % d);
-    const int j = sample_token(s, S, V);
-    scb[t] = cb[(int64_t)j * d + c];
-    if (c == 0) snorms[s] = norms[j];
+    const int lane = (int)(t & (WAVE - 1));
+    const int64_t unit = t >> 6;
+    const int step = (int)(unit % steps);
+    const int64_t tile = unit / steps;
+    if (tile >= tiles + stiles) return;
+    const bool of_sample = tile >= tiles;
+    const int slot = (int)(of_sample ? tile - tiles : tile) * 32 + (lane & 31);
+    const bool there = slot < (of_sample ? S : V);
+    const int j = !there ? 0 : of_sample ? sample_token(slot, S, V) : slot;
+    const CT* row = cb + (int64_t)j * d;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (there) {
+        if constexpr (sizeof(CT) == 2) {
+            const int c = step * 16 + 8 * (lane >> 5);
+            if (c < d) v = *reinterpret_cast<const uint4*>(row + c);   // d is a multiple of 8
+        } else {
+            const uint32_t* w = reinterpret_cast<const uint32_t*>(row) + step * 8 + (lane >> 5);
+            const int left = d - step * 8;   // 4 or at least 8
+            v.x = w[0];
+            v.y = w[2];
+            if (left > 4) { v.z = w[4]; v.w = w[6]; }
+        }
+    }
+    (of_sample ? spacked + (unit - (int64_t)tiles * steps) * WAVE : packed + unit * WAVE)[lane] = v;
+    if (step == 0 && lane < 32) {
+        if (!of_sample) fold[slot] = there ? fold_of<METRIC>(norms[slot]) : NAN;
+        else if (there) snorms[slot] = norms[j];
+    }
 }
 
 // One wavefront per row: a value with between rank and rank + slack of the row's S <= 64 * NS keys
@@ -1231,7 +1366,10 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
         err_abs = a.metric == 0 ? 0.f : 2.f * gamma;
         err_norm = 0.f;
     }
-    CT* scb = reinterpret_cast<CT*>(ws + L.scb);
+    uint4* packed = reinterpret_cast<uint4*>(ws + L.packed);
+    uint4* spacked = reinterpret_cast<uint4*>(ws + L.spacked);
+    float* fold = reinterpret_cast<float*>(ws + L.fold);
+    const int steps = (int)packed_steps(a.d, sizeof(CT) == 2 ? 1 : 0);
     float* snorms = reinterpret_cast<float*>(ws + L.snorms);
     float* skeys = reinterpret_cast<float*>(ws + L.skeys);
     FilterOut fo;
@@ -1242,22 +1380,27 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
     const FilterOut no_list = {nullptr, nullptr, nullptr, 0};
     if (plan.use) {
         if (!mfma) return hipErrorInvalidValue;
-        const int64_t elems = (int64_t)plan.S * a.d;
-        hipLaunchKernelGGL((knn_gather_sample<CT>), dim3((unsigned)((elems + NT - 1) / NT)), dim3(NT), 0, stream, cb,
-                           norms, a.V, a.d, plan.S, scb, snorms);
+        // v = G - n_j / 2 is one sum of d + 1 terms: its error, doubled, is below gamma (n_i + 2 n_j), and the
+        // two norms' add gamma (n_i + n_j)
+        if (a.metric == 0) err_norm = 3.f * gamma;
+        const int64_t threads = (int64_t)(packed_tiles(a.V) + packed_tiles(plan.S)) * steps * WAVE;
+        const dim3 grid((unsigned)((threads + NT - 1) / NT));
+        if (a.metric == 0)
+            hipLaunchKernelGGL((knn_pack<CT, 0>), grid, dim3(NT), 0, stream, cb, norms, a.V, a.d, plan.S, steps, packed,
+                               spacked, fold, snorms);
+        else
+            hipLaunchKernelGGL((knn_pack<CT, 1>), grid, dim3(NT), 0, stream, cb, norms, a.V, a.d, plan.S, steps, packed,
+                               spacked, fold, snorms);
     }
-    // all keys of rows [r0, r0 + rows) against the tokens of cbB
-    auto contract = [&](const CT* cbB, const float* nb, int VB, int r0, int rows, float* keys) {
-        hipLaunchKernelGGL((knn_dist_mfma<CT>), dim3((VB + 127) / 128, (rows + 127) / 128), dim3(NT), 0, stream, cb,
-                           cbB, norms, nb, a.V, VB, a.d, r0, rows, a.metric, keys);
-    };
     auto filter = [&](int r0, int rows) {
         const int nct = (a.V + 127) / 128, nrt = (rows + 127) / 128;
         const dim3 grid((unsigned)((nrt + 7) / 8 * 8 * nct));
         if (a.metric == 0)
-            hipLaunchKernelGGL((knn_filter_mfma<CT, 0>), grid, dim3(NT), 0, stream, cb, norms, a.V, a.d, r0, rows, fo);
+            hipLaunchKernelGGL((knn_filter_list<CT, 0>), grid, dim3(NT), 0, stream, packed, fold, norms, a.V, steps, r0,
+                               rows, fo);
         else
-            hipLaunchKernelGGL((knn_filter_mfma<CT, 1>), grid, dim3(NT), 0, stream, cb, norms, a.V, a.d, r0, rows, fo);
+            hipLaunchKernelGGL((knn_filter_list<CT, 1>), grid, dim3(NT), 0, stream, packed, fold, norms, a.V, steps, r0,
+                               rows, fo);
     };
     for (int r0 = 0; r0 < a.V; r0 += L.row_block) {
         const int rows = (a.V - r0) < L.row_block ? (a.V - r0) : L.row_block;
@@ -1273,7 +1416,8 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
                            err_norm, nsel, nmax, a.out, flags + r0)
         if (plan.use) {
             // thresholds from the sample, then the contraction that keeps what lies below them
-            contract(scb, snorms, plan.S, r0, rows, skeys);
+            hipLaunchKernelGGL((knn_sample_keys<CT>), dim3((plan.S + 127) / 128, (rows + 127) / 128), dim3(NT), 0, stream,
+                               packed, spacked, norms, snorms, a.V, plan.S, steps, r0, rows, a.metric, skeys);
             if (plan.S <= 8 * WAVE) launch_sample_rank<8>(skeys, plan, rows, const_cast<float*>(fo.thr), fo.counts, stream);
             else if (plan.S <= 16 * WAVE) launch_sample_rank<16>(skeys, plan, rows, const_cast<float*>(fo.thr), fo.counts, stream);
             else if (plan.S <= 32 * WAVE) launch_sample_rank<32>(skeys, plan, rows, const_cast<float*>(fo.thr), fo.counts, stream);
@@ -1287,7 +1431,9 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
             else if (plan.cap <= 12 * NT) LANTERN_LAUNCH_SELECT(12, 1024, NT, true);
             else LANTERN_LAUNCH_SELECT(16, 1024, NT, true);
         } else {
-            if (mfma) contract(cb, norms, a.V, r0, rows, dist);
+            if (mfma)
+                hipLaunchKernelGGL((knn_dist_mfma<CT>), dim3((a.V + 127) / 128, (rows + 127) / 128), dim3(NT), 0, stream,
+                                   cb, norms, a.V, a.d, r0, rows, a.metric, dist);
             else
                 hipLaunchKernelGGL((knn_dist_direct<CT>), dim3((a.V + NT - 1) / NT, rows), dim3(NT), 0, stream,
                                    cb, a.V, a.d, r0, a.metric, dist);
