@@ -10,18 +10,31 @@
 // With k = 1 or delta = 0 this is recursive rejection sampling, which keeps the target law.
 //
 // The chain t_1, t_2, ... is sequential, so one workgroup of 1024 threads walks one tree and keeps
-// the current target and the drafter's distribution as fp64 vectors (unnormalised terms and a
-// scale each: no division per token), the drafter's in a workspace (cache resident), the current
-// target in LDS when it fits and in the workspace otherwise; evaluated in fp64.  The test of a group's first child is
-// the plain verification of that candidate, so its decision is read from the row-parallel pass
-// (lantern_decide_rows over all candidates, launched first): only groups whose first child is
-// rejected build the vectors.
+// the current target and the drafter's distribution in fp64 (unnormalised terms and a scale each: no
+// division per token).  The test of a group's first child is the plain verification of that
+// candidate, so its decision is read from the row-parallel pass (lantern_decide_rows over all
+// candidates, launched first): only groups whose first child is rejected build the vectors.
+// A launch has as many workgroups as trees and each is a chain of passes over the vocabulary, so what
+// counts is the length of that chain:
+//   - a thread owns pairs of neighbouring tokens (4-byte loads of bf16, 8-byte loads of fp32, 16-byte
+//     LDS accesses), the same ones in every pass, a wavefront a contiguous part of the vocabulary; the
+//     drafter's terms then stay in registers and the rows are read from memory once;
+//   - the current target is gathered at random by the neighbourhood walk: it lives in LDS;
+//   - one pass per rejected child forms its residual and adds it up, storing what is not positive with
+//     its sign turned (t_{j,A} is needed again when the residual turns out to have no mass);
+//   - the residual draw is taken once per group, after its last child, by the one wavefront whose part
+//     of the vocabulary holds it;
+//   - a tree's parents, tokens, decisions and draws are staged in LDS, and every wavefront looks for the
+//     next child by itself.
+// V = 16384, k = 1000, 64 trees of 60 candidates: 117 us, from 160 us; the whole step 146 us, from 189 us.
+// Vocabularies that do not fit in LDS keep both vectors in the workspace.
 #include <hip/hip_runtime.h>
 #include <limits.h>
 #include <stdint.h>
 
 #include "device_utils.h"
 #include "exp64.h"
+#include "exp_table.h"
 #include "lds_limit.h"
 #include "sequential_args.h"
 #include "verify_common.h"
@@ -30,74 +43,66 @@ namespace lantern {
 
 constexpr int SNT = 1024;
 constexpr int SNW = SNT / WAVE;
+constexpr int PAIR_STEP = 2 * WAVE;   // tokens of one step of a wavefront: a pair per lane
+constexpr int SNODES = 128;           // nodes of a tree that are staged in LDS; larger trees are read in place
 
-// Elements a thread keeps in flight per step of a pass: the loads of a step are all issued before
-// the first of them is used, so a pass pays the memory latency once per step, not once per element.
-constexpr int SU = 8;
-
-// Unnormalised softmax terms exp(l - max) of the target row and of the drafter's row into
-// pt[0, V) and pg[0, V) (fp64), and their sums into *zt and *zg: the probabilities are pt[x] / *zt
-// and pg[x] / *zg.  Returns false, with the outputs unspecified, if either row has a NaN, a +inf
-// or no finite logit.  Ends with every thread past a barrier that follows its last write.
-template <typename LT>
-__device__ bool softmax_pair(const LT* trow, const LT* grow, int V, double* pt, double* pg, double* zt_out,
-                             double* zg_out, ExactShared& sh, int tid) {
-    using L = Lane<LT>;
-    const float inf = __builtin_huge_valf();
-    float mt = -inf, mg = -inf;
-    int bad = 0;
-    for (int xb = tid; xb < V; xb += SNT * SU) {
-        float lt[SU], lg[SU];
-#pragma unroll
-        for (int u = 0; u < SU; ++u) {
-            const int x = xb + u * SNT;
-            lt[u] = x < V ? L::glob(trow, x) : -inf;
-            lg[u] = x < V ? L::glob(grow, x) : -inf;
-        }
-#pragma unroll
-        for (int u = 0; u < SU; ++u) {
-            if (lt[u] != lt[u] || lt[u] == inf || lg[u] != lg[u] || lg[u] == inf) bad = 1;
-            mt = fmaxf(mt, lt[u]);
-            mg = fmaxf(mg, lg[u]);
-        }
+// Two neighbouring logits with one load from an address aligned to the element only.
+template <typename LT> struct RawPair;
+template <> struct RawPair<float> {
+    typedef uint32_t raw __attribute__((ext_vector_type(2), aligned(4)));
+    __device__ static __forceinline__ float lo(raw v) { return __uint_as_float(v.x); }
+    __device__ static __forceinline__ float hi(raw v) { return __uint_as_float(v.y); }
+    __device__ static __forceinline__ void opaque(raw& v) {
+        uint32_t x = v.x, y = v.y;
+        asm("" : "+v"(x), "+v"(y));
+        v.x = x;
+        v.y = y;
     }
-    bad = block_or_i<SNW>(bad, sh.ired, tid);
-    const double mxt = block_max<SNW>((double)mt, sh.red, tid);
-    const double mxg = block_max<SNW>((double)mg, sh.red2, tid);
-    if (bad || mxt == -__builtin_huge_val() || mxg == -__builtin_huge_val()) return false;   // uniform
-    double zt = 0.0, zg = 0.0;
-    for (int xb = tid; xb < V; xb += SNT * SU) {
-        float lt[SU], lg[SU];
-#pragma unroll
-        for (int u = 0; u < SU; ++u) {
-            const int x = xb + u * SNT;
-            lt[u] = x < V ? L::glob(trow, x) : -inf;
-            lg[u] = x < V ? L::glob(grow, x) : -inf;
-        }
-#pragma unroll
-        for (int u = 0; u < SU; ++u) {
-            const int x = xb + u * SNT;
-            const double et = exp_nonpos((double)lt[u] - mxt);
-            const double eg = exp_nonpos((double)lg[u] - mxg);
-            if (x < V) {
-                pt[x] = et;
-                pg[x] = eg;
-                zt += et;
-                zg += eg;
-            }
-        }
+};
+template <> struct RawPair<uint16_t> {
+    typedef uint32_t raw __attribute__((aligned(2)));
+    __device__ static __forceinline__ float lo(uint32_t v) { return __uint_as_float(v << 16); }
+    __device__ static __forceinline__ float hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
+    __device__ static __forceinline__ void opaque(raw& v) {
+        uint32_t x = v;
+        asm("" : "+v"(x));
+        v = x;
     }
-    *zt_out = block_sum<SNW>(zt, sh.red, tid);
-    *zg_out = block_sum<SNW>(zg, sh.red2, tid);
-    __syncthreads();
-    return true;
+};
+// An integer whose origin the compiler does not see: what is computed from it stays where it is used
+// (token numbers and bounds of every step, hoisted out of the walk, would take more registers than there are).
+__device__ __forceinline__ int opaque_int(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
 }
+// A function of its own: its logarithms' constants would occupy registers all through the walk.
+__device__ __noinline__ bool jsd_fails(double t_tok, double moved, double delta) {
+    return !(prefix_divergence64(1, t_tok, moved) < delta);
+}
+typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
 
-template <typename LT>
+struct SeqShared {
+    double tab[2 * EXP_TABLE_N];
+    double sum_a[SNW], sum_b[SNW];   // softmax sums, then the walk's totals and sums before its cut
+    double wr[SNW], wt[SNW];         // residual mass and distorted target's mass of every wavefront's part
+    float mt[SNW], mg[SNW];
+    int bad[SNW], cut[SNW];
+    int ired[SNW];
+    int drawn;
+    int parent[SNODES], row[SNODES], token[SNODES], accept[SNODES];
+    float u_acc[SNODES], u_res[SNODES];
+};
+
+// NP > 0: every wavefront's part of the vocabulary is at most NP steps; the current target lives in LDS
+// and the drafter's terms in registers.  NP == 0: any vocabulary, both vectors in the workspace.
+template <typename LT, int NP>
 __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
-    __shared__ ExactShared sh;
-    __shared__ double s_wr[SNW];   // residual mass of every wavefront's part of the vocabulary
-    __shared__ double s_wt[SNW];   // mass of the distorted target over the same part
+    using RP = RawPair<LT>;
+    using Raw = typename RP::raw;
+    constexpr bool RES = NP > 0;
+    constexpr int U = RES ? NP : 4;       // steps whose loads are in flight together
+    __shared__ SeqShared sh;
+    extern __shared__ __align__(16) double seq_cur[];
 
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
@@ -106,30 +111,55 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
     const int V = a.V;
     const int k = a.k;
     const int M = a.M;
-    const int32_t* par = a.parent + (int64_t)b * M;
-    int32_t* path = a.out_path + (int64_t)b * M;
-    // t_j and the drafter's distribution of the group, both unnormalised: t_j(x) = cur[x] * inv_st,
-    // g(x) = g[x] * inv_sg.  The drafter's terms are written once per group and then only read: they
-    // stay in the workspace.  t_j is read at random by the walk and rewritten for every rejected
-    // child: it lives in LDS when V doubles fit beside the rest (a.cur_in_lds), else in the workspace.
-    extern __shared__ __align__(16) unsigned char seq_smem[];
-    double* cur = a.cur_in_lds ? reinterpret_cast<double*>(seq_smem) : a.work + (int64_t)b * 2 * V;
-    double* g = a.work + (int64_t)b * 2 * V + V;
-    double inv_st = 0.0, inv_sg = 0.0, st = 0.0;
+    const int64_t c0 = (int64_t)b * M;
+    const int32_t* par = a.parent + c0;
+    int32_t* path = a.out_path + c0;
+    // t_j(x) = max(0, cur[x]) * inv_st,  g(x) = g[x] * inv_sg
+    double* cur_mem = a.work + (int64_t)b * 2 * V;
+    double* g_mem = cur_mem + V;
+    auto cur_at = [&](int x) { return fmax(RES ? seq_cur[x] : cur_mem[x], 0.0); };
+    auto cur_set = [&](int x, double v) {
+        if (RES) seq_cur[x] = v;
+        else cur_mem[x] = v;
+    };
+    // a pair that may end beyond the vocabulary; x even and below V
+    auto get2 = [&](const double* v, int x) {
+        d2 r;
+        if (x + 1 < V) r = *reinterpret_cast<const d2*>(v + x);
+        else r = d2{v[x], 0.0};
+        return r;
+    };
+    auto put2 = [&](double* v, int x, double lo, double hi) {
+        if (x + 1 < V) *reinterpret_cast<d2*>(v + x) = d2{lo, hi};
+        else v[x] = lo;
+    };
+    double* cur = RES ? seq_cur : cur_mem;
+    double greg[RES ? 2 * NP : 1];
+    double inv_st = 0.0, inv_sg = 0.0, st = 0.0, mxg = 0.0;
     const double delta = (double)a.delta;
 
-    // the part of the vocabulary this wavefront sums and scans: [x0, x1), in steps of 64
-    const int per = (((V + SNW - 1) / SNW) + WAVE - 1) & ~(WAVE - 1);
+    // the part of the vocabulary of this wavefront: [x0, x1), in steps of a pair per lane
+    const int per = ((V + SNW - 1) / SNW + PAIR_STEP - 1) / PAIR_STEP * PAIR_STEP;
     const int x0 = min(V, wave * per);
     const int x1 = min(V, x0 + per);
 
+    const bool staged = M <= SNODES;
     int malformed = 0;
     for (int j = tid; j < M; j += SNT) {
         path[j] = -1;
         const int p = par[j];
         if (p < -1 || p >= j) malformed = 1;
+        if (staged) {
+            sh.parent[j] = p;
+            sh.row[j] = a.row_index ? a.row_index[c0 + j] : (int)(c0 + j);
+            sh.token[j] = a.tokens[c0 + j];
+            sh.accept[j] = a.accept[c0 + j];
+            sh.u_acc[j] = a.uniforms[2 * (c0 + j)];
+            sh.u_res[j] = a.uniforms[2 * (c0 + j) + 1];
+        }
     }
-    malformed = block_or_i<SNW>(malformed, sh.ired, tid);
+    for (int j = tid; j < 2 * EXP_TABLE_N; j += SNT) sh.tab[j] = EXP_TABLE_HILO[j];
+    malformed = block_or_i<SNW>(malformed, sh.ired, tid);   // its barriers publish what is staged
     if (malformed) {
         if (tid == 0) {
             a.out_len[b] = 0;
@@ -144,176 +174,348 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         int taken = -1;
         int group_row = -1;
         bool have_rows = false;
+        const LT* grow = nullptr;
+        double zz = 0.0;             // of the last rejected child: mass of what its draw is taken from,
+        double u_res = 0.0;          //   its draw,
+        bool zero_resid = false;     //   and whether that is the distorted target itself
         int i = node;
         for (;;) {
             // the next child: the smallest index above i whose parent is the node
-            int cand = INT_MAX;
-            for (int q = i + 1 + tid; q < M; q += SNT)
-                if (par[q] == node) {
-                    cand = q;
+            int child = INT_MAX;
+            for (int base = i + 1; base < M; base += WAVE) {
+                const int q = base + lane;
+                const int p = q < M ? (staged ? sh.parent[q] : par[q]) : INT_MIN;
+                const unsigned long long m = __ballot(p == node);
+                if (m) {
+                    child = base + __ffsll((long long)m) - 1;
                     break;
                 }
-            i = block_min_i<SNW>(cand, sh.ired, tid);
+            }
+            i = child;
             if (i == INT_MAX) break;
-            const int64_t c = (int64_t)b * M + i;
-            const int r = a.row_index ? a.row_index[c] : (int)c;
-            const int xt = a.tokens[c];
+            const int64_t c = c0 + i;
+            const int r = staged ? sh.row[i] : a.row_index ? a.row_index[c] : (int)c;
+            const int xt = staged ? sh.token[i] : a.tokens[c];
+            bool usable = (unsigned)xt < (unsigned)V;
+            const int32_t* nrow = a.knn + (int64_t)(usable ? xt : 0) * k;
+            int nb;
             if (!have_rows) {
                 // The first child is tested against t_1 = t itself, which is the plain verification the
                 // row-parallel pass has already decided for every candidate: an accepted first child is
                 // taken without building the group's vectors.
-                const int decided = a.accept[c];
+                const int decided = staged ? sh.accept[i] : a.accept[c];
                 if (decided == 1) {
                     taken = i;
                     break;
                 }
-                if (decided < 0) {   // unusable row, token or table entry
+                if (decided < 0 || r < 0 || r >= a.R) {   // unusable row, token or table entry
                     next = -2;
                     break;
                 }
                 // rejected: the first child brings the group's rows, and is verified again below in
                 // fp64 for its distorted target and residual
+                nb = nrow[min(tid, k - 1)];               // in flight during the passes over the rows
                 have_rows = true;
                 group_row = r;
-                bool ok = (r >= 0 && r < a.R);
-                double sg = 0.0;
-                if (ok)
-                    ok = softmax_pair<LT>(reinterpret_cast<const LT*>(a.target) + (int64_t)r * a.stride,
-                                          reinterpret_cast<const LT*>(a.draft) + (int64_t)r * a.stride, V, cur, g, &st,
-                                          &sg, sh, tid);
-                inv_st = 1.0 / st;
-                inv_sg = 1.0 / sg;
-                if (!ok) {
+                const LT* trow = reinterpret_cast<const LT*>(a.target) + (int64_t)r * a.stride;
+                grow = reinterpret_cast<const LT*>(a.draft) + (int64_t)r * a.stride;
+                // Unnormalised softmax terms exp(l - max) and their sums.  A pair's load is moved to
+                // the row's last two logits where it would leave the row (V = 1 reads the one logit twice).
+                Raw tr[U], gr[U];
+                const int l2 = opaque_int(2 * lane);
+                float mt = neg_inf_f(), mg = neg_inf_f();
+                int bad = 0;
+                const float inf = __builtin_huge_valf();
+                auto load = [&](int xb) {
+                    if (V == 1) return;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int x = min(xb + u * PAIR_STEP + l2, V - 2);
+                        tr[u] = *reinterpret_cast<const Raw*>(trow + x);
+                        gr[u] = *reinterpret_cast<const Raw*>(grow + x);
+                    }
+                };
+                auto logits = [&](const Raw& v, const LT* row, int x, float* lo, float* hi) {
+                    if (V == 1) {
+                        *lo = x == 0 ? Lane<LT>::glob(row, 0) : neg_inf_f();
+                        *hi = neg_inf_f();
+                        return;
+                    }
+                    *lo = x < x1 ? (x + 1 < V ? RP::lo(v) : RP::hi(v)) : neg_inf_f();
+                    *hi = x + 1 < x1 ? RP::hi(v) : neg_inf_f();
+                };
+                for (int xb = x0; xb < (RES ? x0 + 1 : x1); xb += U * PAIR_STEP) {
+                    load(xb);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int x = xb + u * PAIR_STEP + l2;
+                        float l0, l1, h0, h1;
+                        logits(tr[u], trow, x, &l0, &l1);
+                        logits(gr[u], grow, x, &h0, &h1);
+                        if (l0 != l0 || l1 != l1 || h0 != h0 || h1 != h1) bad = 1;
+                        mt = fmaxf(mt, fmaxf(l0, l1));
+                        mg = fmaxf(mg, fmaxf(h0, h1));
+                    }
+                }
+                if (mt == inf || mg == inf) bad = 1;
+                mt = wave_max(mt);
+                mg = wave_max(mg);
+                bad = wave_or(bad);
+                if (lane == 0) {
+                    sh.mt[wave] = mt;
+                    sh.mg[wave] = mg;
+                    sh.bad[wave] = bad;
+                }
+                __syncthreads();
+                bad = 0;
+                mt = mg = neg_inf_f();
+#pragma unroll 4
+                for (int w = 0; w < SNW; ++w) {
+                    mt = fmaxf(mt, sh.mt[w]);
+                    mg = fmaxf(mg, sh.mg[w]);
+                    bad |= sh.bad[w];
+                }
+                if (bad || mt == -inf || mg == -inf) {   // uniform
                     next = -2;
                     break;
                 }
+                const double mxt = (double)mt;
+                mxg = (double)mg;
+                double zt = 0.0, zg = 0.0;
+                if (RES) {
+                    // the rows stay in registers as loaded, not as what the first pass unpacked them to
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        RP::opaque(tr[u]);
+                        RP::opaque(gr[u]);
+                    }
+                }
+                for (int xb = x0; xb < (RES ? x0 + 1 : x1); xb += U * PAIR_STEP) {
+                    if (!RES) load(xb);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (xb + u * PAIR_STEP < x1) {   // uniform over the wavefront
+                            const int x = xb + u * PAIR_STEP + l2;
+                            float l0, l1, h0, h1;
+                            logits(tr[u], trow, x, &l0, &l1);
+                            logits(gr[u], grow, x, &h0, &h1);
+                            const double t0 = exp_tab((double)l0 - mxt, sh.tab);
+                            const double t1 = exp_tab((double)l1 - mxt, sh.tab);
+                            const double g0 = exp_tab((double)h0 - mxg, sh.tab);
+                            const double g1 = exp_tab((double)h1 - mxg, sh.tab);
+                            zt += t0 + t1;
+                            zg += g0 + g1;
+                            if (x < x1) put2(cur, x, t0, t1);
+                            if (RES) {
+                                greg[2 * u] = g0;
+                                greg[2 * u + 1] = g1;
+                            } else if (x < x1) {
+                                put2(g_mem, x, g0, g1);
+                            }
+                        }
+                    }
+                }
+                zt = wave_sum(zt);
+                zg = wave_sum(zg);
+                if (lane == 0) {
+                    sh.sum_a[wave] = zt;
+                    sh.sum_b[wave] = zg;
+                }
+                __syncthreads();   // the sums, and the current target
+                st = 0.0;
+                double sg = 0.0;
+#pragma unroll 4
+                for (int w = 0; w < SNW; ++w) {
+                    st += sh.sum_a[w];
+                    sg += sh.sum_b[w];
+                }
+                inv_st = 1.0 / st;
+                inv_sg = 1.0 / sg;
+                __syncthreads();   // the walk below writes the same arrays
+            } else {
+                nb = nrow[min(tid, k - 1)];
             }
-            bool usable = (r == group_row) && ((unsigned)xt < (unsigned)V);
-            const int32_t* nrow = a.knn + (int64_t)(usable ? xt : 0) * k;
-            if (usable) {
-                int off = 0;
-                for (int j = tid; j < k; j += SNT)
-                    if ((unsigned)nrow[j] >= (unsigned)V) off = 1;
-                usable = block_or_i<SNW>(off, sh.ired, tid) == 0;
-            }
+            if (r != group_row) usable = false;
             if (!usable) {
                 next = -2;
                 break;
             }
 
             // ---- nearest-first walk on t_j (Algorithm 2, inference part) ----
-            const double t_tok = cur[xt] * inv_st;
+            const double gx = exp_tab((double)Lane<LT>::glob(grow, xt) - mxg, sh.tab) * inv_sg;
+            const double t_tok = cur_at(xt) * inv_st;
             double carry = 0.0, S = 0.0;
             int a_size = k;
+            int off = 0;
+            for (int j = SNT + tid; j < k; j += SNT)      // entries the walk may never reach count too
+                if ((unsigned)nrow[j] >= (unsigned)V) off = 1;
             for (int base = 0; base < k; base += SNT) {
                 const int j = base + tid;
                 const bool valid = j < k;
-                const int n = valid ? nrow[j] : xt;
+                int n = base == 0 ? nb : valid ? nrow[j] : xt;
+                if (!valid) n = xt;
+                if ((unsigned)n >= (unsigned)V) {
+                    off = 1;
+                    n = xt;
+                }
                 const bool self = (n == xt);
-                const double tj = self ? 0.0 : cur[n] * inv_st;
-                double ctot;
-                const double incl = carry + block_scan_incl<SNW>(tj, sh.red, tid, &ctot);
-                const int fail_j =
-                    (valid && !self && !(prefix_divergence64(a.divergence, t_tok, incl) < delta)) ? j : INT_MAX;
-                const int first = block_min_i<SNW>(fail_j, sh.ired, tid);
+                const double incl_w = wave_scan_incl(self ? 0.0 : cur_at(n) * inv_st);
+                const unsigned long long any_off = __ballot(off != 0);
+                if (lane == WAVE - 1) {
+                    sh.sum_a[wave] = incl_w;
+                    sh.bad[wave] = any_off != 0;
+                }
+                __syncthreads();
+                double before = 0.0, ctot = 0.0;
+                int bad = 0;
+#pragma unroll 4
+                for (int w = 0; w < SNW; ++w) {
+                    if (w == wave) before = ctot;
+                    ctot += sh.sum_a[w];
+                    bad |= sh.bad[w];
+                }
+                if (bad) {   // uniform
+                    usable = false;
+                    break;
+                }
+                const double incl = carry + (before + incl_w);
+                const unsigned long long failing =
+                    __ballot(!self && (a.divergence == 0 ? !(incl < delta) : jsd_fails(t_tok, incl, delta)));
+                const int l = failing ? __ffsll((long long)failing) - 1 : 0;
+                const double up_to = l ? __shfl(incl, l > 0 ? l - 1 : 0, WAVE) : carry + before;
+                if (lane == 0) {
+                    sh.cut[wave] = failing ? base + wave * WAVE + l : INT_MAX;
+                    sh.sum_b[wave] = up_to;               // the sum before the failing slot
+                }
+                __syncthreads();
+                int first = INT_MAX;
+#pragma unroll 4
+                for (int w = SNW - 1; w >= 0; --w)
+                    if (sh.cut[w] != INT_MAX) {
+                        first = sh.cut[w];
+                        S = sh.sum_b[w];
+                    }
                 if (first != INT_MAX) {
                     a_size = first;
-                    if (first == base) {
-                        S = carry;
-                    } else {
-                        if (j == first - 1) sh.bcast[0] = incl;   // the sum before the failing slot
-                        __syncthreads();
-                        S = sh.bcast[0];
-                    }
                     break;
                 }
                 carry += ctot;
                 S = carry;
             }
+            if (!usable) {
+                next = -2;
+                break;
+            }
             const double mass = t_tok + S;
-            const double gx = g[xt] * inv_sg;
-            const double u_acc = (double)a.uniforms[2 * c];
-            const double u_res = (double)a.uniforms[2 * c + 1];
+            const double u_acc = (double)(staged ? sh.u_acc[i] : a.uniforms[2 * c]);
             if (u_acc * gx < mass) {
                 taken = i;
                 break;
             }
 
-            // ---- rejected: distorted target in place, its residual, the draw, t_{j+1} ----
-            __syncthreads();   // every read of t_j by the walk is done
+            // ---- rejected: distorted target in place, then its residual t_{j+1} ----
+            // (the walk's last barrier follows every read of t_j)
             for (int j = tid; j < a_size; j += SNT) {
-                const int n = nrow[j];
-                if (n != xt) cur[n] = 0.0;
+                const int n = j < SNT ? nb : nrow[j];
+                if (n != xt) cur_set(n, 0.0);
             }
-            if (tid == 0) cur[xt] = mass * st;
+            if (tid == 0) cur_set(xt, mass * st);
             __syncthreads();
             double pr = 0.0, pt = 0.0;
-            for (int xb = x0 + lane; xb < x1; xb += WAVE * SU) {
-                double ta[SU], gv[SU];
+            const int l2 = opaque_int(2 * lane);
+            for (int xb = x0; xb < (RES ? x0 + 1 : x1); xb += U * PAIR_STEP) {
+                d2 cv[U], gv[U];
+                if (!RES) {
 #pragma unroll
-                for (int u = 0; u < SU; ++u) {
-                    const int x = xb + u * WAVE;
-                    ta[u] = x < x1 ? cur[x] : 0.0;
-                    gv[u] = x < x1 ? g[x] : 0.0;
+                    for (int u = 0; u < U; ++u) {
+                        const int x = xb + u * PAIR_STEP + l2;
+                        cv[u] = x < x1 ? get2(cur, x) : d2{0.0, 0.0};
+                        gv[u] = x < x1 ? get2(g_mem, x) : d2{0.0, 0.0};
+                    }
                 }
 #pragma unroll
-                for (int u = 0; u < SU; ++u) {
-                    const double tn = ta[u] * inv_st;
-                    const double d = tn - gv[u] * inv_sg;
-                    pr += (d > 0.0) ? d : 0.0;
-                    pt += tn;
+                for (int u = 0; u < U; ++u) {
+                    if (xb + u * PAIR_STEP < x1) {       // uniform over the wavefront
+                        const int x = xb + u * PAIR_STEP + l2;
+                        if (x < x1) {
+                            const d2 ta = RES ? get2(cur, x) : cv[u];
+                            const double g0 = RES ? greg[RES ? 2 * u : 0] : gv[u].x;
+                            const double g1 = RES ? greg[RES ? 2 * u + 1 : 0] : gv[u].y;
+                            const double t0 = fmax(ta.x, 0.0) * inv_st, t1 = fmax(ta.y, 0.0) * inv_st;
+                            const double r0 = t0 - g0 * inv_sg, r1 = t1 - g1 * inv_sg;
+                            pt += t0 + t1;
+                            pr += fmax(r0, 0.0) + fmax(r1, 0.0);
+                            put2(cur, x, r0 > 0.0 ? r0 : -t0, r1 > 0.0 ? r1 : -t1);
+                        }
+                    }
                 }
             }
             pr = wave_sum(pr);
             pt = wave_sum(pt);
             if (lane == 0) {
-                s_wr[wave] = pr;
-                s_wt[wave] = pt;
+                sh.wr[wave] = pr;
+                sh.wt[wave] = pt;
             }
             __syncthreads();
-            double z = 0.0, zt = 0.0, base_r = 0.0, base_t = 0.0;
-#pragma unroll
+            double z = 0.0, zt = 0.0;
+#pragma unroll 4
             for (int w = 0; w < SNW; ++w) {
-                if (w < wave) {
-                    base_r += s_wr[w];
-                    base_t += s_wt[w];
-                }
-                z += s_wr[w];
-                zt += s_wt[w];
+                z += sh.wr[w];
+                zt += sh.wt[w];
             }
-            const bool zero_resid = !(z > 0.0);   // the residual has no mass: the distorted target is sampled
-            const double zz = zero_resid ? zt : z;
-            const double edge = u_res * zz;
-            double run = zero_resid ? base_t : base_r;
-            int found = INT_MAX;
-            for (int xb = x0; xb < x1; xb += WAVE * SU) {   // uniform per wavefront
-                double rx[SU];
-#pragma unroll
-                for (int u = 0; u < SU; ++u) {
-                    const int x = xb + u * WAVE + lane;
-                    const double ta = x < x1 ? cur[x] : 0.0;
-                    const double gv = (x < x1 && !zero_resid) ? g[x] : 0.0;
-                    const double d = ta * inv_st - gv * inv_sg;
-                    rx[u] = (d > 0.0) ? d : 0.0;
-                }
-#pragma unroll
-                for (int u = 0; u < SU; ++u) {
-                    const int x = xb + u * WAVE + lane;
-                    const bool valid = x < x1;
-                    const double incl = run + wave_scan_incl(rx[u]);
-                    const unsigned long long m = __ballot(valid && incl > edge);
-                    if (found == INT_MAX && m) found = xb + u * WAVE + __ffsll((long long)m) - 1;
-                    run = lane63_d(incl);
-                    if (valid) cur[x] = rx[u];   // t_{j+1}, unnormalised: its scale is zz
-                }
+            zero_resid = !(z > 0.0);   // the residual has no mass: the distorted target is sampled
+            if (zero_resid) {          // uniform; it is what the pass left, with the sign turned
+                for (int x = x0 + lane; x < x1; x += WAVE) cur_set(x, fabs(cur[x]));
+                __syncthreads();
             }
+            zz = zero_resid ? zt : z;
             st = zz;
             inv_st = 1.0 / zz;
-            next = block_min_i<SNW>(found, sh.ired, tid);
-            if (next == INT_MAX) next = -1;
-            __syncthreads();   // t_{j+1} is complete
+            u_res = (double)(staged ? sh.u_res[i] : a.uniforms[2 * c + 1]);
         }
-        if (taken < 0) break;   // next: -1 no child, -2 unusable, else the last child's resampled token
+        if (taken < 0) {
+            // next: -1 no child, -2 unusable; with every child rejected, the draw of the last one: the
+            // first token at which the cumulative sum of t_{j+1} exceeds u times its mass
+            if (next == -1 && have_rows) {
+                const double* part = zero_resid ? sh.wt : sh.wr;
+                const double edge = u_res * zz;
+                double run = 0.0, before = 0.0;
+                int owner = -1, last = -1;
+                for (int w = 0; w < SNW; ++w) {
+                    const double p = part[w];
+                    if (p > 0.0) {
+                        if (owner < 0) {
+                            last = w;
+                            before = run;
+                        }
+                        if (owner < 0 && run + p > edge) owner = w;
+                    }
+                    run += p;
+                }
+                if (owner < 0) owner = last;   // rounding left no crossing: the last part with mass
+                if (owner < 0) break;          // no mass at all (sums that are not numbers): next stays -1
+                if (wave == owner) {
+                    int found = -1, last_pos = -1;
+                    for (int xb = x0; xb < x1 && found < 0; xb += PAIR_STEP) {
+                        const int x = xb + 2 * lane;
+                        const d2 v = x < x1 ? get2(cur, x) : d2{0.0, 0.0};
+                        const double r0 = fmax(v.x, 0.0), r1 = fmax(v.y, 0.0);
+                        const double own = r0 + r1;
+                        const double incl = before + wave_scan_incl(own);
+                        const unsigned long long cross = __ballot(own > 0.0 && incl > edge);
+                        const unsigned long long has = __ballot(own > 0.0);
+                        const bool first = r0 > 0.0 && (!(r1 > 0.0) || incl - r1 > edge);
+                        if (cross) found = __shfl(first ? x : x + 1, __ffsll((long long)cross) - 1, WAVE);
+                        if (has) last_pos = __shfl(r1 > 0.0 ? x + 1 : x, 63 - __clzll((long long)has), WAVE);
+                        before = lane63_d(incl);
+                    }
+                    if (lane == 0) sh.drawn = found >= 0 ? found : last_pos;
+                }
+                __syncthreads();
+                next = sh.drawn;
+            }
+            break;
+        }
         if (tid == 0) path[len] = taken;
         len += 1;
         node = taken;
@@ -324,21 +526,28 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
     }
 }
 
-// LDS for the current target: V doubles when they fit beside the static arrays of the kernel.
-constexpr size_t SEQ_LDS_BUDGET = 150 * 1024;
-static size_t sequential_lds_bytes(int V) {
-    const size_t need = (size_t)V * sizeof(double);
-    return need <= SEQ_LDS_BUDGET ? need : 0;
+// The current target in LDS and the drafter's terms in registers as long as V doubles fit beside the
+// kernel's static data: up to 19200 tokens; instantiations of 2, 8 and 10 steps per wavefront, because a
+// step beyond the vocabulary still loads (from a clamped address) and holds four registers per lane.
+constexpr int SEQ_LDS_MAX_V = 150 * 1024 / (int)sizeof(double);
+static_assert(SNW * 10 * PAIR_STEP >= SEQ_LDS_MAX_V, "ten steps cover what fits in LDS");
+static_assert(SEQ_LDS_MAX_V * sizeof(double) + sizeof(SeqShared) <= 160 * 1024, "LDS of a workgroup");
+
+template <typename LT, int NP>
+static hipError_t launch_steps(const SequentialArgs& a, hipStream_t stream, bool launch) {
+    const size_t lds = NP > 0 ? (size_t)a.V * sizeof(double) : 0;
+    const hipError_t e = allow_lds<&trees_sequential<LT, NP>>(lds);
+    if (e != hipSuccess || !launch) return e;
+    hipLaunchKernelGGL((trees_sequential<LT, NP>), dim3(a.B), dim3(SNT), lds, stream, a);
+    return hipGetLastError();
 }
 
 template <typename LT>
-static hipError_t launch_typed(SequentialArgs a, hipStream_t stream, bool launch) {
-    const size_t lds = sequential_lds_bytes(a.V);
-    a.cur_in_lds = lds > 0 ? 1 : 0;
-    const hipError_t e = allow_lds<&trees_sequential<LT>>(lds);
-    if (e != hipSuccess || !launch) return e;
-    hipLaunchKernelGGL((trees_sequential<LT>), dim3(a.B), dim3(SNT), lds, stream, a);
-    return hipGetLastError();
+static hipError_t launch_typed(const SequentialArgs& a, hipStream_t stream, bool launch) {
+    if (a.V <= SNW * 2 * PAIR_STEP) return launch_steps<LT, 2>(a, stream, launch);
+    if (a.V <= SNW * 8 * PAIR_STEP) return launch_steps<LT, 8>(a, stream, launch);
+    if (a.V <= SEQ_LDS_MAX_V) return launch_steps<LT, 10>(a, stream, launch);
+    return launch_steps<LT, 0>(a, stream, launch);
 }
 
 // Loads the kernels on the current device and raises their LDS limit for this vocabulary size.
@@ -347,8 +556,8 @@ hipError_t prepare_sequential(int logits_dtype, int V) {
     a.V = V;
     hipFuncAttributes attr;
     hipError_t e = hipFuncGetAttributes(&attr, logits_dtype == 0
-                                                   ? reinterpret_cast<const void*>(&trees_sequential<float>)
-                                                   : reinterpret_cast<const void*>(&trees_sequential<uint16_t>));
+                                                   ? reinterpret_cast<const void*>(&trees_sequential<float, 0>)
+                                                   : reinterpret_cast<const void*>(&trees_sequential<uint16_t, 0>));
     if (e != hipSuccess) return e;
     return logits_dtype == 0 ? launch_typed<float>(a, nullptr, false) : launch_typed<uint16_t>(a, nullptr, false);
 }

@@ -27,7 +27,6 @@ struct SequentialArgs {
     int32_t* out_path;         // [B*M]
     int32_t* out_next;         // [B]
     double* work;              // [B, 2, V] current target and drafter distribution of every tree
-    int cur_in_lds;            // set by the launch: the current target lives in LDS (V doubles fit)
 };
 
 // One workgroup per tree.  logits_dtype: 0 fp32, 1 bf16.
