@@ -86,6 +86,34 @@ LANTERN_HD double exp_tab(double d, const double* tab) {
     return ldexp(res, n);
 }
 
+// exp_tab for d <= 0 (or -inf, result 0) with fewer instructions: no upper clamp, and the rounding to an
+// integer as in exp_tab_core; the scaling keeps results below the normal range.
+LANTERN_HD double exp_tab_nonpos(double d, const double* tab) {
+    const double INV_STEP = 184.6649652337873;
+    const double STEP_HI = 0x1.62e42fee00000p-8;
+    const double STEP_LO = 0x1.a39ef35793c76p-40;
+    const double MAGIC = 6755399441055744.0;               // 1.5 * 2^52
+#if defined(__HIP_DEVICE_COMPILE__)
+    double c;                                               // fmax would quiet its operands first
+    asm("v_max_f64 %0, %1, %2" : "=v"(c) : "v"(d), "s"(-1000.0));
+    d = c;
+#else
+    d = fmax(d, -1000.0);
+#endif
+    const double t = __builtin_fma(d, INV_STEP, MAGIC);
+    unsigned long long tb;
+    __builtin_memcpy(&tb, &t, 8);
+    const int mi = (int)(unsigned)tb;
+    const double m = t - MAGIC;
+    double r = __builtin_fma(-m, STEP_HI, d);
+    r = __builtin_fma(-m, STEP_LO, r);
+    const int j = mi & 127;
+    const double hi = tab[2 * j], lo = tab[2 * j + 1];
+    const double p = exp_poly5(r);
+    const double res = hi + __builtin_fma(hi, p, lo);
+    return ldexp(res, mi >> 7);
+}
+
 // exp_tab for arguments known to lie in [-700, 700], with fewer instructions: the rounding to an
 // integer is one fused multiply-add onto 1.5 * 2^52 (the integer then sits in the low word of
 // the sum), and the scaling by 2^n is an integer addition to the exponent field (the result

@@ -26,7 +26,8 @@
 //     of the vocabulary holds it;
 //   - a tree's parents, tokens, decisions and draws are staged in LDS, and every wavefront looks for the
 //     next child by itself.
-// V = 16384, k = 1000, 64 trees of 60 candidates: 117 us, from 160 us; the whole step 146 us, from 189 us.
+// V = 16384, k = 1000, 64 trees of 60 candidates: 98 us (117 with the rows
+// unpacked once for both passes, which spills).  Second half of the plain step (PLAIN), one group per tree: 29 us.
 // Vocabularies that do not fit in LDS keep both vectors in the workspace.
 #include <hip/hip_runtime.h>
 #include <limits.h>
@@ -52,6 +53,10 @@ template <> struct RawPair<float> {
     typedef uint32_t raw __attribute__((ext_vector_type(2), aligned(4)));
     __device__ static __forceinline__ float lo(raw v) { return __uint_as_float(v.x); }
     __device__ static __forceinline__ float hi(raw v) { return __uint_as_float(v.y); }
+    __device__ static __forceinline__ raw twice(const float* p) {
+        const uint32_t w = __float_as_uint(*p);
+        return raw{w, w};
+    }
     __device__ static __forceinline__ void opaque(raw& v) {
         uint32_t x = v.x, y = v.y;
         asm("" : "+v"(x), "+v"(y));
@@ -63,6 +68,7 @@ template <> struct RawPair<uint16_t> {
     typedef uint32_t raw __attribute__((aligned(2)));
     __device__ static __forceinline__ float lo(uint32_t v) { return __uint_as_float(v << 16); }
     __device__ static __forceinline__ float hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
+    __device__ static __forceinline__ raw twice(const uint16_t* p) { return *p * 0x10001u; }
     __device__ static __forceinline__ void opaque(raw& v) {
         uint32_t x = v;
         asm("" : "+v"(x));
@@ -95,7 +101,10 @@ struct SeqShared {
 
 // NP > 0: every wavefront's part of the vocabulary is at most NP steps; the current target lives in LDS
 // and the drafter's terms in registers.  NP == 0: any vocabulary, both vectors in the workspace.
-template <typename LT, int NP>
+// PLAIN: the second half of the plain tree step instead (NP > 0, no workspace).  Every child's test is
+// the decision already made; where all children of the last node are rejected, the first one is
+// evaluated once more for its residual and the draw.
+template <typename LT, int NP, bool PLAIN = false>
 __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
     using RP = RawPair<LT>;
     using Raw = typename RP::raw;
@@ -134,7 +143,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         else v[x] = lo;
     };
     double* cur = RES ? seq_cur : cur_mem;
-    double greg[RES ? 2 * NP : 1];
+    double greg[RES ? 2 * NP : 1] = {};
     double inv_st = 0.0, inv_sg = 0.0, st = 0.0, mxg = 0.0;
     const double delta = (double)a.delta;
 
@@ -168,6 +177,24 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         return;
     }
 
+    // node i of a staged tree in slot i / 64 of lane i % 64: the search for a child touches no memory
+    constexpr int SLOTS = SNODES / WAVE;
+    int node_parent[SLOTS], node_accept[SLOTS];
+#pragma unroll
+    for (int q = 0; q < SLOTS; ++q) {
+        const int j = q * WAVE + lane;
+        node_parent[q] = staged && j < M ? sh.parent[j] : INT_MIN;
+        node_accept[q] = staged && j < M ? sh.accept[j] : 0;
+    }
+    auto decision_of = [&](int i) {      // i uniform
+        if (!staged) return (int)a.accept[c0 + i];
+        int d = 0;
+#pragma unroll
+        for (int q = 0; q < SLOTS; ++q)
+            if (i / WAVE == q) d = __builtin_amdgcn_readlane(node_accept[q], i % WAVE);
+        return d;
+    };
+
     int node = -1, len = 0, next = -1;
     for (;;) {   // one sibling group per round; every branch below is uniform over the workgroup
         next = -1;
@@ -179,19 +206,41 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         double u_res = 0.0;          //   its draw,
         bool zero_resid = false;     //   and whether that is the distorted target itself
         int i = node;
+        int first_child = -1;
         for (;;) {
             // the next child: the smallest index above i whose parent is the node
             int child = INT_MAX;
-            for (int base = i + 1; base < M; base += WAVE) {
-                const int q = base + lane;
-                const int p = q < M ? (staged ? sh.parent[q] : par[q]) : INT_MIN;
-                const unsigned long long m = __ballot(p == node);
-                if (m) {
-                    child = base + __ffsll((long long)m) - 1;
-                    break;
+            if (staged) {
+#pragma unroll
+                for (int q = SLOTS - 1; q >= 0; --q) {
+                    const unsigned long long m = __ballot(node_parent[q] == node && q * WAVE + lane > i);
+                    if (m) child = q * WAVE + __ffsll((long long)m) - 1;
+                }
+            } else {
+                for (int base = i + 1; base < M; base += WAVE) {
+                    const int q = base + lane;
+                    const unsigned long long m = __ballot(q < M && par[q] == node);
+                    if (m) {
+                        child = base + __ffsll((long long)m) - 1;
+                        break;
+                    }
                 }
             }
             i = child;
+            if (PLAIN) {
+                if (i != INT_MAX) {
+                    const int decided = decision_of(i);
+                    if (decided == 0) {
+                        if (first_child < 0) first_child = i;
+                        continue;
+                    }
+                    if (decided == 1) taken = i;
+                    else next = -2;                       // an unusable row ends the walk
+                    break;
+                }
+                if (first_child < 0) break;
+                i = first_child;
+            }
             if (i == INT_MAX) break;
             const int64_t c = c0 + i;
             const int r = staged ? sh.row[i] : a.row_index ? a.row_index[c] : (int)c;
@@ -203,7 +252,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 // The first child is tested against t_1 = t itself, which is the plain verification the
                 // row-parallel pass has already decided for every candidate: an accepted first child is
                 // taken without building the group's vectors.
-                const int decided = staged ? sh.accept[i] : a.accept[c];
+                const int decided = PLAIN ? 0 : decision_of(i);
                 if (decided == 1) {
                     taken = i;
                     break;
@@ -227,7 +276,14 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 int bad = 0;
                 const float inf = __builtin_huge_valf();
                 auto load = [&](int xb) {
-                    if (V == 1) return;
+                    if (V == 1) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            tr[u] = RP::twice(trow);
+                            gr[u] = RP::twice(grow);
+                        }
+                        return;
+                    }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int x = min(xb + u * PAIR_STEP + l2, V - 2);
@@ -235,12 +291,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                         gr[u] = *reinterpret_cast<const Raw*>(grow + x);
                     }
                 };
-                auto logits = [&](const Raw& v, const LT* row, int x, float* lo, float* hi) {
-                    if (V == 1) {
-                        *lo = x == 0 ? Lane<LT>::glob(row, 0) : neg_inf_f();
-                        *hi = neg_inf_f();
-                        return;
-                    }
+                auto logits = [&](const Raw& v, int x, float* lo, float* hi) {
                     *lo = x < x1 ? (x + 1 < V ? RP::lo(v) : RP::hi(v)) : neg_inf_f();
                     *hi = x + 1 < x1 ? RP::hi(v) : neg_inf_f();
                 };
@@ -248,11 +299,9 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                     load(xb);
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int x = xb + u * PAIR_STEP + l2;
-                        float l0, l1, h0, h1;
-                        logits(tr[u], trow, x, &l0, &l1);
-                        logits(gr[u], grow, x, &h0, &h1);
-                        if (l0 != l0 || l1 != l1 || h0 != h0 || h1 != h1) bad = 1;
+                        // every pair lies inside the row, moved or not: no bounds in this pass
+                        const float l0 = RP::lo(tr[u]), l1 = RP::hi(tr[u]), h0 = RP::lo(gr[u]), h1 = RP::hi(gr[u]);
+                        if (__builtin_isunordered(l0, l1) || __builtin_isunordered(h0, h1)) bad = 1;
                         mt = fmaxf(mt, fmaxf(l0, l1));
                         mg = fmaxf(mg, fmaxf(h0, h1));
                     }
@@ -292,26 +341,40 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 }
                 for (int xb = x0; xb < (RES ? x0 + 1 : x1); xb += U * PAIR_STEP) {
                     if (!RES) load(xb);
+                    // Two steps a turn, the registers moved down behind them: unrolled in full, this is
+                    // code that a group runs once, and fetching it costs more than the moves.
+#pragma unroll 1
+                    for (int xc = xb; xc < xb + U * PAIR_STEP; xc += 2 * PAIR_STEP) {
+                        double gn[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        if (xb + u * PAIR_STEP < x1) {   // uniform over the wavefront
-                            const int x = xb + u * PAIR_STEP + l2;
-                            float l0, l1, h0, h1;
-                            logits(tr[u], trow, x, &l0, &l1);
-                            logits(gr[u], grow, x, &h0, &h1);
-                            const double t0 = exp_tab((double)l0 - mxt, sh.tab);
-                            const double t1 = exp_tab((double)l1 - mxt, sh.tab);
-                            const double g0 = exp_tab((double)h0 - mxg, sh.tab);
-                            const double g1 = exp_tab((double)h1 - mxg, sh.tab);
-                            zt += t0 + t1;
-                            zg += g0 + g1;
-                            if (x < x1) put2(cur, x, t0, t1);
-                            if (RES) {
-                                greg[2 * u] = g0;
-                                greg[2 * u + 1] = g1;
-                            } else if (x < x1) {
-                                put2(g_mem, x, g0, g1);
+                        for (int u = 0; u < 2; ++u) {
+                            if (xc + u * PAIR_STEP < x1) {   // uniform over the wavefront
+                                const int x = xc + u * PAIR_STEP + l2;
+                                float l0, l1, h0, h1;
+                                logits(tr[u], x, &l0, &l1);
+                                logits(gr[u], x, &h0, &h1);
+                                const double t0 = exp_tab_nonpos((double)l0 - mxt, sh.tab);
+                                const double t1 = exp_tab_nonpos((double)l1 - mxt, sh.tab);
+                                const double g0 = exp_tab_nonpos((double)h0 - mxg, sh.tab);
+                                const double g1 = exp_tab_nonpos((double)h1 - mxg, sh.tab);
+                                zt += t0 + t1;
+                                zg += g0 + g1;
+                                if (x < x1) put2(cur, x, t0, t1);
+                                if (!RES && x < x1) put2(g_mem, x, g0, g1);
+                                gn[2 * u] = g0;
+                                gn[2 * u + 1] = g1;
                             }
+                        }
+#pragma unroll
+                        for (int u = 0; u + 2 < U; ++u) {
+                            tr[u] = tr[u + 2];
+                            gr[u] = gr[u + 2];
+                        }
+                        if (RES) {
+#pragma unroll
+                            for (int q = 0; q + 4 < 2 * NP; ++q) greg[q] = greg[RES ? q + 4 : 0];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) greg[RES ? 2 * NP - 4 + q : 0] = gn[q];
                         }
                     }
                 }
@@ -342,7 +405,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
             }
 
             // ---- nearest-first walk on t_j (Algorithm 2, inference part) ----
-            const double gx = exp_tab((double)Lane<LT>::glob(grow, xt) - mxg, sh.tab) * inv_sg;
+            const double gx = exp_tab_nonpos((double)Lane<LT>::glob(grow, xt) - mxg, sh.tab) * inv_sg;
             const double t_tok = cur_at(xt) * inv_st;
             double carry = 0.0, S = 0.0;
             int a_size = k;
@@ -409,7 +472,8 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
             const double mass = t_tok + S;
             const double u_acc = (double)(staged ? sh.u_acc[i] : a.uniforms[2 * c]);
             if (u_acc * gx < mass) {
-                taken = i;
+                if (PLAIN) have_rows = false;   // nothing to draw from (the decision is made elsewhere)
+                else taken = i;
                 break;
             }
 
@@ -472,6 +536,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
             st = zz;
             inv_st = 1.0 / zz;
             u_res = (double)(staged ? sh.u_res[i] : a.uniforms[2 * c + 1]);
+            if (PLAIN) break;
         }
         if (taken < 0) {
             // next: -1 no child, -2 unusable; with every child rejected, the draw of the last one: the
@@ -481,6 +546,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 const double edge = u_res * zz;
                 double run = 0.0, before = 0.0;
                 int owner = -1, last = -1;
+#pragma unroll 4
                 for (int w = 0; w < SNW; ++w) {
                     const double p = part[w];
                     if (p > 0.0) {
@@ -533,21 +599,22 @@ constexpr int SEQ_LDS_MAX_V = 150 * 1024 / (int)sizeof(double);
 static_assert(SNW * 10 * PAIR_STEP >= SEQ_LDS_MAX_V, "ten steps cover what fits in LDS");
 static_assert(SEQ_LDS_MAX_V * sizeof(double) + sizeof(SeqShared) <= 160 * 1024, "LDS of a workgroup");
 
-template <typename LT, int NP>
+template <typename LT, int NP, bool PLAIN>
 static hipError_t launch_steps(const SequentialArgs& a, hipStream_t stream, bool launch) {
     const size_t lds = NP > 0 ? (size_t)a.V * sizeof(double) : 0;
-    const hipError_t e = allow_lds<&trees_sequential<LT, NP>>(lds);
+    const hipError_t e = allow_lds<&trees_sequential<LT, NP, PLAIN>>(lds);
     if (e != hipSuccess || !launch) return e;
-    hipLaunchKernelGGL((trees_sequential<LT, NP>), dim3(a.B), dim3(SNT), lds, stream, a);
+    hipLaunchKernelGGL((trees_sequential<LT, NP, PLAIN>), dim3(a.B), dim3(SNT), lds, stream, a);
     return hipGetLastError();
 }
 
-template <typename LT>
+template <typename LT, bool PLAIN>
 static hipError_t launch_typed(const SequentialArgs& a, hipStream_t stream, bool launch) {
-    if (a.V <= SNW * 2 * PAIR_STEP) return launch_steps<LT, 2>(a, stream, launch);
-    if (a.V <= SNW * 8 * PAIR_STEP) return launch_steps<LT, 8>(a, stream, launch);
-    if (a.V <= SEQ_LDS_MAX_V) return launch_steps<LT, 10>(a, stream, launch);
-    return launch_steps<LT, 0>(a, stream, launch);
+    if (a.V <= SNW * 2 * PAIR_STEP) return launch_steps<LT, 2, PLAIN>(a, stream, launch);
+    if (a.V <= SNW * 8 * PAIR_STEP) return launch_steps<LT, 8, PLAIN>(a, stream, launch);
+    if (a.V <= SEQ_LDS_MAX_V) return launch_steps<LT, 10, PLAIN>(a, stream, launch);
+    if constexpr (PLAIN) return hipErrorInvalidValue;   // tree_plain_fits tells
+    else return launch_steps<LT, 0, false>(a, stream, launch);
 }
 
 // Loads the kernels on the current device and raises their LDS limit for this vocabulary size.
@@ -559,11 +626,20 @@ hipError_t prepare_sequential(int logits_dtype, int V) {
                                                    ? reinterpret_cast<const void*>(&trees_sequential<float, 0>)
                                                    : reinterpret_cast<const void*>(&trees_sequential<uint16_t, 0>));
     if (e != hipSuccess) return e;
-    return logits_dtype == 0 ? launch_typed<float>(a, nullptr, false) : launch_typed<uint16_t>(a, nullptr, false);
+    e = logits_dtype == 0 ? launch_typed<float, false>(a, nullptr, false) : launch_typed<uint16_t, false>(a, nullptr, false);
+    if (e == hipSuccess && tree_plain_fits(V))
+        e = logits_dtype == 0 ? launch_typed<float, true>(a, nullptr, false) : launch_typed<uint16_t, true>(a, nullptr, false);
+    return e;
 }
 
 hipError_t launch_trees_sequential(const SequentialArgs& a, int logits_dtype, hipStream_t stream) {
-    return logits_dtype == 0 ? launch_typed<float>(a, stream, true) : launch_typed<uint16_t>(a, stream, true);
+    return logits_dtype == 0 ? launch_typed<float, false>(a, stream, true) : launch_typed<uint16_t, false>(a, stream, true);
+}
+
+bool tree_plain_fits(int V) { return V <= SEQ_LDS_MAX_V; }
+
+hipError_t launch_trees_plain(const SequentialArgs& a, int logits_dtype, hipStream_t stream) {
+    return logits_dtype == 0 ? launch_typed<float, true>(a, stream, true) : launch_typed<uint16_t, true>(a, stream, true);
 }
 
 }  // namespace lantern

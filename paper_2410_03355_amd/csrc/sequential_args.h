@@ -32,6 +32,11 @@ struct SequentialArgs {
 // One workgroup per tree.  logits_dtype: 0 fp32, 1 bf16.
 hipError_t launch_trees_sequential(const SequentialArgs& a, int logits_dtype, hipStream_t stream);
 
+// The second half of a plain tree step by the same kernel (work unused): walks every tree over the
+// decisions and draws the one residual the walk asks for, for vocabularies that fit in LDS as doubles.
+bool tree_plain_fits(int V);
+hipError_t launch_trees_plain(const SequentialArgs& a, int logits_dtype, hipStream_t stream);
+
 // Loads the kernels on the current device and raises their LDS limit for this vocabulary size.
 hipError_t prepare_sequential(int logits_dtype, int V);
 

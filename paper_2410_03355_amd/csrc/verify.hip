@@ -30,6 +30,7 @@
 #include "exp_table.h"
 #include "fast_cut.h"
 #include "lds_limit.h"
+#include "sequential_args.h"
 #include "tree_walk.h"
 #include "verify_args.h"
 #include "verify_common.h"
@@ -1214,6 +1215,30 @@ hipError_t launch_resample_selected(const VerifyArgs& a, int logits_dtype, hipSt
 
 hipError_t launch_tree_finish(const VerifyArgs& a, const int32_t* parent, int M, int32_t* out_len, int32_t* out_path,
                               int logits_dtype, hipStream_t stream) {
+    // a vocabulary whose target fits in LDS in fp64 takes the kernel that evaluates every exponential once
+    if (tree_plain_fits(a.V)) {
+        SequentialArgs s{};
+        s.target = a.target;
+        s.draft = a.draft;
+        s.R = a.R;
+        s.V = a.V;
+        s.stride = a.stride;
+        s.row_index = a.row_index;
+        s.parent = parent;
+        s.B = a.n_sel;
+        s.M = M;
+        s.tokens = a.tokens;
+        s.knn = a.knn;
+        s.k = a.k;
+        s.divergence = a.divergence;
+        s.delta = a.delta;
+        s.uniforms = a.uniforms;
+        s.accept = a.out_accept;
+        s.out_len = out_len;
+        s.out_path = out_path;
+        s.out_next = a.out_resample;
+        return launch_trees_plain(s, logits_dtype, stream);
+    }
     if (logits_dtype == 0) return launch_selected_typed<float>(a, parent, M, out_len, out_path, stream);
     return launch_selected_typed<uint16_t>(a, parent, M, out_len, out_path, stream);
 }

@@ -50,3 +50,16 @@ def test_sequential_rule(oracle_mod, lantern_gpu, V, k, B, M, dtype, offset, div
     got = lantern_gpu.verify_trees_sequential(t, d, ri, par, M, tok, tab, 0.05, u, divergence=divergence)
     for g, w in zip(got, want):
         np.testing.assert_array_equal(g.cpu().numpy().reshape(-1), np.asarray(w).reshape(-1))
+
+
+@pytest.mark.parametrize("divergence", ["tvd", "jsd"])
+@pytest.mark.parametrize("V,k,B,M,dtype,offset", SHAPES)
+def test_plain_rule(oracle_mod, lantern_gpu, V, k, B, M, dtype, offset, divergence):
+    (tl, dl, row_index, parent, tokens, table, un), dev = _step(V, k, B, M, dtype, offset, seed=V + k)
+    acc, res, _ = oracle_mod.verify_rows(tl, dl, row_index, tokens, table, k, 0.05, un, threads=8,
+                                         divergence=divergence)
+    want = (acc, *oracle_mod.accept_trees(acc.reshape(B, M), res.reshape(B, M), parent, M))
+    t, d, ri, par, tok, tab, u = dev
+    got = lantern_gpu.verify_trees(t, d, ri, par, M, tok, tab, 0.05, u, divergence=divergence)
+    for g, w in zip(got, want):
+        np.testing.assert_array_equal(g.cpu().numpy().reshape(-1), np.asarray(w).reshape(-1))
