@@ -1216,6 +1216,7 @@ hipError_t launch_resample_selected(const VerifyArgs& a, int logits_dtype, hipSt
 hipError_t launch_tree_finish(const VerifyArgs& a, const int32_t* parent, int M, int32_t* out_len, int32_t* out_path,
                               int logits_dtype, hipStream_t stream) {
     // a vocabulary whose target fits in LDS in fp64 takes the kernel that evaluates every exponential once
+    // (V = 16384 bf16: 27 us for one tree and 33 us for 64, against 30 and 35 us for tree_finish)
     if (tree_plain_fits(a.V)) {
         SequentialArgs s{};
         s.target = a.target;
