@@ -26,7 +26,7 @@
 //     of the vocabulary holds it;
 //   - a tree's parents, tokens, decisions and draws are staged in LDS, and every wavefront looks for the
 //     next child by itself.
-// V = 16384, k = 1000, 64 trees of 60 candidates: 98 us (117 with the rows
+// V = 16384, k = 1000, 64 trees of 60 candidates: 91 us (117 with the rows
 // unpacked once for both passes, which spills).  Second half of the plain step (PLAIN), one group per tree: 29 us.
 // Vocabularies that do not fit in LDS keep both vectors in the workspace.
 #include <hip/hip_runtime.h>
@@ -177,17 +177,19 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         return;
     }
 
-    // node i of a staged tree in slot i / 64 of lane i % 64: the search for a child touches no memory
-    constexpr int SLOTS = SNODES / WAVE;
+    // PLAIN: node i of a staged tree in slot i / 64 of lane i % 64, so that the search for a child touches no
+    // memory (its chain of LDS reads was 3.6 of 28 us); the sequential rule has no registers left for it
+    constexpr int SLOTS = PLAIN ? SNODES / WAVE : 1;
     int node_parent[SLOTS], node_accept[SLOTS];
 #pragma unroll
     for (int q = 0; q < SLOTS; ++q) {
         const int j = q * WAVE + lane;
-        node_parent[q] = staged && j < M ? sh.parent[j] : INT_MIN;
-        node_accept[q] = staged && j < M ? sh.accept[j] : 0;
+        node_parent[q] = PLAIN && staged && j < M ? sh.parent[j] : INT_MIN;
+        node_accept[q] = PLAIN && staged && j < M ? sh.accept[j] : 0;
     }
     auto decision_of = [&](int i) {      // i uniform
         if (!staged) return (int)a.accept[c0 + i];
+        if (!PLAIN) return sh.accept[i];
         int d = 0;
 #pragma unroll
         for (int q = 0; q < SLOTS; ++q)
@@ -210,7 +212,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         for (;;) {
             // the next child: the smallest index above i whose parent is the node
             int child = INT_MAX;
-            if (staged) {
+            if (PLAIN && staged) {
 #pragma unroll
                 for (int q = SLOTS - 1; q >= 0; --q) {
                     const unsigned long long m = __ballot(node_parent[q] == node && q * WAVE + lane > i);
@@ -219,7 +221,8 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
             } else {
                 for (int base = i + 1; base < M; base += WAVE) {
                     const int q = base + lane;
-                    const unsigned long long m = __ballot(q < M && par[q] == node);
+                    const int p = q < M ? (staged ? sh.parent[q] : par[q]) : INT_MIN;
+                    const unsigned long long m = __ballot(p == node);
                     if (m) {
                         child = base + __ffsll((long long)m) - 1;
                         break;
