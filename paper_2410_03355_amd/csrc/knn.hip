@@ -29,6 +29,7 @@
 
 #include "device_utils.h"
 #include "knn_args.h"
+#include "knn_plan.h"
 #include "lantern.h"
 #include "lds_sort.h"
 
@@ -49,89 +50,6 @@ constexpr int CAND_CAP = 4096;    // candidate slots per row held in LDS
 constexpr int SLOW_WGS = 128;     // workgroups (and fp64 row buffers) of the exact pass
 
 __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
-// Tails of the binomial law of n trials with success probability p, summed term by term from the
-// given end (the terms fall off geometrically there): P(X >= r) and P(X <= r).
-static double binomial_log_pmf(int n, double p, int x) {
-    return lgamma((double)n + 1.0) - lgamma((double)x + 1.0) - lgamma((double)(n - x) + 1.0) + (double)x * log(p) +
-           (double)(n - x) * log1p(-p);
-}
-static double binomial_upper_tail(int n, double p, int r) {
-    if (r <= 0) return 1.0;
-    if (r > n) return 0.0;
-    double term = exp(binomial_log_pmf(n, p, r)), sum = 0.0;
-    for (int x = r; x <= n && (term > 1e-300 || x < (int)(n * p)); ++x) {
-        sum += term;
-        term *= (double)(n - x) / (double)(x + 1) * p / (1.0 - p);
-        if (x > (int)(n * p) && term < sum * 1e-17) break;
-    }
-    return sum;
-}
-static double binomial_lower_tail(int n, double p, int r) {
-    if (r < 0) return 0.0;
-    if (r >= n) return 1.0;
-    double term = exp(binomial_log_pmf(n, p, r)), sum = 0.0;
-    for (int x = r; x >= 0; --x) {
-        sum += term;
-        if (x == 0) break;
-        term *= (double)x / (double)(n - x + 1) * (1.0 - p) / p;
-        if (x < (int)(n * p) && term < sum * 1e-17) break;
-    }
-    return sum;
-}
-
-// Plan of the sampled-threshold path for one shape.  A row's threshold has between `rank` and
-// `rank + slack` of the row's keys to `S` sampled tokens at or below it.  The row's list is too short
-// (fewer than the k-1+pad candidates the selection wants) only if at least rank - 1 of the sampled
-// tokens are among the row's k-2+pad nearest, and too long for its `cap` slots only if at most
-// rank + slack of them are among its cap+1 nearest (the row's own token may be in the sample: hence
-// the - 1).  The sample takes one token from each of S strata of the vocabulary, so the number of
-// sampled tokens in a given set is a sum of independent trials, whose tails are no heavier than
-// those of the binomial law with the same mean (Hoeffding): `rank` is the smallest and `cap` the
-// smallest of 1024 .. 4096 for which that bound puts either miss below 1e-10 per row, whatever
-// the codebook.  A row that misses all the same is flagged and ranked by the all-pairs pass.
-// use == false: the shape takes the whole-key-block path.
-struct FilterPlan {
-    bool use;
-    int S;      // sampled tokens, a multiple of 64, at most 4096
-    int rank;   // the threshold has between rank and rank + slack of a row's S sample keys at or below it
-    int slack;
-    int cap;    // slots of a row's candidate list: 1024, 2048, 3072 or 4096
-};
-
-static FilterPlan filter_plan(int V, int d, int k, int cb_dtype) {
-    FilterPlan P = {false, 0, 0, 0, 0};
-    const bool vec = cb_dtype == 1 ? (d % 8) == 0 : (d % 4) == 0;   // what the matrix-core kernels need
-    const int need = k - 1;
-    const int want = need + 8 + need / 128;
-    // 64 candidates or fewer: the lists would be several times longer than what the selection wants
-    if (!vec || V < 4096 || want <= 64 || want > 1024) return P;
-    int S = V / 8;
-    if (S > 4096) S = 4096;
-    S = S / 64 * 64;
-    const double miss = 1e-10;
-    const double others = (double)(V - 1);
-    // too short: Binomial(S, (want - 1) / (V - 1)) >= rank - 1
-    const double p_lo = (double)(want - 1) / others;
-    int rank = (int)(S * p_lo) + 2;
-    while (rank < S && binomial_upper_tail(S, p_lo, rank - 1) > miss) ++rank;
-    if (rank >= S) return P;
-    // the search for the threshold stops anywhere between rank and rank + slack (a sixteenth more)
-    const int slack = rank / 16 < S - rank ? rank / 16 : S - rank;
-    // too long: Binomial(S, (cap + 1) / (V - 1)) <= rank + slack
-    int cap = 0;
-    for (int c = 1024; c <= 4096 && cap == 0; c += 1024) {
-        const double p_hi = (double)(c + 1) / others;
-        if (p_hi >= 1.0 || binomial_lower_tail(S, p_hi, rank + slack) <= miss) cap = c;
-    }
-    if (cap == 0) return P;
-    P.use = true;
-    P.S = S;
-    P.rank = rank;
-    P.slack = slack;
-    P.cap = cap;
-    return P;
-}
 
 // The sampled-threshold path reads its operands from copies in the order in which the matrix cores
 // take them: 32 tokens to a tile, and per tile and step (16 bf16 or 8 fp32 coordinates) the 16 bytes of
@@ -957,7 +875,8 @@ __device__ __forceinline__ void for_keys(int npt, F body) {
 // LIST: the row's keys are not a row of the key block but its candidate list of the filtering
 // contraction, list.counts[row] pairs (key, token) with NK * TNT >= list.cap; every token not on
 // the list has an approximate key above every key on it, so the proof below reads the same.  A
-// list that was cut at its capacity, or is shorter than the selection wants, flags the row.
+// list that was cut at its capacity, is longer than the registers hold (the proof takes every listed
+// token for seen), or is shorter than the selection wants, flags the row.
 template <typename CT, int NK, int CAP, int TNT, bool LIST>
 __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(const CT* cb, int V, int d, int k, int metric, int r0,
                                                  const float* dist, FilterOut list, float err_rel, float err_abs,
@@ -998,7 +917,7 @@ __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(con
     uint32_t toks[LIST ? NKR : 1];
     const int npt = NK > 0 ? NK : (V + TNT - 1) / TNT;   // keys per thread
     const int listed = LIST ? list.counts[row] : 0;
-    if (LIST && (listed > list.cap || listed < want)) {
+    if (LIST && (listed > min(list.cap, NK * TNT) || listed < want)) {
         if (tid == 0) flags[row] = 1;
         return;
     }
@@ -1423,12 +1342,15 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
             else if (plan.S <= 32 * WAVE) launch_sample_rank<32>(skeys, plan, rows, const_cast<float*>(fo.thr), fo.counts, stream);
             else launch_sample_rank<64>(skeys, plan, rows, const_cast<float*>(fo.thr), fo.counts, stream);
             filter(r0, rows);
-            // a list of cap slots on 256 threads: cap / 256 pairs per thread; 64 < want_slots <= 1024
+            static_assert(LIST_THREADS == NT, "threads per row of the selection from lists");
+            const int pairs = list_pairs(want_slots, plan.cap);   // 64 < want_slots <= 1024
             if (want_slots <= 256) {
-                if (plan.cap <= 4 * NT) LANTERN_LAUNCH_SELECT(4, 256, NT, true);
-                else LANTERN_LAUNCH_SELECT(8, 256, NT, true);
-            } else if (plan.cap <= 8 * NT) LANTERN_LAUNCH_SELECT(8, 1024, NT, true);
-            else if (plan.cap <= 12 * NT) LANTERN_LAUNCH_SELECT(12, 1024, NT, true);
+                if (pairs == 4) LANTERN_LAUNCH_SELECT(4, 256, NT, true);
+                else if (pairs == 8) LANTERN_LAUNCH_SELECT(8, 256, NT, true);
+                else if (pairs == 12) LANTERN_LAUNCH_SELECT(12, 256, NT, true);
+                else LANTERN_LAUNCH_SELECT(16, 256, NT, true);
+            } else if (pairs == 8) LANTERN_LAUNCH_SELECT(8, 1024, NT, true);
+            else if (pairs == 12) LANTERN_LAUNCH_SELECT(12, 1024, NT, true);
             else LANTERN_LAUNCH_SELECT(16, 1024, NT, true);
         } else {
             if (mfma)

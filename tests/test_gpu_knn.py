@@ -151,6 +151,27 @@ def test_sampled_threshold_path_falls_back(oracle_mod, lantern_gpu):
     np.testing.assert_array_equal(got.cpu().numpy(), oracle_mod.build_knn(cb.cpu().numpy(), k, threads=16))
 
 
+@pytest.mark.parametrize("V,k,crowd", [(84000, 240, 2600), (200000, 100, 3700)])
+def test_long_lists_of_narrow_tables(oracle_mod, lantern_gpu, V, k, crowd):
+    """Narrow tables of large vocabularies: candidate lists of 3072 and 4096 slots beside 256 selected.  `crowd`
+    codes near the origin, none of them in the token sample, and 60 sampled codes around them: the threshold of
+    every row of the crowd lies at those 60, and its list holds the whole crowd."""
+    S = 4096                                                     # of the token sample at these vocabularies
+    s = np.arange(S, dtype=np.int64)
+    sample = np.minimum((s * V + ((((s * 2654435761) & 0xFFFFFFFF) >> 16) * V >> 16)) // S, V - 1)
+    others = np.setdiff1d(np.arange(V // 2, V), sample)[:crowd]
+    rng = np.random.default_rng(V)
+    cb = rng.standard_normal((V, 8)) * 10 + 60
+    cb[others] = rng.standard_normal((crowd, 8)) * 0.05
+    shell = rng.standard_normal((60, 8))
+    cb[sample[:60]] = shell / np.linalg.norm(shell, axis=1, keepdims=True)
+    cb = cb.astype(np.float32)
+    got = _gpu_table(lantern_gpu, torch.from_numpy(cb), k, max_exact_rows=256)   # the shell's rows may be among them
+    rows = (int(others[0]), int(others[0]) + 120)
+    want = oracle_mod.build_knn(cb, k, rows=rows, threads=16)
+    np.testing.assert_array_equal(got[rows[0]:rows[1]], want)
+
+
 def test_exact_ties_and_duplicates(oracle_mod, lantern_gpu):
     """Integer lattice (many exactly equal distances) and repeated codes: the
     lower index wins and the token itself stays in slot 0."""
