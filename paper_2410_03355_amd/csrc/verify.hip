@@ -52,7 +52,7 @@ struct FastShared {
 static_assert(sizeof(FastShared<4>) % 16 == 0 && sizeof(FastShared<8>) % 16 == 0 && sizeof(FastShared<16>) % 16 == 0,
               "the exact path's LDS region must be 16-byte aligned");
 
-template <typename LT, bool VEC, int TNT = NT>
+template <typename LT, int FORM, int TNT = NT>
 __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned char* ex, const unsigned char* lds_row,
                           bool have_max, float max_t, float max_g, const unsigned char* lds_grow = nullptr);
 
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(TNT, 4) void verify_fast(VerifyArgs a) {
                 done = exact_one_pass<LT, TNT, NV, FULL>(a, row, lrow, m.nb, rt, rg, Zt, Zg, a_size, xt, m.lg_tok,
                                                          m.u_acc, smem, ex_lds, s_row);
             // one call, so that it is inlined: as a function its argument block goes through memory
-            if (!done) exact_row<LT, FULL, TNT>(a, row, ex_lds, s_row, false, 0.f, 0.f);
+            if (!done) exact_row<LT, FULL ? ROW_WHOLE : ROW_ANY, TNT>(a, row, ex_lds, s_row, false, 0.f, 0.f);
         }
     }
 }
@@ -724,7 +724,7 @@ __device__ __forceinline__ double resid_term(int x, int xt, int V, float lt, flo
 // TNT: threads of the calling workgroup.  Token order of the vector layout: vector vi = chunk*TNT + tid, so (chunk,
 // wavefront, lane, element) is ascending token order.  Every pass over the row
 // loads the next chunk's vectors before it works on the current one.
-template <typename LT, bool VEC, int TNT>
+template <typename LT, int FORM, int TNT>
 __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned char* ex, const unsigned char* lds_row,
                           bool have_max, float max_t, float max_g, const unsigned char* lds_grow) {
     constexpr int TNW = TNT / WAVE;
@@ -768,15 +768,15 @@ __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned
         mgf = max_g;
     } else {
         float tn[EPV], gn[EPV];
-        VecLoad<LT, VEC>::load(trow, lds_row, tid, V, tn);
-        VecLoad<LT, VEC>::load(grow, lds_grow, tid, V, gn);
+        VecLoad<LT, FORM>::load(trow, lds_row, tid, V, tn);
+        VecLoad<LT, FORM>::load(grow, lds_grow, tid, V, gn);
         for (int c = 0; c < nchunk; ++c) {
             float tf[EPV], gf[EPV];
 #pragma unroll
             for (int e = 0; e < EPV; ++e) { tf[e] = tn[e]; gf[e] = gn[e]; }
             if (c + 1 < nchunk) {
-                VecLoad<LT, VEC>::load(trow, lds_row, (c + 1) * TNT + tid, V, tn);
-                VecLoad<LT, VEC>::load(grow, lds_grow, (c + 1) * TNT + tid, V, gn);
+                VecLoad<LT, FORM>::load(trow, lds_row, (c + 1) * TNT + tid, V, tn);
+                VecLoad<LT, FORM>::load(grow, lds_grow, (c + 1) * TNT + tid, V, gn);
             }
 #pragma unroll
             for (int e = 0; e < EPV; ++e) {
@@ -811,15 +811,15 @@ __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned
     double zt = 0.0, zg = 0.0;
     {
         float tn[EPV], gn[EPV];
-        VecLoad<LT, VEC>::load(trow, lds_row, tid, V, tn);
-        VecLoad<LT, VEC>::load(grow, lds_grow, tid, V, gn);
+        VecLoad<LT, FORM>::load(trow, lds_row, tid, V, tn);
+        VecLoad<LT, FORM>::load(grow, lds_grow, tid, V, gn);
         for (int c = 0; c < nchunk; ++c) {
             float tf[EPV], gf[EPV];
 #pragma unroll
             for (int e = 0; e < EPV; ++e) { tf[e] = tn[e]; gf[e] = gn[e]; }
             if (c + 1 < nchunk) {
-                VecLoad<LT, VEC>::load(trow, lds_row, (c + 1) * TNT + tid, V, tn);
-                VecLoad<LT, VEC>::load(grow, lds_grow, (c + 1) * TNT + tid, V, gn);
+                VecLoad<LT, FORM>::load(trow, lds_row, (c + 1) * TNT + tid, V, tn);
+                VecLoad<LT, FORM>::load(grow, lds_grow, (c + 1) * TNT + tid, V, gn);
             }
             double st = 0.0, sg = 0.0;
 #pragma unroll
@@ -880,16 +880,16 @@ __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned
         // per (chunk, wavefront) partial sums of the residual, in token order
         {
             float tn[EPV], gn[EPV];
-            VecLoad<LT, VEC>::load(trow, lds_row, tid, V, tn);
-            VecLoad<LT, VEC>::load(grow, lds_grow, tid, V, gn);
+            VecLoad<LT, FORM>::load(trow, lds_row, tid, V, tn);
+            VecLoad<LT, FORM>::load(grow, lds_grow, tid, V, gn);
             for (int c = 0; c < nchunk; ++c) {
                 const int vi = c * TNT + tid;
                 float tf[EPV], gf[EPV];
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) { tf[e] = tn[e]; gf[e] = gn[e]; }
                 if (c + 1 < nchunk) {
-                    VecLoad<LT, VEC>::load(trow, lds_row, vi + TNT, V, tn);
-                    VecLoad<LT, VEC>::load(grow, lds_grow, vi + TNT, V, gn);
+                    VecLoad<LT, FORM>::load(trow, lds_row, vi + TNT, V, tn);
+                    VecLoad<LT, FORM>::load(grow, lds_grow, vi + TNT, V, gn);
                 }
                 double s = 0.0;
 #pragma unroll
@@ -933,8 +933,8 @@ __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned
             const int c = ent / TNW;
             const int vi = c * TNT + tid;
             float tf[EPV], gf[EPV];
-            VecLoad<LT, VEC>::load(trow, lds_row, vi, V, tf);
-            VecLoad<LT, VEC>::load(grow, lds_grow, vi, V, gf);
+            VecLoad<LT, FORM>::load(trow, lds_row, vi, V, tf);
+            VecLoad<LT, FORM>::load(grow, lds_grow, vi, V, gf);
             double r[EPV];
             double s = 0.0;
 #pragma unroll
@@ -973,7 +973,7 @@ __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned
 template <typename LT>
 __global__ __launch_bounds__(NT) void verify_exact(VerifyArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    exact_row<LT, false>(a, verification_of_block(blockIdx.x, a.N, a.row_index != nullptr), smem, nullptr, false, 0.f, 0.f);
+    exact_row<LT, ROW_ELEMENTS>(a, verification_of_block(blockIdx.x, a.N, a.row_index != nullptr), smem, nullptr, false, 0.f, 0.f);
 }
 
 // VERIFY_SELECTED: workgroup i evaluates verification select[i] and writes out_resample[i].
@@ -1006,7 +1006,7 @@ __device__ __forceinline__ void selected_row(const VerifyArgs& a, int v, unsigne
         lds_t = st;
         lds_g = sg;
     }
-    exact_row<LT, VEC, SEL_NT>(a, v, smem, lds_t, false, 0.f, 0.f, lds_g);
+    exact_row<LT, VEC ? ROW_WHOLE : ROW_ELEMENTS, SEL_NT>(a, v, smem, lds_t, false, 0.f, 0.f, lds_g);
 }
 
 // VERIFY_SELECTED: workgroup i evaluates verification select[i] and writes out_resample[i].

@@ -244,58 +244,55 @@ __device__ __forceinline__ double block_scan_incl(double v, double* red, int tid
 
 // The exact path walks a row four logits per lane at a time (8-byte loads for
 // bf16, 16-byte loads for fp32): vector vi covers tokens [4 vi, 4 vi + 4).
-// Tokens at or beyond V read as -inf.  With VEC the row is 16-byte aligned and
-// V a multiple of four; lds, when not null, holds the same row in LDS.
+// Tokens at or beyond V read as -inf.  lds, when not null, holds the same row in LDS.
+//   ROW_WHOLE     the row is 16-byte aligned and V a multiple of four
+//   ROW_ANY       any address and any V (a last, partial vector element by element); a row in LDS is aligned and
+//                 padded with -inf to whole vectors
+//   ROW_ELEMENTS  any row, element by element from memory (lds is not looked at)
 constexpr int EXV = 4;
+enum RowForm { ROW_ELEMENTS = 0, ROW_WHOLE = 1, ROW_ANY = 2 };
 
-template <typename LT, bool VEC>
-struct VecLoad;
+// Four logits: from an address aligned to the element only, and vector vi of an aligned row.
+__device__ __forceinline__ void load4_any(const float* p, float (&o)[EXV]) {
+    const uint4 v = load16_any(p);
+    o[0] = __uint_as_float(v.x); o[1] = __uint_as_float(v.y);
+    o[2] = __uint_as_float(v.z); o[3] = __uint_as_float(v.w);
+}
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+__device__ __forceinline__ void unpack4(uint32_t lo, uint32_t hi, float (&o)[EXV]) {
+    o[0] = __uint_as_float(lo << 16); o[1] = __uint_as_float(lo & 0xFFFF0000u);
+    o[2] = __uint_as_float(hi << 16); o[3] = __uint_as_float(hi & 0xFFFF0000u);
+}
+__device__ __forceinline__ void load4_any(const uint16_t* p, float (&o)[EXV]) {
+    const u32x2_any v = *reinterpret_cast<const u32x2_any*>(p);
+    unpack4(v.x, v.y, o);
+}
+__device__ __forceinline__ void load4_vector(const float* p, int vi, float (&o)[EXV]) {
+    const float4 v = reinterpret_cast<const float4*>(p)[vi];
+    o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
+}
+__device__ __forceinline__ void load4_vector(const uint16_t* p, int vi, float (&o)[EXV]) {
+    const uint2 v = reinterpret_cast<const uint2*>(p)[vi];
+    unpack4(v.x, v.y, o);
+}
 
-template <bool VEC>
-struct VecLoad<float, VEC> {
-    __device__ static __forceinline__ void load(const float* row, const unsigned char* lds, int vi, int V,
+template <typename LT, int FORM>
+struct VecLoad {
+    __device__ static __forceinline__ void load(const LT* row, const unsigned char* lds, int vi, int V,
                                                 float (&out)[EXV]) {
-        if (VEC) {
-            if ((vi + 1) * EXV <= V) {
-                const float4 v = lds ? reinterpret_cast<const float4*>(lds)[vi]
-                                     : reinterpret_cast<const float4*>(row)[vi];
-                out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
+        if (FORM != ROW_ELEMENTS) {
+            const bool whole = (vi + 1) * EXV <= V;
+            if (whole || (FORM == ROW_ANY && lds && vi * EXV < V)) {
+                if (lds) load4_vector(reinterpret_cast<const LT*>(lds), vi, out);
+                else if (FORM == ROW_WHOLE) load4_vector(row, vi, out);
+                else load4_any(row + vi * EXV, out);
                 return;
-            }
-#pragma unroll
-            for (int e = 0; e < EXV; ++e) out[e] = neg_inf_f();
-        } else {
-#pragma unroll
-            for (int e = 0; e < EXV; ++e) {
-                const int x = vi * EXV + e;
-                out[e] = x < V ? row[x] : neg_inf_f();
             }
         }
-    }
-};
-
-template <bool VEC>
-struct VecLoad<uint16_t, VEC> {
-    __device__ static __forceinline__ void load(const uint16_t* row, const unsigned char* lds, int vi, int V,
-                                                float (&out)[EXV]) {
-        if (VEC) {
-            if ((vi + 1) * EXV <= V) {
-                const uint2 v = lds ? reinterpret_cast<const uint2*>(lds)[vi]
-                                    : reinterpret_cast<const uint2*>(row)[vi];
-                out[0] = __uint_as_float(v.x << 16);
-                out[1] = __uint_as_float(v.x & 0xFFFF0000u);
-                out[2] = __uint_as_float(v.y << 16);
-                out[3] = __uint_as_float(v.y & 0xFFFF0000u);
-                return;
-            }
 #pragma unroll
-            for (int e = 0; e < EXV; ++e) out[e] = neg_inf_f();
-        } else {
-#pragma unroll
-            for (int e = 0; e < EXV; ++e) {
-                const int x = vi * EXV + e;
-                out[e] = x < V ? Lane<uint16_t>::glob(row, x) : neg_inf_f();
-            }
+        for (int e = 0; e < EXV; ++e) {
+            const int x = vi * EXV + e;
+            out[e] = FORM != ROW_WHOLE && x < V ? Lane<LT>::glob(row, x) : neg_inf_f();
         }
     }
 };

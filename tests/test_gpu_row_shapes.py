@@ -61,3 +61,98 @@ def test_filtered_and_unusable_rows(oracle_mod, lantern_gpu, dtype, V):
     np.testing.assert_array_equal(got_acc.cpu().numpy(), acc)
     np.testing.assert_array_equal(got_res.cpu().numpy(), res)
     assert list(acc[2:5]) == [-1, -1, -1]
+
+
+# Rows that the fp32 pass leaves to the fp64 one: a constant target, and a bound that the k/2-th table slot meets to
+# within the rounding of a float, so that the cut cannot be told in fp32.
+UNSETTLED = {torch.bfloat16: [8, 11, 2047, 4100, 12288, 12291, 16384, 16389, 32763, 40003, 65535],
+             torch.float32: [4, 7, 1023, 6144, 8190, 8192, 8195, 16381, 20002, 32766]}
+
+
+@pytest.mark.parametrize("divergence", ["tvd", "jsd"])
+@pytest.mark.parametrize("start", [0, 3])
+@pytest.mark.parametrize("dtype,V", [(dt, V) for dt, sizes in UNSETTLED.items() for V in sizes])
+def test_rows_that_fp32_cannot_settle(oracle_mod, lantern_gpu, dtype, V, start, divergence):
+    N, k = 6, min(V, 81)                     # an odd width: also rows that are whole vectors take the general kernel
+    _, draft, tokens, table, uniforms = _inputs(V, k, N, dtype, start, 3 * V + start)
+    target = torch.full_like(draft, 0.75)
+    target[:, :start] = float("nan")         # outside the rows: must not be looked at
+    target[:, start + V:] = float("nan")
+    uniforms[1::2, 0] = 0.25
+    m = k // 2
+    if divergence == "tvd":
+        delta = float(np.float32(m / V))
+    else:
+        t0, moved = 1.0 / V, m / V
+        mid = t0 + moved / 2
+        kl_a = (t0 + moved) * np.log((t0 + moved) / mid)
+        delta = float(np.float32(0.5 * (kl_a + t0 * np.log(t0 / mid) + moved * np.log(2.0))))
+    dev = [x.cuda() for x in (target, draft, tokens, table, uniforms)]
+    t_dev, g_dev = dev[0][:, start:start + V], dev[1][:, start:start + V]
+    acc, res, _ = oracle_mod.verify(target[:, start:start + V].contiguous(), draft[:, start:start + V].contiguous(),
+                                    tokens, table.numpy(), k, delta, uniforms, threads=6, divergence=divergence)
+    decided, path = lantern_gpu.decide_rows(t_dev, g_dev, None, dev[2], dev[3], delta, dev[4], divergence=divergence,
+                                            want_path=True)
+    np.testing.assert_array_equal(decided.cpu().numpy(), acc)
+    assert path.cpu().tolist() == [1] * N
+    if divergence == "tvd":
+        got_acc, got_res = lantern_gpu.verify(t_dev, g_dev, dev[2], dev[3], delta, dev[4])
+    else:
+        index = torch.arange(N, dtype=torch.int32, device="cuda")
+        got_acc, got_res = lantern_gpu.verify_rows(t_dev, g_dev, index, dev[2], dev[3], delta, dev[4], divergence="jsd")
+    np.testing.assert_array_equal(got_acc.cpu().numpy(), acc)
+    np.testing.assert_array_equal(got_res.cpu().numpy(), res)
+
+
+@pytest.mark.parametrize("dtype,V,k", [(torch.bfloat16, 16392, 2049), (torch.bfloat16, 16387, 8192),
+                                       (torch.float32, 8200, 3075), (torch.bfloat16, 32776, 4097),
+                                       (torch.float32, 16390, 8191)])
+def test_cuts_beyond_four_slots_per_thread(oracle_mod, lantern_gpu, dtype, V, k):
+    """Tables wider than the slots that 512 and 1024 threads scan together, the cut in the part beyond."""
+    start, N = 1, 4
+    target, draft, tokens, table, uniforms = _inputs(V, k, N, dtype, start, V + k)
+    target[:2] = 0.5
+    uniforms[1, 0] = 0.25
+    dev = [x.cuda() for x in (target, draft, tokens, table, uniforms)]
+    t_dev, g_dev = dev[0][:, start:start + V], dev[1][:, start:start + V]
+    for delta in ((k - 0.5) / V, (k + 3) / V, 0.6 * k / V):
+        acc, res, _ = oracle_mod.verify(target[:, start:start + V].contiguous(), draft[:, start:start + V].contiguous(),
+                                        tokens, table.numpy(), k, delta, uniforms, threads=6)
+        got_acc, got_res = lantern_gpu.verify(t_dev, g_dev, dev[2], dev[3], delta, dev[4])
+        np.testing.assert_array_equal(got_acc.cpu().numpy(), acc)
+        np.testing.assert_array_equal(got_res.cpu().numpy(), res)
+
+
+def _replay_us(call):
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(10):
+            call()
+    times = []
+    for _ in range(9):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        graph.replay()
+        end.record()
+        torch.cuda.synchronize()
+        times.append(begin.elapsed_time(end) * 100)
+    return sorted(times)[len(times) // 2]
+
+
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 16384), (torch.float32, 8192)])
+def test_unsettled_rows_cost_the_same_in_every_kernel(lantern_gpu, dtype, V):
+    """The fp64 pass of a row in the general kernel (odd table width) against the one for whole rows: both read
+    vectors, so the first takes 3 to 12 % longer; element by element it took 1.70 (bf16) and 1.36 (fp32) times as long."""
+    N = 960
+    draft = torch.randn(N, V, device="cuda").to(dtype)
+    target = torch.zeros(N, V, device="cuda", dtype=dtype)
+    tokens = draft.float().argmax(dim=1).to(torch.int32)
+    uniforms = torch.full((N, 2), 0.5, device="cuda")
+    took = {}
+    for k in (80, 81):
+        table = ((torch.arange(V, device="cuda")[:, None] + torch.arange(k, device="cuda")[None, :]) % V).to(torch.int32)
+        lantern_gpu.prepare(dtype, V, k)
+        took[k] = _replay_us(lambda: lantern_gpu.decide_rows(target, draft, None, tokens, table, 40 / V, uniforms))
+    assert took[81] < 1.25 * took[80]
