@@ -56,6 +56,12 @@ template <typename LT, int FORM, int TNT = NT>
 __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned char* ex, const unsigned char* lds_row,
                           bool have_max, float max_t, float max_g, const unsigned char* lds_grow = nullptr);
 
+// What a kernel of the fp32 pass knows about its rows.
+//   ROWS_FULL   16-byte aligned, and every vector slot of every thread is filled: no bounds checks
+//   ROWS_WHOLE  16-byte aligned whole vectors, not every slot filled: slots beyond the row are not loaded
+//   ROWS_ANY    any address and any length of at least one vector: every slot is loaded, clamped to the row
+enum RowsKnown { ROWS_FULL, ROWS_WHOLE, ROWS_ANY };
+
 // ---------------------------------------------------------------------------
 // fp64 evaluation of a row in one pass, with what the fp32 pass already knows
 // ---------------------------------------------------------------------------
@@ -91,11 +97,11 @@ struct OnePassLayout {
 // The exponential's table sits at the very start of the workgroup's LDS (before the row): the
 // address of a lookup is then the masked integer itself, with no base to add.
 constexpr int EXP_TABLE_BYTES = 2 * EXP_TABLE_N * (int)sizeof(double);
-__host__ __device__ inline OnePassLayout one_pass_layout(int V, int threads) {
+__host__ __device__ inline OnePassLayout one_pass_layout(int V, int segments) {
     OnePassLayout L;
     size_t off = (sizeof(ExactShared) + 15) & ~size_t(15);
     L.mask = off;      off += (((size_t)V + 31) / 32) * 4;  off = (off + 15) & ~size_t(15);
-    L.seg = off;       off += 8 * (threads / WAVE) * 2 * sizeof(double);   // up to 8 vector chunks per thread
+    L.seg = off;       off += (size_t)segments * 2 * sizeof(double);
     L.amb = off;       off += AMB_CAP * sizeof(AmbEntry);
     L.amb_count = off; off += 16;
     L.total = off;
@@ -159,7 +165,7 @@ __device__ __forceinline__ void one_pass_token(OnePassAcc& acc, float lt, float 
 // its sums; a_size: its (definite) cut.
 // tab_lds: where the exponential's table goes in LDS.
 // Returns false (the same in every thread) when the row is left to the general path.
-template <typename LT, int TNT, int NV, bool FULL>
+template <typename LT, int TNT, int NV, int ROWS>
 __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int lrow,
                                                const int (&nb)[4], float ref_t, float ref_g,
                                                float Zt32, float Zg32, int a_size, int xt, float lg_tok, float u_acc32,
@@ -168,6 +174,7 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
     using L = Lane<LT>;
     constexpr int EPV = L::EPV;
     constexpr int TNW = TNT / WAVE;
+    constexpr bool FULL = ROWS == ROWS_FULL;
     constexpr int NSEG = NV * TNW;                           // one wavefront scans them, 64 at a time
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
@@ -175,7 +182,7 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
     const int V = a.V;
     const int k = a.k;
     const int nvec = (V + EPV - 1) / EPV;                    // the last one padded with -inf (in LDS as well)
-    const OnePassLayout lay = one_pass_layout(V, TNT);
+    const OnePassLayout lay = one_pass_layout(V, NSEG);
     ExactShared& sh = *reinterpret_cast<ExactShared*>(ex);
     uint32_t* mask = reinterpret_cast<uint32_t*>(ex + lay.mask);
     double* seg = reinterpret_cast<double*>(ex + lay.seg);
@@ -189,15 +196,18 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
     const LT* grow = reinterpret_cast<const LT*>(a.draft) + (int64_t)lrow * a.stride;
     auto draft_vector = [&](int vi) {
         if (FULL) return reinterpret_cast<const uint4*>(grow)[vi];
+        if (ROWS == ROWS_WHOLE)
+            return vi < nvec ? reinterpret_cast<const uint4*>(grow)[vi]
+                             : make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
         return row_vector_finish<LT, EPV>(load16_any(row_vector_address<LT, EPV>(grow, vi, V)), vi, V, L::NEG_INF_WORD);
     };
     uint4 G[NV];
 #pragma unroll
     for (int c = 0; c < NV; ++c) {
         const int vi = c * TNT + tid;
-        G[c] = FULL ? draft_vector(vi) : load16_any(row_vector_address<LT, EPV>(grow, vi, V));
+        G[c] = ROWS != ROWS_ANY ? draft_vector(vi) : load16_any(row_vector_address<LT, EPV>(grow, vi, V));
     }
-    if (!FULL) {
+    if (ROWS == ROWS_ANY) {
 #pragma unroll
         for (int c = 0; c < NV; ++c) G[c] = row_vector_finish<LT, EPV>(G[c], c * TNT + tid, V, L::NEG_INF_WORD);
     }
@@ -453,8 +463,6 @@ struct RowMeta {
 
 // fp32 path, one workgroup per row.
 // TNT threads, NV 16-byte vectors per thread and row.
-// FULL: rows are 16-byte aligned and fill all NV vector slots of every thread (no bounds checks);
-// otherwise they may start at any element and have any length of at least one vector.
 // VT: the token's table row can be read with 16-byte loads (k a multiple of four, table 16-byte
 // aligned); the other case is a kernel of its own because a load that only one of two paths
 // issues makes the hardware wait counters, which are placed statically, wait for every load.
@@ -465,9 +473,10 @@ struct RowMeta {
 // rather than the row maximum: any element of the row works, because the sum then holds
 // a term equal to one (Z >= 1) and every term is at most Z; rows whose sum exceeds 2^46
 // (an element more than 32 above the reference) are left to the exact path.
-template <typename LT, int TNT, int NV, bool FULL, bool VT>
-__global__ __launch_bounds__(TNT, 4) void verify_fast(VerifyArgs a) {
+template <typename LT, int TNT, int NV, int ROWS, bool VT>
+__global__ __launch_bounds__(TNT, NV > 8 ? 3 : 4) void verify_fast(VerifyArgs a) {
     using L = Lane<LT>;
+    constexpr bool FULL = ROWS == ROWS_FULL;
     constexpr int EPV = L::EPV;
     constexpr int TNW = TNT / WAVE;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -504,6 +513,13 @@ __global__ __launch_bounds__(TNT, 4) void verify_fast(VerifyArgs a) {
             if (FULL) {
                 T[c] = load_stream16(reinterpret_cast<const uint4*>(trow) + vi);
                 G[c] = load_stream16(reinterpret_cast<const uint4*>(grow) + vi);
+            } else if (ROWS == ROWS_WHOLE) {
+                if (vi < nvec) {
+                    T[c] = load_stream16(reinterpret_cast<const uint4*>(trow) + vi);
+                    G[c] = load_stream16(reinterpret_cast<const uint4*>(grow) + vi);
+                } else {
+                    T[c] = G[c] = make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
+                }
             } else {
                 T[c] = load_stream16_any(row_vector_address<LT, EPV>(trow, vi, V));
                 G[c] = load_stream16_any(row_vector_address<LT, EPV>(grow, vi, V));
@@ -539,7 +555,7 @@ __global__ __launch_bounds__(TNT, 4) void verify_fast(VerifyArgs a) {
 #pragma unroll
         for (int c = 0; c < NV; ++c) {
             const int vi = c * TNT + tid;
-            if (!FULL) {
+            if (ROWS == ROWS_ANY) {
                 T[c] = row_vector_finish<LT, EPV>(T[c], vi, V, L::NEG_INF_WORD);
                 G[c] = row_vector_finish<LT, EPV>(G[c], vi, V, L::NEG_INF_WORD);
             }
@@ -677,10 +693,10 @@ __global__ __launch_bounds__(TNT, 4) void verify_fast(VerifyArgs a) {
             // pass from the registers.
             bool done = false;
             if (!bad && sums_ok && cut_definite && a.mode == VERIFY_FULL)
-                done = exact_one_pass<LT, TNT, NV, FULL>(a, row, lrow, m.nb, rt, rg, Zt, Zg, a_size, xt, m.lg_tok,
+                done = exact_one_pass<LT, TNT, NV, ROWS>(a, row, lrow, m.nb, rt, rg, Zt, Zg, a_size, xt, m.lg_tok,
                                                          m.u_acc, smem, ex_lds, s_row);
             // one call, so that it is inlined: as a function its argument block goes through memory
-            if (!done) exact_row<LT, FULL ? ROW_WHOLE : ROW_ANY, TNT>(a, row, ex_lds, s_row, false, 0.f, 0.f);
+            if (!done) exact_row<LT, ROWS == ROWS_ANY ? ROW_ANY : ROW_WHOLE, TNT>(a, row, ex_lds, s_row, false, 0.f, 0.f);
         }
     }
 }
@@ -1056,10 +1072,10 @@ __global__ __launch_bounds__(SEL_NT) void tree_finish(VerifyArgs a, const int32_
 
 // Dynamic LDS of verify_fast: raw row, reductions, then the exact paths' region.
 template <typename LT>
-static size_t fast_lds_bytes(int V, int threads) {
+static size_t fast_lds_bytes(int V, int threads, int nv) {
     const size_t row_bytes = ((size_t)V * sizeof(LT) + 15) & ~size_t(15);
     const size_t head = threads == 256 ? sizeof(FastShared<4>) : threads == 512 ? sizeof(FastShared<8>) : sizeof(FastShared<16>);
-    const size_t one_pass = one_pass_layout(V, threads).total;
+    const size_t one_pass = one_pass_layout(V, nv * (threads / WAVE)).total;
     const size_t exact = exact_lds_bytes(V, threads);
     return EXP_TABLE_BYTES + row_bytes + head + (one_pass > exact ? one_pass : exact);
 }
@@ -1072,30 +1088,57 @@ static bool whole_vectors(const VerifyArgs& a) {
     return (align & 15) == 0 && a.V % Lane<LT>::EPV == 0;
 }
 
+// The table can be read with 16-byte loads: four slots of a thread at a time.
+static bool vector_table(const VerifyArgs& a) {
+    return (a.k & 3) == 0 && (reinterpret_cast<uintptr_t>(a.knn) & 15) == 0;
+}
+
 // launch == false: only the LDS limits are raised (lantern_prepare), nothing is enqueued.
-template <typename LT, int TNT, int NV>
+// OTHER: what the kernels for rows that do not fill every slot know (ROWS_WHOLE or ROWS_ANY).
+template <typename LT, int TNT, int NV, int OTHER = ROWS_ANY>
 static hipError_t launch_fast_nv(const VerifyArgs& a, hipStream_t stream, bool launch) {
-    const size_t lds = fast_lds_bytes<LT>(a.V, TNT);
+    const size_t lds = fast_lds_bytes<LT>(a.V, TNT, NV);
     const bool full = a.V == NV * TNT * Lane<LT>::EPV && whole_vectors<LT>(a);
-    // three instantiations: whole rows with a vector-readable table, other rows with one, and the rest
-    const bool vt = ((a.k & 3) == 0) && ((reinterpret_cast<uintptr_t>(a.knn) & 15) == 0);
+    // three instantiations: full rows with a vector-readable table, other rows with one, and the rest
+    const bool vt = vector_table(a);
     if (!launch) {   // every one of them may be needed later
-        hipError_t e = allow_lds<&verify_fast<LT, TNT, NV, true, true>>(lds);
-        if (e == hipSuccess) e = allow_lds<&verify_fast<LT, TNT, NV, false, true>>(lds);
-        if (e == hipSuccess) e = allow_lds<&verify_fast<LT, TNT, NV, false, false>>(lds);
+        hipError_t e = allow_lds<&verify_fast<LT, TNT, NV, ROWS_FULL, true>>(lds);
+        if (e == hipSuccess) e = allow_lds<&verify_fast<LT, TNT, NV, OTHER, true>>(lds);
+        if (e == hipSuccess) e = allow_lds<&verify_fast<LT, TNT, NV, OTHER, false>>(lds);
         return e;
     }
-    const hipError_t e = (full && vt) ? allow_lds<&verify_fast<LT, TNT, NV, true, true>>(lds)
-                         : vt         ? allow_lds<&verify_fast<LT, TNT, NV, false, true>>(lds)
-                                      : allow_lds<&verify_fast<LT, TNT, NV, false, false>>(lds);
+    const hipError_t e = (full && vt) ? allow_lds<&verify_fast<LT, TNT, NV, ROWS_FULL, true>>(lds)
+                         : vt         ? allow_lds<&verify_fast<LT, TNT, NV, OTHER, true>>(lds)
+                                      : allow_lds<&verify_fast<LT, TNT, NV, OTHER, false>>(lds);
     if (e != hipSuccess) return e;
     if (full && vt)
-        hipLaunchKernelGGL((verify_fast<LT, TNT, NV, true, true>), dim3(a.N), dim3(TNT), lds, stream, a);
+        hipLaunchKernelGGL((verify_fast<LT, TNT, NV, ROWS_FULL, true>), dim3(a.N), dim3(TNT), lds, stream, a);
     else if (vt)
-        hipLaunchKernelGGL((verify_fast<LT, TNT, NV, false, true>), dim3(a.N), dim3(TNT), lds, stream, a);
+        hipLaunchKernelGGL((verify_fast<LT, TNT, NV, OTHER, true>), dim3(a.N), dim3(TNT), lds, stream, a);
     else
-        hipLaunchKernelGGL((verify_fast<LT, TNT, NV, false, false>), dim3(a.N), dim3(TNT), lds, stream, a);
+        hipLaunchKernelGGL((verify_fast<LT, TNT, NV, OTHER, false>), dim3(a.N), dim3(TNT), lds, stream, a);
     return hipGetLastError();
+}
+
+// Rows of 32 to 64 KiB: 256 threads with 16 vectors each instead of 512 with 8.  A row that is rejected in fp64
+// is done sooner by 512 threads (its workgroup is what the launch waits for); rows that are only read in fp32 pass
+// faster through 256 where that lets a compute unit hold three workgroups instead of two (three rows in LDS, three
+// wavefronts per SIMD), and where every slot is filled.  Measured, 512 threads against 256:
+//   decisions, 3840 rows of 9000 fp32     58.7 / 48.4 us    60 rows 8.0 / 7.6       three fit
+//   decisions, 3840 rows of 32768 bf16    88.3 / 82.8       60 rows 9.6 / 9.2       full
+//   decisions, 3840 rows of 24576 bf16    75.5 / 75.3       60 rows 9.0 / 9.2       neither
+//   tokens too, 45 % rejected: 3840 rows of 9000 fp32 177 / 157, 60 rows 23.1 / 28.5      three fit
+//                              3840 rows of 24576 bf16 245 / 285, 60 rows 32.9 / 43.1     two fit
+// So decisions take 256 in the first two cases, tokens where three fit and there are more rows than two per unit.
+// Only aligned whole vectors: at any other address the 16 vectors do not fit three wavefronts' registers.
+constexpr int COMPUTE_UNITS = 256;
+constexpr size_t LDS_OF_A_UNIT = 160 * 1024;
+template <typename LT>
+static bool fewer_threads(const VerifyArgs& a) {
+    if (!whole_vectors<LT>(a)) return false;
+    const bool three = 3 * fast_lds_bytes<LT>(a.V, NT, 16) <= LDS_OF_A_UNIT;
+    if (a.mode == VERIFY_DECIDE) return three || (a.V == 16 * NT * Lane<LT>::EPV && vector_table(a));
+    return three && a.N > 2 * COMPUTE_UNITS;
 }
 
 // Up to 8 vectors per thread and row stay in registers; the number of threads follows from that, so a
@@ -1110,7 +1153,13 @@ static hipError_t launch_fast(const VerifyArgs& a, hipStream_t stream, bool laun
     if (nv <= 2) return launch_fast_nv<LT, 256, 2>(a, stream, launch);
     if (nv <= 4) return launch_fast_nv<LT, 256, 4>(a, stream, launch);
     if (nv <= 8) return launch_fast_nv<LT, 256, 8>(a, stream, launch);
-    if (nv <= 16) return launch_fast_nv<LT, 512, 8>(a, stream, launch);
+    if (nv <= 16) {
+        if (launch)
+            return fewer_threads<LT>(a) ? launch_fast_nv<LT, 256, 16, ROWS_WHOLE>(a, stream, true)
+                                        : launch_fast_nv<LT, 512, 8>(a, stream, true);
+        const hipError_t e = launch_fast_nv<LT, 256, 16, ROWS_WHOLE>(a, stream, false);
+        return e == hipSuccess ? launch_fast_nv<LT, 512, 8>(a, stream, false) : e;
+    }
     return launch_fast_nv<LT, 1024, 8>(a, stream, launch);
 }
 
