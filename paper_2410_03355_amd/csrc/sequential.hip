@@ -26,8 +26,11 @@
 //     of the vocabulary holds it;
 //   - a tree's parents, tokens, decisions and draws are staged in LDS, and every wavefront looks for the
 //     next child by itself.
-// V = 16384, k = 1000, 64 trees of 60 candidates: 91 us (117 with the rows
-// unpacked once for both passes, which spills).  Second half of the plain step (PLAIN), one group per tree: 29 us.
+// A group's pairs of logits and, in their room, the drafter's terms take 4 registers per step; the Jensen-Shannon
+// bound's logarithms are a function call, over which few registers live, in kernels of their own.  So the walk under
+// total variation keeps out of scratch memory: setting that up is 1 to 3 us of every walk (64 trees none of which draws,
+// V = 8192 fp32: 43.6 -> 39.7 us the step) and the spilled terms more (V = 16384 fp32, 64 trees: 163 -> 148 us).
+// Second half of the plain step (PLAIN), one group per tree: 29 us.
 // Vocabularies that do not fit in LDS keep both vectors in the workspace.
 #include <hip/hip_runtime.h>
 #include <limits.h>
@@ -47,34 +50,27 @@ constexpr int SNW = SNT / WAVE;
 constexpr int PAIR_STEP = 2 * WAVE;   // tokens of one step of a wavefront: a pair per lane
 constexpr int SNODES = 128;           // nodes of a tree that are staged in LDS; larger trees are read in place
 
-// Two neighbouring logits with one load from an address aligned to the element only.
+// Two neighbouring logits with one load from an address aligned to the element only, and the two words that
+// hold them afterwards: the logits as fp32, later a double.
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 template <typename LT> struct RawPair;
 template <> struct RawPair<float> {
     typedef uint32_t raw __attribute__((ext_vector_type(2), aligned(4)));
-    __device__ static __forceinline__ float lo(raw v) { return __uint_as_float(v.x); }
-    __device__ static __forceinline__ float hi(raw v) { return __uint_as_float(v.y); }
+    __device__ static __forceinline__ u2 words(raw v) { return u2{v.x, v.y}; }
     __device__ static __forceinline__ raw twice(const float* p) {
         const uint32_t w = __float_as_uint(*p);
         return raw{w, w};
     }
-    __device__ static __forceinline__ void opaque(raw& v) {
-        uint32_t x = v.x, y = v.y;
-        asm("" : "+v"(x), "+v"(y));
-        v.x = x;
-        v.y = y;
-    }
 };
 template <> struct RawPair<uint16_t> {
     typedef uint32_t raw __attribute__((aligned(2)));
-    __device__ static __forceinline__ float lo(uint32_t v) { return __uint_as_float(v << 16); }
-    __device__ static __forceinline__ float hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
+    __device__ static __forceinline__ u2 words(raw v) { return u2{v << 16, v & 0xFFFF0000u}; }
     __device__ static __forceinline__ raw twice(const uint16_t* p) { return *p * 0x10001u; }
-    __device__ static __forceinline__ void opaque(raw& v) {
-        uint32_t x = v;
-        asm("" : "+v"(x));
-        v = x;
-    }
 };
+__device__ __forceinline__ float lo_of(u2 v) { return __uint_as_float(v.x); }
+__device__ __forceinline__ float hi_of(u2 v) { return __uint_as_float(v.y); }
+__device__ __forceinline__ double double_of(u2 v) { return __hiloint2double((int)v.y, (int)v.x); }
+__device__ __forceinline__ u2 words_of(double d) { return u2{(uint32_t)__double2loint(d), (uint32_t)__double2hiint(d)}; }
 // An integer whose origin the compiler does not see: what is computed from it stays where it is used
 // (token numbers and bounds of every step, hoisted out of the walk, would take more registers than there are).
 __device__ __forceinline__ int opaque_int(int v) {
@@ -104,7 +100,7 @@ struct SeqShared {
 // PLAIN: the second half of the plain tree step instead (NP > 0, no workspace).  Every child's test is
 // the decision already made; where all children of the last node are rejected, the first one is
 // evaluated once more for its residual and the draw.
-template <typename LT, int NP, bool PLAIN = false>
+template <typename LT, int NP, bool PLAIN, bool JSD>
 __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
     using RP = RawPair<LT>;
     using Raw = typename RP::raw;
@@ -143,7 +139,8 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         else v[x] = lo;
     };
     double* cur = RES ? seq_cur : cur_mem;
-    double greg[RES ? 2 * NP : 1] = {};
+    // the two rows' pairs of every step, then (NP > 0) the drafter's two terms of the step in their room
+    u2 tr[U], gr[U];
     double inv_st = 0.0, inv_sg = 0.0, st = 0.0, mxg = 0.0;
     const double delta = (double)a.delta;
 
@@ -273,37 +270,42 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 grow = reinterpret_cast<const LT*>(a.draft) + (int64_t)r * a.stride;
                 // Unnormalised softmax terms exp(l - max) and their sums.  A pair's load is moved to
                 // the row's last two logits where it would leave the row (V = 1 reads the one logit twice).
-                Raw tr[U], gr[U];
                 const int l2 = opaque_int(2 * lane);
                 float mt = neg_inf_f(), mg = neg_inf_f();
                 int bad = 0;
                 const float inf = __builtin_huge_valf();
                 auto load = [&](int xb) {
+                    Raw t[U], g[U];
                     if (V == 1) {
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
-                            tr[u] = RP::twice(trow);
-                            gr[u] = RP::twice(grow);
+                            t[u] = RP::twice(trow);
+                            g[u] = RP::twice(grow);
                         }
-                        return;
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const int x = min(xb + u * PAIR_STEP + l2, V - 2);
+                            t[u] = *reinterpret_cast<const Raw*>(trow + x);
+                            g[u] = *reinterpret_cast<const Raw*>(grow + x);
+                        }
                     }
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int x = min(xb + u * PAIR_STEP + l2, V - 2);
-                        tr[u] = *reinterpret_cast<const Raw*>(trow + x);
-                        gr[u] = *reinterpret_cast<const Raw*>(grow + x);
+                        tr[u] = RP::words(t[u]);
+                        gr[u] = RP::words(g[u]);
                     }
                 };
-                auto logits = [&](const Raw& v, int x, float* lo, float* hi) {
-                    *lo = x < x1 ? (x + 1 < V ? RP::lo(v) : RP::hi(v)) : neg_inf_f();
-                    *hi = x + 1 < x1 ? RP::hi(v) : neg_inf_f();
+                auto logits = [&](u2 v, int x, float* lo, float* hi) {
+                    *lo = x < x1 ? (x + 1 < V ? lo_of(v) : hi_of(v)) : neg_inf_f();
+                    *hi = x + 1 < x1 ? hi_of(v) : neg_inf_f();
                 };
                 for (int xb = x0; xb < (RES ? x0 + 1 : x1); xb += U * PAIR_STEP) {
                     load(xb);
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         // every pair lies inside the row, moved or not: no bounds in this pass
-                        const float l0 = RP::lo(tr[u]), l1 = RP::hi(tr[u]), h0 = RP::lo(gr[u]), h1 = RP::hi(gr[u]);
+                        const float l0 = lo_of(tr[u]), l1 = hi_of(tr[u]), h0 = lo_of(gr[u]), h1 = hi_of(gr[u]);
                         if (__builtin_isunordered(l0, l1) || __builtin_isunordered(h0, h1)) bad = 1;
                         mt = fmaxf(mt, fmaxf(l0, l1));
                         mg = fmaxf(mg, fmaxf(h0, h1));
@@ -334,17 +336,10 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 const double mxt = (double)mt;
                 mxg = (double)mg;
                 double zt = 0.0, zg = 0.0;
-                if (RES) {
-                    // the rows stay in registers as loaded, not as what the first pass unpacked them to
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        RP::opaque(tr[u]);
-                        RP::opaque(gr[u]);
-                    }
-                }
                 for (int xb = x0; xb < (RES ? x0 + 1 : x1); xb += U * PAIR_STEP) {
                     if (!RES) load(xb);
-                    // Two steps a turn, the registers moved down behind them: unrolled in full, this is
+                    // Two steps a turn, the registers moved down behind them and what comes of the two put at the
+                    // end (NP > 0: after the last turn every step is back in its place): unrolled in full, this is
                     // code that a group runs once, and fetching it costs more than the moves.
 #pragma unroll 1
                     for (int xc = xb; xc < xb + U * PAIR_STEP; xc += 2 * PAIR_STEP) {
@@ -375,9 +370,10 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                         }
                         if (RES) {
 #pragma unroll
-                            for (int q = 0; q + 4 < 2 * NP; ++q) greg[q] = greg[RES ? q + 4 : 0];
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) greg[RES ? 2 * NP - 4 + q : 0] = gn[q];
+                            for (int u = 0; u < 2; ++u) {
+                                tr[U - 2 + u] = words_of(gn[2 * u]);
+                                gr[U - 2 + u] = words_of(gn[2 * u + 1]);
+                            }
                         }
                     }
                 }
@@ -446,7 +442,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 }
                 const double incl = carry + (before + incl_w);
                 const unsigned long long failing =
-                    __ballot(!self && (a.divergence == 0 ? !(incl < delta) : jsd_fails(t_tok, incl, delta)));
+                    __ballot(!self && (JSD && (!PLAIN || a.divergence) ? jsd_fails(t_tok, incl, delta) : !(incl < delta)));
                 const int l = failing ? __ffsll((long long)failing) - 1 : 0;
                 const double up_to = l ? __shfl(incl, l > 0 ? l - 1 : 0, WAVE) : carry + before;
                 if (lane == 0) {
@@ -506,8 +502,8 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                         const int x = xb + u * PAIR_STEP + l2;
                         if (x < x1) {
                             const d2 ta = RES ? get2(cur, x) : cv[u];
-                            const double g0 = RES ? greg[RES ? 2 * u : 0] : gv[u].x;
-                            const double g1 = RES ? greg[RES ? 2 * u + 1 : 0] : gv[u].y;
+                            const double g0 = RES ? double_of(tr[u]) : gv[u].x;
+                            const double g1 = RES ? double_of(gr[u]) : gv[u].y;
                             const double t0 = fmax(ta.x, 0.0) * inv_st, t1 = fmax(ta.y, 0.0) * inv_st;
                             const double r0 = t0 - g0 * inv_sg, r1 = t1 - g1 * inv_sg;
                             pt += t0 + t1;
@@ -602,22 +598,34 @@ constexpr int SEQ_LDS_MAX_V = 150 * 1024 / (int)sizeof(double);
 static_assert(SNW * 10 * PAIR_STEP >= SEQ_LDS_MAX_V, "ten steps cover what fits in LDS");
 static_assert(SEQ_LDS_MAX_V * sizeof(double) + sizeof(SeqShared) <= 160 * 1024, "LDS of a workgroup");
 
-template <typename LT, int NP, bool PLAIN>
+template <typename LT, int NP, bool PLAIN, bool JSD>
 static hipError_t launch_steps(const SequentialArgs& a, hipStream_t stream, bool launch) {
     const size_t lds = NP > 0 ? (size_t)a.V * sizeof(double) : 0;
-    const hipError_t e = allow_lds<&trees_sequential<LT, NP, PLAIN>>(lds);
+    const hipError_t e = allow_lds<&trees_sequential<LT, NP, PLAIN, JSD>>(lds);
     if (e != hipSuccess || !launch) return e;
-    hipLaunchKernelGGL((trees_sequential<LT, NP, PLAIN>), dim3(a.B), dim3(SNT), lds, stream, a);
+    hipLaunchKernelGGL((trees_sequential<LT, NP, PLAIN, JSD>), dim3(a.B), dim3(SNT), lds, stream, a);
     return hipGetLastError();
 }
 
+template <typename LT, bool PLAIN, bool JSD>
+static hipError_t launch_bound(const SequentialArgs& a, hipStream_t stream, bool launch) {
+    if (a.V <= SNW * 2 * PAIR_STEP) return launch_steps<LT, 2, PLAIN, JSD>(a, stream, launch);
+    if (a.V <= SNW * 8 * PAIR_STEP) return launch_steps<LT, 8, PLAIN, JSD>(a, stream, launch);
+    if (a.V <= SEQ_LDS_MAX_V) return launch_steps<LT, 10, PLAIN, JSD>(a, stream, launch);
+    if constexpr (PLAIN) return hipErrorInvalidValue;   // tree_plain_fits tells
+    else return launch_steps<LT, 0, false, JSD>(a, stream, launch);
+}
+
+// A kernel for each bound on the neighbourhood: see the top of the file.
 template <typename LT, bool PLAIN>
 static hipError_t launch_typed(const SequentialArgs& a, hipStream_t stream, bool launch) {
-    if (a.V <= SNW * 2 * PAIR_STEP) return launch_steps<LT, 2, PLAIN>(a, stream, launch);
-    if (a.V <= SNW * 8 * PAIR_STEP) return launch_steps<LT, 8, PLAIN>(a, stream, launch);
-    if (a.V <= SEQ_LDS_MAX_V) return launch_steps<LT, 10, PLAIN>(a, stream, launch);
-    if constexpr (PLAIN) return hipErrorInvalidValue;   // tree_plain_fits tells
-    else return launch_steps<LT, 0, false>(a, stream, launch);
+    if constexpr (PLAIN) {
+        return launch_bound<LT, true, true>(a, stream, launch);
+    } else {
+        if (launch) return a.divergence ? launch_bound<LT, false, true>(a, stream, true) : launch_bound<LT, false, false>(a, stream, true);
+        const hipError_t e = launch_bound<LT, false, false>(a, stream, false);
+        return e == hipSuccess ? launch_bound<LT, false, true>(a, stream, false) : e;
+    }
 }
 
 // Loads the kernels on the current device and raises their LDS limit for this vocabulary size.
@@ -626,8 +634,8 @@ hipError_t prepare_sequential(int logits_dtype, int V) {
     a.V = V;
     hipFuncAttributes attr;
     hipError_t e = hipFuncGetAttributes(&attr, logits_dtype == 0
-                                                   ? reinterpret_cast<const void*>(&trees_sequential<float, 0>)
-                                                   : reinterpret_cast<const void*>(&trees_sequential<uint16_t, 0>));
+                                                   ? reinterpret_cast<const void*>(&trees_sequential<float, 0, false, false>)
+                                                   : reinterpret_cast<const void*>(&trees_sequential<uint16_t, 0, false, false>));
     if (e != hipSuccess) return e;
     e = logits_dtype == 0 ? launch_typed<float, false>(a, nullptr, false) : launch_typed<uint16_t, false>(a, nullptr, false);
     if (e == hipSuccess && tree_plain_fits(V))

@@ -1,0 +1,57 @@
+"""Resources of the built kernels, as the library's own code objects state them (no GPU needed)."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+import paper_2410_03355_amd as lantern
+
+READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _device_objects(blob):
+    """gfx950 code objects of every offload bundle in the library: after the magic the number of entries, then per
+    entry its offset from the magic, its size, and the length and text of its target."""
+    at = blob.find(MAGIC)
+    while at >= 0:
+        count, = struct.unpack_from("<Q", blob, at + len(MAGIC))
+        pos = at + len(MAGIC) + 8
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", blob, pos)
+            target = blob[pos + 24:pos + 24 + length]
+            pos += 24 + length
+            if b"gfx950" in target and size:
+                yield blob[at + offset:at + offset + size]
+        at = blob.find(MAGIC, at + len(MAGIC))
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{mangled name: (bytes of scratch per lane, spilled vector registers)}"""
+    if not os.path.exists(lantern.LIB_PATH):
+        lantern.build()
+    with open(lantern.LIB_PATH, "rb") as f:
+        blob = f.read()
+    found = {}
+    for i, obj in enumerate(_device_objects(blob)):
+        path = tmp_path_factory.mktemp("objects") / f"{i}.o"
+        path.write_bytes(obj)
+        notes = subprocess.run([READELF, "--notes", str(path)], check=True, capture_output=True, text=True).stdout
+        for part in notes.split("- .agpr_count")[1:]:
+            value = {key: re.search(r"\." + key + r":\s+(\S+)", part).group(1)
+                     for key in ("name", "private_segment_fixed_size", "vgpr_spill_count")}
+            found[value["name"]] = (int(value["private_segment_fixed_size"]), int(value["vgpr_spill_count"]))
+    assert len(found) > 50
+    return found
+
+
+def test_sequential_walk_keeps_out_of_scratch(kernels):
+    """The walk under total variation (template arguments: logit type, steps, plain rule, divergence)."""
+    walks = {name: r for name, r in kernels.items() if re.search(r"trees_sequentialI[ft]Li\d+ELb0ELb0EE", name)}
+    assert len(walks) == 8
+    for name, (scratch, spilled) in walks.items():
+        steps = int(re.search(r"Li(\d+)E", name).group(1))
+        assert (scratch, spilled) <= ((8, 1) if steps == 10 else (0, 0)), name
