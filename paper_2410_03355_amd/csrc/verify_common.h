@@ -280,19 +280,30 @@ template <typename LT, int FORM>
 struct VecLoad {
     __device__ static __forceinline__ void load(const LT* row, const unsigned char* lds, int vi, int V,
                                                 float (&out)[EXV]) {
-        if (FORM != ROW_ELEMENTS) {
-            const bool whole = (vi + 1) * EXV <= V;
-            if (whole || (FORM == ROW_ANY && lds && vi * EXV < V)) {
+        if (FORM == ROW_WHOLE) {
+            if ((vi + 1) * EXV <= V) {
+                load4_vector(lds ? reinterpret_cast<const LT*>(lds) : row, vi, out);
+                return;
+            }
+#pragma unroll
+            for (int e = 0; e < EXV; ++e) out[e] = neg_inf_f();
+        } else if (FORM == ROW_ANY) {
+            if ((vi + 1) * EXV <= V || (lds && vi * EXV < V)) {
                 if (lds) load4_vector(reinterpret_cast<const LT*>(lds), vi, out);
-                else if (FORM == ROW_WHOLE) load4_vector(row, vi, out);
                 else load4_any(row + vi * EXV, out);
                 return;
             }
-        }
 #pragma unroll
-        for (int e = 0; e < EXV; ++e) {
-            const int x = vi * EXV + e;
-            out[e] = FORM != ROW_WHOLE && x < V ? Lane<LT>::glob(row, x) : neg_inf_f();
+            for (int e = 0; e < EXV; ++e) {
+                const int x = vi * EXV + e;
+                out[e] = x < V ? Lane<LT>::glob(row, x) : neg_inf_f();
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < EXV; ++e) {
+                const int x = vi * EXV + e;
+                out[e] = x < V ? Lane<LT>::glob(row, x) : neg_inf_f();
+            }
         }
     }
 };

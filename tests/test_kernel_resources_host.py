@@ -30,7 +30,7 @@ def _device_objects(blob):
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    """{mangled name: (bytes of scratch per lane, spilled vector registers)}"""
+    """{mangled name: (bytes of scratch per lane, spilled vector registers, vector registers)}"""
     if not os.path.exists(lantern.LIB_PATH):
         lantern.build()
     with open(lantern.LIB_PATH, "rb") as f:
@@ -42,8 +42,9 @@ def kernels(tmp_path_factory):
         notes = subprocess.run([READELF, "--notes", str(path)], check=True, capture_output=True, text=True).stdout
         for part in notes.split("- .agpr_count")[1:]:
             value = {key: re.search(r"\." + key + r":\s+(\S+)", part).group(1)
-                     for key in ("name", "private_segment_fixed_size", "vgpr_spill_count")}
-            found[value["name"]] = (int(value["private_segment_fixed_size"]), int(value["vgpr_spill_count"]))
+                     for key in ("name", "private_segment_fixed_size", "vgpr_spill_count", "vgpr_count")}
+            found[value["name"]] = (int(value["private_segment_fixed_size"]), int(value["vgpr_spill_count"]),
+                                    int(value["vgpr_count"]))
     assert len(found) > 50
     return found
 
@@ -52,6 +53,13 @@ def test_sequential_walk_keeps_out_of_scratch(kernels):
     """The walk under total variation (template arguments: logit type, steps, plain rule, divergence)."""
     walks = {name: r for name, r in kernels.items() if re.search(r"trees_sequentialI[ft]Li\d+ELb0ELb0EE", name)}
     assert len(walks) == 8
-    for name, (scratch, spilled) in walks.items():
+    for name, (scratch, spilled, _) in walks.items():
         steps = int(re.search(r"Li(\d+)E", name).group(1))
         assert (scratch, spilled) <= ((8, 1) if steps == 10 else (0, 0)), name
+
+
+def test_smallest_full_rows_leave_room_for_five_wavefronts(kernels):
+    """The fp32 pass over fp32 rows of 4 KiB (256 threads, one vector, full rows, vector table): up to 96 registers
+    five wavefronts fit a SIMD, and 30720 such rows take 87 us instead of 104."""
+    name, = [n for n in kernels if re.search(r"verify_fastIfLi256ELi1ELi0ELb1EE", n)]
+    assert kernels[name][0] == 0 and kernels[name][2] <= 96
