@@ -30,7 +30,9 @@
 // bound's logarithms are a function call, over which few registers live, in kernels of their own.  So the walk under
 // total variation keeps out of scratch memory: setting that up is 1 to 3 us of every walk (64 trees none of which draws,
 // V = 8192 fp32: 43.6 -> 39.7 us the step) and the spilled terms more (V = 16384 fp32, 64 trees: 163 -> 148 us).
-// Second half of the plain step (PLAIN), one group per tree: 29 us.
+// Second half of the plain step (PLAIN): its first wavefront walks the tree over the decisions as every other walk
+// does (tree_walk.h), then the workgroup evaluates the one candidate whose draw is wanted.  V = 16384 bf16, 1 / 64
+// trees that draw: 24 / 28 us, without a draw 4 us; 27 / 31 and 10 us with the search for children among the passes.
 // Vocabularies that do not fit in LDS keep both vectors in the workspace.
 #include <hip/hip_runtime.h>
 #include <limits.h>
@@ -41,6 +43,7 @@
 #include "exp_table.h"
 #include "lds_limit.h"
 #include "sequential_args.h"
+#include "tree_walk.h"
 #include "verify_common.h"
 
 namespace lantern {
@@ -97,8 +100,8 @@ struct SeqShared {
 
 // NP > 0: every wavefront's part of the vocabulary is at most NP steps; the current target lives in LDS
 // and the drafter's terms in registers.  NP == 0: any vocabulary, both vectors in the workspace.
-// PLAIN: the second half of the plain tree step instead (NP > 0, no workspace).  Every child's test is
-// the decision already made; where all children of the last node are rejected, the first one is
+// PLAIN: the second half of the plain tree step instead (NP > 0, no workspace; JSD says nothing then).  The walk
+// over the decisions already made comes first; where all children of the last node are rejected, the first one is
 // evaluated once more for its residual and the draw.
 template <typename LT, int NP, bool PLAIN, bool JSD>
 __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
@@ -149,50 +152,50 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
     const int x0 = min(V, wave * per);
     const int x1 = min(V, x0 + per);
 
-    const bool staged = M <= SNODES;
-    int malformed = 0;
-    for (int j = tid; j < M; j += SNT) {
-        path[j] = -1;
-        const int p = par[j];
-        if (p < -1 || p >= j) malformed = 1;
-        if (staged) {
-            sh.parent[j] = p;
-            sh.row[j] = a.row_index ? a.row_index[c0 + j] : (int)(c0 + j);
-            sh.token[j] = a.tokens[c0 + j];
-            sh.accept[j] = a.accept[c0 + j];
-            sh.u_acc[j] = a.uniforms[2 * (c0 + j)];
-            sh.u_res[j] = a.uniforms[2 * (c0 + j) + 1];
-        }
-    }
+    const bool staged = !PLAIN && M <= SNODES;
     for (int j = tid; j < 2 * EXP_TABLE_N; j += SNT) sh.tab[j] = EXP_TABLE_HILO[j];
-    malformed = block_or_i<SNW>(malformed, sh.ired, tid);   // its barriers publish what is staged
-    if (malformed) {
-        if (tid == 0) {
-            a.out_len[b] = 0;
-            a.out_next[b] = -3;
+    int first = -1;                      // PLAIN: the child whose draw is wanted
+    if (PLAIN) {
+        if (wave == 0) {
+            int walked;
+            const int found = walk_tree(a.accept + c0, nullptr, par, M, b, path, &walked);
+            for (int j = walked + lane; j < M; j += WAVE) path[j] = -1;
+            if (lane == 0) {
+                a.out_len[b] = walked;
+                sh.drawn = found;
+            }
         }
-        return;
+        __syncthreads();
+        first = sh.drawn;
+        if (first < 0) {                 // uniform: nothing to draw
+            if (tid == 0) a.out_next[b] = first;
+            return;
+        }
+        first -= b * M;
+    } else {
+        int malformed = 0;
+        for (int j = tid; j < M; j += SNT) {
+            path[j] = -1;
+            const int p = par[j];
+            if (p < -1 || p >= j) malformed = 1;
+            if (staged) {
+                sh.parent[j] = p;
+                sh.row[j] = a.row_index ? a.row_index[c0 + j] : (int)(c0 + j);
+                sh.token[j] = a.tokens[c0 + j];
+                sh.accept[j] = a.accept[c0 + j];
+                sh.u_acc[j] = a.uniforms[2 * (c0 + j)];
+                sh.u_res[j] = a.uniforms[2 * (c0 + j) + 1];
+            }
+        }
+        malformed = block_or_i<SNW>(malformed, sh.ired, tid);   // its barriers publish what is staged
+        if (malformed) {
+            if (tid == 0) {
+                a.out_len[b] = 0;
+                a.out_next[b] = -3;
+            }
+            return;
+        }
     }
-
-    // PLAIN: node i of a staged tree in slot i / 64 of lane i % 64, so that the search for a child touches no
-    // memory (its chain of LDS reads was 3.6 of 28 us); the sequential rule has no registers left for it
-    constexpr int SLOTS = PLAIN ? SNODES / WAVE : 1;
-    int node_parent[SLOTS], node_accept[SLOTS];
-#pragma unroll
-    for (int q = 0; q < SLOTS; ++q) {
-        const int j = q * WAVE + lane;
-        node_parent[q] = PLAIN && staged && j < M ? sh.parent[j] : INT_MIN;
-        node_accept[q] = PLAIN && staged && j < M ? sh.accept[j] : 0;
-    }
-    auto decision_of = [&](int i) {      // i uniform
-        if (!staged) return (int)a.accept[c0 + i];
-        if (!PLAIN) return sh.accept[i];
-        int d = 0;
-#pragma unroll
-        for (int q = 0; q < SLOTS; ++q)
-            if (i / WAVE == q) d = __builtin_amdgcn_readlane(node_accept[q], i % WAVE);
-        return d;
-    };
 
     int node = -1, len = 0, next = -1;
     for (;;) {   // one sibling group per round; every branch below is uniform over the workgroup
@@ -205,17 +208,12 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         double u_res = 0.0;          //   its draw,
         bool zero_resid = false;     //   and whether that is the distorted target itself
         int i = node;
-        int first_child = -1;
         for (;;) {
-            // the next child: the smallest index above i whose parent is the node
-            int child = INT_MAX;
-            if (PLAIN && staged) {
-#pragma unroll
-                for (int q = SLOTS - 1; q >= 0; --q) {
-                    const unsigned long long m = __ballot(node_parent[q] == node && q * WAVE + lane > i);
-                    if (m) child = q * WAVE + __ffsll((long long)m) - 1;
-                }
+            if (PLAIN) {
+                i = first;
             } else {
+                // the next child: the smallest index above i whose parent is the node
+                int child = INT_MAX;
                 for (int base = i + 1; base < M; base += WAVE) {
                     const int q = base + lane;
                     const int p = q < M ? (staged ? sh.parent[q] : par[q]) : INT_MIN;
@@ -225,34 +223,25 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                         break;
                     }
                 }
+                i = child;
+                if (i == INT_MAX) break;
             }
-            i = child;
-            if (PLAIN) {
-                if (i != INT_MAX) {
-                    const int decided = decision_of(i);
-                    if (decided == 0) {
-                        if (first_child < 0) first_child = i;
-                        continue;
-                    }
-                    if (decided == 1) taken = i;
-                    else next = -2;                       // an unusable row ends the walk
-                    break;
-                }
-                if (first_child < 0) break;
-                i = first_child;
-            }
-            if (i == INT_MAX) break;
             const int64_t c = c0 + i;
             const int r = staged ? sh.row[i] : a.row_index ? a.row_index[c] : (int)c;
             const int xt = staged ? sh.token[i] : a.tokens[c];
             bool usable = (unsigned)xt < (unsigned)V;
             const int32_t* nrow = a.knn + (int64_t)(usable ? xt : 0) * k;
+            float u_acc32 = 0.f, u_res32 = 0.f;               // PLAIN: in flight during the passes as well
+            if (PLAIN) {
+                u_acc32 = a.uniforms[2 * c];
+                u_res32 = a.uniforms[2 * c + 1];
+            }
             int nb;
             if (!have_rows) {
                 // The first child is tested against t_1 = t itself, which is the plain verification the
                 // row-parallel pass has already decided for every candidate: an accepted first child is
                 // taken without building the group's vectors.
-                const int decided = PLAIN ? 0 : decision_of(i);
+                const int decided = PLAIN ? 0 : staged ? sh.accept[i] : a.accept[c];
                 if (decided == 1) {
                     taken = i;
                     break;
@@ -469,7 +458,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 break;
             }
             const double mass = t_tok + S;
-            const double u_acc = (double)(staged ? sh.u_acc[i] : a.uniforms[2 * c]);
+            const double u_acc = (double)(PLAIN ? u_acc32 : staged ? sh.u_acc[i] : a.uniforms[2 * c]);
             if (u_acc * gx < mass) {
                 if (PLAIN) have_rows = false;   // nothing to draw from (the decision is made elsewhere)
                 else taken = i;
@@ -534,7 +523,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
             zz = zero_resid ? zt : z;
             st = zz;
             inv_st = 1.0 / zz;
-            u_res = (double)(staged ? sh.u_res[i] : a.uniforms[2 * c + 1]);
+            u_res = (double)(PLAIN ? u_res32 : staged ? sh.u_res[i] : a.uniforms[2 * c + 1]);
             if (PLAIN) break;
         }
         if (taken < 0) {
@@ -586,7 +575,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         node = taken;
     }
     if (tid == 0) {
-        a.out_len[b] = len;
+        if (!PLAIN) a.out_len[b] = len;
         a.out_next[b] = next;
     }
 }
@@ -620,7 +609,7 @@ static hipError_t launch_bound(const SequentialArgs& a, hipStream_t stream, bool
 template <typename LT, bool PLAIN>
 static hipError_t launch_typed(const SequentialArgs& a, hipStream_t stream, bool launch) {
     if constexpr (PLAIN) {
-        return launch_bound<LT, true, true>(a, stream, launch);
+        return launch_bound<LT, true, true>(a, stream, launch);   // no loop over groups: registers to spare
     } else {
         if (launch) return a.divergence ? launch_bound<LT, false, true>(a, stream, true) : launch_bound<LT, false, false>(a, stream, true);
         const hipError_t e = launch_bound<LT, false, false>(a, stream, false);

@@ -1262,11 +1262,32 @@ hipError_t launch_resample_selected(const VerifyArgs& a, int logits_dtype, hipSt
     return launch_selected_typed<uint16_t>(a, nullptr, 0, nullptr, nullptr, stream);
 }
 
+// Which kernel ends a plain tree step.  The one that keeps the row pair in registers and evaluates every
+// exponential once (1024 threads, the target in LDS as doubles: one workgroup to a compute unit beyond some 9000
+// tokens) against tree_finish (512 threads, several passes over rows staged in LDS, or read element by element
+// where they are not aligned whole vectors).  Time after the decisions, 60 candidates a tree, tree_finish / registers:
+//   V     aligned bf16, 1 / 64 / 512 trees       aligned fp32, 1 / 64 / 512          not aligned, about V, fp32
+//   1024  10.1 11.0 19.6 / 12.1 13.1 27.4 us     6.7 11.4 19.2 / 7.7 13.4 28.6       6.7 12.5 24.6 / 7.5 13.1 29.4
+//   2048                                                                              15.0 18.1 30.7 / 12.8 13.9 33.6
+//   4096  8.3 14.6 27.6 / 8.7 15.4 33.4          8.0 14.6 28.4 / 8.7 15.6 35.6       10.6 22.1 33.8 / 9.5 17.4 44.5
+//   8192  10.9 20.0 35.4 / 10.7 19.8 44.2        10.6 21.5 36.2 / 10.8 20.4 42.1     22.1 31.9 36.5 / 19.4 22.3 59.5
+//   9216  21.2 23.0 45.8 / 19.4 21.1 49.4        21.0 24.9 41.7 / 19.7 22.5 50.6
+//  12288  25.1 30.1 39.6 / 21.4 23.5 49.2        25.3 32.3 61.0 / 21.9 24.3 52.1     32.3 41.7 52.2 / 22.1 26.2 61.1
+//  16384  30.4 35.0 55.1 / 24.2 27.7 49.5        30.3 36.0 74.2 / 24.5 27.5 53.1     17.2 46.7 81.1 / 14.5 30.6 55.3
+// Trees whose walk ends without a draw take 3 to 6 us in either.  So: registers beyond 8192 tokens (2048 where rows
+// are not aligned) as long as every tree has a compute unit, and beyond 12288 for any number of trees.
+static bool draw_from_registers(const VerifyArgs& a, size_t logit_bytes) {
+    if (!tree_plain_fits(a.V)) return false;
+    if (a.V > 12288) return true;
+    const uintptr_t align = reinterpret_cast<uintptr_t>(a.target) | reinterpret_cast<uintptr_t>(a.draft) |
+                            (uintptr_t)(a.stride * (int64_t)logit_bytes);
+    const bool whole = (align & 15) == 0 && a.V % EXV == 0;
+    return a.n_sel <= COMPUTE_UNITS && a.V > (whole ? 8192 : 2048);
+}
+
 hipError_t launch_tree_finish(const VerifyArgs& a, const int32_t* parent, int M, int32_t* out_len, int32_t* out_path,
                               int logits_dtype, hipStream_t stream) {
-    // a vocabulary whose target fits in LDS in fp64 takes the kernel that evaluates every exponential once
-    // (V = 16384 bf16: 27 us for one tree and 33 us for 64, against 30 and 35 us for tree_finish)
-    if (tree_plain_fits(a.V)) {
+    if (draw_from_registers(a, logits_dtype == 0 ? sizeof(float) : sizeof(uint16_t))) {
         SequentialArgs s{};
         s.target = a.target;
         s.draft = a.draft;

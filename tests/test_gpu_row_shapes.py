@@ -5,6 +5,8 @@ import numpy as np
 import pytest
 import torch
 
+from parity_utils import replay_us
+
 pytestmark = pytest.mark.gpu
 
 EDGES = {torch.bfloat16: [8, 9, 15, 2048, 2055, 16383, 16384, 16385, 32768, 32771, 65535, 65536, 65537],
@@ -123,24 +125,6 @@ def test_cuts_beyond_four_slots_per_thread(oracle_mod, lantern_gpu, dtype, V, k)
         np.testing.assert_array_equal(got_res.cpu().numpy(), res)
 
 
-def _replay_us(call):
-    call()
-    torch.cuda.synchronize()
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):
-        for _ in range(10):
-            call()
-    times = []
-    for _ in range(9):
-        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        begin.record()
-        graph.replay()
-        end.record()
-        torch.cuda.synchronize()
-        times.append(begin.elapsed_time(end) * 100)
-    return sorted(times)[len(times) // 2]
-
-
 @pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 16384), (torch.float32, 8192)])
 def test_unsettled_rows_cost_the_same_in_every_kernel(lantern_gpu, dtype, V):
     """The fp64 pass of a row in the general kernel (odd table width) against the one for whole rows: both read
@@ -154,7 +138,7 @@ def test_unsettled_rows_cost_the_same_in_every_kernel(lantern_gpu, dtype, V):
     for k in (80, 81):
         table = ((torch.arange(V, device="cuda")[:, None] + torch.arange(k, device="cuda")[None, :]) % V).to(torch.int32)
         lantern_gpu.prepare(dtype, V, k)
-        took[k] = _replay_us(lambda: lantern_gpu.decide_rows(target, draft, None, tokens, table, 40 / V, uniforms))
+        took[k] = replay_us(lambda: lantern_gpu.decide_rows(target, draft, None, tokens, table, 40 / V, uniforms))
     assert took[81] < 1.25 * took[80], took
 
 
@@ -197,6 +181,6 @@ def test_aligned_rows_just_beyond_32_kib_are_the_faster_ones(lantern_gpu):
     uniforms = torch.full((N, 2), 0.25, device="cuda")
     table = ((torch.arange(V, device="cuda")[:, None] + torch.arange(k, device="cuda")[None, :]) % V).to(torch.int32)
     lantern_gpu.prepare(torch.float32, V, k)
-    took = [_replay_us(lambda: lantern_gpu.decide_rows(target[:, start:start + V], draft[:, start:start + V], None,
+    took = [replay_us(lambda: lantern_gpu.decide_rows(target[:, start:start + V], draft[:, start:start + V], None,
                                                        tokens, table, 0.3, uniforms)) for start in (0, 1)]
     assert took[0] < 0.94 * took[1], took

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from parity_utils import random_trees
+from parity_utils import random_trees, replay_us
 
 pytestmark = pytest.mark.gpu
 
@@ -63,3 +63,41 @@ def test_plain_rule(oracle_mod, lantern_gpu, V, k, B, M, dtype, offset, divergen
     got = lantern_gpu.verify_trees(t, d, ri, par, M, tok, tab, 0.05, u, divergence=divergence)
     for g, w in zip(got, want):
         np.testing.assert_array_equal(g.cpu().numpy().reshape(-1), np.asarray(w).reshape(-1))
+
+
+@pytest.mark.parametrize("divergence", ["tvd", "jsd"])
+@pytest.mark.parametrize("V,k,B,M,dtype,offset", [
+    # the lines between the two kernels that end a plain step: aligned rows at 8192 tokens, others at 2048, both at
+    # 12288 where there are more trees than compute units
+    (8192, 40, 3, 70, torch.bfloat16, 0), (8200, 40, 3, 70, torch.bfloat16, 0), (8196, 40, 257, 3, torch.float32, 0),
+    (8196, 40, 256, 3, torch.float32, 0), (2048, 33, 3, 20, torch.float32, 1), (2049, 33, 257, 2, torch.bfloat16, 1),
+    (2050, 33, 256, 2, torch.float32, 3), (12288, 64, 257, 2, torch.bfloat16, 0), (12296, 64, 257, 2, torch.bfloat16, 0),
+    (5001, 1100, 2, 300, torch.bfloat16, 1)])
+def test_plain_rule_between_the_kernels(oracle_mod, lantern_gpu, V, k, B, M, dtype, offset, divergence):
+    test_plain_rule(oracle_mod, lantern_gpu, V, k, B, M, dtype, offset, divergence)
+
+
+@pytest.mark.parametrize("dtype,V,draw,limit", [(torch.float32, 1024, True, 1.2), (torch.bfloat16, 4096, True, 1.2),
+                                                (torch.float32, 8192, False, 0.65), (torch.bfloat16, 16384, False, 0.4)])
+def test_what_follows_the_decisions_costs_little(lantern_gpu, dtype, V, draw, limit):
+    """A plain step of 64 trees less its decisions, against lantern_resample_selected of 64 candidates.  With every
+    candidate rejected both draw from a row: the same time.  With every candidate accepted the walk remains, against
+    finding that there is nothing to draw: 0.39 (V = 8192) and 0.27 times (16384).  With a walk that stages the tree in
+    1024 threads first it was 1.4 times with the draw, and 0.95 and 0.55 without."""
+    B, M, k = 64, 60, 100
+    parent = random_trees(np.random.default_rng(V), B, M, max_children=4)
+    g = torch.Generator(device="cuda").manual_seed(V)
+    target = torch.randn(B * M, V, generator=g, device="cuda").to(dtype)
+    draft = (target.float() + 0.3 * torch.randn(B * M, V, generator=g, device="cuda")).to(dtype)
+    tokens = (draft.float() - target.float()).argmax(dim=1).to(torch.int32)
+    uniforms = torch.full((B * M, 2), 1 - 2.0 ** -24 if draw else 0.0, device="cuda")
+    table = ((torch.arange(V, device="cuda")[:, None] + torch.arange(k, device="cuda")[None, :]) % V).to(torch.int32)
+    par = torch.from_numpy(parent.reshape(-1)).cuda()
+    lantern_gpu.prepare(dtype, V, k)
+    select = torch.arange(0, B * M, M, dtype=torch.int32, device="cuda")
+    step = replay_us(lambda: lantern_gpu.verify_trees(target, draft, None, par, M, tokens, table, 0.0, uniforms))
+    decide = replay_us(lambda: lantern_gpu.decide_rows(target, draft, None, tokens, table, 0.0, uniforms))
+    draws = replay_us(lambda: lantern_gpu.resample_selected(target, draft, None, tokens, table, 0.0, uniforms, select))
+    accepted = lantern_gpu.decide_rows(target, draft, None, tokens, table, 0.0, uniforms)
+    assert int((accepted == 1).sum()) == (0 if draw else B * M)
+    assert step - decide < limit * draws, (step, decide, draws)
