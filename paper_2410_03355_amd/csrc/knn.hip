@@ -235,9 +235,26 @@ __device__ double exact_key(const CT* cb, int d, int i, int j, int metric, bool 
     return key == key ? key : (double)INFINITY;   // no similarity (a code of zero norm): the farthest
 }
 
+// The approximate cosine keys are good to a few roundings as long as no squared norm, and no product of two, leaves
+// the range of normal floats.  A code beyond COSINE_MIN .. COSINE_MAX (squared norm) leaves every row to the
+// all-pairs pass, unless its exact keys do not depend on the norm: a code of zeros or with a coordinate
+// that is no finite number has no similarity to any other.  n: the squared norm as computed in fp32.
+constexpr float COSINE_MIN = 0x1p-60f, COSINE_MAX = 0x1p62f;
+template <typename CT>
+__device__ __forceinline__ bool cosine_in_doubt(const CT* code, int d, float n) {
+    if (n >= COSINE_MIN && n <= COSINE_MAX) return false;
+    bool nonzero = false;
+    for (int t = 0; t < d; ++t) {
+        const float x = cb_f32<CT>(code, t);
+        if (!(fabsf(x) < INFINITY)) return false;
+        nonzero |= x != 0.f;
+    }
+    return nonzero;
+}
+
 template <typename CT>
 __global__ __launch_bounds__(NT) void knn_dist_direct(const CT* cb, int V, int d, int r0, int metric,
-                                                      float* dist) {
+                                                      float* dist, int* doubt) {
     const int row = blockIdx.y;
     const int i = r0 + row;
     const int j = blockIdx.x * NT + threadIdx.x;
@@ -260,6 +277,7 @@ __global__ __launch_bounds__(NT) void knn_dist_direct(const CT* cb, int V, int d
             nj = fmaf(y, y, nj);
             dot = fmaf(x, y, dot);
         }
+        if (row == 0 && cosine_in_doubt(cj, d, nj)) *doubt = 1;   // every column of every row block
         key = -dot / sqrtf(ni * nj);
     }
     dist[(int64_t)row * V + j] = key;
@@ -301,7 +319,7 @@ template <> __device__ __forceinline__ float sum_squares<uint16_t>(const uint4& 
 constexpr int NORM_ROWS = 32;
 constexpr int NORM_WAVE_VECS = 16;
 template <typename CT>
-__global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, float* norms, float* nmax) {
+__global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, float* norms, float* nmax, int* doubt) {
     __shared__ float red[NW];
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x >> 6;
     const int vecs = d * (int)sizeof(CT) / 16;   // 16-byte vectors per row
@@ -329,7 +347,10 @@ __global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, floa
             const int i = blockIdx.x * NORM_ROWS + q * NW + w;
             const float t = wave_sum(n[q]);
             if (i < V) {
-                if (lane == 0) norms[i] = t;
+                if (lane == 0) {
+                    norms[i] = t;
+                    if (cosine_in_doubt(cb + (int64_t)i * d, d, t)) *doubt = 1;
+                }
                 m = fmaxf(m, t);
             }
         }
@@ -339,6 +360,7 @@ __global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, floa
             float n = 0.f;
             for (int c = 0; c < vecs; ++c) n = sum_squares<CT>(cbv[(int64_t)i * vecs + c], n);
             norms[i] = n;
+            if (cosine_in_doubt(cb + (int64_t)i * d, d, n)) *doubt = 1;
             m = fmaxf(m, n);
         }
     }
@@ -881,7 +903,7 @@ template <typename CT, int NK, int CAP, int TNT, bool LIST>
 __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(const CT* cb, int V, int d, int k, int metric, int r0,
                                                  const float* dist, FilterOut list, float err_rel, float err_abs,
                                                  float err_norm, const float* norms, const float* nmax,
-                                                 int32_t* out, int* flags) {
+                                                 const int* doubt, int32_t* out, int* flags) {
     static_assert(!LIST || NK > 0, "a candidate list is held in registers");
     constexpr int TNW = TNT / WAVE;
     using Shared = SelectShared<CAP, TNT>;
@@ -907,7 +929,7 @@ __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(con
     if (need == 0) return;
     const int pad = 8 + need / 128;
     const int want = min(V - 1, need + pad);
-    if (want > CAP) {
+    if (want > CAP || (metric != 0 && *doubt)) {
         if (tid == 0) flags[row] = 1;
         return;
     }
@@ -1184,7 +1206,8 @@ __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(con
     bool ok = true;
     if (LIST || count < V - 1) {
         const double last = sh.last;
-        double eabs = (double)err_abs;
+        // products and sums below the normal floats may lose up to the smallest of those each
+        double eabs = (double)err_abs + (metric == 0 ? (d + 8) * 0x1p-124 : 0.0);
         if (norms) {
             // Squared l2: the error of a key grows with the norms of its two codes, and the bound needs the
             // largest norm a discarded token can have.  A token with norm n_j > 4 (n_i + last) is further
@@ -1196,10 +1219,14 @@ __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(con
             const double far = 4.004 * (ni + last);
             const double nbound = far < (double)*nmax ? far : (double)*nmax;   // far may be inf or NaN: then the maximum
             eabs += (double)err_norm * (ni + nbound);
+            if (!(ni < 0x1p120)) ok = false;
         }
         const double num = (double)thr - eabs;
         const double floor_discarded = num - 1.01 * (double)err_rel * fabs(num);
-        ok = count >= need && last <= floor_discarded;
+        // Squared l2 beyond the floats: a discarded token may have an approximate key that is infinite or no number.
+        // Its code or the difference then has a square of about 2^127 or more, or a coordinate that is no
+        // finite number, and with the row's own norm below 2^120 its exact key lies above 2^126.
+        ok = ok && count >= need && last <= floor_discarded && (metric != 0 || thr < 0x1p124f);
     }
     if (!ok && tid == 0) flags[row] = 1;
 }
@@ -1238,9 +1265,12 @@ __global__ __launch_bounds__(NT) void knn_exact_rows(const CT* cb, int V, int d,
     }
 }
 
-__global__ void knn_clear_stats(int* stats, float* nmax) {
+__global__ void knn_clear_stats(int* stats, float* nmax, int* doubt) {
     stats[threadIdx.x] = 0;
-    if (threadIdx.x == 0) *nmax = 0.f;
+    if (threadIdx.x == 0) {
+        *nmax = 0.f;
+        *doubt = 0;
+    }
 }
 __global__ void knn_copy_stats(const int* stats, int32_t* out) { *out = stats[0]; }
 
@@ -1261,7 +1291,8 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
     int* stats = reinterpret_cast<int*>(ws + L.stats);
     float* norms = reinterpret_cast<float*>(ws + L.norms);
     float* nmax = reinterpret_cast<float*>(ws + L.nmax);
-    hipLaunchKernelGGL(knn_clear_stats, dim3(1), dim3(64), 0, stream, stats, nmax);
+    int* doubt = reinterpret_cast<int*>(nmax) + 1;   // a code whose cosine keys the error bound does not cover
+    hipLaunchKernelGGL(knn_clear_stats, dim3(1), dim3(64), 0, stream, stats, nmax, doubt);
     // matrix-core path: rows 16-byte aligned and coordinates in whole vectors
     const bool aligned = (reinterpret_cast<uintptr_t>(a.codebook) & 15) == 0;
     const bool mfma = aligned && (sizeof(CT) == 2 ? (a.d % 8) == 0 : (a.d % 4) == 0) && a.V >= 32;
@@ -1273,7 +1304,7 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
     if (mfma) {
         const int per_wg = a.d * (int)sizeof(CT) / 16 >= NORM_WAVE_VECS ? NORM_ROWS : NT;
         hipLaunchKernelGGL((knn_norms<CT>), dim3((a.V + per_wg - 1) / per_wg), dim3(NT), 0, stream, cb, a.V, a.d, norms,
-                           nmax);
+                           nmax, doubt);
         // n_i + n_j - 2 G: errors of the two norms and of G are each below gamma (n_i + n_j) / 2 ... gamma (n_i + n_j)
         err_rel = 0.f;
         err_abs = a.metric == 0 ? 0.f : 4.f * gamma;
@@ -1332,7 +1363,7 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
 #define LANTERN_LAUNCH_SELECT(NKV, CAPV, TNTV, LISTV)                                                       \
         hipLaunchKernelGGL((knn_select<CT, NKV, CAPV, TNTV, LISTV>), dim3(rows), dim3(TNTV), 0, stream, cb, \
                            a.V, a.d, a.k, a.metric, r0, dist, LISTV ? fo : no_list, err_rel, err_abs,       \
-                           err_norm, nsel, nmax, a.out, flags + r0)
+                           err_norm, nsel, nmax, doubt, a.out, flags + r0)
         if (plan.use) {
             // thresholds from the sample, then the contraction that keeps what lies below them
             hipLaunchKernelGGL((knn_sample_keys<CT>), dim3((plan.S + 127) / 128, (rows + 127) / 128), dim3(NT), 0, stream,
@@ -1358,7 +1389,7 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
                                    cb, norms, a.V, a.d, r0, rows, a.metric, dist);
             else
                 hipLaunchKernelGGL((knn_dist_direct<CT>), dim3((a.V + NT - 1) / NT, rows), dim3(NT), 0, stream,
-                                   cb, a.V, a.d, r0, a.metric, dist);
+                                   cb, a.V, a.d, r0, a.metric, dist, doubt);
 #define LANTERN_LAUNCH_SELECT_NK(NKV, TNTV)                                                                 \
             do {                                                                                            \
                 if (want_slots <= 256) LANTERN_LAUNCH_SELECT(NKV, 256, TNTV, false);                        \

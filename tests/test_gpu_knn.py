@@ -239,6 +239,26 @@ def test_keys_that_are_not_numbers(oracle_mod, lantern_gpu, V, d, k, dtype, metr
     np.testing.assert_array_equal(got, want)
 
 
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("V,d,k,dtype", [
+    (4200, 8, 300, torch.float32), (4200, 16, 300, torch.bfloat16),   # sampled thresholds and candidate lists
+    (2000, 8, 100, torch.float32),                                    # contraction, whole rows
+    (1500, 7, 100, torch.float32),                                    # direct keys
+])
+def test_codes_near_the_ends_of_the_floats(oracle_mod, lantern_gpu, V, d, k, dtype, metric):
+    """Codes whose squares, or products of two squared norms, fall below the normal fp32 numbers or beyond the
+    largest: the approximate keys say little there, and rows they cannot settle go to the all-pairs pass."""
+    g = torch.Generator().manual_seed(V + d)
+    base = torch.randn(V, d, generator=g)
+    spread = torch.exp(torch.rand(V, 1, generator=g) * -50)
+    rows = (100, 150)
+    for scale in (1e-10, 1e-15, 1e-19, 3e-21, 1e-22, 1e-24, 1e10, 1e18, 5e18, 3e19, spread, 1e19 * spread):
+        cb = (base * scale).to(dtype).contiguous()
+        got = lantern_gpu.build_knn(cb.cuda(), k, metric=metric).cpu().numpy()[rows[0]:rows[1]]
+        want = oracle_mod.build_knn(cb.float().numpy(), k, rows=rows, metric=metric, threads=16)
+        np.testing.assert_array_equal(got, want, err_msg=str(scale if isinstance(scale, float) else "spread"))
+
+
 def test_cosine_metric(oracle_mod, lantern_gpu):
     g = torch.Generator().manual_seed(77)
     cb = torch.randn(700, 12, generator=g) * (torch.rand(700, 1, generator=g) * 4 + 0.2)
