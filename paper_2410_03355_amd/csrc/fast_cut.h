@@ -1,13 +1,13 @@
 // The fp32 neighbourhood walk shared by the sampling and greedy kernels
 // (Algorithm 2, inference part, as a prefix scan over the k table slots).
 //
-// Every thread of the workgroup exponentiates its 4 consecutive slots of the
-// first 1024 (of the first 4 per thread in larger workgroups; gathering the raw target logits from LDS) and the wavefront scans
+// Every thread of the workgroup exponentiates its 4 consecutive slots (the first 1024 slots with 256
+// threads, 2048 with 512, 4096 with 1024; gathering the raw target logits from LDS) and the wavefront scans
 // the partial sums; after a barrier every wavefront adds the totals of the
 // wavefronts before it, compares the inclusive sums of its own slots with
 // delta * Z under the rounding margin and publishes the first slot that does
-// not pass; after a second barrier every thread combines the four results.
-// Slots beyond 1024 are walked by wavefront 0 alone, 1024 at a time.
+// not pass; after a second barrier every thread combines the wavefronts' results.
+// Slots beyond those are walked by wavefront 0 alone, 1024 at a time.
 #pragma once
 
 #include "verify_common.h"

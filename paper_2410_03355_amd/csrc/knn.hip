@@ -4,9 +4,10 @@
 //   1. approximate keys (fp32) for every pair (query i, token j) into the
 //      workspace: squared l2 distance, or minus cosine similarity
 //   2. per row: find a threshold with at least k-1+pad approximate keys at or below it
-//      (bisection with counting passes), recompute
+//      (a histogram of the row's list, or bisection with counting passes over a whole row), recompute
 //      the survivors' keys in fp64 exactly as the definition states (coordinate
-//      order, every operation rounded separately), sort them by (key, index)
+//      order, every operation rounded separately), rank them by (key, index) (buckets over the
+//      keys' range; a sorting network for more than 1024 of them or for many equal keys)
 //      and emit the first k-1 after the token itself.  A row is emitted only if
 //      the approximation's error bound proves no discarded token could belong
 //      to it; otherwise it is flagged.
@@ -63,7 +64,7 @@ struct KnnLayout {
     size_t stats, norms, nmax, dist, flags, slow, total;
     // sampled-threshold path (filter.use): the codebook and the sample as matrix-core operands, what the
     // contraction folds in per token, the sample's norms, a row block's keys to the sample, its thresholds,
-    // list lengths and candidate lists (or, in their place, bit rows); `dist` is then not laid out
+    // list lengths and candidate lists; `dist` is then not laid out
     size_t packed, spacked, fold, snorms, skeys, thr, counts, cand;
     FilterPlan filter;
     int row_block;   // query rows per pass through the key block
@@ -881,7 +882,7 @@ __device__ __forceinline__ int bucket_add(uint32_t* h, int b) {   // what the co
 // unsigned integers; NK == 0: they are re-read from the workspace in every pass.
 // A threshold with between k-1+pad and `fit` keys at or below it is found by bisection over the
 // keys' integer range, every step one counting pass over the registers (compare, add, one
-// reduction): no sorting network or histogram over all V keys is needed to pick candidates.
+// reduction); a list first narrows that range to one bucket of a histogram of its keys.
 // Runs body(e) for every key slot of a thread: fully unrolled when the keys sit in registers.
 template <int NK, typename F>
 __device__ __forceinline__ void for_keys(int npt, F body) {
@@ -1046,7 +1047,7 @@ __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(con
         hi = top < hi ? top : hi;
         best = sh.cut[1];
         thr_key = (uint32_t)hi;
-        for (int w = tid; w < Shared::BUCKETS / 2; w += TNT) sh.hist[w] = 0u;   // own words only up to here; read again after two barriers
+        for (int w = tid; w < Shared::BUCKETS / 2; w += TNT) sh.hist[w] = 0u;   // every count has been read before the barrier above; used again after two more
     }
     for (int pass = 0; pass < 40 && best > fit && hi - lo > 1; ++pass) {
         const int64_t mid64 = lo + ((hi - lo) >> 1);

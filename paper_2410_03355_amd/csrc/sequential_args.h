@@ -33,7 +33,8 @@ struct SequentialArgs {
 hipError_t launch_trees_sequential(const SequentialArgs& a, int logits_dtype, hipStream_t stream);
 
 // The second half of a plain tree step by the same kernel (work unused): walks every tree over the
-// decisions and draws the one residual the walk asks for, for vocabularies that fit in LDS as doubles.
+// decisions and draws the one residual the walk asks for.  tree_plain_fits: whether the vocabulary's target
+// fits in LDS as doubles, which it needs.
 bool tree_plain_fits(int V);
 hipError_t launch_trees_plain(const SequentialArgs& a, int logits_dtype, hipStream_t stream);
 

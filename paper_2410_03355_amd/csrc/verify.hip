@@ -18,7 +18,8 @@
 // aligned whole vectors) run the exact path for every row (kernel verify_exact).
 // Three modes (verify_args.h): decisions and resampled tokens; decisions only;
 // the fp64 path for selected verifications in 512-thread workgroups
-// (resample_selected, and tree_finish, which first walks its draft tree).
+// (resample_selected, and tree_finish, which first walks its draft tree; draw_from_registers
+// says which plain tree steps end in the kernel of sequential.hip instead).
 // Letters: t = target probability (the paper's q), g = drafter probability
 // (the paper's p), xt = draft token.
 #include <hip/hip_runtime.h>
@@ -75,12 +76,12 @@ enum RowsKnown { ROWS_FULL, ROWS_WHOLE, ROWS_ANY };
 // target and drafter terms of the tokens whose residual is certainly positive; tokens whose sign
 // fp32 cannot tell go on a short list with their fp64 terms.  Once the normalisers are known a
 // segment's residual mass is  P_t / Z_t - P_g / Z_g  plus its listed tokens, a scan over the
-// (at most 64) segment masses finds the segment that holds the draw, and that segment alone is
-// re-evaluated token by token.
+// segment masses (one per vector slot and wavefront: up to 128 with 1024 threads) finds the segment
+// that holds the draw, and that segment alone is re-evaluated token by token.
 // No global load sits inside the pass (under a saturated memory system each costs microseconds):
 // the drafter's row is fetched again, all of it at once, before the pass starts (keeping it in
 // registers from the fp32 pass on would cost that pass registers it does not have), the target row
-// is in LDS, the first 1024 table slots in registers.
+// is in LDS, the first four table slots per thread in registers.
 constexpr int AMB_CAP = 40;          // tokens whose residual sign fp32 leaves open (about one per row)
 constexpr double TAU_SIGN = 2.0e-5;  // covers the error of ln(Z_t32 / Z_g32) in the sign test (<= 8.8e-6)
 
@@ -90,7 +91,7 @@ struct AmbEntry {
     int pad;
 };
 
-// LDS of this path, in the region the neighbour scan no longer needs.
+// LDS of this path, behind the row and the reductions (the general path's data take the same region).
 struct OnePassLayout {
     size_t mask, seg, amb_count, amb, total;
 };

@@ -46,8 +46,9 @@ constexpr float LOG2E_F = 1.44269504088896340736f;
 // (1.24 * 32 + 2) * 2^-24 = 2.5e-6.  Terms more than 32 below the reference are
 // below e^-32 each (V * 1.3e-14 relative to the sum, which is >= 1); terms more
 // than 32 above it are excluded by requiring the sum to stay below 2^46.
-// Sums are trees of depth <= 32 (per thread, wavefront scan, across waves),
-// adding 32 * 2^-24 = 1.9e-6.  A comparison of one sum against another carries
+// Sums are trees of depth <= 32, adding 32 * 2^-24 = 1.9e-6: a term passes 3 additions within its
+// vector, one per further vector of the thread, 6 in the wavefront, one per further wavefront
+// (3 + 7 + 6 + 15 = 31 with 1024 threads of 8 vectors, 3 + 15 + 6 + 3 with 256 of 16).  A comparison of one sum against another carries
 // both bounds on both sides: at most 1.8e-5, covered by TAU_CUT and TAU_ACC.
 constexpr float TAU_CUT = 2.0e-5f;
 constexpr float TAU_ACC = 3.0e-5f;

@@ -65,6 +65,21 @@ def test_bench_records_are_of_this_library(lib):
         assert f"version {version}" in open(os.path.join(ROOT, source.split(" ")[0])).read()
 
 
+def test_bench_split_never_exceeds_the_build(lib):
+    """The recorded parts of a table build are printed beside a build time only if they fit into it."""
+    import importlib.util
+    from synth import workloads
+    spec = importlib.util.spec_from_file_location("bench_for_test", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    for name, (us, _, version, _) in bench.MEASURED_KNN_SPLIT.items():
+        total_ms = sum(us.values()) * 1e-3
+        fits = bench.knn_report(workloads.CONFIGS[name], total_ms * 1.1, version)
+        parts = fits["contraction_ms"] + fits["threshold_ms"] + fits["select_ms"] + fits["exact_check_ms"]
+        assert parts <= fits["build_ms"]
+        assert "select_ms" not in bench.knn_report(workloads.CONFIGS[name], total_ms * 0.9, version)
+
+
 def test_verify_argument_errors(lib):
     import paper_2410_03355_amd as L
     p = ctypes.c_void_p(4096)  # never dereferenced: validation fails first
