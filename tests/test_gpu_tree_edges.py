@@ -82,8 +82,8 @@ def test_plain_rule_between_the_kernels(oracle_mod, lantern_gpu, V, k, B, M, dty
 def test_what_follows_the_decisions_costs_little(lantern_gpu, dtype, V, draw, limit):
     """A plain step of 64 trees less its decisions, against lantern_resample_selected of 64 candidates.  With every
     candidate rejected both draw from a row: the same time.  With every candidate accepted the walk remains, against
-    finding that there is nothing to draw: 0.39 (V = 8192) and 0.27 times (16384).  With a walk that stages the tree in
-    1024 threads first it was 1.4 times with the draw, and 0.95 and 0.55 without."""
+    finding that there is nothing to draw: 0.25 to 0.36 times (V = 8192) and 0.22 to 0.25 (16384).  With a walk that
+    stages the tree in 1024 threads first it was 1.3 to 1.5 times with the draw, and 0.76 to 0.87 and 0.50 to 0.57 without."""
     B, M, k = 64, 60, 100
     parent = random_trees(np.random.default_rng(V), B, M, max_children=4)
     g = torch.Generator(device="cuda").manual_seed(V)
@@ -95,9 +95,10 @@ def test_what_follows_the_decisions_costs_little(lantern_gpu, dtype, V, draw, li
     par = torch.from_numpy(parent.reshape(-1)).cuda()
     lantern_gpu.prepare(dtype, V, k)
     select = torch.arange(0, B * M, M, dtype=torch.int32, device="cuda")
-    step = replay_us(lambda: lantern_gpu.verify_trees(target, draft, None, par, M, tokens, table, 0.0, uniforms))
-    decide = replay_us(lambda: lantern_gpu.decide_rows(target, draft, None, tokens, table, 0.0, uniforms))
-    draws = replay_us(lambda: lantern_gpu.resample_selected(target, draft, None, tokens, table, 0.0, uniforms, select))
+    step, decide, draws = replay_us(
+        lambda: lantern_gpu.verify_trees(target, draft, None, par, M, tokens, table, 0.0, uniforms),
+        lambda: lantern_gpu.decide_rows(target, draft, None, tokens, table, 0.0, uniforms),
+        lambda: lantern_gpu.resample_selected(target, draft, None, tokens, table, 0.0, uniforms, select))
     accepted = lantern_gpu.decide_rows(target, draft, None, tokens, table, 0.0, uniforms)
     assert int((accepted == 1).sum()) == (0 if draw else B * M)
     assert step - decide < limit * draws, (step, decide, draws)
