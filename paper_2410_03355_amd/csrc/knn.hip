@@ -236,11 +236,12 @@ __device__ double exact_key(const CT* cb, int d, int i, int j, int metric, bool 
     return key == key ? key : (double)INFINITY;   // no similarity (a code of zero norm): the farthest
 }
 
-// The approximate cosine keys are good to a few roundings as long as no squared norm, and no product of two, leaves
-// the range of normal floats.  A code beyond COSINE_MIN .. COSINE_MAX (squared norm) leaves every row to the
-// all-pairs pass, unless its exact keys do not depend on the norm: a code of zeros or with a coordinate
-// that is no finite number has no similarity to any other.  n: the squared norm as computed in fp32.
-constexpr float COSINE_MIN = 0x1p-60f, COSINE_MAX = 0x1p62f;
+// The approximate cosine keys are good to their error bound as long as a product of two coordinates that falls below
+// the normal floats is nothing beside the codes' norms and no sum leaves the floats.  A code beyond
+// COSINE_MIN .. COSINE_MAX (squared norm) leaves every row to the all-pairs pass, unless its exact keys do not
+// depend on the norm: a code of zeros or with a coordinate that is no finite number has no similarity
+// to any other.  n: the squared norm as computed in fp32.
+constexpr float COSINE_MIN = 0x1p-100f, COSINE_MAX = 0x1p120f;
 template <typename CT>
 __device__ __forceinline__ bool cosine_in_doubt(const CT* code, int d, float n) {
     if (n >= COSINE_MIN && n <= COSINE_MAX) return false;
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(NT) void knn_dist_direct(const CT* cb, int V, int d
             dot = fmaf(x, y, dot);
         }
         if (row == 0 && cosine_in_doubt(cj, d, nj)) *doubt = 1;   // every column of every row block
-        key = -dot / sqrtf(ni * nj);
+        key = -(dot / sqrtf(nj)) / sqrtf(ni);   // the product of the norms may leave the floats
     }
     dist[(int64_t)row * V + j] = key;
 }
@@ -310,7 +311,8 @@ template <> __device__ __forceinline__ float sum_squares<uint16_t>(const uint4& 
     return n;
 }
 
-// Squared norms of the rows and their maximum, for rows that are whole 16-byte vectors at 16-byte
+// Squared norms of the rows (for the cosine key one over their roots: a product of two squared norms
+// may leave the floats) and the largest squared norm, for rows that are whole 16-byte vectors at 16-byte
 // aligned addresses.  *nmax is cleared beforehand; a norm is never below +0, so the bit patterns
 // order like the values and an unsigned maximum collects it, asked for only by a workgroup that
 // sees a smaller value there (a NaN norm is stored but left out of the maximum).  Rows of 256 bytes
@@ -320,7 +322,7 @@ template <> __device__ __forceinline__ float sum_squares<uint16_t>(const uint4& 
 constexpr int NORM_ROWS = 32;
 constexpr int NORM_WAVE_VECS = 16;
 template <typename CT>
-__global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, float* norms, float* nmax, int* doubt) {
+__global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, int metric, float* norms, float* nmax, int* doubt) {
     __shared__ float red[NW];
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x >> 6;
     const int vecs = d * (int)sizeof(CT) / 16;   // 16-byte vectors per row
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, floa
             const float t = wave_sum(n[q]);
             if (i < V) {
                 if (lane == 0) {
-                    norms[i] = t;
+                    norms[i] = metric == 0 ? t : rsqrtf(t);
                     if (cosine_in_doubt(cb + (int64_t)i * d, d, t)) *doubt = 1;
                 }
                 m = fmaxf(m, t);
@@ -360,7 +362,7 @@ __global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, floa
         if (i < V) {
             float n = 0.f;
             for (int c = 0; c < vecs; ++c) n = sum_squares<CT>(cbv[(int64_t)i * vecs + c], n);
-            norms[i] = n;
+            norms[i] = metric == 0 ? n : rsqrtf(n);
             if (cosine_in_doubt(cb + (int64_t)i * d, d, n)) *doubt = 1;
             m = fmaxf(m, n);
         }
@@ -379,8 +381,9 @@ __global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, floa
 
 // Accumulator element r of lane l of a 32x32 MFMA tile is row 8*(r/4) + 4*(l/32) + r%4,
 // column l%32 (rows come from the A operand, columns from the B operand).
+// ni, nj: the two norms as knn_norms leaves them.
 __device__ __forceinline__ float approx_key(float g, float ni, float nj, int metric) {
-    return metric == 0 ? (ni + nj) - 2.f * g : -g * rsqrtf(ni * nj);
+    return metric == 0 ? (ni + nj) - 2.f * g : -(g * nj) * ni;
 }
 
 // Columns are the VB tokens of the column operand (the codebook itself, or a sample of it) with
@@ -586,12 +589,13 @@ struct FilterOut {
 //   squared l2   v = G_ij - n_j / 2 (the matrix cores start from - n_j / 2),  key = n_i - 2 v
 //   cosine       v = G_ij / sqrt(n_j),                                        key = - v / sqrt(n_i)
 // fold[j]: - n_j / 2 or 1 / sqrt(n_j); NaN beyond the vocabulary, where v then passes no comparison.
+// n in the functions: a norm as knn_norms leaves it (n_i, or 1 / sqrt(n_i)).
 template <int METRIC>
-__device__ __forceinline__ float fold_of(float n) { return METRIC == 0 ? -0.5f * n : rsqrtf(n); }
+__device__ __forceinline__ float fold_of(float n) { return METRIC == 0 ? -0.5f * n : n; }
 template <int METRIC>
-__device__ __forceinline__ float value_at(float key, float n) { return METRIC == 0 ? 0.5f * (n - key) : -key * sqrtf(n); }
+__device__ __forceinline__ float value_at(float key, float n) { return METRIC == 0 ? 0.5f * (n - key) : -key / n; }
 template <int METRIC>
-__device__ __forceinline__ float key_of_value(float v, float n, float rn) { return METRIC == 0 ? n - 2.f * v : -v * rn; }
+__device__ __forceinline__ float key_of_value(float v, float n) { return METRIC == 0 ? n - 2.f * v : -v * n; }
 // Element r of a lane's column is token 8*(r/4) + 4*(lane/32) + r%4 of the tile: four loads of four.
 __device__ __forceinline__ void load_fold(const float* fold, int tile, int lane, float (&o)[16]) {
 #pragma unroll
@@ -602,7 +606,7 @@ __device__ __forceinline__ void load_fold(const float* fold, int tile, int lane,
 }
 
 // LDS of the filtering contraction: per row of the workgroup's 128 the value its threshold stands for,
-// its norm and a counter (first: keys kept; then: next free slot of the row's list).
+// its norm (knn_norms) and a counter (first: keys kept; then: next free slot of the row's list).
 struct FilterShared {
     float val[128];
     float norm[128];
@@ -708,7 +712,7 @@ __global__ __launch_bounds__(NT, 2) void knn_filter_list(const uint4* packed, co
         for (int b = 0; b < 2; ++b) {
             const int l = l_base + b * 32 + (lane & 31);
             const uint32_t h = hits[b];
-            const float n = sh.norm[l], rn = METRIC == 0 ? 0.f : rsqrtf(n);
+            const float n = sh.norm[l];
             int slot = h ? atomicAdd(&sh.slots[l], __popc(h)) : 0;
             uint2* list = f.cand + (int64_t)(il_wg + l) * f.cap;   // only dereferenced for rows of the block
 #pragma unroll
@@ -717,7 +721,7 @@ __global__ __launch_bounds__(NT, 2) void knn_filter_list(const uint4* packed, co
                 for (int r = 0; r < 16; ++r)
                     if ((h >> (16 * a + r)) & 1u) {
                         const int j = (t_base + a) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                        const float key = key_of_value<METRIC>(acc[a][b][r], n, rn);
+                        const float key = key_of_value<METRIC>(acc[a][b][r], n);
                         if (slot < f.cap) list[slot] = make_uint2(min(ord_key(key), 0xFFFFFFFEu), (uint32_t)j);
                         ++slot;
                     }
@@ -1304,8 +1308,8 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
     float err_rel, err_abs, err_norm;
     if (mfma) {
         const int per_wg = a.d * (int)sizeof(CT) / 16 >= NORM_WAVE_VECS ? NORM_ROWS : NT;
-        hipLaunchKernelGGL((knn_norms<CT>), dim3((a.V + per_wg - 1) / per_wg), dim3(NT), 0, stream, cb, a.V, a.d, norms,
-                           nmax, doubt);
+        hipLaunchKernelGGL((knn_norms<CT>), dim3((a.V + per_wg - 1) / per_wg), dim3(NT), 0, stream, cb, a.V, a.d,
+                           a.metric, norms, nmax, doubt);
         // n_i + n_j - 2 G: errors of the two norms and of G are each below gamma (n_i + n_j) / 2 ... gamma (n_i + n_j)
         err_rel = 0.f;
         err_abs = a.metric == 0 ? 0.f : 4.f * gamma;

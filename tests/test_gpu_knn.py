@@ -252,11 +252,14 @@ def test_codes_near_the_ends_of_the_floats(oracle_mod, lantern_gpu, V, d, k, dty
     base = torch.randn(V, d, generator=g)
     spread = torch.exp(torch.rand(V, 1, generator=g) * -50)
     rows = (100, 150)
-    for scale in (1e-10, 1e-15, 1e-19, 3e-21, 1e-22, 1e-24, 1e10, 1e18, 5e18, 3e19, spread, 1e19 * spread):
+    for scale in (1e-13, 1e-15, 1e-19, 3e-21, 1e-22, 1e-24, 1e13, 1e18, 5e18, 3e19, spread, 1e19 * spread):
         cb = (base * scale).to(dtype).contiguous()
-        got = lantern_gpu.build_knn(cb.cuda(), k, metric=metric).cpu().numpy()[rows[0]:rows[1]]
+        got, exact_rows = lantern_gpu.build_knn(cb.cuda(), k, metric=metric, return_stats=True)
+        got = got.cpu().numpy()[rows[0]:rows[1]]
         want = oracle_mod.build_knn(cb.float().numpy(), k, rows=rows, metric=metric, threads=16)
         np.testing.assert_array_equal(got, want, err_msg=str(scale if isinstance(scale, float) else "spread"))
+        if isinstance(scale, float) and scale in (1e-13, 1e13):
+            assert int(exact_rows) == 0      # well inside the floats
 
 
 def test_cosine_metric(oracle_mod, lantern_gpu):
