@@ -35,17 +35,17 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 # (FETCH_SIZE scaled by the factor a plain 256 MiB copy gives in the same run).  Counters cannot be
 # read from inside this process, so the figure is a record of that run: it is reported only while the
 # library still has the version it was measured at, and with the file it comes from.
-_FETCH_SCALE = 262144.0 / 131094.8   # what FETCH_SIZE read for a 256 MiB copy in the same run
+_FETCH_SCALE = 262144.0 / 131091.8   # what FETCH_SIZE read for a 256 MiB copy in the same run
 MEASURED_TRAFFIC = {
     # (workload, variant, mode): (bytes per launch, library version, source)
-    ("stress", "plain", "sample"): ((130995.6 * _FETCH_SCALE + 240.2) * 1024, 228,
-                                    "profiles/verify_fast_stress_plain.md (FETCH_SIZE, WRITE_SIZE; version 228)"),
-    ("stress", "reject", "sample"): ((165151.1 * _FETCH_SCALE + 291.3) * 1024, 228,
-                                     "profiles/verify_fast_stress_plain.md (reject mix; version 228)"),
-    ("wide_latent", "plain", "sample"): ((124419.0 * _FETCH_SCALE + 240.4) * 1024, 228,
-                                         "profiles/verify_fast_stress_plain.md (wide_latent; version 228)"),
-    ("stress", "plain", "greedy"): ((69193.5 * _FETCH_SCALE + 240.0) * 1024, 228,
-                                    "profiles/greedy_fast_stress_plain.md (version 228)"),
+    ("stress", "plain", "sample"): ((130996.6 * _FETCH_SCALE + 240.1) * 1024, 229,
+                                    "profiles/verify_fast_stress_plain.md (FETCH_SIZE, WRITE_SIZE; version 229)"),
+    ("stress", "reject", "sample"): ((165171.0 * _FETCH_SCALE + 291.1) * 1024, 229,
+                                     "profiles/verify_fast_stress_plain.md (reject mix; version 229)"),
+    ("wide_latent", "plain", "sample"): ((124423.8 * _FETCH_SCALE + 240.3) * 1024, 229,
+                                         "profiles/verify_fast_stress_plain.md (wide_latent; version 229)"),
+    ("stress", "plain", "greedy"): ((69193.7 * _FETCH_SCALE + 240.0) * 1024, 229,
+                                    "profiles/greedy_fast_stress_plain.md (version 229)"),
 }
 
 
@@ -56,12 +56,12 @@ MEASURED_TRAFFIC = {
 # so does the wide-latent table (a sample of 1024 tokens).
 MEASURED_KNN_SPLIT = {
     # workload: ({kernel: us per build}, extra contraction flop, library version, source)
-    "stress": ({"sample_contraction": 50.7, "thresholds": 35.6, "filter_contraction": 208.7, "selection": 187.7,
-                "exact_check": 4.1, "operands_and_norms": 9.2}, 2.0 * 16384 * 2048 * 8, 228,
-               "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 228)"),
-    "wide_latent": ({"sample_contraction": 20.9, "thresholds": 13.6, "filter_contraction": 77.9, "selection": 104.4,
-                     "exact_check": 4.1, "operands_and_norms": 13.0}, 2.0 * 8192 * 1024 * 256, 228,
-                    "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 228)"),
+    "stress": ({"sample_contraction": 50.4, "thresholds": 35.6, "filter_contraction": 207.3, "selection": 187.7,
+                "exact_check": 5.7, "operands_and_norms": 9.6}, 2.0 * 16384 * 2048 * 8, 229,
+               "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 229)"),
+    "wide_latent": ({"sample_contraction": 21.0, "thresholds": 12.9, "filter_contraction": 78.6, "selection": 107.4,
+                     "exact_check": 4.1, "operands_and_norms": 14.6}, 2.0 * 8192 * 1024 * 256, 229,
+                    "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 229)"),
 }
 
 
