@@ -38,14 +38,14 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 _FETCH_SCALE = 262144.0 / 131091.8   # what FETCH_SIZE read for a 256 MiB copy in the same run
 MEASURED_TRAFFIC = {
     # (workload, variant, mode): (bytes per launch, library version, source)
-    ("stress", "plain", "sample"): ((130996.6 * _FETCH_SCALE + 240.1) * 1024, 229,
-                                    "profiles/verify_fast_stress_plain.md (FETCH_SIZE, WRITE_SIZE; version 229)"),
-    ("stress", "reject", "sample"): ((165171.0 * _FETCH_SCALE + 291.1) * 1024, 229,
-                                     "profiles/verify_fast_stress_plain.md (reject mix; version 229)"),
-    ("wide_latent", "plain", "sample"): ((124423.8 * _FETCH_SCALE + 240.3) * 1024, 229,
-                                         "profiles/verify_fast_stress_plain.md (wide_latent; version 229)"),
-    ("stress", "plain", "greedy"): ((69193.7 * _FETCH_SCALE + 240.0) * 1024, 229,
-                                    "profiles/greedy_fast_stress_plain.md (version 229)"),
+    ("stress", "plain", "sample"): ((130996.6 * _FETCH_SCALE + 240.1) * 1024, 230,
+                                    "profiles/verify_fast_stress_plain.md (FETCH_SIZE, WRITE_SIZE; version 230)"),
+    ("stress", "reject", "sample"): ((165171.0 * _FETCH_SCALE + 291.1) * 1024, 230,
+                                     "profiles/verify_fast_stress_plain.md (reject mix; version 230)"),
+    ("wide_latent", "plain", "sample"): ((124423.8 * _FETCH_SCALE + 240.3) * 1024, 230,
+                                         "profiles/verify_fast_stress_plain.md (wide_latent; version 230)"),
+    ("stress", "plain", "greedy"): ((69193.7 * _FETCH_SCALE + 240.0) * 1024, 230,
+                                    "profiles/greedy_fast_stress_plain.md (version 230)"),
 }
 
 
@@ -57,11 +57,11 @@ MEASURED_TRAFFIC = {
 MEASURED_KNN_SPLIT = {
     # workload: ({kernel: us per build}, extra contraction flop, library version, source)
     "stress": ({"sample_contraction": 50.4, "thresholds": 35.6, "filter_contraction": 207.3, "selection": 187.7,
-                "exact_check": 5.7, "operands_and_norms": 9.6}, 2.0 * 16384 * 2048 * 8, 229,
-               "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 229)"),
+                "exact_check": 5.7, "operands_and_norms": 9.6}, 2.0 * 16384 * 2048 * 8, 230,
+               "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 230)"),
     "wide_latent": ({"sample_contraction": 21.0, "thresholds": 12.9, "filter_contraction": 78.6, "selection": 107.4,
-                     "exact_check": 4.1, "operands_and_norms": 14.6}, 2.0 * 8192 * 1024 * 256, 229,
-                    "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 229)"),
+                     "exact_check": 4.1, "operands_and_norms": 11.3}, 2.0 * 8192 * 1024 * 256, 230,
+                    "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 230)"),
 }
 
 

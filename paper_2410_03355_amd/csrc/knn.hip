@@ -345,17 +345,17 @@ __global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, int 
                 n[q] = sum_squares<CT>(v, n[q]);
             }
         }
+        float t = 0.f;   // of the row that lane q finishes
 #pragma unroll
         for (int q = 0; q < RPW; ++q) {
-            const int i = blockIdx.x * NORM_ROWS + q * NW + w;
-            const float t = wave_sum(n[q]);
-            if (i < V) {
-                if (lane == 0) {
-                    norms[i] = metric == 0 ? t : rsqrtf(t);
-                    if (cosine_in_doubt(cb + (int64_t)i * d, d, t)) *doubt = 1;
-                }
-                m = fmaxf(m, t);
-            }
+            const float sum = wave_sum(n[q]);
+            if (lane == q) t = sum;
+        }
+        const int i = blockIdx.x * NORM_ROWS + lane * NW + w;
+        if (lane < RPW && i < V) {
+            norms[i] = metric == 0 ? t : rsqrtf(t);
+            m = fmaxf(m, t);
+            if (cosine_in_doubt(cb + (int64_t)i * d, d, t)) *doubt = 1;
         }
     } else {
         const int i = blockIdx.x * NT + threadIdx.x;
