@@ -147,4 +147,69 @@ LANTERN_HD double exp_tab_core(double d, const unsigned char* tab_bytes) {
     return out;
 }
 
+// The form that the fp64 pass over a rejected row uses: 16 instructions a value.  Terms are counted in steps of
+// ln2/256 from a whole number of steps K common to the row: e^l 2^(-K/256), with the logit l taken as it is (no
+// subtraction of a reference: K only scales the terms).
+//   l = m ln2/256 + r with m = rint(l 256/ln2), |r| <= ln2/512: one fused multiply-add onto 1.5 2^52 - K leaves
+//   m - K in the low word of the sum; e^r - 1 is a polynomial of degree four whose cubic coefficient is raised to
+//   cover the fifth-order term (error below 6e-18); the table (EXP_FINE) holds 2^(j/256) as hi (1 + rest), so the
+//   remainder goes in with the polynomial, and its hi comes without the j 2^44 that (m - K) 2^44 puts back with the
+//   exponent: one addition to the high word, and the value is one fused multiply-add.
+// Error: half an ulp of that last step and below 0.05 ulp of the rest, for |l| <= 5000 and results in the normal
+// range; the caller clamps.  start: EXP_UNITS_START - K.  tab_bytes: the table, on the device at offset 0 of
+// the workgroup's LDS (the lookup's address is then two instructions, with no base to add).
+constexpr double EXP_UNITS_START = 6755399441055744.0;       // 1.5 * 2^52
+constexpr double EXP_UNITS_INV = 0x1.71547652b82fep+8;       // 256 / ln 2
+constexpr double EXP_UNITS_HI = 0x1.62e42ff000000p-9;        // ln2/256 to 32 bits: exact times |m| < 2^21
+constexpr double EXP_UNITS_LO = -0x1.718432a1b0e26p-43;      // ln2/256 - EXP_UNITS_HI
+struct ExpUnits {
+    unsigned mi;     // m - K, two's complement
+    double hi, p;    // the value is hi (1 + p) with (m - K) 2^44 added to the bits of hi
+};
+LANTERN_HD ExpUnits exp_units_parts(double l, double start, const unsigned char* tab_bytes) {
+    ExpUnits u;
+    const double t = __builtin_fma(l, EXP_UNITS_INV, start);
+    unsigned long long tb;
+    __builtin_memcpy(&tb, &t, 8);
+    u.mi = (unsigned)tb;
+    const double m = t - start;
+    double r = __builtin_fma(-m, EXP_UNITS_HI, l);
+    r = __builtin_fma(-m, EXP_UNITS_LO, r);
+    double rest;
+#if defined(__HIP_DEVICE_COMPILE__)
+    (void)tab_bytes;
+    typedef double pair_t __attribute__((ext_vector_type(2)));
+    const pair_t entry = *(const __attribute__((address_space(3))) pair_t*)((u.mi << 4) & 0xFF0u);
+    u.hi = entry.x;
+    rest = entry.y;
+#else
+    __builtin_memcpy(&u.hi, tab_bytes + ((u.mi << 4) & 0xFF0u), 8);
+    __builtin_memcpy(&rest, tab_bytes + ((u.mi << 4) & 0xFF0u) + 8, 8);
+#endif
+    double q = __builtin_fma(r, 4.1666666666666664354e-02, 0.16666667995547);   // 1/24, 1/6 + 1.33e-8
+    q = __builtin_fma(q, r, 0.5);
+    q = __builtin_fma(q, r, 1.0);
+    u.p = __builtin_fma(q, r, rest);
+    return u;
+}
+LANTERN_HD double exp_units_scaled(double hi, unsigned steps) {   // steps 2^44 added to the bits
+    unsigned long long hb;
+    __builtin_memcpy(&hb, &hi, 8);
+    const unsigned high = (unsigned)(hb >> 32) + (steps << 12);
+    hb = ((unsigned long long)high << 32) | (unsigned)hb;
+    __builtin_memcpy(&hi, &hb, 8);
+    return hi;
+}
+LANTERN_HD double exp_units(double l, double start, const unsigned char* tab_bytes) {
+    const ExpUnits u = exp_units_parts(l, start, tab_bytes);
+    const double hi = exp_units_scaled(u.hi, u.mi);
+    return __builtin_fma(hi, u.p, hi);
+}
+// The same where the result may leave the normal range (below it: rounded there, in the end zero).
+LANTERN_HD double exp_units_any(double l, double start, const unsigned char* tab_bytes) {
+    const ExpUnits u = exp_units_parts(l, start, tab_bytes);
+    const double hi = exp_units_scaled(u.hi, u.mi & 255u);
+    return ldexp(__builtin_fma(hi, u.p, hi), (int)u.mi >> 8);
+}
+
 }  // namespace lantern

@@ -55,7 +55,8 @@ static_assert(sizeof(FastShared<4>) % 16 == 0 && sizeof(FastShared<8>) % 16 == 0
 
 template <typename LT, int FORM, int TNT = NT>
 __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned char* ex, const unsigned char* lds_row,
-                          bool have_max, float max_t, float max_g, const unsigned char* lds_grow = nullptr);
+                          bool have_max, float max_t, float max_g, const unsigned char* lds_grow = nullptr,
+                          unsigned char* tab_lds = nullptr);
 
 // What a kernel of the fp32 pass knows about its rows.
 //   ROWS_FULL   16-byte aligned, and every vector slot of every thread is filled: no bounds checks
@@ -78,12 +79,16 @@ enum RowsKnown { ROWS_FULL, ROWS_WHOLE, ROWS_ANY };
 // segment's residual mass is  P_t / Z_t - P_g / Z_g  plus its listed tokens, a scan over the
 // segment masses (one per vector slot and wavefront: up to 128 with 1024 threads) finds the segment
 // that holds the draw, and that segment alone is re-evaluated token by token.
+// Bound by the issue of vector instructions: 43 a token, 15 of them for each exponential (exp_units), against 80 with
+// A looked up in a bit mask, a reference subtracted from every logit, registers moved down for every two tokens and a
+// wavefront sum for every vector.  3840 rows of 16384 bf16 logits of which 45 % are rejected: 125 -> 102 us, of 8192
+// fp32 logits 82 -> 63; 960 rows of 8192 bf16 at any address 35 -> 27, of 65536 bf16 234 -> 182.
 // No global load sits inside the pass (under a saturated memory system each costs microseconds):
 // the drafter's row is fetched again, all of it at once, before the pass starts (keeping it in
 // registers from the fp32 pass on would cost that pass registers it does not have), the target row
 // is in LDS, the first four table slots per thread in registers.
 constexpr int AMB_CAP = 40;          // tokens whose residual sign fp32 leaves open (about one per row)
-constexpr double TAU_SIGN = 2.0e-5;  // covers the error of ln(Z_t32 / Z_g32) in the sign test (<= 8.8e-6)
+constexpr double TAU_SIGN = 2.0e-5;  // covers the error of ln(Z_t32 / Z_g32) in the sign test (<= 1.16e-5)
 
 struct AmbEntry {
     double et, eg;   // unnormalised fp64 terms
@@ -93,70 +98,134 @@ struct AmbEntry {
 
 // LDS of this path, behind the row and the reductions (the general path's data take the same region).
 struct OnePassLayout {
-    size_t mask, seg, amb_count, amb, total;
+    size_t seg, keep, amb_count, amb, total;
 };
 // The exponential's table sits at the very start of the workgroup's LDS (before the row): the
-// address of a lookup is then the masked integer itself, with no base to add.
+// address of a lookup is then the masked integer itself, with no base to add.  The general path, which
+// comes after this one or instead of it, keeps its own (smaller) table there.
 constexpr int EXP_TABLE_BYTES = 2 * EXP_TABLE_N * (int)sizeof(double);
-__host__ __device__ inline OnePassLayout one_pass_layout(int V, int segments) {
+constexpr int EXP_FINE_BYTES = 2 * EXP_FINE_N * (int)sizeof(double);
+__host__ __device__ inline OnePassLayout one_pass_layout(int segments) {
     OnePassLayout L;
     size_t off = (sizeof(ExactShared) + 15) & ~size_t(15);
-    L.mask = off;      off += (((size_t)V + 31) / 32) * 4;  off = (off + 15) & ~size_t(15);
     L.seg = off;       off += (size_t)segments * 2 * sizeof(double);
+    L.keep = off;      off += 4 * sizeof(double);
     L.amb = off;       off += AMB_CAP * sizeof(AmbEntry);
     L.amb_count = off; off += 16;
     L.total = off;
     return L;
 }
 
-// One residual term of the token-by-token evaluation: max(0, t_A(x) - g(x)), zero on A and at xt
-// (the token's own residual is zero in a rejected row: u g >= mass with u < 1).
-__device__ __forceinline__ double one_pass_term(float lt, float lg, bool zero, double rt, double rg, double inv_zt,
-                                                double inv_zg, const double* tab) {
-    const double d = exp_tab((double)lt - rt, tab) * inv_zt - exp_tab((double)lg - rg, tab) * inv_zg;
-    return (!zero && d > 0.0) ? d : 0.0;
+// max of two floats, the second uniform, as the one hardware instruction (fmaxf first quiets both operands, two more
+// instructions per call; no NaN reaches this path).
+__device__ __forceinline__ float max_f32_1(float a, float uniform) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "s"(uniform), "v"(a));
+    return r;
+}
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ float uniform_f(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+__device__ __forceinline__ double uniform_d(double v) {
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)), __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
 
-// What the pass does for one token: its fp64 terms into the normalisers; into the segment's sums
-// when the residual is certainly positive; onto the list when that cannot be told.
-// The sign test works on the exponents: t(x) > g(x) <=> (l_t - r_t) - (l_g - r_g) > ln(Z_t / Z_g),
-// where only the two fp32 sums on the right carry an error (at most 4.4e-6 relative each: terms
-// 2.5e-6, tree sums 1.9e-6, i.e. 8.8e-6 on the logarithm), so a margin of TAU_SIGN = 2e-5 on either
-// side of ln(Z_t32 / Z_g32) makes "positive" and "not positive" certain.  floor_t, floor_g: the row's
-// reference logit minus 700; logits below it (filtered tokens at -inf among them) are evaluated
-// there: a term of 1e-304 of the sum either way.
-// max of two floats as the one hardware instruction (fmaxf first quiets both operands, two more
-// instructions per call; no NaN reaches this path).
-__device__ __forceinline__ float max_f32_1(float a, float b) {
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+// A row's terms e^l 2^(-K/256), K its reference logit in steps of ln2/256.  floor: the least logit that is
+// evaluated as it is; lower ones (filtered tokens at -inf among them) are evaluated there.  The target's floor lies
+// 700 below its reference and the drafter's 650: terms of 1e-282 of the sum at most, and a target logit at its floor
+// is below any drafter logit by more than the sums can make up for (both lie in [1, 2^46]).
+struct UnitRow {
+    double start;    // EXP_UNITS_START - K
+    float floor;
+    __device__ __forceinline__ double arg(float l) const { return (double)max_f32_1(l, floor); }
+    __device__ __forceinline__ double term(float l, const unsigned char* tab) const { return exp_units(arg(l), start, tab); }
+    // a single term that a decision looks at: nothing at -inf
+    __device__ __forceinline__ double term_any(float l, const unsigned char* tab) const {
+        return exp_units_any((double)fmaxf(l, floor - 400.f), start, tab);
+    }
+};
+constexpr float UNITS_MAX_REF = 4096.f;      // what exp_units allows, floors and terms above the reference included
+__device__ __forceinline__ UnitRow unit_row(float ref, float below) {
+    UnitRow r;
+    r.start = EXP_UNITS_START - __builtin_rint((double)ref * EXP_UNITS_INV);
+    r.floor = uniform_f(ref - below);
     return r;
 }
 
+// What the pass does for the EPV tokens of a vector: their fp64 terms into the normalisers, and into the segment's
+// sums when the residual is certainly positive; returns whether some token of the lane is neither that nor
+// certainly without residual.
+// The sign test works on the logits: t(x) > g(x) <=> l_t - l_g > ln(Z_t / Z_g) + r_t - r_g, where only the two
+// fp32 sums carry an error (at most 4.4e-6 relative each: terms 2.5e-6, tree sums 1.9e-6, i.e. 8.8e-6 on the
+// logarithm, and their ratio's fp32 logarithm 2.8e-6), so a margin of TAU_SIGN = 2e-5 on either side makes "positive" and "not positive" certain.
 struct OnePassAcc {
-    double zt, zg, pt, pg;
+    double zt, zg;
 };
-__device__ __forceinline__ void one_pass_token(OnePassAcc& acc, float lt, float lg, bool zero, int x, double rt,
-                                               double rg, float floor_t, float floor_g, double ln_hi, double ln_lo,
-                                               const unsigned char* tab, AmbEntry* amb, int* amb_count) {
-    const double dt = (double)max_f32_1(lt, floor_t) - rt;
-    const double dg = (double)max_f32_1(lg, floor_g) - rg;
-    const double et = exp_tab_core(dt, tab);
-    const double eg = exp_tab_core(dg, tab);
-    acc.zt += et;
-    acc.zg += eg;
-    const double dd = dt - dg;                               // t(x) > g(x)  <=>  dd > ln(Z_t / Z_g)
-    const bool pos = !zero && (dd > ln_hi);
-    const bool neg = zero || (dd < ln_lo);
-    const double m = pos ? 1.0 : 0.0;
-    acc.pt = __builtin_fma(et, m, acc.pt);
-    acc.pg = __builtin_fma(eg, m, acc.pg);
-    if (!pos && !neg) {
-        const int slot = atomicAdd(amb_count, 1);
-        if (slot < AMB_CAP) {
-            amb[slot].et = et;
-            amb[slot].eg = eg;
-            amb[slot].x = x;
+typedef uint32_t u2x32 __attribute__((ext_vector_type(2)));
+template <typename LT>
+__device__ __forceinline__ bool one_pass_vector(const uint4& tv, const uint4& gv, const UnitRow& rt, const UnitRow& rg,
+                                                double sign_hi, double sign_lo, const unsigned char* tab,
+                                                OnePassAcc& acc, double* pt, double* pg) {
+    using L = Lane<LT>;
+    bool open = false;
+    double st = 0.0, sg = 0.0;
+#pragma unroll
+    for (int e = 0; e < L::EPV; ++e) {
+        const double at = rt.arg(L::get(tv, e)), ag = rg.arg(L::get(gv, e));
+        const double et = exp_units(at, rt.start, tab);
+        const double eg = exp_units(ag, rg.start, tab);
+        const double dd = at - ag;
+        const bool pos = dd > sign_hi;
+        open |= (dd > sign_lo) & !pos;
+        acc.zt += et;
+        acc.zg += eg;
+        const double one = pos ? 1.0 : 0.0;
+        st = __builtin_fma(et, one, st);
+        sg = __builtin_fma(eg, one, sg);
+        // the sums so far are due here: left alone, the compiler keeps the terms of all tokens in registers it lacks
+        if (e % 2 == 1) asm volatile("" : "+v"(acc.zt), "+v"(acc.zg), "+v"(st), "+v"(sg));
+    }
+    *pt = st;
+    *pg = sg;
+    return open;
+}
+
+// Sums over the wavefront of N pairs of doubles per lane, v[2 i] and v[2 i + 1]: out(i, which, sum) is run by
+// one lane for each.  Two values to a register at each of the first two steps (halves of the wavefront, then rows of 16
+// lanes, exchanged between two registers), so that N = 8 pairs take 72 instructions; one scan each would be 320.
+__device__ __forceinline__ double fold_halves(double a, double b) {   // lanes 0..31: a's sum, 32..63: b's
+    u2x32 lo = __builtin_bit_cast(u2x32, a), hi = __builtin_bit_cast(u2x32, b);
+    const auto x = __builtin_amdgcn_permlane32_swap(lo[0], hi[0], false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(lo[1], hi[1], false, false);
+    return __builtin_bit_cast(double, u2x32{x[0], y[0]}) + __builtin_bit_cast(double, u2x32{x[1], y[1]});
+}
+__device__ __forceinline__ double fold_rows(double a, double b) {     // rows 0, 2 of 16 lanes: a's, rows 1, 3: b's
+    u2x32 lo = __builtin_bit_cast(u2x32, a), hi = __builtin_bit_cast(u2x32, b);
+    const auto x = __builtin_amdgcn_permlane16_swap(lo[0], hi[0], false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(lo[1], hi[1], false, false);
+    return __builtin_bit_cast(double, u2x32{x[0], y[0]}) + __builtin_bit_cast(double, u2x32{x[1], y[1]});
+}
+template <int N, typename F>
+__device__ __forceinline__ void wave_pair_sums(const double (&v)[2 * N], int lane, F out) {
+    double w[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = fold_halves(v[2 * i], v[2 * i + 1]);
+    if constexpr (N == 1) {
+        double s = w[0];
+        s += dpp_d<DPP_ROW_SHR1, 0xF>(s);
+        s += dpp_d<DPP_ROW_SHR2, 0xF>(s);
+        s += dpp_d<DPP_ROW_SHR4, 0xF>(s);
+        s += dpp_d<DPP_ROW_SHR8, 0xF>(s);
+        s += dpp_d<DPP_ROW_BCAST15, 0xA>(s);
+        if ((lane & 31) == 31) out(0, lane >> 5, s);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; i += 2) {
+            double s = fold_rows(w[i], w[i + 1]);
+            s += dpp_d<DPP_ROW_SHR1, 0xF>(s);
+            s += dpp_d<DPP_ROW_SHR2, 0xF>(s);
+            s += dpp_d<DPP_ROW_SHR4, 0xF>(s);
+            s += dpp_d<DPP_ROW_SHR8, 0xF>(s);
+            if ((lane & 15) == 15) out(i + ((lane >> 4) & 1), lane >> 5, s);
         }
     }
 }
@@ -164,14 +233,14 @@ __device__ __forceinline__ void one_pass_token(OnePassAcc& acc, float lt, float 
 // s_row: raw target row in LDS.
 // nb: table slots 4*tid .. 4*tid+3.  ref_t, ref_g: the fp32 pass's reference logits; Zt32, Zg32:
 // its sums; a_size: its (definite) cut.
-// tab_lds: where the exponential's table goes in LDS.
+// tab_lds: the start of the workgroup's LDS, where the exponential's table goes.
 // Returns false (the same in every thread) when the row is left to the general path.
 template <typename LT, int TNT, int NV, int ROWS>
 __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int lrow,
                                                const int (&nb)[4], float ref_t, float ref_g,
                                                float Zt32, float Zg32, int a_size, int xt, float lg_tok, float u_acc32,
                                                unsigned char* tab_lds, unsigned char* ex,
-                                               const unsigned char* s_row) {
+                                               unsigned char* s_row) {
     using L = Lane<LT>;
     constexpr int EPV = L::EPV;
     constexpr int TNW = TNT / WAVE;
@@ -183,17 +252,17 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
     const int V = a.V;
     const int k = a.k;
     const int nvec = (V + EPV - 1) / EPV;                    // the last one padded with -inf (in LDS as well)
-    const OnePassLayout lay = one_pass_layout(V, NSEG);
+    if (!(fabsf(ref_t) <= UNITS_MAX_REF && fabsf(ref_g) <= UNITS_MAX_REF)) return false;   // uniform
+    const OnePassLayout lay = one_pass_layout(NSEG);
     ExactShared& sh = *reinterpret_cast<ExactShared*>(ex);
-    uint32_t* mask = reinterpret_cast<uint32_t*>(ex + lay.mask);
     double* seg = reinterpret_cast<double*>(ex + lay.seg);
-    double* tab = reinterpret_cast<double*>(tab_lds);
+    double* keep = reinterpret_cast<double*>(ex + lay.keep);
+    const unsigned char* tab = tab_lds;
     AmbEntry* amb = reinterpret_cast<AmbEntry*>(ex + lay.amb);
     int* amb_count = reinterpret_cast<int*>(ex + lay.amb_count);
-    const int nwords = (V + 31) >> 5;
-    const double rt = (double)ref_t, rg = (double)ref_g;
+    UnitRow rt = unit_row(ref_t, 700.f), rg = unit_row(ref_g, 650.f);
     const float u_res32 = a.uniforms[2 * (int64_t)row + 1];  // in flight during the pass
-    // the drafter's row, every load issued now; it arrives while the table and the mask are set up
+    // the drafter's row, every load issued now; it arrives while the table and the marks are set up
     const LT* grow = reinterpret_cast<const LT*>(a.draft) + (int64_t)lrow * a.stride;
     auto draft_vector = [&](int vi) {
         if (FULL) return reinterpret_cast<const uint4*>(grow)[vi];
@@ -201,6 +270,10 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
             return vi < nvec ? reinterpret_cast<const uint4*>(grow)[vi]
                              : make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
         return row_vector_finish<LT, EPV>(load16_any(row_vector_address<LT, EPV>(grow, vi, V)), vi, V, L::NEG_INF_WORD);
+    };
+    auto target_vector = [&](int vi) {
+        return FULL || vi < nvec ? reinterpret_cast<const uint4*>(s_row)[vi]
+                                 : make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
     };
     uint4 G[NV];
 #pragma unroll
@@ -213,92 +286,135 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
         for (int c = 0; c < NV; ++c) G[c] = row_vector_finish<LT, EPV>(G[c], c * TNT + tid, V, L::NEG_INF_WORD);
     }
 
-    // ---- table of the exponential, empty mask, empty list ----
-    if (tid < 2 * EXP_TABLE_N) tab[tid] = EXP_TABLE_HILO[tid];   // 2 * 128 doubles (cache-resident)
-    for (int w = tid; w < nwords; w += TNT) mask[w] = 0u;
+    // ---- table of the exponential (cache-resident), empty list ----
+    for (int j = tid; j < EXP_FINE_N; j += TNT)
+        reinterpret_cast<ulonglong2*>(tab_lds)[j] = make_ulonglong2(EXP_FINE[2 * j], EXP_FINE[2 * j + 1]);
     if (tid == 0) *amb_count = 0;
     __syncthreads();
 
-    // ---- A as a bitmask, and its mass (unnormalised) ----
-    double s_loc = 0.0;
+    // ---- the mass of A (unnormalised); then A's tokens and xt are marked -inf in the row in LDS: t_A is zero on A
+    // without the token and the token's own residual is zero in a rejected row (u g >= mass with u < 1) ----
+    const int32_t* nrow = a.knn + (int64_t)xt * k;
+    auto each_member = [&](auto body) {                      // entries in range: the fp32 pass has checked all k
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int n = nb[q];                                 // in range: the fp32 pass has checked all k entries
-        if (tid * 4 + q < a_size && n != xt) {
-            s_loc += exp_tab((double)L::lds(s_row, n) - rt, tab);
-            atomicOr(&mask[n >> 5], 1u << (n & 31));
-        }
-    }
-    if (a_size > TNT * 4) {
-        const int32_t* nrow = a.knn + (int64_t)xt * k;
+        for (int q = 0; q < 4; ++q)
+            if (tid * 4 + q < a_size && nb[q] != xt) body(nb[q]);
         for (int j = TNT * 4 + tid; j < a_size; j += TNT) {
             const int n = nrow[j];
-            if (n != xt) {
-                s_loc += exp_tab((double)L::lds(s_row, n) - rt, tab);
-                atomicOr(&mask[n >> 5], 1u << (n & 31));
-            }
+            if (n != xt) body(n);
         }
+    };
+    double s_loc = 0.0;
+    each_member([&](int n) { s_loc += rt.term_any(L::lds(s_row, n), tab); });
+    s_loc = wave_sum(s_loc);
+    if (lane == 0) sh.red[wave] = s_loc;
+    // ln(Z_t / Z_g) from the fp32 sums (both finite and at least one).  Their terms are
+    // 2^(l * LOG2E_F - c) with c = ref * LOG2E_F rounded to fp32, against e^(l - ref): per
+    // term the two differ by (l - ref) (LOG2E_F - log2 e), which the term's error bound holds, and by
+    // the rounding of c, common to the row and known exactly (the product of two floats is exact in
+    // fp64): that one is put back.  The logarithm itself may be off by 2.7e-6 (one unit in the last place of a
+    // binary logarithm below 46).
+    const double LN2_D = 0.69314718055994530942;
+    const double rt64 = (double)ref_t, rg64 = (double)ref_g;
+    const double adj_t = ((double)(ref_t * LOG2E_F) - rt64 * (double)LOG2E_F) * LN2_D;
+    const double adj_g = ((double)(ref_g * LOG2E_F) - rg64 * (double)LOG2E_F) * LN2_D;
+    const double sign = (double)__builtin_amdgcn_logf(Zt32 / Zg32) * LN2_D + adj_t - adj_g + (rt64 - rg64);
+    if (tid == 0) {                                          // kept in LDS: registers are short during the pass
+        keep[0] = sign + TAU_SIGN;
+        keep[1] = sign - TAU_SIGN;
+        keep[2] = rt.start;
+        keep[3] = rg.start;
+        sh.bcast[0] = rt.term_any(L::lds(s_row, xt), tab);
+        sh.bcast[1] = rg.term_any(lg_tok, tab);
     }
-    const double S = block_sum<TNW>(s_loc, sh.red, tid);     // its barriers also publish the mask
-    const double e_tx = exp_tab((double)L::lds(s_row, xt) - rt, tab);
-    const double e_gx = exp_tab((double)lg_tok - rg, tab);
+    __syncthreads();                                         // every read of a member's logit is done
+    each_member([&](int n) { L::lds_set_neg_inf(s_row, n); });
+    if (tid == 0) {
+        double S = sh.bcast[0];
+#pragma unroll
+        for (int w = 0; w < TNW; ++w) S += sh.red[w];
+        sh.bcast[0] = S;                                     // mass of A and the token
+        L::lds_set_neg_inf(s_row, xt);
+    }
+    __syncthreads();
 
     // ---- the pass: normalisers, and per segment the terms of the certainly positive residuals ----
-    // Rolled loops with the vectors shifted down by one chunk / two elements per turn, so that
-    // registers are indexed statically and the code stays small.
     OnePassAcc acc;
     acc.zt = 0.0;
     acc.zg = 0.0;
-    const float floor_t = ref_t - 700.f, floor_g = ref_g - 700.f;
-    // ln(Z_t / Z_g) from the fp32 sums (both finite and at least one).  Their terms are
-    // 2^(l * LOG2E_F - c) with c = ref * LOG2E_F rounded to fp32, the fp64 terms here e^(l - ref): per
-    // term the two differ by (l - ref) (LOG2E_F - log2 e), which the term's error bound holds, and by
-    // the rounding of c, common to the row and known exactly (the product of two floats is exact in
-    // fp64): that one is put back.
-    const double LN2_D = 0.69314718055994530942;
-    const double adj_t = ((double)(ref_t * LOG2E_F) - rt * (double)LOG2E_F) * LN2_D;
-    const double adj_g = ((double)(ref_g * LOG2E_F) - rg * (double)LOG2E_F) * LN2_D;
-    const double ln_z = log((double)Zt32 / (double)Zg32) + adj_t - adj_g;
-    const double ln_hi = ln_z + TAU_SIGN, ln_lo = ln_z - TAU_SIGN;
+    // A rolled loop with the vectors shifted down behind it and each chunk's two sums put at the end (after the
+    // last turn they are in the chunks' order): registers are indexed statically and the code stays small.
+    uint32_t open = 0;                                       // bit c: a token of chunk c is not settled
+    {
+        const double sign_hi = keep[0], sign_lo = keep[1];
+        constexpr int STEP = NV * EPV <= 32 ? NV : 16 / EPV; // at most 32 tokens a turn
 #pragma unroll 1
-    for (int c = 0; c < NV; ++c) {
-        uint4 gv = G[0];
+        for (int c = 0; c < NV; c += STEP) {
+            uint4 sums[STEP];
 #pragma unroll
-        for (int i = 0; i + 1 < NV; ++i) G[i] = G[i + 1];
-        const int vi = c * TNT + tid;
-        const bool live = FULL || vi < nvec;
-        uint4 tv = live ? reinterpret_cast<const uint4*>(s_row)[vi]
-                        : make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
-        const int x0 = vi * EPV;
-        unsigned in_a = live ? (mask[x0 >> 5] >> (x0 & 31)) & ((1u << EPV) - 1u) : 0u;   // EPV divides 32
-        acc.pt = 0.0;
-        acc.pg = 0.0;
-#pragma unroll 1
-        for (int e = 0; e < EPV; e += 2) {
-            const float lt0 = L::get(tv, 0), lt1 = L::get(tv, 1), lg0 = L::get(gv, 0), lg1 = L::get(gv, 1);
-            // t_A is zero on A without the token, the token's own residual is zero in a rejected row,
-            // and a filtered target token has t = 0
-            const bool zero0 = (in_a & 1u) || (x0 + e == xt) || lt0 == neg_inf_f();
-            const bool zero1 = (in_a & 2u) || (x0 + e + 1 == xt) || lt1 == neg_inf_f();
-            one_pass_token(acc, lt0, lg0, zero0, x0 + e, rt, rg, floor_t, floor_g, ln_hi, ln_lo, tab_lds, amb, amb_count);
-            one_pass_token(acc, lt1, lg1, zero1, x0 + e + 1, rt, rg, floor_t, floor_g, ln_hi, ln_lo, tab_lds, amb, amb_count);
-            tv = L::drop2(tv);
-            gv = L::drop2(gv);
-            in_a >>= 2;
-        }
-        const double pt = wave_sum_dpp(acc.pt);
-        const double pg = wave_sum_dpp(acc.pg);
-        if (lane == 0) {
-            seg[2 * (c * TNW + wave)] = pt;
-            seg[2 * (c * TNW + wave) + 1] = pg;
+            for (int u = 0; u < STEP; ++u) {
+                double pt, pg;
+                const bool o = one_pass_vector<LT>(target_vector((c + u) * TNT + tid), G[u], rt, rg, sign_hi, sign_lo, tab,
+                                                   acc, &pt, &pg);
+                open |= o ? 1u << (c + u) : 0u;
+                sums[u] = __builtin_bit_cast(uint4, double2{pt, pg});
+            }
+#pragma unroll
+            for (int i = 0; i + STEP < NV; ++i) G[i] = G[i + STEP];
+#pragma unroll
+            for (int u = 0; u < STEP; ++u) G[NV - STEP + u] = sums[u];
         }
     }
-    const double zt = block_sum<TNW>(acc.zt, sh.red, tid);
-    const double zg = block_sum<TNW>(acc.zg, sh.red2, tid); // its barriers publish seg and the list
+    rt.start = keep[2];
+    rg.start = keep[3];
+    while (__any(open != 0)) {                               // once or so a row: which tokens, and their terms once more
+        if (open) {
+            const int c = __ffs((int)open) - 1;
+            open &= open - 1;
+#pragma unroll 1
+            for (int e = 0; e < EPV; ++e) {
+                const int x = (c * TNT + tid) * EPV + e;     // a token beyond V is not open, its vector may be
+                const float lt = x < V ? L::lds(s_row, x) : neg_inf_f(), lg = L::glob(grow, x < V ? x : V - 1);
+                const double dd = rt.arg(lt) - rg.arg(lg);
+                if (dd > keep[1] && !(dd > keep[0])) {
+                    const int slot = atomicAdd(amb_count, 1);
+                    if (slot < AMB_CAP) {
+                        amb[slot].et = rt.term(lt, tab);
+                        amb[slot].eg = rg.term(lg, tab);
+                        amb[slot].x = x;
+                    }
+                }
+            }
+        }
+    }
+    {
+        double sums[2 * NV];
+#pragma unroll
+        for (int c = 0; c < NV; ++c) {
+            const double2 p = __builtin_bit_cast(double2, G[c]);
+            sums[2 * c] = p.x;
+            sums[2 * c + 1] = p.y;
+        }
+        wave_pair_sums<NV>(sums, lane, [&](int c, int which, double sum) { seg[2 * (c * TNW + wave) + which] = sum; });
+    }
+    acc.zt = wave_sum(acc.zt);
+    acc.zg = wave_sum(acc.zg);
+    if (lane == 0) {
+        sh.red[wave] = acc.zt;
+        sh.red2[wave] = acc.zg;
+    }
+    __syncthreads();                                         // publishes the sums, the segments and the list
+    const double taken = sh.bcast[0];
+    double zt = taken, zg = 0.0;                             // the marked tokens' terms are not in the sums
+#pragma unroll
+    for (int w = 0; w < TNW; ++w) {
+        zt += sh.red[w];
+        zg += sh.red2[w];
+    }
 
     // ---- decision ----
-    const double mass = (e_tx + S) / zt;
-    const double g_tok = e_gx / zg;
+    const double mass = taken / zt;
+    const double g_tok = sh.bcast[1] / zg;
     const bool accepted = ((double)u_acc32 * g_tok < mass);
     if (tid == 0) {
         double ap;
@@ -368,35 +484,39 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
             }
         }
         if (lane == 0) {
-            sh.bcast[0] = before;
-            sh.bcast[1] = cthr;
-            sh.bcast[2] = Z;
+            sh.bcast[2] = before;   // the first two may still be read
+            sh.bcast[3] = cthr;
+            sh.bcast[4] = Z;
             sh.ibcast[0] = s;
         }
     }
     __syncthreads();
-    // a list that overflowed, or a residual without mass (by rounding): the general path
-    // (uniform over the workgroup)
-    if (n_amb > AMB_CAP || !(sh.bcast[2] > 0.0)) {
-        __syncthreads();   // the general path reuses this LDS
+    // a list that overflowed, or a residual without mass (by rounding): the general path, which finds the row as
+    // it was (uniform over the workgroup)
+    if (n_amb > AMB_CAP || !(sh.bcast[4] > 0.0)) {
+        const LT* trow = reinterpret_cast<const LT*>(a.target) + (int64_t)lrow * a.stride;
+        for (int j = tid; j < a_size; j += TNT) reinterpret_cast<LT*>(s_row)[nrow[j]] = trow[nrow[j]];
+        if (tid == 0) reinterpret_cast<LT*>(s_row)[xt] = trow[xt];
+        __syncthreads();
         return false;
     }
+    // One residual term of the token-by-token evaluation: max(0, t_A(x) - g(x)), zero on A and at xt
+    auto residual = [&](float lt, float lg) {
+        const double d = rt.term(lt, tab) * inv_zt - rg.term(lg, tab) * inv_zg;
+        return d > 0.0 ? d : 0.0;
+    };
     const int ent = sh.ibcast[0];
     if (wave == (ent % TNW)) {
-        const double P = sh.bcast[0], cthr = sh.bcast[1];
+        const double P = sh.bcast[2], cthr = sh.bcast[3];
         const int vi = (ent / TNW) * TNT + tid;
         const int x0 = vi * EPV;
-        const bool live = FULL || vi < nvec;
-        const uint4 ninf = make_uint4(L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD, L::NEG_INF_WORD);
         const uint4 gv = draft_vector(vi);                   // this segment of the drafter's row, once more
-        const uint4 tv = live ? reinterpret_cast<const uint4*>(s_row)[vi] : ninf;
-        const unsigned in_a = live ? (mask[x0 >> 5] >> (x0 & 31)) & ((1u << EPV) - 1u) : 0u;
+        const uint4 tv = target_vector(vi);
         double r[EPV];
         double sum = 0.0;
 #pragma unroll
         for (int e = 0; e < EPV; ++e) {
-            r[e] = one_pass_term(L::get(tv, e), L::get(gv, e), ((in_a >> e) & 1u) || (x0 + e == xt), rt, rg, inv_zt,
-                                 inv_zg, tab);
+            r[e] = residual(L::get(tv, e), L::get(gv, e));
             sum += r[e];
         }
         const double incl = wave_scan_incl(sum);
@@ -426,23 +546,13 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
             // the one the cumulative sum reaches next; failing that, the last one before it.
             const int seg_x0 = ((ent / TNW) * TNT + (ent % TNW) * WAVE) * EPV;   // first token of the segment
             int before = -1, after = INT_MAX;
-            for (int v0 = 0; v0 < nvec; v0 += WAVE) {
-                const int v = v0 + lane;
-                const bool lv = v < nvec;
-                const uint4 gq = draft_vector(lv ? v : nvec - 1);
-                const uint4 tq = lv ? reinterpret_cast<const uint4*>(s_row)[v] : ninf;
-                const unsigned ia = lv ? (mask[(v * EPV) >> 5] >> ((v * EPV) & 31)) & ((1u << EPV) - 1u) : 0u;
-                int first = INT_MAX, last = -1;
-#pragma unroll
-                for (int e = 0; e < EPV; ++e) {
-                    const int x = v * EPV + e;
-                    const bool has = one_pass_term(L::get(tq, e), L::get(gq, e), ((ia >> e) & 1u) || x == xt, rt, rg,
-                                                   inv_zt, inv_zg, tab) > 0.0;
-                    if (has && x >= seg_x0 && x < first) first = x;
-                    if (has && x < seg_x0) last = x;
-                }
-                after = min(after, wave_min(first));
-                before = max(before, -wave_min(-last));
+            for (int x1 = 0; x1 < V; x1 += WAVE) {
+                const int x = x1 + lane;
+                const bool has = x < V && residual(L::lds(s_row, x < V ? x : 0), L::glob(grow, x < V ? x : 0)) > 0.0;
+                const unsigned long long m = __ballot(has);
+                const unsigned long long ahead = __ballot(has && x >= seg_x0), behind = m & ~ahead;
+                if (ahead && after == INT_MAX) after = x1 + __ffsll((long long)ahead) - 1;
+                if (behind) before = x1 + 63 - __clzll((long long)behind);
             }
             found = after != INT_MAX ? after : before;
         }
@@ -481,7 +591,7 @@ __global__ __launch_bounds__(TNT, NV > 8 ? 3 : 4) void verify_fast(VerifyArgs a)
     constexpr int EPV = L::EPV;
     constexpr int TNW = TNT / WAVE;
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char* s_row = smem + EXP_TABLE_BYTES;           // the fp64 path's table goes in front
+    unsigned char* s_row = smem + EXP_FINE_BYTES;            // the fp64 paths' table goes in front
     const int row_bytes = (a.V * (int)sizeof(LT) + 15) & ~15;
     FastShared<TNW>& sh = *reinterpret_cast<FastShared<TNW>*>(s_row + row_bytes);
     unsigned char* ex_lds = s_row + row_bytes + sizeof(FastShared<TNW>);
@@ -697,7 +807,7 @@ __global__ __launch_bounds__(TNT, NV > 8 ? 3 : 4) void verify_fast(VerifyArgs a)
                 done = exact_one_pass<LT, TNT, NV, ROWS>(a, row, lrow, m.nb, rt, rg, Zt, Zg, a_size, xt, m.lg_tok,
                                                          m.u_acc, smem, ex_lds, s_row);
             // one call, so that it is inlined: as a function its argument block goes through memory
-            if (!done) exact_row<LT, ROWS == ROWS_ANY ? ROW_ANY : ROW_WHOLE, TNT>(a, row, ex_lds, s_row, false, 0.f, 0.f);
+            if (!done) exact_row<LT, ROWS == ROWS_ANY ? ROW_ANY : ROW_WHOLE, TNT>(a, row, ex_lds, s_row, false, 0.f, 0.f, nullptr, smem);
         }
     }
 }
@@ -737,13 +847,15 @@ __device__ __forceinline__ double resid_term(int x, int xt, int V, float lt, flo
 
 // Evaluates one row in fp64 with the whole workgroup.  ex: LDS region of
 // exact_lds_bytes().  lds_row, lds_grow: the raw target / draft row in LDS, or null.  have_max:
-// the caller has the row maxima and knows both rows are free of NaN and +inf.
+// the caller has the row maxima and knows both rows are free of NaN and +inf.  tab_lds: where the exponential's table
+// goes, or null: at the end of the region (exact_table_offset() bytes are enough otherwise).
 // TNT: threads of the calling workgroup.  Token order of the vector layout: vector vi = chunk*TNT + tid, so (chunk,
 // wavefront, lane, element) is ascending token order.  Every pass over the row
 // loads the next chunk's vectors before it works on the current one.
 template <typename LT, int FORM, int TNT>
 __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned char* ex, const unsigned char* lds_row,
-                          bool have_max, float max_t, float max_g, const unsigned char* lds_grow) {
+                          bool have_max, float max_t, float max_g, const unsigned char* lds_grow,
+                          unsigned char* tab_lds) {
     constexpr int TNW = TNT / WAVE;
     const bool selected = a.mode == VERIFY_SELECTED;
     const int out = selected ? (int)blockIdx.x : row;   // slot of the outputs this workgroup writes
@@ -758,7 +870,7 @@ __device__ __forceinline__ void exact_row(const VerifyArgs& a, int row, unsigned
     const int V = a.V;
     const int k = a.k;
     const int nwords = (V + 31) >> 5;
-    double* tab = reinterpret_cast<double*>(ex + exact_table_offset(V, TNT));
+    double* tab = reinterpret_cast<double*>(tab_lds ? tab_lds : ex + exact_table_offset(V, TNT));
     for (int i = tid; i < 2 * EXP_TABLE_N; i += TNT) tab[i] = EXP_TABLE_HILO[i];   // published by the first barrier below
     double* wtot = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(mask) + (((size_t)nwords * 4 + 7) & ~size_t(7)));
     const int nvec = (V + EPV - 1) / EPV;
@@ -1076,9 +1188,9 @@ template <typename LT>
 static size_t fast_lds_bytes(int V, int threads, int nv) {
     const size_t row_bytes = ((size_t)V * sizeof(LT) + 15) & ~size_t(15);
     const size_t head = threads == 256 ? sizeof(FastShared<4>) : threads == 512 ? sizeof(FastShared<8>) : sizeof(FastShared<16>);
-    const size_t one_pass = one_pass_layout(V, nv * (threads / WAVE)).total;
-    const size_t exact = exact_lds_bytes(V, threads);
-    return EXP_TABLE_BYTES + row_bytes + head + (one_pass > exact ? one_pass : exact);
+    const size_t one_pass = one_pass_layout(nv * (threads / WAVE)).total;
+    const size_t exact = exact_table_offset(V, threads);
+    return EXP_FINE_BYTES + row_bytes + head + (one_pass > exact ? one_pass : exact);
 }
 
 // Rows of 16-byte aligned whole vectors, stride included.

@@ -172,7 +172,7 @@ constexpr int MAXW = 16;
 struct ExactShared {
     double red[MAXW];
     double red2[MAXW];
-    double bcast[4];
+    double bcast[6];
     int ired[MAXW];
     int ibcast[2];
 };
