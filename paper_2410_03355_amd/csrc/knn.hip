@@ -60,12 +60,15 @@ constexpr size_t PACKED_STEP_BYTES = 64 * 16;
 __host__ __device__ inline size_t packed_tiles(int tokens) { return ((size_t)tokens + 31) / 32; }
 __host__ __device__ inline size_t packed_steps(int d, int cb_dtype) { return cb_dtype == 1 ? ((size_t)d + 15) / 16 : ((size_t)d + 7) / 8; }
 
+// Largest sample whose keys to 32 rows fit the registers of one workgroup (knn_thresholds).
+constexpr int THRESHOLDS_MAX_S = 2048;
+
 struct KnnLayout {
     size_t stats, norms, nmax, dist, flags, slow, total;
     // sampled-threshold path (filter.use): the codebook and the sample as matrix-core operands, what the
-    // contraction folds in per token, the sample's norms, a row block's keys to the sample, its thresholds,
-    // list lengths and candidate lists; `dist` is then not laid out
-    size_t packed, spacked, fold, snorms, skeys, thr, counts, cand;
+    // contraction folds in per token and per sampled token, the sample's norms and a row block's keys to it (samples
+    // too large for knn_thresholds only), its thresholds, list lengths and candidate lists; `dist` is then not laid out
+    size_t packed, spacked, fold, sfold, snorms, skeys, thr, counts, cand;
     FilterPlan filter;
     int row_block;   // query rows per pass through the key block
     int slow_wgs;    // workgroups (and fp64 row buffers) of the exact pass
@@ -80,17 +83,19 @@ static KnnLayout knn_layout(int V, int d, int cb_dtype, const FilterPlan& plan, 
     L.stats = off; off = align_up(off + 256, 256);   // int32[0]: rows that took the exact all-pairs pass
     L.norms = off; off = align_up(off + sizeof(float) * (size_t)V, 256);
     L.nmax = off;  off = align_up(off + 256, 256);
-    L.dist = L.packed = L.spacked = L.fold = L.snorms = L.skeys = L.thr = L.counts = L.cand = off;
+    L.dist = L.packed = L.spacked = L.fold = L.sfold = L.snorms = L.skeys = L.thr = L.counts = L.cand = off;
     if (plan.use) {
         const size_t steps = packed_steps(d, cb_dtype);
         L.packed = off;  off = align_up(off + packed_tiles(V) * steps * PACKED_STEP_BYTES, 256);
         L.spacked = off; off = align_up(off + packed_tiles(plan.S) * steps * PACKED_STEP_BYTES, 256);
         L.fold = off;    off = align_up(off + sizeof(float) * 32 * packed_tiles(V), 256);
+        L.sfold = off;   off = align_up(off + sizeof(float) * (size_t)plan.S, 256);
         L.snorms = off; off = align_up(off + sizeof(float) * (size_t)plan.S, 256);
-        L.skeys = off;  off = align_up(off + sizeof(float) * (size_t)L.row_block * plan.S, 256);
+        L.skeys = off;
+        if (plan.S > THRESHOLDS_MAX_S) off = align_up(off + sizeof(float) * (size_t)L.row_block * plan.S, 256);
         L.thr = off;    off = align_up(off + sizeof(float) * (size_t)L.row_block, 256);
         L.counts = off; off = align_up(off + sizeof(int) * (size_t)L.row_block, 256);
-        L.cand = off;   off = align_up(off + sizeof(uint2) * (size_t)L.row_block * plan.cap, 256);
+        L.cand = off;   off = align_up(off + (plan.tokens ? sizeof(uint32_t) : sizeof(uint2)) * (size_t)L.row_block * plan.cap, 256);
     } else {
         L.dist = off;   off = align_up(off + sizeof(float) * (size_t)L.row_block * V, 256);
     }
@@ -112,7 +117,7 @@ static KnnLayout knn_layout_within(int V, int d, int cb_dtype, const FilterPlan&
     return none;
 }
 
-static const FilterPlan NO_FILTER = {false, 0, 0, 0, 0};
+static const FilterPlan NO_FILTER = {false, false, false, 0, 0, 0, 0};
 
 // What lantern_build_knn asks of its caller: the layout of the path the shape takes.  A codebook
 // that turns out not to be 16-byte aligned falls back to whole key blocks of as many rows as
@@ -236,6 +241,86 @@ __device__ double exact_key(const CT* cb, int d, int i, int j, int metric, bool 
     return key == key ? key : (double)INFINITY;   // no similarity (a code of zero norm): the farthest
 }
 
+// The same key for rows of whole 16-byte vectors at aligned addresses, the row's own code as doubles in LDS (`own`).
+// The arithmetic is the definition's, in its order; U vectors of the other code are on their way together.
+// norm2 (cosine key): the sum of squares of the row's own code, in order.
+typedef uint32_t vec4u __attribute__((ext_vector_type(4)));
+template <typename CT, int METRIC>
+struct KeySum {
+    static constexpr int EPV = 16 / (int)sizeof(CT);
+    double acc = 0.0, nj = 0.0;
+    __device__ __forceinline__ void add(const vec4u& v, const double* own) {
+#pragma clang fp contract(off)
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+            const uint32_t word = EPV == 4 ? v[e] : v[e >> 1];
+            const float yf = EPV == 4 ? __uint_as_float(word) : __uint_as_float((e & 1) ? (word & 0xFFFF0000u) : (word << 16));
+            const double x = own[e], y = (double)yf;
+            if (METRIC == 0) {
+                const double diff = x - y;
+                const double sq = diff * diff;
+                acc = acc + sq;
+            } else {
+                const double yy = y * y;
+                const double xy = x * y;
+                nj = nj + yy;
+                acc = acc + xy;
+            }
+        }
+    }
+    __device__ __forceinline__ double key(double norm2) const {
+#pragma clang fp contract(off)
+        double k = acc;
+        if (METRIC != 0) {
+            const double den = sqrt(norm2) * sqrt(nj);
+            k = -(acc / den);
+        }
+        return k == k ? k : (double)INFINITY;
+    }
+};
+constexpr int VEC_MAX_D = 1024;   // own code in LDS: 8 KiB
+template <typename CT, int METRIC, int U>
+__device__ __forceinline__ double exact_key_vec(const CT* cb, int vecs, const double* own, int j, double norm2) {
+    constexpr int EPV = KeySum<CT, METRIC>::EPV;
+    const vec4u* cj = reinterpret_cast<const vec4u*>(cb) + (int64_t)j * vecs;
+    KeySum<CT, METRIC> sum;
+    int c = 0;
+    for (; c + U <= vecs; c += U) {
+        vec4u v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = cj[c + u];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            sum.add(v[u], own + (c + u) * EPV);
+            asm volatile("" : "+v"(sum.acc) : : "memory");   // the own code is read vector by vector, not all at once into registers
+        }
+    }
+    if (c + 2 <= vecs) {
+        const vec4u v0 = cj[c], v1 = cj[c + 1];
+        sum.add(v0, own + c * EPV);
+        sum.add(v1, own + (c + 1) * EPV);
+        c += 2;
+    }
+    for (; c < vecs; ++c) sum.add(cj[c], own + c * EPV);
+    return sum.key(norm2);
+}
+inline size_t own_code_bytes(int d, int vecs) { return vecs ? (size_t)d * sizeof(double) : 0; }
+// The row's own code as doubles into LDS, by the whole workgroup (a barrier follows at the caller), and the sum of
+// its squares in order.
+template <typename CT>
+__device__ __forceinline__ void own_code(const CT* row, int d, double* own, int tid, int threads) {
+    for (int t = tid; t < d; t += threads) own[t] = (double)cb_f32<CT>(row, t);
+}
+__device__ __forceinline__ double own_norm2(const double* own, int d) {
+#pragma clang fp contract(off)
+    double n = 0.0;
+    for (int t = 0; t < d; ++t) {
+        const double xx = own[t] * own[t];
+        n = n + xx;
+    }
+    return n;
+}
+
 // The approximate cosine keys are good to their error bound as long as a product of two coordinates that falls below
 // the normal floats is nothing beside the codes' norms and no sum leaves the floats.  A code beyond
 // COSINE_MIN .. COSINE_MAX (squared norm) leaves every row to the all-pairs pass, unless its exact keys do not
@@ -311,6 +396,10 @@ template <> __device__ __forceinline__ float sum_squares<uint16_t>(const uint4& 
     return n;
 }
 
+// Whether fp32 values formed from a code are numbers whatever the other code: its squared norm n is moderate, and under
+// the cosine key not zero.
+__device__ __forceinline__ bool plain_code(float n, int metric) { return n < 0x1p120f && (metric == 0 || n > 0.f); }
+
 // Squared norms of the rows (for the cosine key one over their roots: a product of two squared norms
 // may leave the floats) and the largest squared norm, for rows that are whole 16-byte vectors at 16-byte
 // aligned addresses.  *nmax is cleared beforehand; a norm is never below +0, so the bit patterns
@@ -355,7 +444,8 @@ __global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, int 
         if (lane < RPW && i < V) {
             norms[i] = metric == 0 ? t : rsqrtf(t);
             m = fmaxf(m, t);
-            if (cosine_in_doubt(cb + (int64_t)i * d, d, t)) *doubt = 1;
+            if (cosine_in_doubt(cb + (int64_t)i * d, d, t)) doubt[0] = 1;
+            if (!plain_code(t, metric)) doubt[1] = 1;
         }
     } else {
         const int i = blockIdx.x * NT + threadIdx.x;
@@ -363,7 +453,8 @@ __global__ __launch_bounds__(NT) void knn_norms(const CT* cb, int V, int d, int 
             float n = 0.f;
             for (int c = 0; c < vecs; ++c) n = sum_squares<CT>(cbv[(int64_t)i * vecs + c], n);
             norms[i] = metric == 0 ? n : rsqrtf(n);
-            if (cosine_in_doubt(cb + (int64_t)i * d, d, n)) *doubt = 1;
+            if (cosine_in_doubt(cb + (int64_t)i * d, d, n)) doubt[0] = 1;
+            if (!plain_code(n, metric)) doubt[1] = 1;
             m = fmaxf(m, n);
         }
     }
@@ -577,12 +668,21 @@ __global__ __launch_bounds__(NT) void knn_dist_mfma(const CT* cb, const float* n
 
 // Where the filtering contraction leaves a row block's candidates.
 struct FilterOut {
-    const float* thr;   // [rows] threshold of each row of the block
+    const float* thr;   // [rows] threshold of each row of the block, as a value (below)
     int* counts;        // [rows] keys at or below the threshold so far (may pass cap: the list is then cut)
-    uint2* cand;        // [rows, cap] (order-preserving key, token), in no particular order
+    void* cand;         // [rows, cap] tokens or (order-preserving key, token), in no particular order
     int cap;
 };
-
+// The mask moved up by one, the freed bit set where the value lies below `least` (both numbers): a subtraction and
+// its sign shifted in.  A compare would leave its result in scalar registers, which the next instruction may only
+// read two cycles later.
+__device__ __forceinline__ uint32_t shift_in_below(uint32_t mask, float value, float least) {
+    return __builtin_amdgcn_alignbit(mask, __float_as_uint(value - least), 31);
+}
+// The same where a value or `least` may be no number, or both the same infinity: what does not compare is below.
+__device__ __forceinline__ uint32_t shift_in_unless(uint32_t mask, float value, float least) {
+    return (mask + mask) + (value >= least ? 0u : 1u);
+}
 // The filtering contraction takes the tokens as rows of its tiles and the query rows as columns: a
 // lane then holds one query's values only, its threshold is one register, and a hit costs a compare.
 // What is compared is not the key but its token-dependent part, larger for nearer tokens:
@@ -605,34 +705,52 @@ __device__ __forceinline__ void load_fold(const float* fold, int tile, int lane,
     }
 }
 
-// LDS of the filtering contraction: per row of the workgroup's 128 the value its threshold stands for,
-// its norm (knn_norms) and a counter (first: keys kept; then: next free slot of the row's list).
+// What the filtering contraction writes for a row.
+enum ListForm {
+    LIST_TOKENS,   // uint32 tokens
+    LIST_PAIRS     // uint2 (order-preserving key, token)
+};
+
+// LDS of the filtering contraction.  A hit is staged as 512 * (row of the tile) + (token of the tile), the hits of a row
+// next to each other, STAGE of them at a time.
+template <int FORM>
 struct FilterShared {
-    float val[128];
-    float norm[128];
-    int slots[128];
+    static constexpr int STAGE = FORM == LIST_TOKENS ? FILTER_STAGE : 4096;
+    int next[128];      // keys of the row kept; then the next free place among the tile's hits
+    int start[128];     // first place of the row's hits
+    int base[128];      // where they go in the row's list
+    int total;
+    uint16_t stage[STAGE];
+    float value[FORM == LIST_PAIRS ? STAGE : 1];
+    float norm[FORM == LIST_PAIRS ? 128 : 1];
 };
 
 // Filtering contraction: rows [r0, r0 + rows) against the whole codebook, keeping for every row
-// only the (key, token) pairs at or below the row's threshold.  A workgroup owns a tile of 128
-// rows by 128 tokens.  It contracts, counts the kept keys per row in LDS, reserves each row's
-// slots in its list with one atomic add per row, and then places the keys (the accumulators stay
-// in registers meanwhile, which values are kept in a bit mask per lane).
+// only the tokens (and keys) at or below the row's threshold.  A workgroup owns a tile of 128
+// rows by TT * 128 tokens.  It contracts, counts the kept keys per row in LDS, reserves each row's
+// slots in its list with one atomic add per row, and stages the hits in LDS row by row, from where they are written
+// out as runs (left to the lanes that found them, the writes were as many requests as hits, 26 million for
+// V = 16384, k = 1000, and each hit cost a dozen instructions for its key and address).
 // Grid: one-dimensional, 8 * ceil(row tiles / 8) * column tiles workgroups, dealt so that all
 // column tiles of a row strip run on one XCD (workgroups go to the eight XCDs in turn) and a
 // row's list and counter stay in that XCD's L2.
-// Bound by the compares and the placing of hits at small d, by the operand loads at large d.  With
-// queries across the lanes and packed operands 278 -> 210 us (V = 16384, d = 8 fp32, k = 1000) and
-// 145 -> 82 us (V = 8192, d = 256 bf16, k = 100) against tiles with queries as rows, whose hits took
-// two ballots and four population counts per element, read from the codebook itself.
-template <typename CT, int METRIC>
-__global__ __launch_bounds__(NT, 2) void knn_filter_list(const uint4* packed, const float* fold, const float* norms, int V,
-                                                         int steps, int r0, int rows, FilterOut f) {
-    __shared__ FilterShared sh;
+// A hit is a bit of a lane's mask: compare and shift in, two instructions a value.  Tokens alone are placed by walking
+// the masks' bits, so several column tiles share one reservation; with keys, whose registers cannot be numbered at run
+// time, by going over all 32 values, and the tile is one.
+// V = 16384, d = 8 fp32, k = 1000: 193 us with hits written by the lanes that found them, 189 staged with their keys,
+// 126 staged as tokens, 108 with 512 tokens to a tile and masks of shifted-in signs.  V = 8192, d = 256 bf16,
+// k = 100 (keys kept; bound by the operand loads): 78 -> 73.
+template <typename CT, int METRIC, int FORM, int TT>
+__global__ __launch_bounds__(NT, 4) void knn_filter_list(const uint4* packed, const float* fold, const float* norms, int V,
+                                                         int steps, int r0, int rows, const int* doubt, FilterOut f) {
+    static_assert(TT == 1 || FORM == LIST_TOKENS, "keys stay in the accumulators until they are placed");
+    static_assert(TT * 128 <= 512, "nine bits of a staged hit");
+    constexpr int STAGE = FilterShared<FORM>::STAGE;
+    __shared__ FilterShared<FORM> sh;
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
     const int wave = tid >> 6;
-    const int nct = (V + 127) / 128, nrt = (rows + 127) / 128;
+    const int nct = (V + 128 * TT - 1) / (128 * TT), nrt = (rows + 127) / 128;
     const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
     const int ti = (q / nct) * 8 + xcd;
     const int tj = q % nct;
@@ -640,27 +758,31 @@ __global__ __launch_bounds__(NT, 2) void knn_filter_list(const uint4* packed, co
     const int tiles = (int)packed_tiles(V);
     const int il_wg = ti * 128;        // first row of the workgroup within the block
     const int l_base = (wave >> 1) * 64;
-    const int t_base = tj * 4 + (wave & 1) * 2;   // first token tile
-    const bool live = t_base < tiles;
+    const bool plain = doubt[1] == 0;
     if (tid < 128) {
-        const bool row_ok = il_wg + tid < rows;
-        const float n = row_ok ? norms[r0 + il_wg + tid] : 1.f;
-        sh.norm[tid] = n;
-        sh.val[tid] = row_ok ? value_at<METRIC>(f.thr[il_wg + tid], n) : NAN;   // beyond the block: nothing is kept
-        sh.slots[tid] = 0;
+        sh.next[tid] = 0;
+        if (FORM == LIST_PAIRS) sh.norm[tid] = norms[r0 + min(il_wg + tid, rows - 1)];
     }
-    __syncthreads();
-    f32x16 acc[2][2];   // [token strip][query strip]
-    uint32_t hits[2] = {0u, 0u};
-    if (live) {
+    float least[2];                    // of the lane's two rows; beyond the block nothing is kept
+    const uint4* bp[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int il = il_wg + l_base + b * 32 + (lane & 31);
+        const float t = f.thr[min(il, rows - 1)];
+        least[b] = il < rows ? t : plain ? INFINITY : NAN;
+        bp[b] = packed_operand(packed, (r0 + il_wg + l_base) / 32 + b, tiles, steps, lane);
+    }
+    f32x16 acc[2][2];      // [token strip][query strip]
+    uint32_t hits[TT][2];  // bit 31 - (16 a + r): element r of token strip a
+#pragma unroll
+    for (int c = 0; c < TT; ++c) {
+        const int t_base = (tj * TT + c) * 4 + (wave & 1) * 2;   // first token tile
+        hits[c][0] = hits[c][1] = 0u;
+        if (t_base >= tiles) continue;                           // uniform
         const uint4* ap[2];
-        const uint4* bp[2];
         float fd[2][16];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            ap[t] = packed_operand(packed, t_base + t, tiles, steps, lane);
-            bp[t] = packed_operand(packed, (r0 + il_wg + l_base) / 32 + t, tiles, steps, lane);
-        }
+        for (int t = 0; t < 2; ++t) ap[t] = packed_operand(packed, t_base + t, tiles, steps, lane);
         if (METRIC == 0) {
 #pragma unroll
             for (int a = 0; a < 2; ++a) load_fold(fold, min(t_base + a, tiles - 1), lane, fd[a]);
@@ -682,49 +804,106 @@ __global__ __launch_bounds__(NT, 2) void knn_filter_list(const uint4* packed, co
                     for (int r = 0; r < 16; ++r) acc[a][b][r] *= fd[a][r];
             }
         }
-        const bool second = t_base + 1 < tiles;   // else strip 1 is strip 0 once more
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const int l = l_base + b * 32 + (lane & 31);
-            const float least = sh.val[l];
-            uint32_t h = 0;   // bit 16 a + r
+            uint32_t h = 0;
+            if (plain) {
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
+                for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) h |= acc[a][b][r] >= least ? 1u << (16 * a + r) : 0u;
-            if (!second) h &= 0xFFFFu;
+                    for (int r = 0; r < 16; ++r) h = shift_in_below(h, acc[a][b][r], least[b]);
+            } else {
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) h = shift_in_unless(h, acc[a][b][r], least[b]);
+            }
+            h = ~h;
+            if ((t_base + 2) * 32 > V) {   // the last tiles: nothing beyond the vocabulary (nor strip 0 once more)
+                const int left = V - t_base * 32 - 4 * (lane >> 5);
+                for (int i = 0; i < 32; ++i)
+                    if (i + (i & 28) >= left) h &= ~(0x80000000u >> i);
+            }
             // the row itself is no candidate
-            const int own = r0 + il_wg + l - t_base * 32;   // within the two strips?
-            if ((unsigned)own < 64u && ((own >> 2) & 1) == (lane >> 5))
-                h &= ~(1u << (16 * (own >> 5) + 4 * ((own & 31) >> 3) + (own & 3)));
-            hits[b] = h;
-            if (h) atomicAdd(&sh.slots[l], __popc(h));
+            const int own = r0 + il_wg + l_base + b * 32 + (lane & 31) - t_base * 32;   // within the two strips?
+            if ((unsigned)own < 64u && ((own >> 2) & 1) == (lane >> 5)) h &= ~(0x80000000u >> (4 * (own >> 3) + (own & 3)));
+            hits[c][b] = h;
         }
     }
-    __syncthreads();
-    if (tid < 128) {
-        const int n = sh.slots[tid];   // n > 0 only for rows of the block
-        sh.slots[tid] = n > 0 ? atomicAdd(f.counts + il_wg + tid, n) : 0;
+    __syncthreads();                   // the counters are cleared
+    int mine[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        mine[b] = 0;
+#pragma unroll
+        for (int c = 0; c < TT; ++c) mine[b] += __popc(hits[c][b]);
+        if (mine[b]) atomicAdd(&sh.next[l_base + b * 32 + (lane & 31)], mine[b]);
     }
     __syncthreads();
-    if (live) {
+    if (wave == 0) {                   // places of the rows' hits, and their slots in the lists; two rows a lane
+        const int2 n = *reinterpret_cast<const int2*>(&sh.next[2 * lane]);   // above 0 only for rows of the block
+        int2 base = make_int2(0, 0);
+        if (n.x > 0) base.x = atomicAdd(f.counts + il_wg + 2 * lane, n.x);
+        if (n.y > 0) base.y = atomicAdd(f.counts + il_wg + 2 * lane + 1, n.y);
+        const int incl = wave_scan_i<OpSum>(n.x + n.y, 0);
+        const int2 at = make_int2(incl - n.x - n.y, incl - n.y);
+        *reinterpret_cast<int2*>(&sh.start[2 * lane]) = at;
+        *reinterpret_cast<int2*>(&sh.next[2 * lane]) = at;
+        *reinterpret_cast<int2*>(&sh.base[2 * lane]) = base;
+        if (lane == WAVE - 1) sh.total = incl;
+    }
+    __syncthreads();
+    const int total = sh.total;
+    int place[2] = {0, 0};
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+        if (mine[b]) place[b] = atomicAdd(&sh.next[l_base + b * 32 + (lane & 31)], mine[b]);
+    for (int from = 0; from < total; from += STAGE) {   // once, unless more than STAGE of the tile's pairs are kept
+        if (from) __syncthreads();
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const int l = l_base + b * 32 + (lane & 31);
-            const uint32_t h = hits[b];
-            const float n = sh.norm[l];
-            int slot = h ? atomicAdd(&sh.slots[l], __popc(h)) : 0;
-            uint2* list = f.cand + (int64_t)(il_wg + l) * f.cap;   // only dereferenced for rows of the block
+            int at = place[b] - from;
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if ((h >> (16 * a + r)) & 1u) {
-                        const int j = (t_base + a) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                        const float key = key_of_value<METRIC>(acc[a][b][r], n);
-                        if (slot < f.cap) list[slot] = make_uint2(min(ord_key(key), 0xFFFFFFFEu), (uint32_t)j);
-                        ++slot;
+            for (int c = 0; c < TT; ++c) {
+                uint32_t h = hits[c][b];
+                const int mark = (l_base + b * 32 + (lane & 31)) * 512 + c * 128 + (wave & 1) * 64 + 4 * (lane >> 5);
+                if (FORM == LIST_TOKENS) {
+                    while (h) {
+                        const int i = __clz((int)h);
+                        h &= ~(0x80000000u >> i);
+                        if ((unsigned)at < (unsigned)STAGE) sh.stage[at] = (uint16_t)(mark + i + (i & 28));
+                        ++at;
                     }
+                } else {
+#pragma unroll
+                    for (int a = 0; a < 2; ++a)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (h & (0x80000000u >> (16 * a + r))) {
+                                if ((unsigned)at < (unsigned)STAGE) {
+                                    sh.stage[at] = (uint16_t)(mark + 32 * a + 8 * (r >> 2) + (r & 3));
+                                    sh.value[at] = acc[a][b][r];
+                                }
+                                ++at;
+                            }
+                }
+            }
+        }
+        __syncthreads();
+        for (int e = tid; e < min(total - from, STAGE); e += NT) {
+            const int s = sh.stage[e];
+            const int row = s >> 9;
+            const int slot = sh.base[row] + (from + e - sh.start[row]);
+            const uint32_t j = (uint32_t)(tj * (128 * TT) + (s & 511));
+            if (slot < f.cap) {
+                const int64_t at = (int64_t)(il_wg + row) * f.cap + slot;
+                if (FORM == LIST_TOKENS) {
+                    static_cast<uint32_t*>(f.cand)[at] = j;
+                } else {
+                    const float key = key_of_value<METRIC>(sh.value[e], sh.norm[row]);
+                    static_cast<uint2*>(f.cand)[at] = make_uint2(min(ord_key(key), 0xFFFFFFFEu), j);
+                }
+            }
         }
     }
 }
@@ -739,10 +918,10 @@ __host__ __device__ inline int sample_token(int s, int S, int V) {
 }
 
 // The packed operands of the codebook (its `tiles` tiles) and, after them, of the sample; one thread per
-// lane of a step.  Also fold[] for every token of those tiles, and the sample's norms.
+// lane of a step.  Also fold[] for every token of those tiles, and the sample's fold and norms.
 template <typename CT, int METRIC>
 __global__ __launch_bounds__(NT) void knn_pack(const CT* cb, const float* norms, int V, int d, int S, int steps,
-                                               uint4* packed, uint4* spacked, float* fold, float* snorms) {
+                                               uint4* packed, uint4* spacked, float* fold, float* sfold, float* snorms) {
     const int tiles = (int)packed_tiles(V), stiles = (int)packed_tiles(S);
     const int64_t t = (int64_t)blockIdx.x * NT + threadIdx.x;
     const int lane = (int)(t & (WAVE - 1));
@@ -771,18 +950,22 @@ __global__ __launch_bounds__(NT) void knn_pack(const CT* cb, const float* norms,
     (of_sample ? spacked + (unit - (int64_t)tiles * steps) * WAVE : packed + unit * WAVE)[lane] = v;
     if (step == 0 && lane < 32) {
         if (!of_sample) fold[slot] = there ? fold_of<METRIC>(norms[slot]) : NAN;
-        else if (there) snorms[slot] = norms[j];
+        else if (there) {
+            snorms[slot] = norms[j];
+            sfold[slot] = fold_of<METRIC>(norms[j]);
+        }
     }
 }
 
 // One wavefront per row: a value with between rank and rank + slack of the row's S <= 64 * NS keys
 // to the sample at or below it (bisection over the integer range of the keys, each step one
-// count) becomes the row's threshold; the row's list length is cleared.
+// count) becomes the row's threshold (as the value that the filtering contraction compares); the row's list length is
+// cleared.  For samples beyond what knn_thresholds holds.
 // (At most four wavefronts per SIMD are aimed at: with more as its goal the compiler's scheduler
 // keeps the register count down by waiting for each of the 64 loads of the largest variant in turn.)
 template <int NS>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, NS > 32 ? 4 : 8))) void knn_sample_rank(const float* skeys, int S, int rows, int rank, int slack,
-                                                      float* thr, int* counts) {
+                                                      const float* norms, int r0, int metric, float* thr, int* counts) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int row = blockIdx.x * NW + (threadIdx.x >> 6);
     if (row >= rows) return;   // whole wavefronts leave; no workgroup barrier below
@@ -819,13 +1002,159 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, NS > 32 ?
         }
     }
     if (lane == 0) {
-        thr[row] = ord_inv((uint32_t)hi);
+        const float key = ord_inv((uint32_t)hi), n = norms[r0 + row];
+        thr[row] = metric == 0 ? value_at<0>(key, n) : value_at<1>(key, n);
+        counts[row] = 0;
+    }
+}
+
+// Thresholds of 32 rows per workgroup of sixteen wavefronts, from the rows' values to the sample (what the filtering
+// contraction compares: larger for nearer tokens).  A wavefront holds the values to its part of the S <= 512 TPW
+// sampled tokens in the accumulators, a lane those of one row (and another lane the other half): the sample's keys
+// never leave the registers.  Searched is a value with between rank and rank + slack of a row's sample values at or
+// above it; every step counts (two instructions a value, a subtraction and its sign shifted into a mask: a compare and an addition
+// of its bit would have to wait for each other through the scalar registers) and adds up over the wavefronts through LDS.  The first
+// guesses are those of a normal distribution with the values' mean and variance (z, per_count: its quantile for the
+// wanted count and the step per count there, in standard deviations), as long as they fall between what is known;
+// after three of them, or when they do not, the interval's integer image is halved, which always ends.
+// Bound by the counts' issue and the operands; V = 16384, d = 8 fp32, S = 2048: 34 us against 82 for a
+// contraction that wrote the keys (47) and a kernel that ranked them by halving alone (35).
+constexpr int THR_THREADS = 1024;
+constexpr int THR_WAVES = THR_THREADS / WAVE;
+template <typename CT, int METRIC, int TPW>
+__global__ __launch_bounds__(THR_THREADS, 4) void knn_thresholds(const uint4* packed, const uint4* spacked, const float* sfold,
+                                                                 int V, int S, int steps, int r0, int rows, int rank,
+                                                                 int slack, float z, float per_count, const int* doubt,
+                                                                 float* least, int* counts) {
+    __shared__ float4 stat[THR_WAVES][32];      // per wavefront and row: sum, sum of squares, least, greatest
+    __shared__ int found[2][THR_WAVES][32];
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wave = threadIdx.x >> 6;
+    const int q = lane & 31;                    // row of the strip
+    const int i0 = r0 + blockIdx.x * 32;
+    const int tiles = S / 32;                   // S is a multiple of 64
+    const int t0 = wave * TPW;
+    const int mine = min(max(tiles - t0, 0), TPW);   // tiles of this wavefront
+    const bool plain = doubt[1] == 0;
+    f32x16 acc[TPW];
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) {
+        float fd[16];
+        load_fold(sfold, min(t0 + u, tiles - 1), lane, fd);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[u][r] = METRIC == 0 ? fd[r] : 0.f;
+    }
+    {
+        const uint4* bp = packed_operand(packed, i0 / 32, (int)packed_tiles(V), steps, lane);
+        const uint4* ap[TPW];
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) ap[u] = packed_operand(spacked, t0 + u, tiles, steps, lane);
+        uint4 nb = bp[0], na[TPW];
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) na[u] = ap[u][0];
+        for (int st = 0; st < steps; ++st) {
+            const uint4 b = nb;
+            uint4 a[TPW];
+            const int n = min(st + 1, steps - 1) * WAVE;   // the next step's operands are on their way meanwhile
+            nb = bp[n];
+#pragma unroll
+            for (int u = 0; u < TPW; ++u) {
+                a[u] = na[u];
+                na[u] = ap[u][n];
+            }
+#pragma unroll
+            for (int u = 0; u < TPW; ++u) mfma_step<CT>(a[u], b, acc[u]);
+        }
+    }
+    float sum = 0.f, squares = 0.f, low = INFINITY, high = neg_inf_f();
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) {
+        if (u < mine) {                         // uniform
+            if (METRIC != 0) {
+                float fd[16];
+                load_fold(sfold, t0 + u, lane, fd);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[u][r] *= fd[r];
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float v = acc[u][r];
+                sum += v;
+                squares = fmaf(v, v, squares);
+                low = fminf(low, v);
+                high = fmaxf(high, v);
+            }
+        }
+    }
+    sum += __shfl_xor(sum, 32, WAVE);
+    squares += __shfl_xor(squares, 32, WAVE);
+    low = fminf(low, __shfl_xor(low, 32, WAVE));
+    high = fmaxf(high, __shfl_xor(high, 32, WAVE));
+    if (lane < 32) stat[wave][q] = make_float4(sum, squares, low, high);
+    __syncthreads();
+    sum = squares = 0.f;
+    low = INFINITY;
+    high = neg_inf_f();
+#pragma unroll
+    for (int w = 0; w < THR_WAVES; ++w) {
+        const float4 x = stat[w][q];
+        sum += x.x;
+        squares += x.y;
+        low = fminf(low, x.z);
+        high = fmaxf(high, x.w);
+    }
+    const float mean = sum / (float)S;
+    const float sd = sqrtf(fmaxf(squares / (float)S - mean * mean, 0.f));
+    // values as ordered integers: count(lo) >= rank (as far as is known), count(hi) < rank.  No number among a row's
+    // values: an empty interval, and a threshold that leaves the list empty; the row is then flagged.
+    int64_t lo = (int64_t)ord_key(low), hi = (int64_t)ord_key(high) + 1;
+    float guess = mean + z * sd;
+    bool done = hi - lo <= 1;
+    for (int pass = 0; __any(!done); ++pass) {  // the same in every wavefront: all hold the same rows' state
+        int64_t at = (int64_t)ord_key(guess);
+        if (pass >= 4 || !(at > lo && at < hi)) at = lo + ((hi - lo) >> 1);
+        const float t = ord_inv((uint32_t)at);
+        int c = 16 * mine;
+#pragma unroll
+        for (int u = 0; u < TPW; ++u)
+            if (u < mine) {
+                uint32_t below = 0;
+                if (plain) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) below = shift_in_below(below, acc[u][r], t);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) below = shift_in_unless(below, acc[u][r], t);
+                }
+                c -= __popc(below);
+            }
+        c += __shfl_xor(c, 32, WAVE);
+        if (lane < 32) found[pass & 1][wave][q] = c;
+        __syncthreads();                        // one barrier a pass: the buffers alternate
+        c = 0;
+#pragma unroll
+        for (int w = 0; w < THR_WAVES; ++w) c += found[pass & 1][w][q];
+        if (!done) {
+            if (c >= rank) {
+                lo = at;
+                done = c <= rank + slack;
+            } else {
+                hi = at;
+            }
+            done |= hi - lo <= 1;
+            guess = t + ((float)(c - rank) - 0.5f * (float)slack) * per_count * sd;
+        }
+    }
+    const int row = blockIdx.x * 32 + q;
+    if (wave == 0 && lane < 32 && row < rows) {
+        least[row] = ord_inv((uint32_t)lo);
         counts[row] = 0;
     }
 }
 
 // ---- stage 2: select, re-rank exactly, emit ----
 constexpr int CROWDED = 64;   // candidates in one bucket above which a row takes the sorting network
+constexpr int NARROW_THREADS = 128;   // threads per row where at most 256 candidates are wanted of a list
 constexpr int SEL_MAXW = 8;   // wavefronts of the largest selection workgroup (512 threads)
 template <int CAP, int TNT>
 struct SelectShared {
@@ -878,6 +1207,91 @@ __device__ __forceinline__ int bucket_add(uint32_t* h, int b) {   // what the co
     return (int)((atomicAdd(&h[b >> 1], 1u << (16 * (b & 1))) >> (16 * (b & 1))) & 0xFFFFu);
 }
 
+// The candidates of the buckets, ranked: `count` of them in sh.key, sh.idx, those of a bucket next to each other.  A
+// candidate's rank is its bucket's start plus the smaller ones in the bucket.  The first `need` are written.
+template <int BUCKETS, int TNT, int CAP, typename SH, typename F>
+__device__ __forceinline__ void rank_in_buckets(SH& sh, int count, int need, int tid, F bucket_of, int32_t* orow) {
+    constexpr int PT = CAP > TNT ? CAP / TNT : 1;
+    double key[PT];
+    int from[PT], to[PT];
+#pragma unroll
+    for (int e = 0; e < PT; ++e) key[e] = sh.key[min(e * TNT + tid, count - 1)];   // in flight together
+#pragma unroll
+    for (int e = 0; e < PT; ++e) {
+        const int b = bucket_of(key[e]);
+        from[e] = bucket_start(sh.hist, b);
+        to[e] = min(b + 1 < BUCKETS ? bucket_start(sh.hist, b + 1) : count, count);
+    }
+#pragma unroll
+    for (int e = 0; e < PT; ++e) {
+        const int p = e * TNT + tid;
+        if (p < count) {
+            const int tok = sh.idx[p];
+            int rank = from[e], equal = 0;
+            for (int q = from[e]; q < to[e]; ++q) {
+                const double kq = sh.key[q];
+                rank += kq < key[e] ? 1 : 0;
+                equal += kq == key[e] ? 1 : 0;
+            }
+            if (equal > 1)   // in the order of their tokens
+                for (int q = from[e]; q < to[e]; ++q) rank += (int)((sh.key[q] == key[e]) & (sh.idx[q] < tok));
+            // a row that fails the proof is written again by the all-pairs pass
+            if (rank < need) orow[1 + rank] = tok;
+            if (rank == need - 1) sh.last = key[e];
+        }
+    }
+}
+// The candidates in sh.key, sh.idx (in any order) sorted by (key, token); the first `need` are written.
+template <int TNT, typename SH>
+__device__ __forceinline__ void sort_candidates(SH& sh, int count, int need, int tid, int32_t* orow) {
+    int P = 4;   // the sort takes four elements per thread
+    while (P < count) P <<= 1;
+    for (int c = count + tid; c < P; c += TNT) {
+        sh.key[c] = INFINITY;
+        sh.idx[c] = INT_MAX;
+    }
+    // the slots' first contents may be in any order
+    struct Cand {
+        double key;
+        int idx;
+    };
+    bitonic_sort_lds<TNT, Cand>(
+        P, tid, [&](int p) { return Cand{sh.key[p], sh.idx[p]}; },
+        [&](int p, const Cand& c) { sh.key[p] = c.key; sh.idx[p] = c.idx; },
+        [](const Cand& a, const Cand& b) { return (a.key > b.key) | ((a.key == b.key) & (a.idx > b.idx)); },
+        [](bool sw, const Cand& a, const Cand& b) { return Cand{sw ? b.key : a.key, sw ? b.idx : a.idx}; });
+    for (int s = tid; s < need; s += TNT) orow[1 + s] = sh.idx[lds_slot(s)];
+    if (tid == 0) sh.last = sh.key[lds_slot(need - 1)];
+}
+
+// Whether no discarded token can belong to the row: each has an approximate key of at least thr, hence an exact key
+// of at least thr less the approximation's error; the last token taken (exact key `last`) must lie at or below that.
+__device__ __forceinline__ bool proven(double last, float thr, int d, int metric, float err_rel, float err_abs, float err_norm,
+                                       float norm, float nmax, bool by_norms) {
+    bool ok = true;
+    // products and sums below the normal floats may lose up to the smallest of those each
+    double eabs = (double)err_abs + (metric == 0 ? (d + 8) * 0x1p-124 : 0.0);
+    if (by_norms) {
+        // Squared l2: the error of a key grows with the norms of its two codes, and the bound needs the
+        // largest norm a discarded token can have.  A token with norm n_j > 4 (n_i + last) is further
+        // away than the last one taken whatever its approximate key says, since |c_i - c_j|^2 >=
+        // (sqrt n_j - sqrt n_i)^2 > (2 sqrt(n_i + last) - sqrt n_i)^2 >= last; so only norms up to that
+        // (taken a thousandth larger, for the rounding of the fp32 norms) have to be covered.  A few
+        // codes of very large norm then no longer send every row to the all-pairs pass.
+        const double ni = (double)norm;
+        const double far = 4.004 * (ni + last);
+        const double nbound = far < (double)nmax ? far : (double)nmax;   // far may be inf or NaN: then the maximum
+        eabs += (double)err_norm * (ni + nbound);
+        if (!(ni < 0x1p120)) ok = false;
+    }
+    const double num = (double)thr - eabs;
+    const double floor_discarded = num - 1.01 * (double)err_rel * fabs(num);
+    // Squared l2 beyond the floats: a discarded token may have an approximate key that is infinite or no number.
+    // Its code or the difference then has a square of about 2^127 or more, or a coordinate that is no
+    // finite number, and with the row's own norm below 2^120 its exact key lies above 2^126.
+    return ok && last <= floor_discarded && (metric != 0 || thr < 0x1p124f);
+}
+
 // Error model of the approximate keys:
 //   |approximate - exact| <= err_rel * |exact| + err_abs + err_norm * (norm_i + max norm)
 // (the last term applies when norms is not null: keys formed as n_i + n_j - 2 G_ij).
@@ -905,14 +1319,15 @@ __device__ __forceinline__ void for_keys(int npt, F body) {
 // list that was cut at its capacity, is longer than the registers hold (the proof takes every listed
 // token for seen), or is shorter than the selection wants, flags the row.
 template <typename CT, int NK, int CAP, int TNT, bool LIST>
-__global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(const CT* cb, int V, int d, int k, int metric, int r0,
+__global__ __launch_bounds__(TNT, NK >= 64 ? 4 : !LIST ? 8 : NK == 32 ? 5 : (CAP > 256 || NK == 24) ? 6 : 8) void knn_select(const CT* cb, int V, int d, int k, int metric, int r0,
                                                  const float* dist, FilterOut list, float err_rel, float err_abs,
                                                  float err_norm, const float* norms, const float* nmax,
-                                                 const int* doubt, int32_t* out, int* flags) {
+                                                 const int* doubt, int32_t* out, int* flags, int vecs) {
     static_assert(!LIST || NK > 0, "a candidate list is held in registers");
     constexpr int TNW = TNT / WAVE;
     using Shared = SelectShared<CAP, TNT>;
     __shared__ Shared sh;
+    extern __shared__ __align__(16) double own[];   // vecs > 0: the row's own code
     const int row = blockIdx.x;
     const int i = r0 + row;
     const int tid = threadIdx.x;
@@ -961,7 +1376,7 @@ __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(con
         return (j < V && j != i) ? min(ord_key(drow[j]), 0xFFFFFFFEu) : 0xFFFFFFFFu;
     };
     if (LIST) {
-        const uint2* lrow = list.cand + (int64_t)row * list.cap;
+        const uint2* lrow = static_cast<const uint2*>(list.cand) + (int64_t)row * list.cap;
 #pragma unroll
         for (int e = 0; e < NKR; ++e) {
             const int slot = e * TNT + tid;
@@ -1002,6 +1417,7 @@ __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(con
         }
     }
 
+    if (CAP <= 1024 && vecs) own_code<CT>(cb + (int64_t)i * d, d, own, tid, TNT);
     // range of the keys
     for (int w = tid; w < Shared::BUCKETS / 2; w += TNT) sh.hist[w] = 0u;
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
@@ -1116,12 +1532,15 @@ __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(con
         double ck[CPT];
         int ct[CPT], at[CPT];
         float fmin_ = INFINITY, fmax_ = neg_inf_f();
+        const double norm2 = vecs && metric != 0 ? own_norm2(own, d) : 0.0;
 #pragma unroll
         for (int e = 0; e < CPT; ++e) {
             const int c = e * TNT + tid;
             if (c < count) {
                 ct[e] = sh.idx[c];
-                ck[e] = exact_key<CT>(cb, d, i, ct[e], metric, vec4);
+                ck[e] = vecs == 0 ? exact_key<CT>(cb, d, i, ct[e], metric, vec4)
+                        : metric == 0 ? exact_key_vec<CT, 0, 4>(cb, vecs, own, ct[e], 0.0)
+                                      : exact_key_vec<CT, 1, 4>(cb, vecs, own, ct[e], norm2);
                 fmin_ = fminf(fmin_, (float)ck[e]);
                 fmax_ = fmaxf(fmax_, (float)ck[e]);
             }
@@ -1160,80 +1579,219 @@ __global__ __launch_bounds__(TNT, (LIST || NK < 64) ? 8 : 4) void knn_select(con
         __syncthreads();
         if (!sh.cut[2]) {
             emitted = true;
-#pragma unroll
-            for (int e = 0; e < CPT; ++e) {
-                const int p = e * TNT + tid;
-                if (p >= count) continue;
-                const double key = sh.key[p];
-                const int tok = sh.idx[p];
-                const int b = bucket_of(key);
-                const int from = bucket_start(sh.hist, b);
-                const int to = b + 1 < Shared::BUCKETS ? bucket_start(sh.hist, b + 1) : count;
-                int rank = from;
-                for (int q = from; q < to; ++q) {
-                    const double kq = sh.key[q];
-                    rank += (int)((kq < key) | ((kq == key) & (sh.idx[q] < tok)));
-                }
-                // a row that fails the proof below is written again by the all-pairs pass
-                if (rank < need) orow[1 + rank] = tok;
-                if (rank == need - 1) sh.last = key;
-            }
+            rank_in_buckets<Shared::BUCKETS, TNT, CAP>(sh, count, need, tid, bucket_of, orow);
         }
     }
     if (!emitted) {   // uniform
-        int P = 4;   // the sort takes four elements per thread
-        while (P < count) P <<= 1;
-        for (int c = tid; c < P; c += TNT) {
-            if (c >= count) {
-                sh.key[c] = INFINITY;
-                sh.idx[c] = INT_MAX;
-            } else if (CAP > 1024) {
-                sh.key[c] = exact_key<CT>(cb, d, i, sh.idx[c], metric, vec4);
-            }
-        }
-        // ascending by (key, idx); the slots' first contents may be in any order
-        struct Cand {
-            double key;
-            int idx;
-        };
-        bitonic_sort_lds<TNT, Cand>(
-            P, tid, [&](int p) { return Cand{sh.key[p], sh.idx[p]}; },
-            [&](int p, const Cand& c) { sh.key[p] = c.key; sh.idx[p] = c.idx; },
-            [](const Cand& a, const Cand& b) { return (a.key > b.key) | ((a.key == b.key) & (a.idx > b.idx)); },
-            [](bool sw, const Cand& a, const Cand& b) { return Cand{sw ? b.key : a.key, sw ? b.idx : a.idx}; });
-        for (int s = tid; s < need; s += TNT) orow[1 + s] = sh.idx[lds_slot(s)];
-        if (tid == 0) sh.last = sh.key[lds_slot(need - 1)];
+        if (CAP > 1024)
+            for (int c = tid; c < count; c += TNT) sh.key[c] = exact_key<CT>(cb, d, i, sh.idx[c], metric, vec4);
+        sort_candidates<TNT>(sh, count, need, tid, orow);
     }
     __syncthreads();
     // proof that no discarded token belongs to the row: every discarded j has an
     // approximate key above thr, hence an exact key above thr - err; the last
     // token taken must lie at or below that.
     bool ok = true;
-    if (LIST || count < V - 1) {
-        const double last = sh.last;
-        // products and sums below the normal floats may lose up to the smallest of those each
-        double eabs = (double)err_abs + (metric == 0 ? (d + 8) * 0x1p-124 : 0.0);
-        if (norms) {
-            // Squared l2: the error of a key grows with the norms of its two codes, and the bound needs the
-            // largest norm a discarded token can have.  A token with norm n_j > 4 (n_i + last) is further
-            // away than the last one taken whatever its approximate key says, since |c_i - c_j|^2 >=
-            // (sqrt n_j - sqrt n_i)^2 > (2 sqrt(n_i + last) - sqrt n_i)^2 >= last; so only norms up to that
-            // (taken a thousandth larger, for the rounding of the fp32 norms) have to be covered.  A few
-            // codes of very large norm then no longer send every row to the all-pairs pass.
-            const double ni = (double)norms[i];
-            const double far = 4.004 * (ni + last);
-            const double nbound = far < (double)*nmax ? far : (double)*nmax;   // far may be inf or NaN: then the maximum
-            eabs += (double)err_norm * (ni + nbound);
-            if (!(ni < 0x1p120)) ok = false;
-        }
-        const double num = (double)thr - eabs;
-        const double floor_discarded = num - 1.01 * (double)err_rel * fabs(num);
-        // Squared l2 beyond the floats: a discarded token may have an approximate key that is infinite or no number.
-        // Its code or the difference then has a square of about 2^127 or more, or a coordinate that is no
-        // finite number, and with the row's own norm below 2^120 its exact key lies above 2^126.
-        ok = ok && count >= need && last <= floor_discarded && (metric != 0 || thr < 0x1p124f);
-    }
+    if (LIST || count < V - 1)
+        ok = count >= need && proven(sh.last, thr, d, metric, err_rel, err_abs, err_norm, norms ? norms[i] : 0.f, *nmax, norms != nullptr);
     if (!ok && tid == 0) flags[row] = 1;
+}
+
+// ---- stage 2 for lists of tokens alone: every listed token's key in fp64, then as above ----
+// Where a code is a few vectors the keys cost less than narrowing the list to the candidates wanted: no approximate
+// keys are kept, and of the phases between which the workgroup waits (range, histogram, starts, boundary, compaction,
+// range, histogram, starts, placing, ranking) four are left out.  One histogram over the list's exact keys finds
+// the bucket in which the count passes `need`; the tokens up to it are placed and ranked as above.  If they are more than
+// the LDS holds (many nearly equal keys), the keys below that bucket are set aside and the bucket itself is divided
+// again, until they fit or its keys are equal; then the places come from a histogram of their own.
+// Every token not on the list has a value below the row's threshold, which is what the proof uses.
+// V = 16384, d = 8, k = 1000 (lists of 1624 tokens, 16384 rows): 175 us, and 182 for the selection from pairs, whose
+// lists take the filtering contraction 80 us longer.
+template <typename CT, int NP, int VECS, int METRIC>
+__global__ __launch_bounds__(LIST_THREADS, 4) void knn_rank_list(const CT* cb, int V, int d, int k, int r0,
+                                                                 FilterOut list, float err_rel, float err_abs,
+                                                                 float err_norm, const float* norms, const float* nmax,
+                                                                 const int* doubt, int32_t* out, int* flags) {
+    constexpr int CAP = 1024, TNT = LIST_THREADS, TNW = TNT / WAVE;
+    using Shared = SelectShared<CAP, TNT>;
+    constexpr int BUCKETS = Shared::BUCKETS;
+    __shared__ Shared sh;
+    __shared__ float ends[2 * TNW];
+    __shared__ double own[VECS * KeySum<CT, METRIC>::EPV];
+    const int row = blockIdx.x;
+    const int i = r0 + row;
+    const int tid = threadIdx.x;
+    const int lane = tid & (WAVE - 1);
+    const int wave = tid >> 6;
+    int32_t* orow = out + (int64_t)i * k;
+    const int need = k - 1;                                 // at least one: the plan wants more than 64
+    const int want = min(V - 1, need + 8 + need / 128);
+    const int listed = list.counts[row];
+    if (tid == 0) {
+        orow[0] = i;
+        flags[row] = 0;
+        sh.cut[2] = 0;
+        sh.last = INFINITY;
+    }
+    if (listed > min(list.cap, NP * TNT) || listed < want || (METRIC != 0 && *doubt)) {
+        if (tid == 0) flags[row] = 1;
+        return;
+    }
+    int tok[NP];
+    double key[NP];
+    {
+        const uint32_t* lrow = static_cast<const uint32_t*>(list.cand) + (int64_t)row * list.cap;
+#pragma unroll
+        for (int e = 0; e < NP; ++e) tok[e] = (int)lrow[min(e * TNT + tid, listed - 1)];   // no branch: all loads in flight together
+    }
+    own_code<CT>(cb + (int64_t)i * d, d, own, tid, TNT);
+    for (int w = tid; w < BUCKETS / 2; w += TNT) sh.hist[w] = 0u;
+    __syncthreads();
+    const double norm2 = METRIC != 0 ? own_norm2(own, d) : 0.0;
+    float low = INFINITY, high = neg_inf_f();
+    constexpr int BATCH = VECS > 1 ? 2 : 4;                 // slots whose codes are on their way together
+#pragma unroll
+    for (int e0 = 0; e0 < NP; e0 += BATCH)
+        if (e0 * TNT < listed) {                            // uniform
+            vec4u v[BATCH][VECS];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u)
+#pragma unroll
+                for (int q = 0; q < VECS; ++q) v[u][q] = reinterpret_cast<const vec4u*>(cb)[(uint32_t)tok[e0 + u] * VECS + q];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                KeySum<CT, METRIC> sum;
+#pragma unroll
+                for (int q = 0; q < VECS; ++q) sum.add(v[u][q], own + q * KeySum<CT, METRIC>::EPV);
+                key[e0 + u] = sum.key(norm2);
+                if ((e0 + u) * TNT + tid < listed) {
+                    low = fminf(low, (float)key[e0 + u]);
+                    high = fmaxf(high, (float)key[e0 + u]);
+                }
+            }
+        }
+    // `in`: keys that certainly belong to the first ones, `open`: those the next histogram is over
+    uint32_t in = 0, open = 0;
+#pragma unroll
+    for (int e = 0; e < NP; ++e) open |= e * TNT + tid < listed ? 1u << e : 0u;
+    int at[NP];                           // bucket * 65536 + place in it
+    float scale = 0.f;
+    auto bucket_of = [&](double x) -> int {   // keys a rounding outside the range belong to its ends
+        return scale > 0.f ? min(max((int)(((float)x - low) * scale), 0), BUCKETS - 1) : 0;
+    };
+    // range of the keys of `mask` (low, high as this thread has them), their histogram, its starts
+    auto histogram = [&](uint32_t mask, auto each) {
+        low = -wave_max(-low);
+        high = wave_max(high);
+        if (lane == 0) {
+            ends[wave] = low;
+            ends[TNW + wave] = high;
+        }
+        __syncthreads();
+        low = ends[0];
+        high = ends[TNW];
+#pragma unroll
+        for (int w = 1; w < TNW; ++w) {
+            low = fminf(low, ends[w]);
+            high = fmaxf(high, ends[TNW + w]);
+        }
+        const float range = high - low;   // no range (or none that floats can divide): one bucket
+        scale = (range > 1e-30f && range < INFINITY) ? (float)(BUCKETS - 1) / range : 0.f;
+#pragma unroll
+        for (int e = 0; e < NP; ++e)
+            if ((mask >> e) & 1u) {
+                const int b = bucket_of(key[e]);
+                at[e] = (b << 16) + bucket_add(sh.hist, b);
+            }
+        __syncthreads();
+        bucket_starts<BUCKETS, TNT>(sh.hist, sh.red_c[0], tid, each);
+        __syncthreads();
+    };
+    auto clear = [&] {
+        __syncthreads();
+        for (int w = tid; w < BUCKETS / 2; w += TNT) sh.hist[w] = 0u;
+        __syncthreads();
+    };
+    int base = 0;                         // keys set aside so far
+    auto find_cut = [&](int bucket, int start, int n) {
+        if (base + start < need && base + start + n >= need) {
+            sh.cut[0] = bucket;
+            sh.cut[1] = start + n;
+            sh.red_u[0] = (unsigned)start;
+        }
+        if (n > CROWDED && base + start < need) sh.cut[2] = 1;
+    };
+    histogram(open, find_cut);
+    int count = sh.cut[1];
+    if (count > CAP) {                    // uniform
+        for (int round = 0; round < 16 && base + count > CAP; ++round) {
+            const int cut = sh.cut[0], below = (int)sh.red_u[0];
+            if (scale == 0.f) break;      // as many equal keys as that
+            const uint32_t was = open;
+            open = 0;
+            float l = INFINITY, h = neg_inf_f();
+#pragma unroll
+            for (int e = 0; e < NP; ++e)
+                if ((was >> e) & 1u) {
+                    const int b = at[e] >> 16;
+                    if (b < cut) in |= 1u << e;
+                    else if (b == cut) {
+                        open |= 1u << e;
+                        l = fminf(l, (float)key[e]);
+                        h = fmaxf(h, (float)key[e]);
+                    }
+                }
+            base += below;
+            low = l;
+            high = h;
+            clear();
+            histogram(open, find_cut);
+            count = sh.cut[1];
+        }
+        if (base + count > CAP) {         // uniform: the all-pairs pass
+            if (tid == 0) flags[row] = 1;
+            return;
+        }
+        const int cut = sh.cut[0];
+        float l = INFINITY, h = neg_inf_f();
+#pragma unroll
+        for (int e = 0; e < NP; ++e) {
+            if (((open >> e) & 1u) && (at[e] >> 16) <= cut) in |= 1u << e;
+            if ((in >> e) & 1u) {
+                l = fminf(l, (float)key[e]);
+                h = fmaxf(h, (float)key[e]);
+            }
+        }
+        count += base;
+        low = l;
+        high = h;
+        clear();
+        if (tid == 0) sh.cut[2] = 0;
+        histogram(in, [&](int, int, int n) {
+            if (n > CROWDED) sh.cut[2] = 1;
+        });
+    } else {
+        const int limit = (sh.cut[0] + 1) << 16;
+#pragma unroll
+        for (int e = 0; e < NP; ++e)
+            if (((open >> e) & 1u) && at[e] < limit) in |= 1u << e;
+    }
+    // `count` keys, in their buckets
+#pragma unroll
+    for (int e = 0; e < NP; ++e)
+        if ((in >> e) & 1u) {
+            const int p = bucket_start(sh.hist, at[e] >> 16) + (at[e] & 0xFFFF);
+            sh.key[p] = key[e];
+            sh.idx[p] = tok[e];
+        }
+    __syncthreads();
+    if (!sh.cut[2]) rank_in_buckets<BUCKETS, TNT, CAP>(sh, count, need, tid, bucket_of, orow);
+    else sort_candidates<TNT>(sh, count, need, tid, orow);
+    __syncthreads();
+    // proof that no token left out belongs to the row: its value is below the threshold
+    const float thr = key_of_value<METRIC>(list.thr[row], norms[i]);
+    const bool ok = proven(sh.last, thr, d, METRIC, err_rel, err_abs, err_norm, METRIC == 0 ? norms[i] : 0.f, *nmax, METRIC == 0);
+    if (tid == 0 && !ok) flags[row] = 1;
 }
 
 // ---- stage 3: flagged rows, all V keys in fp64, rank by counting ----
@@ -1274,17 +1832,10 @@ __global__ void knn_clear_stats(int* stats, float* nmax, int* doubt) {
     stats[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
         *nmax = 0.f;
-        *doubt = 0;
+        doubt[0] = doubt[1] = 0;
     }
 }
 __global__ void knn_copy_stats(const int* stats, int32_t* out) { *out = stats[0]; }
-
-template <int NS>
-static void launch_sample_rank(const float* skeys, const FilterPlan& plan, int rows, float* thr, int* counts,
-                               hipStream_t stream) {
-    hipLaunchKernelGGL((knn_sample_rank<NS>), dim3((rows + NW - 1) / NW), dim3(NT), 0, stream, skeys, plan.S, rows,
-                       plan.rank, plan.slack, thr, counts);
-}
 
 template <typename CT>
 static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t stream) {
@@ -1296,7 +1847,7 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
     int* stats = reinterpret_cast<int*>(ws + L.stats);
     float* norms = reinterpret_cast<float*>(ws + L.norms);
     float* nmax = reinterpret_cast<float*>(ws + L.nmax);
-    int* doubt = reinterpret_cast<int*>(nmax) + 1;   // a code whose cosine keys the error bound does not cover
+    int* doubt = reinterpret_cast<int*>(nmax) + 1;   // a code whose cosine keys the error bound does not cover; one not plain
     hipLaunchKernelGGL(knn_clear_stats, dim3(1), dim3(64), 0, stream, stats, nmax, doubt);
     // matrix-core path: rows 16-byte aligned and coordinates in whole vectors
     const bool aligned = (reinterpret_cast<uintptr_t>(a.codebook) & 15) == 0;
@@ -1325,12 +1876,13 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
     uint4* spacked = reinterpret_cast<uint4*>(ws + L.spacked);
     float* fold = reinterpret_cast<float*>(ws + L.fold);
     const int steps = (int)packed_steps(a.d, sizeof(CT) == 2 ? 1 : 0);
+    float* sfold = reinterpret_cast<float*>(ws + L.sfold);
     float* snorms = reinterpret_cast<float*>(ws + L.snorms);
     float* skeys = reinterpret_cast<float*>(ws + L.skeys);
     FilterOut fo;
     fo.thr = reinterpret_cast<float*>(ws + L.thr);
     fo.counts = reinterpret_cast<int*>(ws + L.counts);
-    fo.cand = reinterpret_cast<uint2*>(ws + L.cand);
+    fo.cand = ws + L.cand;
     fo.cap = plan.cap;
     const FilterOut no_list = {nullptr, nullptr, nullptr, 0};
     if (plan.use) {
@@ -1342,20 +1894,56 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
         const dim3 grid((unsigned)((threads + NT - 1) / NT));
         if (a.metric == 0)
             hipLaunchKernelGGL((knn_pack<CT, 0>), grid, dim3(NT), 0, stream, cb, norms, a.V, a.d, plan.S, steps, packed,
-                               spacked, fold, snorms);
+                               spacked, fold, sfold, snorms);
         else
             hipLaunchKernelGGL((knn_pack<CT, 1>), grid, dim3(NT), 0, stream, cb, norms, a.V, a.d, plan.S, steps, packed,
-                               spacked, fold, snorms);
+                               spacked, fold, sfold, snorms);
     }
+    const int vecs = mfma ? a.d * (int)sizeof(CT) / 16 : 0;   // rows of whole vectors at aligned addresses
+    const int key_vecs = a.d <= VEC_MAX_D ? vecs : 0;
     auto filter = [&](int r0, int rows) {
-        const int nct = (a.V + 127) / 128, nrt = (rows + 127) / 128;
-        const dim3 grid((unsigned)((nrt + 7) / 8 * 8 * nct));
-        if (a.metric == 0)
-            hipLaunchKernelGGL((knn_filter_list<CT, 0>), grid, dim3(NT), 0, stream, packed, fold, norms, a.V, steps, r0,
-                               rows, fo);
-        else
-            hipLaunchKernelGGL((knn_filter_list<CT, 1>), grid, dim3(NT), 0, stream, packed, fold, norms, a.V, steps, r0,
-                               rows, fo);
+        const int nrt = (rows + 127) / 128;
+#define LANTERN_LAUNCH_FILTER(METRICV, FORMV, TTV)                                                                       \
+        hipLaunchKernelGGL((knn_filter_list<CT, METRICV, FORMV, TTV>),                                                   \
+                           dim3((unsigned)((nrt + 7) / 8 * 8 * ((a.V + 128 * TTV - 1) / (128 * TTV)))), dim3(NT), 0, stream, \
+                           packed, fold, norms, a.V, steps, r0, rows, doubt, fo)
+        if (plan.tokens && plan.wide_tiles) {
+            if (a.metric == 0) LANTERN_LAUNCH_FILTER(0, LIST_TOKENS, 4);
+            else LANTERN_LAUNCH_FILTER(1, LIST_TOKENS, 4);
+        } else if (plan.tokens) {
+            if (a.metric == 0) LANTERN_LAUNCH_FILTER(0, LIST_TOKENS, 1);
+            else LANTERN_LAUNCH_FILTER(1, LIST_TOKENS, 1);
+        } else if (a.metric == 0) LANTERN_LAUNCH_FILTER(0, LIST_PAIRS, 1);
+        else LANTERN_LAUNCH_FILTER(1, LIST_PAIRS, 1);
+#undef LANTERN_LAUNCH_FILTER
+    };
+    // thresholds of a block of rows from the sample
+    auto thresholds = [&](int r0, int rows) {
+        float* least = const_cast<float*>(fo.thr);
+        if (plan.S > THRESHOLDS_MAX_S) {
+            hipLaunchKernelGGL((knn_sample_keys<CT>), dim3((plan.S + 127) / 128, (rows + 127) / 128), dim3(NT), 0, stream,
+                               packed, spacked, norms, snorms, a.V, plan.S, steps, r0, rows, a.metric, skeys);
+            hipLaunchKernelGGL((knn_sample_rank<64>), dim3((rows + NW - 1) / NW), dim3(NT), 0, stream, skeys, plan.S, rows,
+                               plan.rank, plan.slack, norms, r0, a.metric, least, fo.counts);
+            return;
+        }
+        const double share = (plan.rank + 0.5 * plan.slack) / plan.S;
+        const double z = normal_upper_quantile(share);
+        const float per_count = (float)(1.0 / (plan.S * normal_density(z)));
+#define LANTERN_LAUNCH_THRESHOLDS(METRICV, TPWV)                                                                         \
+        hipLaunchKernelGGL((knn_thresholds<CT, METRICV, TPWV>), dim3((rows + 31) / 32), dim3(THR_THREADS), 0, stream, packed, \
+                           spacked, sfold, a.V, plan.S, steps, r0, rows, plan.rank, plan.slack, (float)z, per_count, doubt, least, \
+                           fo.counts)
+#define LANTERN_LAUNCH_THRESHOLDS_TPW(METRICV)                                                                           \
+        do {                                                                                                             \
+            if (plan.S <= 512) LANTERN_LAUNCH_THRESHOLDS(METRICV, 1);                                                    \
+            else if (plan.S <= 1024) LANTERN_LAUNCH_THRESHOLDS(METRICV, 2);                                              \
+            else LANTERN_LAUNCH_THRESHOLDS(METRICV, 4);                                                                  \
+        } while (0)
+        if (a.metric == 0) LANTERN_LAUNCH_THRESHOLDS_TPW(0);
+        else LANTERN_LAUNCH_THRESHOLDS_TPW(1);
+#undef LANTERN_LAUNCH_THRESHOLDS_TPW
+#undef LANTERN_LAUNCH_THRESHOLDS
     };
     for (int r0 = 0; r0 < a.V; r0 += L.row_block) {
         const int rows = (a.V - r0) < L.row_block ? (a.V - r0) : L.row_block;
@@ -1366,25 +1954,39 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
         // (12 bytes a slot).
         const int want_slots = (a.k - 1) + 8 + (a.k - 1) / 128;
 #define LANTERN_LAUNCH_SELECT(NKV, CAPV, TNTV, LISTV)                                                       \
-        hipLaunchKernelGGL((knn_select<CT, NKV, CAPV, TNTV, LISTV>), dim3(rows), dim3(TNTV), 0, stream, cb, \
+        hipLaunchKernelGGL((knn_select<CT, NKV, CAPV, TNTV, LISTV>), dim3(rows), dim3(TNTV),                \
+                           (CAPV) <= 1024 ? own_code_bytes(a.d, key_vecs) : 0, stream, cb,          \
                            a.V, a.d, a.k, a.metric, r0, dist, LISTV ? fo : no_list, err_rel, err_abs,       \
-                           err_norm, nsel, nmax, doubt, a.out, flags + r0)
+                           err_norm, nsel, nmax, doubt, a.out, flags + r0, (CAPV) <= 1024 ? key_vecs : 0)
         if (plan.use) {
             // thresholds from the sample, then the contraction that keeps what lies below them
-            hipLaunchKernelGGL((knn_sample_keys<CT>), dim3((plan.S + 127) / 128, (rows + 127) / 128), dim3(NT), 0, stream,
-                               packed, spacked, norms, snorms, a.V, plan.S, steps, r0, rows, a.metric, skeys);
-            if (plan.S <= 8 * WAVE) launch_sample_rank<8>(skeys, plan, rows, const_cast<float*>(fo.thr), fo.counts, stream);
-            else if (plan.S <= 16 * WAVE) launch_sample_rank<16>(skeys, plan, rows, const_cast<float*>(fo.thr), fo.counts, stream);
-            else if (plan.S <= 32 * WAVE) launch_sample_rank<32>(skeys, plan, rows, const_cast<float*>(fo.thr), fo.counts, stream);
-            else launch_sample_rank<64>(skeys, plan, rows, const_cast<float*>(fo.thr), fo.counts, stream);
+            thresholds(r0, rows);
             filter(r0, rows);
             static_assert(LIST_THREADS == NT, "threads per row of the selection from lists");
-            const int pairs = list_pairs(want_slots, plan.cap);   // 64 < want_slots <= 1024
-            if (want_slots <= 256) {
-                if (pairs == 4) LANTERN_LAUNCH_SELECT(4, 256, NT, true);
-                else if (pairs == 8) LANTERN_LAUNCH_SELECT(8, 256, NT, true);
-                else if (pairs == 12) LANTERN_LAUNCH_SELECT(12, 256, NT, true);
-                else LANTERN_LAUNCH_SELECT(16, 256, NT, true);
+            const int pairs = list_pairs(plan.tokens ? 1024 : want_slots, plan.cap);   // 64 < want_slots <= 1024
+#define LANTERN_LAUNCH_RANK(NPV)                                                                                         \
+            do {                                                                                                         \
+                auto* kernel = a.metric == 0 ? (vecs == 1   ? &knn_rank_list<CT, NPV, 1, 0>                              \
+                                                : vecs == 2 ? &knn_rank_list<CT, NPV, 2, 0>                              \
+                                                            : &knn_rank_list<CT, NPV, 4, 0>)                             \
+                                             : (vecs == 1   ? &knn_rank_list<CT, NPV, 1, 1>                              \
+                                                : vecs == 2 ? &knn_rank_list<CT, NPV, 2, 1>                              \
+                                                            : &knn_rank_list<CT, NPV, 4, 1>);                            \
+                hipLaunchKernelGGL(kernel, dim3(rows), dim3(LIST_THREADS), 0, stream, cb, a.V, a.d, a.k, r0, fo, err_rel, \
+                                   err_abs, err_norm, norms, nmax, doubt, a.out, flags + r0);                            \
+            } while (0)
+            if (plan.tokens) {
+                if (pairs == 8) LANTERN_LAUNCH_RANK(8);
+                else if (pairs == 12) LANTERN_LAUNCH_RANK(12);
+                else LANTERN_LAUNCH_RANK(16);
+#undef LANTERN_LAUNCH_RANK
+            } else if (want_slots <= 256) {
+                // two wavefronts a row: its candidates would leave some of four without any
+                static_assert(LIST_THREADS == 2 * NARROW_THREADS, "twice the pairs per thread");
+                if (pairs == 4) LANTERN_LAUNCH_SELECT(8, 256, NARROW_THREADS, true);
+                else if (pairs == 8) LANTERN_LAUNCH_SELECT(16, 256, NARROW_THREADS, true);
+                else if (pairs == 12) LANTERN_LAUNCH_SELECT(24, 256, NARROW_THREADS, true);
+                else LANTERN_LAUNCH_SELECT(32, 256, NARROW_THREADS, true);
             } else if (pairs == 8) LANTERN_LAUNCH_SELECT(8, 1024, NT, true);
             else if (pairs == 12) LANTERN_LAUNCH_SELECT(12, 1024, NT, true);
             else LANTERN_LAUNCH_SELECT(16, 1024, NT, true);

@@ -49,14 +49,29 @@ inline double binomial_lower_tail(int n, double p, int r) {
 // use == false: the shape takes the whole-key-block path.
 struct FilterPlan {
     bool use;
+    bool tokens;   // the lists hold tokens alone and every listed one's key is evaluated in fp64
+    bool wide_tiles;   // (tokens) 512 tokens to a tile of the filtering contraction instead of 128
     int S;      // sampled tokens, a multiple of 64, at most 4096
     int rank;   // the threshold has between rank and rank + slack of a row's S sample keys at or below it
     int slack;
     int cap;    // slots of a row's candidate list: 1024, 2048, 3072 or 4096
 };
 
+constexpr int FILTER_STAGE = 8192;   // hits of a tile that are staged at once
+
+inline double normal_density(double z) { return exp(-0.5 * z * z) * 0.39894228040143267794; }
+// z with P(X > z) = share of a standard normal, by halving (0 < share < 1; to 1e-6, a first guess is made of it).
+inline double normal_upper_quantile(double share) {
+    double lo = -8.0, hi = 8.0;
+    for (int i = 0; i < 24; ++i) {
+        const double mid = 0.5 * (lo + hi);
+        (0.5 * erfc(mid * 0.70710678118654752440) > share ? lo : hi) = mid;
+    }
+    return 0.5 * (lo + hi);
+}
+
 inline FilterPlan filter_plan(int V, int d, int k, int cb_dtype) {
-    FilterPlan P = {false, 0, 0, 0, 0};
+    FilterPlan P = {false, false, false, 0, 0, 0, 0};
     const bool vec = cb_dtype == 1 ? (d % 8) == 0 : (d % 4) == 0;   // what the matrix-core kernels need
     const int need = k - 1;
     const int want = need + 8 + need / 128;
@@ -82,6 +97,20 @@ inline FilterPlan filter_plan(int V, int d, int k, int cb_dtype) {
     }
     if (cap == 0) return P;
     P.use = true;
+    // A list without keys costs the selection the exact keys of all it holds instead of `want` of them, and saves the
+    // keys' way through memory and the phases that narrow the list.  It pays where codes are short, and the
+    // lists are not much longer than what is wanted of them or the contraction over a large vocabulary outweighs the
+    // selection.  Whole builds, pairs / tokens: codes of 32 bytes, V = 4096, k = 64 (surplus 3.2) 50 / 55 us, k = 1000
+    // 104 / 91; V = 6500, k = 100 75 / 79, k = 500 107 / 96; V = 8192, k = 200 105 / 98; V = 16384, k = 1000 355 / 292;
+    // V = 60000, k = 230 2772 / 1809.  Codes of 64 bytes: V = 8192, k = 100 104 / 113, k = 1000 167 / 172; V = 12288,
+    // k = 300 199 / 191, k = 1000 (cosine) 296 / 377; V = 16384, k = 300 (cosine) 328 / 298; V = 33000, k = 100 994 / 807.
+    const double listed = (rank + 0.5 * slack) / S * V;
+    const int row_bytes = d * (cb_dtype == 1 ? 2 : 4);
+    if (row_bytes == 16 || row_bytes == 32) P.tokens = V >= 8192 || listed <= 2.0 * want;
+    else if (row_bytes == 64) P.tokens = V >= 12288 && listed <= 1024;
+    // Four times the tokens to a reservation of list slots, as long as their hits are staged at once and there are
+    // tiles for every compute unit several times over.
+    P.wide_tiles = listed / V * (128.0 * 512.0) <= 0.85 * FILTER_STAGE && V >= 8192;
     P.S = S;
     P.rank = rank;
     P.slack = slack;

@@ -1,0 +1,76 @@
+"""Neighbour tables through candidate lists (Section 4.2; Algorithm 2, precompute part) where the lists are awkward: more
+nearly equal keys than the selection holds at once, more hits in a tile than are staged at once, equal codes, codes
+that are no numbers; and every form that the selection's exact keys take.  Whole tables, or a stretch of rows of the
+larger ones, against the oracle's ranking."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _table(lantern, cb, k, metric, max_exact_rows):
+    got, exact = lantern.build_knn(cb.cuda(), k, metric=metric, return_stats=True)
+    torch.cuda.synchronize()
+    assert int(exact.item()) <= max_exact_rows
+    return got.cpu().numpy()
+
+
+def _clusters(V, d, size, spread, seed):
+    """Clusters of `size` codes next to each other in the codebook."""
+    rng = np.random.default_rng(seed)
+    centre = rng.standard_normal((-(-V // size), d))
+    return (np.repeat(centre, size, axis=0)[:V] + spread * rng.standard_normal((V, d))).astype(np.float32)
+
+
+@pytest.mark.parametrize("V,d,k,size,spread,dtype,metric", [
+    (8192, 8, 1000, 1400, 1e-3, torch.float32, "l2"),        # a cluster is one bucket of the list's range
+    (8192, 8, 1000, 1400, 1e-3, torch.float32, "cosine"),
+    (9000, 16, 900, 1100, 0.02, torch.bfloat16, "l2"),
+    (8192, 8, 100, 700, 1e-3, torch.float32, "l2"),
+    (12288, 16, 100, 300, 0.01, torch.float32, "l2"),        # codes of four vectors
+    (6000, 24, 500, 800, 1e-3, torch.float32, "l2"),         # lists with keys
+])
+def test_clustered_codes(oracle_mod, lantern_gpu, V, d, k, size, spread, dtype, metric):
+    cb = torch.from_numpy(_clusters(V, d, size, spread, V + d + k)).to(dtype)
+    got = _table(lantern_gpu, cb, k, metric, V)
+    want = oracle_mod.build_knn(cb.float().numpy(), k, metric=metric, threads=16)
+    np.testing.assert_array_equal(got, want)
+
+
+@pytest.mark.parametrize("k", [70, 1000])
+def test_more_equal_codes_than_the_selection_holds(oracle_mod, lantern_gpu, k):
+    rng = np.random.default_rng(k)
+    cb = rng.standard_normal((8192, 8)).astype(np.float32)
+    cb[rng.permutation(8192)[:1200]] = cb[17]
+    got = _table(lantern_gpu, torch.from_numpy(cb), k, "l2", 8192)
+    np.testing.assert_array_equal(got, oracle_mod.build_knn(cb, k, threads=16))
+
+
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("V,d,k", [(8192, 8, 300), (5000, 40, 120)])
+def test_codes_that_are_no_numbers(oracle_mod, lantern_gpu, V, d, k, metric):
+    rng = np.random.default_rng(V)
+    cb = rng.standard_normal((V, d)).astype(np.float32)
+    cb[5, 3], cb[700, 0], cb[V - 1, d - 1] = np.nan, np.inf, -np.inf
+    cb[900] = 0.0
+    got = _table(lantern_gpu, torch.from_numpy(cb), k, metric, 16)
+    np.testing.assert_array_equal(got, oracle_mod.build_knn(cb, k, metric=metric, threads=16))
+
+
+@pytest.mark.parametrize("metric", ["l2", "cosine"])
+@pytest.mark.parametrize("V,d,k,dtype", [
+    (8192, 4, 90, torch.float32), (8200, 8, 1000, torch.bfloat16), (4097, 8, 1000, torch.float32),   # one and two vectors
+    (12300, 16, 300, torch.float32), (12288, 32, 200, torch.bfloat16),                               # four vectors
+    (6001, 20, 150, torch.float32), (4500, 120, 700, torch.bfloat16), (8192, 16, 1000, torch.float32),   # lists with keys
+    (2000, 12, 60, torch.float32), (1500, 88, 400, torch.bfloat16), (300, 1028, 50, torch.float32),      # whole rows
+    (20000, 8, 100, torch.float32), (33000, 8, 230, torch.bfloat16),                                     # larger samples
+])
+def test_forms_of_the_exact_keys(oracle_mod, lantern_gpu, V, d, k, dtype, metric):
+    g = torch.Generator().manual_seed(V + d)
+    cb = torch.randn(V, d, generator=g)
+    cb = (cb * (0.5 + torch.rand(V, 1, generator=g))).to(dtype)
+    got = _table(lantern_gpu, cb, k, metric, 0)
+    rows = (0, V) if V < 10000 else (V - 2500, V)
+    want = oracle_mod.build_knn(cb.float().numpy(), k, metric=metric, rows=rows, threads=16)
+    np.testing.assert_array_equal(got[rows[0]:rows[1]], want)
