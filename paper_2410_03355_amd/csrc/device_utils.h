@@ -128,6 +128,12 @@ __device__ __forceinline__ double wave_max(double v) {
     return lane63_d(v);
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ float uniform_f(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+__device__ __forceinline__ double uniform_d(double v) {
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)), __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
 // v_exp_f32: 2^x, flushes denormal results to zero, 2^-inf = 0.
 __device__ __forceinline__ float hw_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 

@@ -205,7 +205,13 @@ LANTERN_HD double exp_units(double l, double start, const unsigned char* tab_byt
     const double hi = exp_units_scaled(u.hi, u.mi);
     return __builtin_fma(hi, u.p, hi);
 }
-// The same where the result may leave the normal range (below it: rounded there, in the end zero).
+// With a table whose hi is whole (j 2^44 put back when it is laid out), for results that may lie below the normal range:
+// rounded there, in the end zero.
+LANTERN_HD double exp_units_nonpos(double l, double start, const unsigned char* tab_bytes) {
+    const ExpUnits u = exp_units_parts(l, start, tab_bytes);
+    return ldexp(__builtin_fma(u.hi, u.p, u.hi), (int)u.mi >> 8);
+}
+// The same from the table as it is.
 LANTERN_HD double exp_units_any(double l, double start, const unsigned char* tab_bytes) {
     const ExpUnits u = exp_units_parts(l, start, tab_bytes);
     const double hi = exp_units_scaled(u.hi, u.mi & 255u);

@@ -30,9 +30,12 @@
 // bound's logarithms are a function call, over which few registers live, in kernels of their own.  So the walk under
 // total variation keeps out of scratch memory: setting that up is 1 to 3 us of every walk (64 trees none of which draws,
 // V = 8192 fp32: 43.6 -> 39.7 us the step) and the spilled terms more (V = 16384 fp32, 64 trees: 163 -> 148 us).
+// The exponentials (two rows of them per group, on one compute unit: 6 of a plain draw's 21 us) are those of the one-pass
+// evaluation, 18 instructions each with the subtraction of the maximum, and what is the same in all lanes is kept
+// in scalar registers: V = 16384 bf16, 64 trees, 90 -> 83 us the walk, 26.6 -> 23.9 the plain draw.
 // Second half of the plain step (PLAIN): its first wavefront walks the tree over the decisions as every other walk
 // does (tree_walk.h), then the workgroup evaluates the one candidate whose draw is wanted.  V = 16384 bf16, 1 / 64
-// trees that draw: 24 / 28 us, without a draw 4 us; 27 / 31 and 10 us with the search for children among the passes.
+// trees that draw: 21 / 24 us, without a draw 4 us (24 / 28 with the exponentials before); 27 / 31 and 10 us with the search for children among the passes.
 // Vocabularies that do not fit in LDS keep both vectors in the workspace.
 #include <hip/hip_runtime.h>
 #include <limits.h>
@@ -87,7 +90,7 @@ __device__ __noinline__ bool jsd_fails(double t_tok, double moved, double delta)
 typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
 
 struct SeqShared {
-    double tab[2 * EXP_TABLE_N];
+    uint64_t tab[2 * EXP_FINE_N];    // at the start of the workgroup's LDS: exp_units reads it there
     double sum_a[SNW], sum_b[SNW];   // softmax sums, then the walk's totals and sums before its cut
     double wr[SNW], wt[SNW];         // residual mass and distorted target's mass of every wavefront's part
     float mt[SNW], mg[SNW];
@@ -114,7 +117,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
 
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // its part of the vocabulary in scalar registers
     const int b = blockIdx.x;
     const int V = a.V;
     const int k = a.k;
@@ -144,7 +147,10 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
     double* cur = RES ? seq_cur : cur_mem;
     // the two rows' pairs of every step, then (NP > 0) the drafter's two terms of the step in their room
     u2 tr[U], gr[U];
+    const unsigned char* tab = reinterpret_cast<const unsigned char*>(sh.tab);
     double inv_st = 0.0, inv_sg = 0.0, st = 0.0, mxg = 0.0;
+    float floor_g = 0.f;
+    auto term = [&](float l, float least, double max) { return exp_units_nonpos((double)fmaxf(l, least) - max, EXP_UNITS_START, tab); };
     const double delta = (double)a.delta;
 
     // the part of the vocabulary of this wavefront: [x0, x1), in steps of a pair per lane
@@ -153,7 +159,10 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
     const int x1 = min(V, x0 + per);
 
     const bool staged = !PLAIN && M <= SNODES;
-    for (int j = tid; j < 2 * EXP_TABLE_N; j += SNT) sh.tab[j] = EXP_TABLE_HILO[j];
+    for (int j = tid; j < EXP_FINE_N; j += SNT) {
+        sh.tab[2 * j] = EXP_FINE[2 * j] + ((uint64_t)j << 44);   // whole: exp_units_nonpos adds the exponent alone
+        sh.tab[2 * j + 1] = EXP_FINE[2 * j + 1];
+    }
     int first = -1;                      // PLAIN: the child whose draw is wanted
     if (PLAIN) {
         if (wave == 0) {
@@ -205,7 +214,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
         bool have_rows = false;
         const LT* grow = nullptr;
         double zz = 0.0;             // of the last rejected child: mass of what its draw is taken from,
-        double u_res = 0.0;          //   its draw,
+        float u_res = 0.f;           //   its draw,
         bool zero_resid = false;     //   and whether that is the distorted target itself
         int i = node;
         for (;;) {
@@ -322,46 +331,54 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                     next = -2;
                     break;
                 }
-                const double mxt = (double)mt;
-                mxg = (double)mg;
+                // terms e^(l - max); filtered tokens are evaluated 1100 below the maximum, where a term is zero
+                const double mxt = uniform_d((double)mt);
+                mxg = uniform_d((double)mg);
+                const float floor_t = uniform_f(mt - 1100.f);
+                floor_g = uniform_f(mg - 1100.f);
                 double zt = 0.0, zg = 0.0;
+                // Some steps a turn, the registers moved down behind them and what comes of them put at the
+                // end (NP > 0: after the last turn every step is back in its place): unrolled in full, this is
+                // code that a group runs once, and fetching it costs more than the moves.
+                constexpr int TURN = 2;
                 for (int xb = x0; xb < (RES ? x0 + 1 : x1); xb += U * PAIR_STEP) {
                     if (!RES) load(xb);
-                    // Two steps a turn, the registers moved down behind them and what comes of the two put at the
-                    // end (NP > 0: after the last turn every step is back in its place): unrolled in full, this is
-                    // code that a group runs once, and fetching it costs more than the moves.
 #pragma unroll 1
-                    for (int xc = xb; xc < xb + U * PAIR_STEP; xc += 2 * PAIR_STEP) {
-                        double gn[4] = {0.0, 0.0, 0.0, 0.0};
+                    for (int xc = xb; xc < xb + U * PAIR_STEP; xc += TURN * PAIR_STEP) {
+                        u2 t2[TURN], g2[TURN];
 #pragma unroll
-                        for (int u = 0; u < 2; ++u) {
+                        for (int u = 0; u < TURN; ++u) {
+                            t2[u] = g2[u] = u2{0u, 0u};
                             if (xc + u * PAIR_STEP < x1) {   // uniform over the wavefront
                                 const int x = xc + u * PAIR_STEP + l2;
-                                float l0, l1, h0, h1;
-                                logits(tr[u], x, &l0, &l1);
-                                logits(gr[u], x, &h0, &h1);
-                                const double t0 = exp_tab_nonpos((double)l0 - mxt, sh.tab);
-                                const double t1 = exp_tab_nonpos((double)l1 - mxt, sh.tab);
-                                const double g0 = exp_tab_nonpos((double)h0 - mxg, sh.tab);
-                                const double g1 = exp_tab_nonpos((double)h1 - mxg, sh.tab);
+                                float l0 = lo_of(tr[u]), l1 = hi_of(tr[u]), h0 = lo_of(gr[u]), h1 = hi_of(gr[u]);
+                                const bool whole = xc + (u + 1) * PAIR_STEP <= x1;
+                                if (!whole) {
+                                    logits(tr[u], x, &l0, &l1);
+                                    logits(gr[u], x, &h0, &h1);
+                                }
+                                const double t0 = term(l0, floor_t, mxt), t1 = term(l1, floor_t, mxt);
+                                const double g0 = term(h0, floor_g, mxg), g1 = term(h1, floor_g, mxg);
                                 zt += t0 + t1;
                                 zg += g0 + g1;
-                                if (x < x1) put2(cur, x, t0, t1);
+                                if (whole) *reinterpret_cast<d2*>(cur + x) = d2{t0, t1};
+                                else if (x < x1) put2(cur, x, t0, t1);
                                 if (!RES && x < x1) put2(g_mem, x, g0, g1);
-                                gn[2 * u] = g0;
-                                gn[2 * u + 1] = g1;
+                                t2[u] = words_of(g0);
+                                g2[u] = words_of(g1);
+                                asm volatile("" : "+v"(zt), "+v"(zg));   // step by step: more terms at once do not fit the registers
                             }
                         }
 #pragma unroll
-                        for (int u = 0; u + 2 < U; ++u) {
-                            tr[u] = tr[u + 2];
-                            gr[u] = gr[u + 2];
+                        for (int u = 0; u + TURN < U; ++u) {
+                            tr[u] = tr[u + TURN];
+                            gr[u] = gr[u + TURN];
                         }
                         if (RES) {
 #pragma unroll
-                            for (int u = 0; u < 2; ++u) {
-                                tr[U - 2 + u] = words_of(gn[2 * u]);
-                                gr[U - 2 + u] = words_of(gn[2 * u + 1]);
+                            for (int u = 0; u < TURN; ++u) {
+                                tr[U - TURN + u] = t2[u];
+                                gr[U - TURN + u] = g2[u];
                             }
                         }
                     }
@@ -380,8 +397,9 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                     st += sh.sum_a[w];
                     sg += sh.sum_b[w];
                 }
-                inv_st = 1.0 / st;
-                inv_sg = 1.0 / sg;
+                st = uniform_d(st);
+                inv_st = uniform_d(1.0 / st);
+                inv_sg = uniform_d(1.0 / sg);
                 __syncthreads();   // the walk below writes the same arrays
             } else {
                 nb = nrow[min(tid, k - 1)];
@@ -393,8 +411,8 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
             }
 
             // ---- nearest-first walk on t_j (Algorithm 2, inference part) ----
-            const double gx = exp_tab_nonpos((double)Lane<LT>::glob(grow, xt) - mxg, sh.tab) * inv_sg;
-            const double t_tok = cur_at(xt) * inv_st;
+            const double gx = uniform_d(term(Lane<LT>::glob(grow, xt), floor_g, mxg) * inv_sg);
+            const double t_tok = uniform_d(cur_at(xt) * inv_st);
             double carry = 0.0, S = 0.0;
             int a_size = k;
             int off = 0;
@@ -457,7 +475,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 next = -2;
                 break;
             }
-            const double mass = t_tok + S;
+            const double mass = uniform_d(t_tok + S);
             const double u_acc = (double)(PLAIN ? u_acc32 : staged ? sh.u_acc[i] : a.uniforms[2 * c]);
             if (u_acc * gx < mass) {
                 if (PLAIN) have_rows = false;   // nothing to draw from (the decision is made elsewhere)
@@ -521,9 +539,10 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 __syncthreads();
             }
             zz = zero_resid ? zt : z;
+            zz = uniform_d(zz);
             st = zz;
-            inv_st = 1.0 / zz;
-            u_res = (double)(PLAIN ? u_res32 : staged ? sh.u_res[i] : a.uniforms[2 * c + 1]);
+            inv_st = uniform_d(1.0 / zz);
+            u_res = PLAIN ? u_res32 : staged ? sh.u_res[i] : a.uniforms[2 * c + 1];
             if (PLAIN) break;
         }
         if (taken < 0) {
@@ -531,7 +550,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
             // first token at which the cumulative sum of t_{j+1} exceeds u times its mass
             if (next == -1 && have_rows) {
                 const double* part = zero_resid ? sh.wt : sh.wr;
-                const double edge = u_res * zz;
+                const double edge = (double)u_res * zz;
                 double run = 0.0, before = 0.0;
                 int owner = -1, last = -1;
 #pragma unroll 4
@@ -550,8 +569,9 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                 if (owner < 0) break;          // no mass at all (sums that are not numbers): next stays -1
                 if (wave == owner) {
                     int found = -1, last_pos = -1;
+                    const int l2 = opaque_int(2 * lane);
                     for (int xb = x0; xb < x1 && found < 0; xb += PAIR_STEP) {
-                        const int x = xb + 2 * lane;
+                        const int x = xb + l2;
                         const d2 v = x < x1 ? get2(cur, x) : d2{0.0, 0.0};
                         const double r0 = fmax(v.x, 0.0), r1 = fmax(v.y, 0.0);
                         const double own = r0 + r1;

@@ -123,12 +123,6 @@ __device__ __forceinline__ float max_f32_1(float a, float uniform) {
     asm("v_max_f32 %0, %1, %2" : "=v"(r) : "s"(uniform), "v"(a));
     return r;
 }
-// A value that is the same in every lane, in scalar registers.
-__device__ __forceinline__ float uniform_f(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
-__device__ __forceinline__ double uniform_d(double v) {
-    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)), __builtin_amdgcn_readfirstlane(__double2loint(v)));
-}
-
 // A row's terms e^l 2^(-K/256), K its reference logit in steps of ln2/256.  floor: the least logit that is
 // evaluated as it is; lower ones (filtered tokens at -inf among them) are evaluated there.  The target's floor lies
 // 700 below its reference and the drafter's 650: terms of 1e-282 of the sum at most, and a target logit at its floor
