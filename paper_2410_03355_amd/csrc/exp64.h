@@ -80,7 +80,13 @@ LANTERN_HD double exp_tab(double d, const double* tab) {
     const int mi = (int)m;
     const int j = mi & 127;
     const int n = mi >> 7;                                  // floor division: j >= 0
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef double pair_t __attribute__((ext_vector_type(2)));
+    const pair_t entry = reinterpret_cast<const pair_t*>(tab)[j];   // one 16-byte load: the table is aligned
+    const double hi = entry.x, lo = entry.y;
+#else
     const double hi = tab[2 * j], lo = tab[2 * j + 1];
+#endif
     const double p = exp_poly5(r);                          // e^r - 1
     const double res = hi + __builtin_fma(hi, p, lo);
     return ldexp(res, n);

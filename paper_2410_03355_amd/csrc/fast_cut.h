@@ -87,16 +87,21 @@ __device__ __forceinline__ SlotTerms slot_terms(const int (&nb)[4], int xt, int 
     float run = 0.f;
     st.skip = 0;
     int bad = 0;
+    // All four logits are read before the first is used, by whatever lanes: read inside the branches that use them, each
+    // waits for the one before (60 rows of 8192 fp32 logits 6.7 -> 6.4 us with the row stored in order of arrival).
+    float logit[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) logit[q] = L::lds(s_row, (unsigned)nb[q] < (unsigned)V ? nb[q] : 0);   // in flight together
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const bool valid = tid * 4 + q < k;
         const int n = nb[q];
         const bool inr = (unsigned)n < (unsigned)V;
         if (valid && !inr) bad = 1;
-        float e = 0.f;
-        if (n == xt || !valid) st.skip |= 1u << q;
-        else if (inr) e = hw_exp2(__builtin_fmaf(L::lds(s_row, n), LOG2E_F, -ct));
-        run += e;
+        const bool skip = n == xt || !valid;
+        if (skip) st.skip |= 1u << q;
+        const float e = hw_exp2(__builtin_fmaf(logit[q], LOG2E_F, -ct));
+        run += skip || !inr ? 0.f : e;
         st.incl[q] = run;
     }
     for (int j = TNT * 4 + tid; j < k; j += TNT)   // entries the walk may never reach are range-checked too

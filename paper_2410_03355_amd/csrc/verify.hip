@@ -277,7 +277,8 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
     }
     if (ROWS == ROWS_ANY) {
 #pragma unroll
-        for (int c = 0; c < NV; ++c) G[c] = row_vector_finish<LT, EPV>(G[c], c * TNT + tid, V, L::NEG_INF_WORD);
+        for (int c = 0; c < NV; ++c)
+            if ((c + 1) * TNT * EPV > V) G[c] = row_vector_finish<LT, EPV>(G[c], c * TNT + tid, V, L::NEG_INF_WORD);   // uniform
     }
 
     // ---- table of the exponential (cache-resident), empty list ----
@@ -341,7 +342,8 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
     uint32_t open = 0;                                       // bit c: a token of chunk c is not settled
     {
         const double sign_hi = keep[0], sign_lo = keep[1];
-        constexpr int STEP = NV * EPV <= 32 ? NV : 16 / EPV; // at most 32 tokens a turn
+        // at most 32 tokens a turn, 16 where rows may start and end anywhere (their kernels have fewer registers left)
+        constexpr int STEP = NV * EPV <= (ROWS == ROWS_ANY ? 16 : 32) ? NV : 16 / EPV;
 #pragma unroll 1
         for (int c = 0; c < NV; c += STEP) {
             uint4 sums[STEP];
@@ -657,14 +659,16 @@ __global__ __launch_bounds__(TNT, NV > 8 ? 3 : 4) void verify_fast(VerifyArgs a)
         const int xs = tok_ok ? xt : 0;
 
         // ---- raw target row to LDS; reference = maximum over vector slot 0 of every thread ----
+        // In the order in which the vectors arrive (left to the scheduler the first write may wait for the last load).
 #pragma unroll
         for (int c = 0; c < NV; ++c) {
             const int vi = c * TNT + tid;
-            if (ROWS == ROWS_ANY) {
+            if (ROWS == ROWS_ANY && (c + 1) * TNT * EPV > V) {   // uniform: the chunk reaches beyond the row
                 T[c] = row_vector_finish<LT, EPV>(T[c], vi, V, L::NEG_INF_WORD);
                 G[c] = row_vector_finish<LT, EPV>(G[c], vi, V, L::NEG_INF_WORD);
             }
             if (FULL || vi < nvec) reinterpret_cast<uint4*>(s_row)[vi] = T[c];
+            __builtin_amdgcn_sched_barrier(0);
         }
         float rt = neg_inf_f(), rg = neg_inf_f();
 #pragma unroll
