@@ -462,8 +462,8 @@ int lantern_verify_trees_greedy(const void* target_logits, lantern_dtype logits_
  * t_{j+1}.  The first accepted child is taken and the walk goes on from it.
  * With k = 1 or delta = 0 and tokens drawn independently from g this is
  * recursive rejection sampling, and the emitted token follows the target.
- * Two launches: the plain verification of all B*M candidates (it decides the
- * first child of every group, whose test is against t_1 itself), then one
+ * Two launches: the plain verification of the first child of every group
+ * (whose test is against t_1 itself), then one
  * workgroup per tree that walks it and evaluates the residual targets in fp64.
  *
  *   row_index, draft_tokens, uniforms, parent  [B*M] as in lantern_verify_trees

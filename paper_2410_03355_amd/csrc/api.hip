@@ -13,7 +13,7 @@ namespace {
 
 bool dtype_ok(int dt) { return dt == LANTERN_F32 || dt == LANTERN_BF16; }
 
-// What the second half of a tree step needs besides the verification arguments.
+// What a tree step needs besides the verification arguments (the decision of first children: parent and M).
 struct TreeFinish {
     const int32_t* parent;
     int M;
@@ -60,6 +60,8 @@ int verify_impl(const void* target_logits, const void* draft_logits, int logits_
     a.stage_rows = 0;
     a.delta = delta;
     a.uniforms = uniforms;
+    a.parent = tree && mode == lantern::VERIFY_DECIDE ? tree->parent : nullptr;
+    a.M = tree ? tree->M : 0;
     a.out_accept = out_accept;
     a.out_resample = out_resample;
     a.out_prob = out_accept_prob;
@@ -69,7 +71,7 @@ int verify_impl(const void* target_logits, const void* draft_logits, int logits_
     a.out_path = out_path;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     hipError_t e;
-    if (tree)   // one workgroup per tree: the walk over out_accept, then the residual draw it asks for
+    if (tree && mode == lantern::VERIFY_SELECTED)   // one workgroup per tree: the walk over out_accept, then the residual draw it asks for
         e = lantern::launch_tree_finish(a, tree->parent, tree->M, tree->out_len, tree->out_path, logits_dtype, stream);
     else if (mode == lantern::VERIFY_SELECTED)
         e = lantern::launch_resample_selected(a, logits_dtype, stream);
@@ -349,12 +351,14 @@ int lantern_verify_trees_sequential(const void* target_logits, const void* draft
     if (!workspace || ((uintptr_t)workspace & 255) != 0 ||
         workspace_bytes < lantern_verify_trees_sequential_workspace_bytes(B, M, V))
         return LANTERN_E_WORKSPACE;
-    // the plain verification of every candidate decides the first child of every sibling group
+    // the plain verification decides the first child of every sibling group
     int32_t* decisions = reinterpret_cast<int32_t*>(static_cast<unsigned char*>(workspace) +
                                                     (size_t)B * 2 * (size_t)V * sizeof(double));
-    const int rc = lantern_decide_rows(target_logits, draft_logits, logits_dtype, R, V, row_stride_elems, row_index,
-                                       B * M, draft_tokens, knn, k, divergence, delta, uniforms, decisions, nullptr,
-                                       hip_stream);
+    const TreeFinish first_children{parent, M, nullptr, nullptr};
+    const int rc = verify_impl(target_logits, draft_logits, (int)logits_dtype, R, row_index, B * M, V, row_stride_elems,
+                               draft_tokens, knn, k, divergence, delta, uniforms, decisions, nullptr, nullptr, nullptr,
+                               nullptr, nullptr, nullptr, hip_stream, lantern::VERIFY_DECIDE, nullptr, 0,
+                               &first_children);
     if (rc != LANTERN_OK) return rc;
     lantern::SequentialArgs a;
     a.accept = decisions;

@@ -12,8 +12,8 @@
 // The chain t_1, t_2, ... is sequential, so one workgroup of 1024 threads walks one tree and keeps
 // the current target and the drafter's distribution in fp64 (unnormalised terms and a scale each: no
 // division per token).  The test of a group's first child is the plain verification of that
-// candidate, so its decision is read from the row-parallel pass (lantern_decide_rows over all
-// candidates, launched first): only groups whose first child is rejected build the vectors.
+// candidate, so its decision is read from the row-parallel pass (lantern_decide_rows over the first
+// children, launched first): only groups whose first child is rejected build the vectors.
 // A launch has as many workgroups as trees and each is a chain of passes over the vocabulary, so what
 // counts is the length of that chain:
 //   - a thread owns pairs of neighbouring tokens (4-byte loads of bf16, 8-byte loads of fp32, 16-byte

@@ -14,6 +14,19 @@ namespace lantern {
 
 constexpr int CACHED = 4;   // nodes per lane that the walk keeps in registers: trees of up to 256 nodes
 
+// Whether node `node` (tree node / M) is the first child of its parent: no earlier node of the tree has the same
+// parent.  Every wavefront finds the same by itself.  In a malformed tree some node may come out either way.
+__device__ __forceinline__ bool first_child(const int32_t* parent, int M, int node) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int begin = node - node % M;
+    const int p = parent[node];
+    for (int base = begin; base < node; base += WAVE) {
+        const int q = min(base + lane, node - 1);
+        if (__ballot(parent[q] == p)) return false;
+    }
+    return true;
+}
+
 // acc, res, par: the tree's M decisions, resampled tokens (or null) and parents; path: its M path
 // slots, of which the first *len_out are written (by lane 0).  Returns what follows the accepted
 // nodes: the resampled token of the first child when every child of the last node was rejected

@@ -31,6 +31,8 @@ struct VerifyArgs {
     int stage_rows;           // VERIFY_SELECTED: both logit rows fit into LDS beside the exact path's data
     float delta;
     const float* uniforms;    // [N, 2]
+    const int32_t* parent;    // null, or [N] parents within trees of M nodes: only the first child of every node is
+    int M;                    //   verified, nothing is written for the others
     int32_t* out_accept;      // [N]
     int32_t* out_resample;    // [N]
     float* out_prob;          // optional diagnostics, may be null
