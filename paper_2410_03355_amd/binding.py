@@ -1,17 +1,24 @@
-"""Thin ctypes binding of liblantern.so: argument marshalling only.
+"""Thin binding of liblantern.so: argument marshalling only.
 
 PyTorch supplies device memory and the current HIP stream; every step of the
 verification path runs in the library's kernels.  There is no CPU fallback: if
 the library is missing, load() raises.
+
+The calls of a decoding step first go to their namesakes in _marshal.so, which
+take plain device tensors and nothing of the caller's (stream, outputs) without
+the interpreter in between; whatever those decline takes the way through ctypes
+below, which words the errors.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
-from .build import LIB_PATH
+from .build import LIB_PATH, MARSHAL_PATH
 
 F32, BF16 = 0, 1
 METRIC_L2, METRIC_COSINE = 0, 1
@@ -32,6 +39,7 @@ EXPORTS = (
 )
 
 _lib = None
+_marshal = None
 
 
 class LanternError(RuntimeError):
@@ -42,13 +50,14 @@ class LanternError(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Loads the built library.  Raises if it has not been built."""
-    global _lib
+    global _lib, _marshal
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise FileNotFoundError(
-            f"{LIB_PATH} not found: build it with `python -m paper_2410_03355_amd.build` "
-            "(there is no fallback implementation)")
+    for path in (LIB_PATH, MARSHAL_PATH):
+        if not os.path.exists(path):
+            raise FileNotFoundError(
+                f"{path} not found: build it with `python -m paper_2410_03355_amd.build` "
+                "(there is no fallback implementation)")
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, f32, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
     lib.lantern_build_knn_workspace_bytes.argtypes = [i32, i32, i32, i32]
@@ -103,8 +112,19 @@ def load() -> ctypes.CDLL:
     lib.lantern_status_string.restype = ctypes.c_char_p
     lib.lantern_version.argtypes = []
     lib.lantern_version.restype = i32
+    loader = importlib.machinery.ExtensionFileLoader("_marshal", MARSHAL_PATH)
+    marshal = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
+    marshal.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS})
+    _marshal = marshal
     _lib = lib
     return lib
+
+
+def _checked_status(got, where: str):
+    """What a function of _marshal.so returned: the results, or a status that is not zero."""
+    if got.__class__ is int:
+        raise LanternError(got, where)
+    return got
 
 
 def status_string(status: int) -> str:
@@ -241,6 +261,13 @@ def verify(target_logits, draft_logits, draft_tokens, knn, delta: float, uniform
     checked: synchronise and raise LanternError(E_TOKEN) (with .rows) if a verification was unusable; by
     default the call is asynchronous and such rows carry -1 in both outputs."""
     lib = load()
+    if out_accept is None and out_resample is None and stream is None:
+        got = _marshal.verify(target_logits, draft_logits, draft_tokens, knn, delta, uniforms)
+        if got is not None:
+            _checked_status(got, "lantern_verify")
+            if checked:
+                _raise_if_unusable(got[0], stream, "lantern_verify")
+            return got
     N, V, k = _check_verify_args(target_logits, draft_logits, draft_tokens, knn, uniforms)
     dev = target_logits.device
     acc = torch.empty(N, dtype=torch.int32, device=dev) if out_accept is None else out_accept
@@ -293,6 +320,10 @@ def verify_greedy(target_logits, draft_tokens, knn, delta: float, stream=None, w
     """lantern_verify_greedy; returns (accept int32[N], token int32[N]) device tensors
     (and the per-row path tensor when want_path)."""
     lib = load()
+    if stream is None and not want_path:
+        got = _marshal.verify_greedy(target_logits, draft_tokens, knn, delta)
+        if got is not None:
+            return _checked_status(got, "lantern_verify_greedy")
     _need_cuda(target_logits, draft_tokens, knn)
     if target_logits.dim() != 2 or target_logits.stride(1) != 1:
         raise ValueError("logits must be a [N, V] tensor with dense rows")
@@ -321,6 +352,10 @@ def accept_chains(accept, resample, L: int, stream=None):
     """lantern_accept_chains; accept / resample are int32 device tensors of B*L rows.
     Returns (kept int32[B], next_token int32[B])."""
     lib = load()
+    if stream is None:
+        got = _marshal.accept_chains(accept, resample, L)
+        if got is not None:
+            return _checked_status(got, "lantern_accept_chains")
     _need_cuda(accept, resample)
     if accept.dtype != torch.int32 or resample.dtype != torch.int32:
         raise TypeError("accept and resample must be int32")
@@ -348,6 +383,10 @@ def verify_rows(target_logits, draft_logits, row_index, draft_tokens, knn, delta
     """lantern_verify_rows: verification i reads logit row row_index[i].
     Returns (accept int32[N], resample int32[N]) device tensors."""
     lib = load()
+    if stream is None:
+        got = _marshal.verify_rows(target_logits, draft_logits, row_index, draft_tokens, knn, delta, uniforms, divergence)
+        if got is not None:
+            return _checked_status(got, "lantern_verify_rows")
     _need_cuda(target_logits, draft_logits, row_index, draft_tokens, knn, uniforms)
     if target_logits.dim() != 2 or target_logits.shape != draft_logits.shape or \
             target_logits.dtype != draft_logits.dtype:
@@ -380,6 +419,10 @@ def verify_rows(target_logits, draft_logits, row_index, draft_tokens, knn, delta
 def verify_greedy_rows(target_logits, row_index, draft_tokens, knn, delta: float, stream=None):
     """lantern_verify_greedy_rows; returns (accept int32[N], token int32[N]) device tensors."""
     lib = load()
+    if stream is None:
+        got = _marshal.verify_greedy_rows(target_logits, row_index, draft_tokens, knn, delta)
+        if got is not None:
+            return _checked_status(got, "lantern_verify_greedy_rows")
     _need_cuda(target_logits, row_index, draft_tokens, knn)
     if target_logits.dim() != 2 or target_logits.stride(1) != 1:
         raise ValueError("logits must be a [R, V] tensor with dense rows")
@@ -406,6 +449,10 @@ def accept_trees(accept, resample, parent, M: int, stream=None):
     """lantern_accept_trees; accept / resample / parent are int32 device tensors of B*M rows.
     Returns (len int32[B], path int32[B, M], next_token int32[B])."""
     lib = load()
+    if stream is None:
+        got = _marshal.accept_trees(accept, resample, parent, M)
+        if got is not None:
+            return _checked_status(got, "lantern_accept_trees")
     given = [t for t in (accept, resample, parent) if t is not None]
     _need_cuda(*given)
     for t in given:
@@ -468,6 +515,10 @@ def decide_rows(target_logits, draft_logits, row_index, draft_tokens, knn, delta
                 divergence: str = "tvd", stream=None, want_path: bool = False):
     """lantern_decide_rows; returns accept int32[N] (device), and the per-row path tensor when want_path."""
     lib = load()
+    if stream is None and not want_path:
+        got = _marshal.decide_rows(target_logits, draft_logits, row_index, draft_tokens, knn, delta, uniforms, divergence)
+        if got is not None:
+            return _checked_status(got, "lantern_decide_rows")
     R, V, N, stride = _rows_args(target_logits, draft_logits, row_index, draft_tokens, knn, uniforms)
     acc = torch.empty(N, dtype=torch.int32, device=target_logits.device)
     path = torch.empty(N, dtype=torch.int32, device=target_logits.device) if want_path else None
@@ -507,6 +558,10 @@ def verify_trees(target_logits, draft_logits, row_index, parent, M: int, draft_t
                  uniforms, divergence: str = "tvd", stream=None):
     """lantern_verify_trees; returns (accept int32[B*M], len int32[B], path int32[B, M], next int32[B])."""
     lib = load()
+    if stream is None:
+        got = _marshal.verify_trees(target_logits, draft_logits, row_index, parent, M, draft_tokens, knn, delta, uniforms, divergence)
+        if got is not None:
+            return _checked_status(got, "lantern_verify_trees")
     R, V, N, stride = _rows_args(target_logits, draft_logits, row_index, draft_tokens, knn, uniforms)
     _need_cuda(parent)
     if parent.dtype != torch.int32 or not parent.is_contiguous() or parent.numel() != N or M < 1 or N % M:
@@ -534,6 +589,11 @@ def verify_trees_sequential(target_logits, draft_logits, row_index, parent, M: i
     workspace: a uint8 device tensor of at least trees_sequential_workspace_bytes(B, M, V) bytes, or None
     to allocate one."""
     lib = load()
+    if stream is None:
+        got = _marshal.verify_trees_sequential(target_logits, draft_logits, row_index, parent, M, draft_tokens, knn, delta, uniforms, divergence,
+                                               workspace)
+        if got is not None:
+            return _checked_status(got, "lantern_verify_trees_sequential")
     R, V, N, stride = _rows_args(target_logits, draft_logits, row_index, draft_tokens, knn, uniforms)
     _need_cuda(parent)
     if parent.dtype != torch.int32 or not parent.is_contiguous() or parent.numel() != N or M < 1 or N % M:
@@ -568,6 +628,10 @@ def verify_trees_greedy(target_logits, row_index, parent, M: int, draft_tokens, 
     """lantern_verify_trees_greedy; returns (accept int32[B*M], token int32[B*M], len int32[B],
     path int32[B, M], next int32[B])."""
     lib = load()
+    if stream is None:
+        got = _marshal.verify_trees_greedy(target_logits, row_index, parent, M, draft_tokens, knn, delta)
+        if got is not None:
+            return _checked_status(got, "lantern_verify_trees_greedy")
     given = [t for t in (target_logits, row_index, parent, draft_tokens, knn) if t is not None]
     _need_cuda(*given)
     if target_logits.dim() != 2 or target_logits.stride(1) != 1:

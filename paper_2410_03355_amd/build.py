@@ -1,17 +1,22 @@
-"""Builds liblantern.so (the C-ABI library of include/lantern.h) for gfx950 with hipcc.
+"""Builds liblantern.so (the C-ABI library of include/lantern.h) for gfx950 with hipcc, and _marshal.so, the host
+half of its step calls for PyTorch (csrc/marshal.cpp, host code only).
 
-hipcc cross-compiles without a GPU.  The library is built in-tree, next to
-this file, so that it travels with the source tree.
+hipcc cross-compiles without a GPU.  The libraries are built in-tree, next to
+this file, so that they travel with the source tree.
 """
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
+
+import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "liblantern.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 SOURCES = ("api.hip", "verify.hip", "greedy.hip", "chain.hip", "sequential.hip", "knn.hip", "random_table.hip", "probe.hip")
 
 HIPCC_FLAGS = (
@@ -32,8 +37,21 @@ def hipcc_path() -> str:
     return "hipcc"
 
 
+def marshal_command() -> list:
+    """Host code against PyTorch's C++ interface: by the host compiler, whose names PyTorch's libraries carry."""
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path())))
+    home = os.path.dirname(torch.__file__)
+    abi = int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            f"-D_GLIBCXX_USE_CXX11_ABI={abi}", "-isystem", os.path.join(home, "include"),
+            "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
+            "-I", os.path.join(_ROOT, "include"),
+            os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH, "-L", os.path.join(home, "lib"),
+            "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build(verbose: bool = False) -> str:
-    """Compiles every source to an object (in parallel, in a scratch directory) and links the library."""
+    """Compiles every source to an object (in parallel, in a scratch directory) and links the libraries."""
     import concurrent.futures
     import tempfile
 
@@ -48,8 +66,15 @@ def build(verbose: bool = False) -> str:
             subprocess.run(cmd, check=True)
             return obj
 
-        with concurrent.futures.ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
+        def marshal() -> None:
+            if verbose:
+                print(" ".join(marshal_command()), flush=True)
+            subprocess.run(marshal_command(), check=True)
+
+        with concurrent.futures.ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, os.cpu_count() or 1, 8)) as pool:
+            host = pool.submit(marshal)
             objs = list(pool.map(compile_one, SOURCES))
+            host.result()
         link = [hipcc_path(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
         if verbose:
             print(" ".join(link), flush=True)
