@@ -38,30 +38,30 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 _FETCH_SCALE = 262144.0 / 131091.8   # what FETCH_SIZE read for a 256 MiB copy in the same run
 MEASURED_TRAFFIC = {
     # (workload, variant, mode): (bytes per launch, library version, source)
-    ("stress", "plain", "sample"): ((130996.6 * _FETCH_SCALE + 240.1) * 1024, 230,
-                                    "profiles/verify_fast_stress_plain.md (FETCH_SIZE, WRITE_SIZE; version 230)"),
-    ("stress", "reject", "sample"): ((165171.0 * _FETCH_SCALE + 291.1) * 1024, 230,
-                                     "profiles/verify_fast_stress_plain.md (reject mix; version 230)"),
-    ("wide_latent", "plain", "sample"): ((124423.8 * _FETCH_SCALE + 240.3) * 1024, 230,
-                                         "profiles/verify_fast_stress_plain.md (wide_latent; version 230)"),
-    ("stress", "plain", "greedy"): ((69193.7 * _FETCH_SCALE + 240.0) * 1024, 230,
-                                    "profiles/greedy_fast_stress_plain.md (version 230)"),
+    ("stress", "plain", "sample"): ((130993.8 * _FETCH_SCALE + 240.2) * 1024, 240,
+                                    "profiles/verify_fast_stress_plain.md (FETCH_SIZE, WRITE_SIZE; version 240)"),
+    ("stress", "reject", "sample"): ((165169.3 * _FETCH_SCALE + 284.6) * 1024, 240,
+                                     "profiles/verify_fast_stress_plain.md (reject mix; version 240)"),
+    ("wide_latent", "plain", "sample"): ((124426.1 * _FETCH_SCALE + 240.4) * 1024, 240,
+                                         "profiles/verify_fast_stress_plain.md (wide_latent; version 240)"),
+    ("stress", "plain", "greedy"): ((69188.6 * _FETCH_SCALE + 240.0) * 1024, 240,
+                                    "profiles/greedy_fast_stress_plain.md (version 240)"),
 }
 
 
 # Per-kernel split of a table build, from the kernel trace summarised under profiles/ (events inside this
 # process only bracket the whole build): us per build, reported under the same rule, and only if the parts do
 # not add up to more than the build took.  The stress table takes the path with sampled thresholds and a
-# filtering contraction (its keys to a sample of 2048 tokens are contracted first: 2 V S d further flop), and
-# so does the wide-latent table (a sample of 1024 tokens).
+# filtering contraction, and so does the wide-latent table.  The thresholds' kernel contracts the rows with a sample of
+# 2048 and 1024 tokens itself; its product is not counted among the contractions.
 MEASURED_KNN_SPLIT = {
     # workload: ({kernel: us per build}, extra contraction flop, library version, source)
-    "stress": ({"sample_contraction": 50.4, "thresholds": 35.6, "filter_contraction": 207.3, "selection": 187.7,
-                "exact_check": 5.7, "operands_and_norms": 9.6}, 2.0 * 16384 * 2048 * 8, 230,
-               "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 230)"),
-    "wide_latent": ({"sample_contraction": 21.0, "thresholds": 12.9, "filter_contraction": 78.6, "selection": 107.4,
-                     "exact_check": 4.1, "operands_and_norms": 11.3}, 2.0 * 8192 * 1024 * 256, 230,
-                    "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 230)"),
+    "stress": ({"thresholds": 34.7, "filter_contraction": 107.4, "selection": 170.9, "exact_check": 4.2,
+                "operands_and_norms": 8.1}, 0.0, 240,
+               "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 240)"),
+    "wide_latent": ({"thresholds": 21.9, "filter_contraction": 72.4, "selection": 72.5, "exact_check": 4.1,
+                     "operands_and_norms": 10.6}, 0.0, 240,
+                    "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 240)"),
 }
 
 

@@ -92,11 +92,12 @@ typedef enum {
 /*
  * Bytes of device workspace lantern_build_knn needs for this problem, or 0 if
  * the arguments are invalid.  The workspace holds, for a block of query rows,
- * either candidate lists and the rows' approximate distances to a sample of
- * the codebook, or their approximate distances to every token (which of the
- * two depends on V and k alone); its contents are scratch.  Sized for few,
- * large launches: up to about 850 MiB (V = 65536, k = 1000), 528 MiB for
- * V = 16384, k = 1000.
+ * either candidate lists (and, for V of about 17000 and more, the rows'
+ * approximate distances to a sample of the codebook), or their approximate
+ * distances to every token (which of the two depends on the shape and type of
+ * the codebook and on k alone); its contents are scratch.  Sized for few,
+ * large launches: up to about 850 MiB (V = 65536, d = 64, k = 1000), 209 MiB
+ * for V = 16384, d = 8, k = 1000.
  */
 size_t lantern_build_knn_workspace_bytes(lantern_dtype cb_dtype, int V, int d, int k);
 
