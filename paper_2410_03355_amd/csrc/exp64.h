@@ -211,13 +211,21 @@ LANTERN_HD double exp_units(double l, double start, const unsigned char* tab_byt
     const double hi = exp_units_scaled(u.hi, u.mi);
     return __builtin_fma(hi, u.p, hi);
 }
-// With a table whose hi is whole (j 2^44 put back when it is laid out), for results that may lie below the normal range:
-// rounded there, in the end zero.
-LANTERN_HD double exp_units_nonpos(double l, double start, const unsigned char* tab_bytes) {
-    const ExpUnits u = exp_units_parts(l, start, tab_bytes);
+// e^d for d <= 0 (or -inf, result 0) from a table whose hi is whole (j 2^44 put back when it is laid out); results below
+// the normal range are rounded there, in the end zero.  The clamp is on the fp64 difference that the caller forms: a floor
+// in fp32 under a row's maximum is the maximum itself once that has no units left (from 2^35 on for 1100).
+LANTERN_HD double exp_units_nonpos(double d, const unsigned char* tab_bytes) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    double c;                                               // fmax would quiet its operands first
+    asm("v_max_f64 %0, %1, %2" : "=v"(c) : "v"(d), "s"(-1100.0));
+    d = c;
+#else
+    d = fmax(d, -1100.0);
+#endif
+    const ExpUnits u = exp_units_parts(d, EXP_UNITS_START, tab_bytes);
     return ldexp(__builtin_fma(u.hi, u.p, u.hi), (int)u.mi >> 8);
 }
-// The same from the table as it is.
+// exp_units for results that may lie below the normal range.
 LANTERN_HD double exp_units_any(double l, double start, const unsigned char* tab_bytes) {
     const ExpUnits u = exp_units_parts(l, start, tab_bytes);
     const double hi = exp_units_scaled(u.hi, u.mi & 255u);

@@ -149,8 +149,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
     u2 tr[U], gr[U];
     const unsigned char* tab = reinterpret_cast<const unsigned char*>(sh.tab);
     double inv_st = 0.0, inv_sg = 0.0, st = 0.0, mxg = 0.0;
-    float floor_g = 0.f;
-    auto term = [&](float l, float least, double max) { return exp_units_nonpos((double)fmaxf(l, least) - max, EXP_UNITS_START, tab); };
+    auto term = [&](float l, double max) { return exp_units_nonpos((double)l - max, tab); };
     const double delta = (double)a.delta;
 
     // the part of the vocabulary of this wavefront: [x0, x1), in steps of a pair per lane
@@ -331,11 +330,8 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                     next = -2;
                     break;
                 }
-                // terms e^(l - max); filtered tokens are evaluated 1100 below the maximum, where a term is zero
                 const double mxt = uniform_d((double)mt);
                 mxg = uniform_d((double)mg);
-                const float floor_t = uniform_f(mt - 1100.f);
-                floor_g = uniform_f(mg - 1100.f);
                 double zt = 0.0, zg = 0.0;
                 // Some steps a turn, the registers moved down behind them and what comes of them put at the
                 // end (NP > 0: after the last turn every step is back in its place): unrolled in full, this is
@@ -357,8 +353,8 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
                                     logits(tr[u], x, &l0, &l1);
                                     logits(gr[u], x, &h0, &h1);
                                 }
-                                const double t0 = term(l0, floor_t, mxt), t1 = term(l1, floor_t, mxt);
-                                const double g0 = term(h0, floor_g, mxg), g1 = term(h1, floor_g, mxg);
+                                const double t0 = term(l0, mxt), t1 = term(l1, mxt);
+                                const double g0 = term(h0, mxg), g1 = term(h1, mxg);
                                 zt += t0 + t1;
                                 zg += g0 + g1;
                                 if (whole) *reinterpret_cast<d2*>(cur + x) = d2{t0, t1};
@@ -411,7 +407,7 @@ __global__ __launch_bounds__(SNT) void trees_sequential(SequentialArgs a) {
             }
 
             // ---- nearest-first walk on t_j (Algorithm 2, inference part) ----
-            const double gx = uniform_d(term(Lane<LT>::glob(grow, xt), floor_g, mxg) * inv_sg);
+            const double gx = uniform_d(term(Lane<LT>::glob(grow, xt), mxg) * inv_sg);
             const double t_tok = uniform_d(cur_at(xt) * inv_st);
             double carry = 0.0, S = 0.0;
             int a_size = k;

@@ -33,6 +33,34 @@ int main() {
     const bool ends = exp_units_any(0.0, start, tab) == 1.0 && exp_units_any(-1100.0, start, tab) == 0.0 &&
                       exp_units_any(-5000.0, EXP_UNITS_START + 1400000.0, tab) == 0.0 &&
                       std::fabs(exp_units_any(-720.0, start, tab) / std::exp(-720.0) - 1.0) < 1e-10;
-    std::printf("%.6f %ld %d\n", worst, differ, ends ? 1 : 0);
+    // e^d, d <= 0, from the table laid out whole: rounding error where the result is normal, otherwise in units of the
+    // smallest number; arguments of any size (what the tree walk subtracts from a maximum near the largest float)
+    static uint64_t whole[2 * EXP_FINE_N];
+    for (int j = 0; j < EXP_FINE_N; ++j) {
+        whole[2 * j] = EXP_FINE[2 * j] + ((uint64_t)j << 44);
+        whole[2 * j + 1] = EXP_FINE[2 * j + 1];
+    }
+    const unsigned char* wtab = reinterpret_cast<const unsigned char*>(whole);
+    std::uniform_real_distribution<double> small(-60.0, 0.0), low(-1110.0, 0.0), edge(-746.0, -700.0);
+    double worst_nonpos = 0.0, worst_below = 0.0;
+    for (int i = 0; i < 400000; ++i) {
+        const double d = i % 3 == 0 ? small(rng) : i % 3 == 1 ? low(rng) : edge(rng);
+        const double v = exp_units_nonpos(d, wtab);
+        const __float128 err = fabsq((__float128)v - expq((__float128)d));
+        if (d > -708.0) {
+            int e;
+            std::frexp(v, &e);
+            worst_nonpos = std::fmax(worst_nonpos, (double)(err / (__float128)std::ldexp(1.0, e - 53)));
+        } else {
+            worst_below = std::fmax(worst_below, (double)(err / (__float128)std::ldexp(1.0, -1074)));
+        }
+    }
+    long wrong = exp_units_nonpos(0.0, wtab) != 1.0;
+    for (double d : {-1100.0, -1101.0, -5000.0, -4e10, -1e30, -6.8e38, -1e300, -(double)INFINITY}) wrong += exp_units_nonpos(d, wtab) != 0.0;
+    for (double top : {1e6, 3.4e10, 4e10, 1e12, 1e30, -1e30, 3.4e38, -3.4e38})   // a row's maximum, below it nothing or -inf
+        for (float l : {(float)top, -3.4028234e38f, -(float)INFINITY})
+            wrong += exp_units_nonpos((double)l - (double)(float)top, wtab) !=
+                     (l == (float)top || (double)l - (double)(float)top > -700.0 ? std::exp((double)l - (double)(float)top) : 0.0);
+    std::printf("%.6f %ld %d %.6f %.6f %ld\n", worst, differ, ends ? 1 : 0, worst_nonpos, worst_below, wrong);
     return 0;
 }

@@ -57,3 +57,21 @@ def test_kinds_of_rows(oracle_mod, lantern_gpu, dtype, V, kind):
         acc, *_ = compare_verify(oracle_mod, lantern_gpu, target, draft, tokens, table, delta, uniforms,
                                  label=f"{kind} V={V} {dtype} delta={delta}")
         assert (acc == 0).any()
+
+
+@pytest.mark.parametrize("below", [620.0, 668.0, 715.0])
+@pytest.mark.parametrize("dtype,V", [(torch.float32, 1024), (torch.float32, 8192), (torch.bfloat16, 2040), (torch.bfloat16, 16384),
+                                     (torch.bfloat16, 33000)])
+def test_draw_of_exactly_zero(oracle_mod, lantern_gpu, dtype, V, below):
+    """A draw of zero takes the first token that has any residual at all: here one that lies hundreds of nats below the
+    row's maximum and is filtered on the drafter's side."""
+    target, draft, tokens, uniforms = _inputs("plain", V, torch.float32, V + 1)
+    first = 3
+    target[:, first], draft[:, :first + 1] = target.max(dim=1).values - below, -float("inf")
+    target[:, :first] = -float("inf")
+    tokens = draft.to(dtype).float().argmax(dim=1).to(torch.int32)
+    uniforms[:, 0], uniforms[:, 1] = 1 - 2.0 ** -24, 0.0
+    table = np.arange(V, dtype=np.int32)[:, None]
+    acc, res, *_ = compare_verify(oracle_mod, lantern_gpu, target.to(dtype), draft.to(dtype), tokens, table, 0.0, uniforms,
+                                  label=f"V={V} {dtype} {below} below")
+    assert (res[acc == 0] == first).all() and (acc == 0).any()
