@@ -126,7 +126,8 @@ __device__ __forceinline__ float max_f32_1(float a, float uniform) {
 // A row's terms e^l 2^(-K/256), K its reference logit in steps of ln2/256.  floor: the least logit that is
 // evaluated as it is; lower ones (filtered tokens at -inf among them) are evaluated there.  The target's floor lies
 // 700 below its reference and the drafter's 650: terms of 1e-282 of the sum at most, and a target logit at its floor
-// is below any drafter logit by more than the sums can make up for (both lie in [1, 2^46]).
+// is below any drafter logit by more than the sums can make up for (both lie in [1, 2^46]).  What such terms decide is the
+// sign of a residual below 1e-260 of the row, which a draw above zero never reaches.
 struct UnitRow {
     double start;    // EXP_UNITS_START - K
     float floor;
@@ -487,9 +488,10 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
         }
     }
     __syncthreads();
-    // a list that overflowed, or a residual without mass (by rounding): the general path, which finds the row as
-    // it was (uniform over the workgroup)
-    if (n_amb > AMB_CAP || !(sh.bcast[4] > 0.0)) {
+    // A list that overflowed, a residual without mass (by rounding), or a draw of exactly zero, which takes the first token
+    // that has any residual, however far below the floors: the general path, which finds the row as it was (uniform over
+    // the workgroup).
+    if (n_amb > AMB_CAP || !(sh.bcast[4] > 0.0) || u_res32 == 0.f) {
         const LT* trow = reinterpret_cast<const LT*>(a.target) + (int64_t)lrow * a.stride;
         for (int j = tid; j < a_size; j += TNT) reinterpret_cast<LT*>(s_row)[nrow[j]] = trow[nrow[j]];
         if (tid == 0) reinterpret_cast<LT*>(s_row)[xt] = trow[xt];
