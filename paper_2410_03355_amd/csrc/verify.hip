@@ -88,7 +88,7 @@ enum RowsKnown { ROWS_FULL, ROWS_WHOLE, ROWS_ANY };
 // registers from the fp32 pass on would cost that pass registers it does not have), the target row
 // is in LDS, the first four table slots per thread in registers.
 constexpr int AMB_CAP = 40;          // tokens whose residual sign fp32 leaves open (about one per row)
-constexpr double TAU_SIGN = 2.0e-5;  // covers the error of ln(Z_t32 / Z_g32) in the sign test (<= 1.16e-5)
+constexpr double TAU_SIGN = 2.0e-5;  // covers the error of ln(Z_t32 / Z_g32) in the sign test (<= 8.8e-6)
 
 struct AmbEntry {
     double et, eg;   // unnormalised fp64 terms
@@ -151,7 +151,7 @@ __device__ __forceinline__ UnitRow unit_row(float ref, float below) {
 // certainly without residual.
 // The sign test works on the logits: t(x) > g(x) <=> l_t - l_g > ln(Z_t / Z_g) + r_t - r_g, where only the two
 // fp32 sums carry an error (at most 4.4e-6 relative each: terms 2.5e-6, tree sums 1.9e-6, i.e. 8.8e-6 on the
-// logarithm, and their ratio's fp32 logarithm 2.8e-6), so a margin of TAU_SIGN = 2e-5 on either side makes "positive" and "not positive" certain.
+// logarithm), so a margin of TAU_SIGN = 2e-5 on either side makes "positive" and "not positive" certain.
 struct OnePassAcc {
     double zt, zg;
 };
@@ -308,16 +308,17 @@ __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int
     // 2^(l * LOG2E_F - c) with c = ref * LOG2E_F rounded to fp32, against e^(l - ref): per
     // term the two differ by (l - ref) (LOG2E_F - log2 e), which the term's error bound holds, and by
     // the rounding of c, common to the row and known exactly (the product of two floats is exact in
-    // fp64): that one is put back.  The logarithm itself may be off by 2.7e-6 (one unit in the last place of a
-    // binary logarithm below 46).
-    const double LN2_D = 0.69314718055994530942;
-    const double rt64 = (double)ref_t, rg64 = (double)ref_g;
-    const double adj_t = ((double)(ref_t * LOG2E_F) - rt64 * (double)LOG2E_F) * LN2_D;
-    const double adj_g = ((double)(ref_g * LOG2E_F) - rg64 * (double)LOG2E_F) * LN2_D;
-    const double sign = (double)__builtin_amdgcn_logf(Zt32 / Zg32) * LN2_D + adj_t - adj_g + (rt64 - rg64);
-    if (tid == 0) {                                          // kept in LDS: registers are short during the pass
+    // fp64): that one is put back.  Quotient and logarithm in fp64, by the last wavefront alone.
+    if (tid == TNT - WAVE) {                                 // kept in LDS: registers are short during the pass
+        const double LN2_D = 0.69314718055994530942;
+        const double rt64 = (double)ref_t, rg64 = (double)ref_g;
+        const double adj_t = ((double)(ref_t * LOG2E_F) - rt64 * (double)LOG2E_F) * LN2_D;
+        const double adj_g = ((double)(ref_g * LOG2E_F) - rg64 * (double)LOG2E_F) * LN2_D;
+        const double sign = log((double)Zt32 / (double)Zg32) + adj_t - adj_g + (rt64 - rg64);
         keep[0] = sign + TAU_SIGN;
         keep[1] = sign - TAU_SIGN;
+    }
+    if (tid == 0) {
         keep[2] = rt.start;
         keep[3] = rg.start;
         sh.bcast[0] = rt.term_any(L::lds(s_row, xt), tab);
