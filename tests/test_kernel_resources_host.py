@@ -8,7 +8,8 @@ import pytest
 
 import paper_2410_03355_amd as lantern
 
-READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
+LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+READELF, OBJDUMP = os.path.join(LLVM, "llvm-readelf"), os.path.join(LLVM, "llvm-objdump")
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
@@ -29,16 +30,24 @@ def _device_objects(blob):
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{mangled name: (bytes of scratch per lane, spilled vector registers, vector registers)}"""
+def objects(tmp_path_factory):
+    """Paths of the library's code objects, each in a file of its own."""
     if not os.path.exists(lantern.LIB_PATH):
         lantern.build()
     with open(lantern.LIB_PATH, "rb") as f:
         blob = f.read()
-    found = {}
+    paths = []
     for i, obj in enumerate(_device_objects(blob)):
-        path = tmp_path_factory.mktemp("objects") / f"{i}.o"
-        path.write_bytes(obj)
+        paths.append(tmp_path_factory.mktemp("objects") / f"{i}.o")
+        paths[-1].write_bytes(obj)
+    return paths
+
+
+@pytest.fixture(scope="module")
+def kernels(objects):
+    """{mangled name: (bytes of scratch per lane, spilled vector registers, vector registers)}"""
+    found = {}
+    for path in objects:
         notes = subprocess.run([READELF, "--notes", str(path)], check=True, capture_output=True, text=True).stdout
         for part in notes.split("- .agpr_count")[1:]:
             value = {key: re.search(r"\." + key + r":\s+(\S+)", part).group(1)
@@ -63,3 +72,16 @@ def test_smallest_full_rows_leave_room_for_five_wavefronts(kernels):
     five wavefronts fit a SIMD, and 30720 such rows take 87 us instead of 104."""
     name, = [n for n in kernels if re.search(r"verify_fastIfLi256ELi1ELi0ELb1EE", n)]
     assert kernels[name][0] == 0 and kernels[name][2] <= 96
+
+
+def test_rows_arrive_without_scratch_memory(objects):
+    """Until a row is in LDS (the first barrier) no kernel of the fp32 pass touches scratch memory."""
+    seen = 0
+    for path in objects:
+        listing = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", "--no-show-raw-insn", "--no-leading-addr", str(path)],
+                                 check=True, capture_output=True, text=True).stdout
+        for name, body in re.findall(r"^<(\S*verify_fast\S*)>:\n(.*?)(?=^<|\Z)", listing, re.S | re.M):
+            arriving = body[:body.index("s_barrier")]
+            assert "global_load_dwordx4" in arriving and "scratch_" not in arriving, name
+            seen += 1
+    assert seen == 42
