@@ -1695,8 +1695,10 @@ __global__ __launch_bounds__(LIST_THREADS, 4) void knn_rank_list(const CT* cb, i
             low = fminf(low, ends[w]);
             high = fmaxf(high, ends[TNW + w]);
         }
-        const float range = high - low;   // no range (or none that floats can divide): one bucket
-        scale = (range > 1e-30f && range < INFINITY) ? (float)(BUCKETS - 1) / range : 0.f;
+        // No range, or none that floats can divide: one bucket.  Codes of small coordinates have small ranges (2047 divided
+        // by the least one here is 0.6 of the largest float).
+        const float range = high - low;
+        scale = (range > 1e-35f && range < INFINITY) ? (float)(BUCKETS - 1) / range : 0.f;
 #pragma unroll
         for (int e = 0; e < NP; ++e)
             if ((mask >> e) & 1u) {

@@ -38,6 +38,17 @@ def test_clustered_codes(oracle_mod, lantern_gpu, V, d, k, size, spread, dtype, 
     np.testing.assert_array_equal(got, want)
 
 
+@pytest.mark.parametrize("V,d,k,dtype,scale", [(8192, 8, 1000, torch.float32, 2.0 ** -52), (8200, 8, 900, torch.bfloat16, 2.0 ** -54),
+                                               (12288, 16, 600, torch.float32, 2.0 ** -54), (8192, 8, 1000, torch.float32, 2.0 ** 55)])
+def test_small_and_large_codes(oracle_mod, lantern_gpu, V, d, k, dtype, scale):
+    """Distances of 1e-30 and less, or 1e33, are as good as any other: no row is left to the all-pairs pass."""
+    cb = (torch.randn(V, d, generator=torch.Generator().manual_seed(V + k)) * scale).to(dtype)
+    got = _table(lantern_gpu, cb, k, "l2", 0)
+    rows = (0, V) if V < 10000 else (V - 2500, V)
+    want = oracle_mod.build_knn(cb.float().numpy(), k, rows=rows, threads=16)
+    np.testing.assert_array_equal(got[rows[0]:rows[1]], want)
+
+
 @pytest.mark.parametrize("k", [70, 1000])
 def test_more_equal_codes_than_the_selection_holds(oracle_mod, lantern_gpu, k):
     rng = np.random.default_rng(k)
