@@ -94,10 +94,10 @@ typedef enum {
  * the arguments are invalid.  The workspace holds, for a block of query rows,
  * either candidate lists (and, for V of about 17000 and more, the rows'
  * approximate distances to a sample of the codebook), or their approximate
- * distances to every token (which of the two depends on the shape and type of
- * the codebook and on k alone); its contents are scratch.  Sized for few,
- * large launches: up to about 850 MiB (V = 65536, d = 64, k = 1000), 209 MiB
- * for V = 16384, d = 8, k = 1000.
+ * distances to every token (which of the two depends on the shape, type and
+ * alignment of the codebook and on k alone); its contents are scratch.  Sized
+ * for few, large launches: up to about 850 MiB (V = 65536, d = 64, k = 1000),
+ * 528 MiB for V = 16384, whose lists take 209 MiB of it at d = 8, k = 1000.
  */
 size_t lantern_build_knn_workspace_bytes(lantern_dtype cb_dtype, int V, int d, int k);
 

@@ -119,12 +119,16 @@ static KnnLayout knn_layout_within(int V, int d, int cb_dtype, const FilterPlan&
 
 static const FilterPlan NO_FILTER = {false, false, false, 0, 0, 0, 0};
 
-// What lantern_build_knn asks of its caller: the layout of the path the shape takes.  A codebook
-// that turns out not to be 16-byte aligned falls back to whole key blocks of as many rows as
-// this size holds.
+// What lantern_build_knn asks of its caller: the layout of the path the shape takes, and where that one filters at least
+// that of whole key blocks: a codebook that turns out not to be 16-byte aligned falls back to those,
+// and fewer rows to a pass leave part of the device idle in its selection (the size of the lists alone / this one:
+// V = 16384 bf16, k = 100, 960 / 8192 rows 2594 / 2357 us; V = 33000, k = 230, 2900 / 3968 rows 21.9 / 19.6 ms).
 size_t knn_workspace_bytes(int V, int d, int k, int cb_dtype) {
     const FilterPlan plan = filter_plan(V, d, k, cb_dtype);
-    return knn_layout(V, d, cb_dtype, plan, plan.use ? FILTER_ROW_BLOCK : whole_row_block(V), SLOW_WGS).total;
+    const size_t whole = knn_layout(V, d, cb_dtype, NO_FILTER, whole_row_block(V), SLOW_WGS).total;
+    if (!plan.use) return whole;
+    const size_t lists = knn_layout(V, d, cb_dtype, plan, FILTER_ROW_BLOCK, SLOW_WGS).total;
+    return lists > whole ? lists : whole;
 }
 
 // ---- scratch of the entry point that allocates nothing ----
@@ -2028,14 +2032,12 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
 }
 
 hipError_t launch_build_knn(const KnnArgs& a, hipStream_t stream) {
-    // The workspace has the size of the shape's own layout.  A codebook that is not 16-byte aligned
-    // cannot take the filtering path: it gets whole key blocks of as many rows as that size holds.
-    FilterPlan plan = filter_plan(a.V, a.d, a.k, a.cb_dtype);
+    // A codebook that is not 16-byte aligned cannot take the filtering path: it gets whole key blocks, for which
+    // the workspace has room as well.
+    const FilterPlan plan = filter_plan(a.V, a.d, a.k, a.cb_dtype);
     KnnLayout L = knn_layout(a.V, a.d, a.cb_dtype, plan, plan.use ? FILTER_ROW_BLOCK : whole_row_block(a.V), SLOW_WGS);
-    if (plan.use && (reinterpret_cast<uintptr_t>(a.codebook) & 15) != 0) {
-        L = knn_layout_within(a.V, a.d, a.cb_dtype, NO_FILTER, SLOW_WGS, L.total);
-        if (L.row_block == 0) return hipErrorInvalidValue;
-    }
+    if (plan.use && (reinterpret_cast<uintptr_t>(a.codebook) & 15) != 0)
+        L = knn_layout(a.V, a.d, a.cb_dtype, NO_FILTER, whole_row_block(a.V), SLOW_WGS);
     if (a.cb_dtype == 0) return build_typed<float>(a, L, stream);
     return build_typed<uint16_t>(a, L, stream);
 }

@@ -246,3 +246,13 @@ def test_sequential_tree_argument_errors(lib):
     assert call(ws=ctypes.c_void_p(4096 + 64)) == B_.E_WORKSPACE
     assert call(ws_bytes=2 * 2 * 16 * 8 + 255) == B_.E_WORKSPACE
     assert call(B=0, tl=nul, dl=nul, ws=nul, ws_bytes=0) == B_.OK   # nothing to do
+
+
+@pytest.mark.parametrize("V,d,k", [(4096, 8, 100), (8192, 8, 1000), (16384, 8, 100), (16384, 8, 1000), (33000, 16, 230), (65536, 64, 1000)])
+def test_knn_workspace_has_room_for_an_unaligned_codebook(lib, V, d, k):
+    """Codebooks that the candidate lists cannot take go through whole key blocks, the passes as few as for a shape that always
+    does: blocks of 8192 rows, or of 512 MiB."""
+    import paper_2410_03355_amd as L
+    rows = min(V, 8192, (512 << 20) // (4 * V) // 128 * 128)
+    for dtype in (L.F32, L.BF16):
+        assert lib.lantern_build_knn_workspace_bytes(dtype, V, d, k) >= 4 * V * rows
