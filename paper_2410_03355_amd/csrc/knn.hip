@@ -735,6 +735,7 @@ struct FilterShared {
 // slots in its list with one atomic add per row, and stages the hits in LDS row by row, from where they are written
 // out as runs (left to the lanes that found them, the writes were as many requests as hits, 26 million for
 // V = 16384, k = 1000, and each hit cost a dozen instructions for its key and address).
+// The reservation is on its way while the hits are staged (V = 40000, d = 64 bf16, k = 100: 1449 -> 1417 us the build).
 // Grid: one-dimensional, 8 * ceil(row tiles / 8) * column tiles workgroups, dealt so that all
 // column tiles of a row strip run on one XCD (workgroups go to the eight XCDs in turn) and a
 // row's list and counter stay in that XCD's L2.
@@ -744,6 +745,7 @@ struct FilterShared {
 // V = 16384, d = 8 fp32, k = 1000: 193 us with hits written by the lanes that found them, 189 staged with their keys,
 // 126 staged as tokens, 108 with 512 tokens to a tile and masks of shifted-in signs.  V = 8192, d = 256 bf16,
 // k = 100 (keys kept; bound by the operand loads): 78 -> 73.
+typedef uint32_t tokens4 __attribute__((ext_vector_type(4), aligned(4)));
 template <typename CT, int METRIC, int FORM, int TT>
 __global__ __launch_bounds__(NT, 4) void knn_filter_list(const uint4* packed, const float* fold, const float* norms, int V,
                                                          int steps, int r0, int rows, const int* doubt, FilterOut f) {
@@ -844,16 +846,15 @@ __global__ __launch_bounds__(NT, 4) void knn_filter_list(const uint4* packed, co
         if (mine[b]) atomicAdd(&sh.next[l_base + b * 32 + (lane & 31)], mine[b]);
     }
     __syncthreads();
+    int2 base = make_int2(0, 0);       // first wavefront: slots of two rows a lane, on their way while the hits are staged
     if (wave == 0) {                   // places of the rows' hits, and their slots in the lists; two rows a lane
         const int2 n = *reinterpret_cast<const int2*>(&sh.next[2 * lane]);   // above 0 only for rows of the block
-        int2 base = make_int2(0, 0);
         if (n.x > 0) base.x = atomicAdd(f.counts + il_wg + 2 * lane, n.x);
         if (n.y > 0) base.y = atomicAdd(f.counts + il_wg + 2 * lane + 1, n.y);
         const int incl = wave_scan_i<OpSum>(n.x + n.y, 0);
         const int2 at = make_int2(incl - n.x - n.y, incl - n.y);
         *reinterpret_cast<int2*>(&sh.start[2 * lane]) = at;
         *reinterpret_cast<int2*>(&sh.next[2 * lane]) = at;
-        *reinterpret_cast<int2*>(&sh.base[2 * lane]) = base;
         if (lane == WAVE - 1) sh.total = incl;
     }
     __syncthreads();
@@ -862,7 +863,39 @@ __global__ __launch_bounds__(NT, 4) void knn_filter_list(const uint4* packed, co
 #pragma unroll
     for (int b = 0; b < 2; ++b)
         if (mine[b]) place[b] = atomicAdd(&sh.next[l_base + b * 32 + (lane & 31)], mine[b]);
-    for (int from = 0; from < total; from += STAGE) {   // once, unless more than STAGE of the tile's pairs are kept
+    if (FORM == LIST_TOKENS && total > STAGE) {
+        // A dense tile (codes of one cluster next to each other in the codebook; uniform): every hit is placed by the lane
+        // that holds it, four to a write.  Staged in rounds, such tiles are what the launch waits for: V = 8192, 512 codes
+        // to a cluster, k = 100, 146 us against 30 (50 with a write for each hit), and 27 without clusters in order.
+        if (wave == 0) *reinterpret_cast<int2*>(&sh.base[2 * lane]) = base;
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int row = l_base + b * 32 + (lane & 31);
+            int slot = sh.base[row] + place[b] - sh.start[row];
+            uint32_t* lrow = static_cast<uint32_t*>(f.cand) + (int64_t)(il_wg + row) * f.cap;
+#pragma unroll
+            for (int c = 0; c < TT; ++c) {
+                uint32_t h = hits[c][b];
+                const uint32_t j0 = (uint32_t)(tj * (128 * TT) + c * 128 + (wave & 1) * 64 + 4 * (lane >> 5));
+                auto next_token = [&]() -> uint32_t {
+                    const int i = __clz((int)h);
+                    h &= ~(0x80000000u >> i);
+                    return j0 + i + (i & 28);
+                };
+                for (int n = __popc(h); n >= 4 && slot + 4 <= f.cap; n -= 4, slot += 4) {
+                    const uint32_t t0 = next_token(), t1 = next_token(), t2 = next_token(), t3 = next_token();
+                    *reinterpret_cast<tokens4*>(lrow + slot) = tokens4{t0, t1, t2, t3};
+                }
+                for (; h; ++slot) {
+                    const uint32_t j = next_token();
+                    if (slot < f.cap) lrow[slot] = j;
+                }
+            }
+        }
+        return;
+    }
+    for (int from = 0; from < total; from += STAGE) {   // once, unless more than STAGE pairs with keys are kept
         if (from) __syncthreads();
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -871,6 +904,11 @@ __global__ __launch_bounds__(NT, 4) void knn_filter_list(const uint4* packed, co
             for (int c = 0; c < TT; ++c) {
                 uint32_t h = hits[c][b];
                 const int mark = (l_base + b * 32 + (lane & 31)) * 512 + c * 128 + (wave & 1) * 64 + 4 * (lane >> 5);
+                const int n = __popc(h);
+                if (at >= STAGE || at + n <= 0) {   // none of these in this round
+                    at += n;
+                    continue;
+                }
                 if (FORM == LIST_TOKENS) {
                     while (h) {
                         const int i = __clz((int)h);
@@ -893,19 +931,27 @@ __global__ __launch_bounds__(NT, 4) void knn_filter_list(const uint4* packed, co
                 }
             }
         }
+        if (wave == 0 && from == 0) *reinterpret_cast<int2*>(&sh.base[2 * lane]) = base;
         __syncthreads();
-        for (int e = tid; e < min(total - from, STAGE); e += NT) {
-            const int s = sh.stage[e];
-            const int row = s >> 9;
-            const int slot = sh.base[row] + (from + e - sh.start[row]);
-            const uint32_t j = (uint32_t)(tj * (128 * TT) + (s & 511));
-            if (slot < f.cap) {
-                const int64_t at = (int64_t)(il_wg + row) * f.cap + slot;
-                if (FORM == LIST_TOKENS) {
-                    static_cast<uint32_t*>(f.cand)[at] = j;
-                } else {
-                    const float key = key_of_value<METRIC>(sh.value[e], sh.norm[row]);
-                    static_cast<uint2*>(f.cand)[at] = make_uint2(min(ord_key(key), 0xFFFFFFFEu), j);
+        const int staged = min(total - from, STAGE);
+        constexpr int BATCH = FORM == LIST_TOKENS ? 4 : 1;   // hits of a thread whose places are looked up together
+        for (int e0 = tid; e0 < staged; e0 += BATCH * NT) {
+            int hit[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) hit[u] = sh.stage[min(e0 + u * NT, staged - 1)];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int e = e0 + u * NT, row = hit[u] >> 9;
+                const int slot = sh.base[row] + (from + e - sh.start[row]);
+                const uint32_t j = (uint32_t)(tj * (128 * TT) + (hit[u] & 511));
+                if (e < staged && slot < f.cap) {
+                    const int64_t at = (int64_t)(il_wg + row) * f.cap + slot;
+                    if (FORM == LIST_TOKENS) {
+                        static_cast<uint32_t*>(f.cand)[at] = j;
+                    } else {
+                        const float key = key_of_value<METRIC>(sh.value[e], sh.norm[row]);
+                        static_cast<uint2*>(f.cand)[at] = make_uint2(min(ord_key(key), 0xFFFFFFFEu), j);
+                    }
                 }
             }
         }

@@ -6,6 +6,8 @@ import numpy as np
 import pytest
 import torch
 
+from parity_utils import replay_us
+
 pytestmark = pytest.mark.gpu
 
 
@@ -56,6 +58,28 @@ def test_more_equal_codes_than_the_selection_holds(oracle_mod, lantern_gpu, k):
     cb[rng.permutation(8192)[:1200]] = cb[17]
     got = _table(lantern_gpu, torch.from_numpy(cb), k, "l2", 8192)
     np.testing.assert_array_equal(got, oracle_mod.build_knn(cb, k, threads=16))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_longer_lists_than_their_room(oracle_mod, lantern_gpu, dtype):
+    """6000 equal codes in a row of the codebook: every pair of a tile is a hit, and lists end inside a run of them."""
+    cb = torch.randn(8192, 8, generator=torch.Generator().manual_seed(9))
+    cb[1000:7000] = cb[1000]
+    cb = cb.to(dtype)
+    got = _table(lantern_gpu, cb, 70, "l2", 8192)
+    np.testing.assert_array_equal(got, oracle_mod.build_knn(cb.float().numpy(), 70, threads=16))
+
+
+@pytest.mark.parametrize("V,d,size,k,dtype", [(8192, 8, 512, 100, torch.float32), (10304, 8, 400, 380, torch.bfloat16)])
+def test_clusters_in_order_cost_no_more(lantern_gpu, V, d, size, k, dtype):
+    """The same codes with those of a cluster next to each other, and in no order: 116 / 119 and 181 / 181 us (231 / 111
+    and 276 / 175 where the tiles of a cluster were what the launch waited for)."""
+    cb = torch.from_numpy(_clusters(V, d, size, 0.1, 3)).to(dtype).cuda()
+    mixed = cb[torch.randperm(V, generator=torch.Generator().manual_seed(1)).cuda()].contiguous()
+    work = torch.empty(lantern_gpu.binding.knn_workspace_bytes(1 if dtype == torch.bfloat16 else 0, V, d, k), dtype=torch.uint8, device="cuda")
+    out = torch.empty((V, k), dtype=torch.int32, device="cuda")
+    ordered_us, mixed_us = replay_us(*(lambda c=c: lantern_gpu.build_knn(c, k, workspace=work, out=out) for c in (cb, mixed)))
+    assert ordered_us < 1.3 * mixed_us
 
 
 @pytest.mark.parametrize("metric", ["l2", "cosine"])
