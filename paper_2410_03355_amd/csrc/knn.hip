@@ -1368,16 +1368,21 @@ __device__ __forceinline__ void for_keys(int npt, F body) {
 // the list has an approximate key above every key on it, so the proof below reads the same.  A
 // list that was cut at its capacity, is longer than the registers hold (the proof takes every listed
 // token for seen), or is shorter than the selection wants, flags the row.
-template <typename CT, int NK, int CAP, int TNT, bool LIST>
+//
+// VECS false: the codes are no whole vectors at aligned addresses (vecs is 0).  A kernel of its own for the smallest vocabularies
+// only, whose selection is a few microseconds: V = 1024, d = 9, k = 700 36.6 us the build with both forms of the
+// exact keys in one kernel, 34.7 without; from V = 2000 on there is no difference.
+template <typename CT, int NK, int CAP, int TNT, bool LIST, bool VECS>
 __global__ __launch_bounds__(TNT, NK >= 64 ? 4 : !LIST ? 8 : NK == 32 ? 5 : (CAP > 256 || NK == 24) ? 6 : 8) void knn_select(const CT* cb, int V, int d, int k, int metric, int r0,
                                                  const float* dist, FilterOut list, float err_rel, float err_abs,
                                                  float err_norm, const float* norms, const float* nmax,
-                                                 const int* doubt, int32_t* out, int* flags, int vecs) {
+                                                 const int* doubt, int32_t* out, int* flags, int vecs_or_0) {
     static_assert(!LIST || NK > 0, "a candidate list is held in registers");
     constexpr int TNW = TNT / WAVE;
     using Shared = SelectShared<CAP, TNT>;
     __shared__ Shared sh;
     extern __shared__ __align__(16) double own[];   // vecs > 0: the row's own code
+    const int vecs = VECS ? vecs_or_0 : 0;
     const int row = blockIdx.x;
     const int i = r0 + row;
     const int tid = threadIdx.x;
@@ -2005,11 +2010,17 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
         // of workgroups a compute unit holds at once, and that number is set by this LDS footprint
         // (12 bytes a slot).
         const int want_slots = (a.k - 1) + 8 + (a.k - 1) / 128;
-#define LANTERN_LAUNCH_SELECT(NKV, CAPV, TNTV, LISTV)                                                       \
-        hipLaunchKernelGGL((knn_select<CT, NKV, CAPV, TNTV, LISTV>), dim3(rows), dim3(TNTV),                \
+#define LANTERN_LAUNCH_SELECT_VECS(NKV, CAPV, TNTV, LISTV, VECSV)                                           \
+        hipLaunchKernelGGL((knn_select<CT, NKV, CAPV, TNTV, LISTV, VECSV>), dim3(rows), dim3(TNTV),         \
                            (CAPV) <= 1024 ? own_code_bytes(a.d, key_vecs) : 0, stream, cb,          \
                            a.V, a.d, a.k, a.metric, r0, dist, LISTV ? fo : no_list, err_rel, err_abs,       \
                            err_norm, nsel, nmax, doubt, a.out, flags + r0, (CAPV) <= 1024 ? key_vecs : 0)
+#define LANTERN_LAUNCH_SELECT(NKV, CAPV, TNTV, LISTV)                                                       \
+        do {                                                                                                \
+            constexpr bool OWN = !LISTV && NKV == 8 && CAPV <= 1024;                                        \
+            if (OWN && key_vecs == 0) LANTERN_LAUNCH_SELECT_VECS(NKV, CAPV, TNTV, LISTV, !OWN);             \
+            else LANTERN_LAUNCH_SELECT_VECS(NKV, CAPV, TNTV, LISTV, true);                                  \
+        } while (0)
         if (plan.use) {
             // thresholds from the sample, then the contraction that keeps what lies below them
             thresholds(r0, rows);
@@ -2067,6 +2078,7 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
 #undef LANTERN_LAUNCH_SELECT_NK
         }
 #undef LANTERN_LAUNCH_SELECT
+#undef LANTERN_LAUNCH_SELECT_VECS
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

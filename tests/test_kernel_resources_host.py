@@ -74,6 +74,15 @@ def test_smallest_full_rows_leave_room_for_five_wavefronts(kernels):
     assert kernels[name][0] == 0 and kernels[name][2] <= 96
 
 
+def test_selection_of_small_tables_by_elements(kernels):
+    """The selection from whole rows of up to 2048 keys whose codes are read element by element (last template argument)
+    holds nothing of the vectors' way: fewer registers, no scratch."""
+    for code in "ft":
+        for slots, most in ((256, 48), (1024, 62)):
+            name, = [n for n in kernels if re.search(rf"knn_selectI{code}Li8ELi{slots}ELi256ELb0ELb0EE", n)]
+            assert kernels[name][0] == 0 and kernels[name][2] <= most, name
+
+
 def test_rows_arrive_without_scratch_memory(objects):
     """Until a row is in LDS (the first barrier) no kernel of the fp32 pass touches scratch memory."""
     seen = 0
