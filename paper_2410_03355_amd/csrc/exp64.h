@@ -162,8 +162,9 @@ LANTERN_HD double exp_tab_core(double d, const unsigned char* tab_bytes) {
 //   remainder goes in with the polynomial, and its hi comes without the j 2^44 that (m - K) 2^44 puts back with the
 //   exponent: one addition to the high word, and the value is one fused multiply-add.
 // Error: half an ulp of that last step and below 0.05 ulp of the rest, for |l| <= 5000 and results in the normal
-// range; the caller clamps.  start: EXP_UNITS_START - K.  tab_bytes: the table, on the device at offset 0 of
-// the workgroup's LDS (the lookup's address is then two instructions, with no base to add).
+// range; the caller clamps.  start: EXP_UNITS_START - K.  tab_bytes: the table, 16-byte aligned; on the device an object
+// of its own in LDS, whose place is known when the kernel is compiled: the lookup's address is then two instructions and
+// a constant of the load, with no base to add.
 constexpr double EXP_UNITS_START = 6755399441055744.0;       // 1.5 * 2^52
 constexpr double EXP_UNITS_INV = 0x1.71547652b82fep+8;       // 256 / ln 2
 constexpr double EXP_UNITS_HI = 0x1.62e42ff000000p-9;        // ln2/256 to 32 bits: exact times |m| < 2^21
@@ -182,15 +183,15 @@ LANTERN_HD ExpUnits exp_units_parts(double l, double start, const unsigned char*
     double r = __builtin_fma(-m, EXP_UNITS_HI, l);
     r = __builtin_fma(-m, EXP_UNITS_LO, r);
     double rest;
+    const unsigned char* at = tab_bytes + ((u.mi << 4) & 0xFF0u);
 #if defined(__HIP_DEVICE_COMPILE__)
-    (void)tab_bytes;
     typedef double pair_t __attribute__((ext_vector_type(2)));
-    const pair_t entry = *(const __attribute__((address_space(3))) pair_t*)((u.mi << 4) & 0xFF0u);
+    const pair_t entry = *reinterpret_cast<const pair_t*>(at);      // one 16-byte load: the table is aligned
     u.hi = entry.x;
     rest = entry.y;
 #else
-    __builtin_memcpy(&u.hi, tab_bytes + ((u.mi << 4) & 0xFF0u), 8);
-    __builtin_memcpy(&rest, tab_bytes + ((u.mi << 4) & 0xFF0u) + 8, 8);
+    __builtin_memcpy(&u.hi, at, 8);
+    __builtin_memcpy(&rest, at + 8, 8);
 #endif
     double q = __builtin_fma(r, 4.1666666666666664354e-02, 0.16666667995547);   // 1/24, 1/6 + 1.33e-8
     q = __builtin_fma(q, r, 0.5);

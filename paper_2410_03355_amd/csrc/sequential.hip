@@ -90,7 +90,7 @@ __device__ __noinline__ bool jsd_fails(double t_tok, double moved, double delta)
 typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
 
 struct SeqShared {
-    uint64_t tab[2 * EXP_FINE_N];    // at the start of the workgroup's LDS: exp_units reads it there
+    alignas(16) uint64_t tab[2 * EXP_FINE_N];
     double sum_a[SNW], sum_b[SNW];   // softmax sums, then the walk's totals and sums before its cut
     double wr[SNW], wt[SNW];         // residual mass and distorted target's mass of every wavefront's part
     float mt[SNW], mg[SNW];

@@ -100,9 +100,8 @@ struct AmbEntry {
 struct OnePassLayout {
     size_t seg, keep, amb_count, amb, total;
 };
-// The exponential's table sits at the very start of the workgroup's LDS (before the row): the
-// address of a lookup is then the masked integer itself, with no base to add.  The general path, which
-// comes after this one or instead of it, keeps its own (smaller) table there.
+// The exponential's table is an LDS object of its own beside the dynamic part.  The general path, which comes after this
+// one or instead of it, keeps its own (smaller) table there.
 constexpr int EXP_TABLE_BYTES = 2 * EXP_TABLE_N * (int)sizeof(double);
 constexpr int EXP_FINE_BYTES = 2 * EXP_FINE_N * (int)sizeof(double);
 __host__ __device__ inline OnePassLayout one_pass_layout(int segments) {
@@ -228,7 +227,7 @@ __device__ __forceinline__ void wave_pair_sums(const double (&v)[2 * N], int lan
 // s_row: raw target row in LDS.
 // nb: table slots 4*tid .. 4*tid+3.  ref_t, ref_g: the fp32 pass's reference logits; Zt32, Zg32:
 // its sums; a_size: its (definite) cut.
-// tab_lds: the start of the workgroup's LDS, where the exponential's table goes.
+// tab_lds: where the exponential's table goes.
 // Returns false (the same in every thread) when the row is left to the general path.
 template <typename LT, int TNT, int NV, int ROWS>
 __device__ __forceinline__ bool exact_one_pass(const VerifyArgs& a, int row, int lrow,
@@ -599,8 +598,9 @@ __global__ __launch_bounds__(TNT, NV > 8 ? 3 : 4) void verify_fast(VerifyArgs a)
     constexpr bool FULL = ROWS == ROWS_FULL;
     constexpr int EPV = L::EPV;
     constexpr int TNW = TNT / WAVE;
-    extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char* s_row = smem + EXP_FINE_BYTES;            // the fp64 paths' table goes in front
+    // The fp64 paths' table: its place is known when the kernel is compiled, so a lookup has no base to add.
+    __shared__ __align__(16) unsigned char table[EXP_FINE_BYTES];
+    extern __shared__ __align__(16) unsigned char s_row[];
     const int row_bytes = (a.V * (int)sizeof(LT) + 15) & ~15;
     FastShared<TNW>& sh = *reinterpret_cast<FastShared<TNW>*>(s_row + row_bytes);
     unsigned char* ex_lds = s_row + row_bytes + sizeof(FastShared<TNW>);
@@ -817,9 +817,9 @@ __global__ __launch_bounds__(TNT, NV > 8 ? 3 : 4) void verify_fast(VerifyArgs a)
             bool done = false;
             if (!bad && sums_ok && cut_definite && a.mode == VERIFY_FULL)
                 done = exact_one_pass<LT, TNT, NV, ROWS>(a, row, lrow, m.nb, rt, rg, Zt, Zg, a_size, xt, m.lg_tok,
-                                                         m.u_acc, smem, ex_lds, s_row);
+                                                         m.u_acc, table, ex_lds, s_row);
             // one call, so that it is inlined: as a function its argument block goes through memory
-            if (!done) exact_row<LT, ROWS == ROWS_ANY ? ROW_ANY : ROW_WHOLE, TNT>(a, row, ex_lds, s_row, false, 0.f, 0.f, nullptr, smem);
+            if (!done) exact_row<LT, ROWS == ROWS_ANY ? ROW_ANY : ROW_WHOLE, TNT>(a, row, ex_lds, s_row, false, 0.f, 0.f, nullptr, table);
         }
     }
 }
@@ -1197,14 +1197,14 @@ __global__ __launch_bounds__(SEL_NT) void tree_finish(VerifyArgs a, const int32_
 // host-side launch
 // ---------------------------------------------------------------------------
 
-// Dynamic LDS of verify_fast: raw row, reductions, then the exact paths' region.
+// Dynamic LDS of verify_fast: raw row, reductions, then the exact paths' region.  (Beside it: EXP_FINE_BYTES of the table.)
 template <typename LT>
 static size_t fast_lds_bytes(int V, int threads, int nv) {
     const size_t row_bytes = ((size_t)V * sizeof(LT) + 15) & ~size_t(15);
     const size_t head = threads == 256 ? sizeof(FastShared<4>) : threads == 512 ? sizeof(FastShared<8>) : sizeof(FastShared<16>);
     const size_t one_pass = one_pass_layout(nv * (threads / WAVE)).total;
     const size_t exact = exact_table_offset(V, threads);
-    return EXP_FINE_BYTES + row_bytes + head + (one_pass > exact ? one_pass : exact);
+    return row_bytes + head + (one_pass > exact ? one_pass : exact);
 }
 
 // Rows of 16-byte aligned whole vectors, stride included.
@@ -1263,7 +1263,7 @@ constexpr size_t LDS_OF_A_UNIT = 160 * 1024;
 template <typename LT>
 static bool fewer_threads(const VerifyArgs& a) {
     if (!whole_vectors<LT>(a)) return false;
-    const bool three = 3 * fast_lds_bytes<LT>(a.V, NT, 16) <= LDS_OF_A_UNIT;
+    const bool three = 3 * (fast_lds_bytes<LT>(a.V, NT, 16) + EXP_FINE_BYTES) <= LDS_OF_A_UNIT;
     if (a.mode == VERIFY_DECIDE) return three || (a.V == 16 * NT * Lane<LT>::EPV && vector_table(a));
     return three && a.N > 2 * COMPUTE_UNITS;
 }

@@ -45,15 +45,17 @@ def objects(tmp_path_factory):
 
 @pytest.fixture(scope="module")
 def kernels(objects):
-    """{mangled name: (bytes of scratch per lane, spilled vector registers, vector registers)}"""
+    """{mangled name: (bytes of scratch per lane, spilled vector registers, vector registers, bytes of LDS fixed at
+    compile time)}"""
     found = {}
     for path in objects:
         notes = subprocess.run([READELF, "--notes", str(path)], check=True, capture_output=True, text=True).stdout
         for part in notes.split("- .agpr_count")[1:]:
             value = {key: re.search(r"\." + key + r":\s+(\S+)", part).group(1)
-                     for key in ("name", "private_segment_fixed_size", "vgpr_spill_count", "vgpr_count")}
+                     for key in ("name", "private_segment_fixed_size", "vgpr_spill_count", "vgpr_count",
+                                 "group_segment_fixed_size")}
             found[value["name"]] = (int(value["private_segment_fixed_size"]), int(value["vgpr_spill_count"]),
-                                    int(value["vgpr_count"]))
+                                    int(value["vgpr_count"]), int(value["group_segment_fixed_size"]))
     assert len(found) > 50
     return found
 
@@ -62,7 +64,7 @@ def test_sequential_walk_keeps_out_of_scratch(kernels):
     """The walk under total variation (template arguments: logit type, steps, plain rule, divergence)."""
     walks = {name: r for name, r in kernels.items() if re.search(r"trees_sequentialI[ft]Li\d+ELb0ELb0EE", name)}
     assert len(walks) == 8
-    for name, (scratch, spilled, _) in walks.items():
+    for name, (scratch, spilled, *_) in walks.items():
         steps = int(re.search(r"Li(\d+)E", name).group(1))
         assert (scratch, spilled) <= ((8, 1) if steps == 10 else (0, 0)), name
 
@@ -94,3 +96,13 @@ def test_rows_arrive_without_scratch_memory(objects):
             assert "global_load_dwordx4" in arriving and "scratch_" not in arriving, name
             seen += 1
     assert seen == 42
+
+
+def test_exponential_tables_are_objects_of_their_own(kernels):
+    """The 4 KiB table of the fp64 exponential has a place in LDS that the compiler gives it and knows, wherever that is: no
+    lookup goes to an absolute address."""
+    assert all(r[3] >= 4096 for n, r in kernels.items() if re.search("verify_fast|trees_sequential", n))
+    csrc = os.path.join(os.path.dirname(lantern.LIB_PATH), "csrc")
+    for name in os.listdir(csrc):
+        with open(os.path.join(csrc, name)) as f:
+            assert "address_space(3)" not in f.read(), name
