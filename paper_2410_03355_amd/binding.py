@@ -7,7 +7,8 @@ the library is missing, load() raises.
 The calls of a decoding step first go to their namesakes in _marshal.so, which
 take plain device tensors and nothing of the caller's (stream, outputs) without
 the interpreter in between; whatever those decline takes the way through ctypes
-below, which words the errors.
+below, which words the errors.  Without a _marshal.so for this PyTorch every call
+takes that way: the same kernels and results, later launches.
 """
 from __future__ import annotations
 
@@ -15,10 +16,11 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch
 
-from .build import LIB_PATH, MARSHAL_PATH
+from .build import LIB_PATH, MARSHAL_PATH, marshal_built_for
 
 F32, BF16 = 0, 1
 METRIC_L2, METRIC_COSINE = 0, 1
@@ -53,11 +55,10 @@ def load() -> ctypes.CDLL:
     global _lib, _marshal
     if _lib is not None:
         return _lib
-    for path in (LIB_PATH, MARSHAL_PATH):
-        if not os.path.exists(path):
-            raise FileNotFoundError(
-                f"{path} not found: build it with `python -m paper_2410_03355_amd.build` "
-                "(there is no fallback implementation)")
+    if not os.path.exists(LIB_PATH):
+        raise FileNotFoundError(
+            f"{LIB_PATH} not found: build it with `python -m paper_2410_03355_amd.build` "
+            "(there is no fallback implementation)")
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, f32, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
     lib.lantern_build_knn_workspace_bytes.argtypes = [i32, i32, i32, i32]
@@ -112,12 +113,30 @@ def load() -> ctypes.CDLL:
     lib.lantern_status_string.restype = ctypes.c_char_p
     lib.lantern_version.argtypes = []
     lib.lantern_version.restype = i32
-    loader = importlib.machinery.ExtensionFileLoader("_marshal", MARSHAL_PATH)
-    marshal = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
-    marshal.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS})
-    _marshal = marshal
+    _marshal = _load_marshal(lib)
     _lib = lib
     return lib
+
+
+class _Declines:
+    """In the place of _marshal.so: every call goes through ctypes."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_marshal(lib):
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", MARSHAL_PATH)
+        marshal = importlib.util.module_from_spec(importlib.util.spec_from_loader("_marshal", loader))
+        if marshal.BUILT_FOR != marshal_built_for():     # PyTorch's C++ interface differs between its versions
+            raise ImportError(f"built for {marshal.BUILT_FOR}, this is {marshal_built_for()}")
+    except ImportError as e:
+        warnings.warn(f"{MARSHAL_PATH} is not used ({e}): step calls take some microseconds longer on the host until it is "
+                      "built with `python -m paper_2410_03355_amd.build`", RuntimeWarning, stacklevel=3)
+        return _Declines()
+    marshal.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS})
+    return marshal
 
 
 def _checked_status(got, where: str):

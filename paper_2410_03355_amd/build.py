@@ -8,7 +8,9 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sys
 import sysconfig
+import warnings
 
 import torch
 
@@ -37,13 +39,18 @@ def hipcc_path() -> str:
     return "hipcc"
 
 
+def marshal_built_for() -> str:
+    """What _marshal.so depends on: it is taken by the same PyTorch and Python alone."""
+    return "PyTorch %s, Python %d.%d" % (torch.__version__, *sys.version_info[:2])
+
+
 def marshal_command() -> list:
     """Host code against PyTorch's C++ interface: by the host compiler, whose names PyTorch's libraries carry."""
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path())))
     home = os.path.dirname(torch.__file__)
     abi = int(torch._C._GLIBCXX_USE_CXX11_ABI)
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-            f"-D_GLIBCXX_USE_CXX11_ABI={abi}", "-isystem", os.path.join(home, "include"),
+            f"-D_GLIBCXX_USE_CXX11_ABI={abi}", f'-DLANTERN_BUILT_FOR="{marshal_built_for()}"', "-isystem", os.path.join(home, "include"),
             "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
             "-I", os.path.join(_ROOT, "include"),
             os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH, "-L", os.path.join(home, "lib"),
@@ -51,7 +58,8 @@ def marshal_command() -> list:
 
 
 def build(verbose: bool = False) -> str:
-    """Compiles every source to an object (in parallel, in a scratch directory) and links the libraries."""
+    """Compiles every source to an object (in parallel, in a scratch directory) and links the libraries.  Where _marshal.so
+    cannot be built (it takes a host compiler and the headers of Python and PyTorch) there is none, and a warning."""
     import concurrent.futures
     import tempfile
 
@@ -69,7 +77,12 @@ def build(verbose: bool = False) -> str:
         def marshal() -> None:
             if verbose:
                 print(" ".join(marshal_command()), flush=True)
-            subprocess.run(marshal_command(), check=True)
+            if os.path.exists(MARSHAL_PATH):
+                os.remove(MARSHAL_PATH)
+            try:
+                subprocess.run(marshal_command(), check=True)
+            except (OSError, subprocess.CalledProcessError) as e:
+                warnings.warn(f"{MARSHAL_PATH} could not be built: {e}", RuntimeWarning)
 
         with concurrent.futures.ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, os.cpu_count() or 1, 8)) as pool:
             host = pool.submit(marshal)

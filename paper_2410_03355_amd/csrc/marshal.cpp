@@ -383,4 +383,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+// BUILT_FOR: the versions that these libraries' interfaces were compiled for (binding.py compares them).
+PyMODINIT_FUNC PyInit__marshal() {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "BUILT_FOR", LANTERN_BUILT_FOR) != 0) Py_CLEAR(m);
+    return m;
+}
