@@ -92,68 +92,8 @@ LANTERN_HD double exp_tab(double d, const double* tab) {
     return ldexp(res, n);
 }
 
-// exp_tab for d <= 0 (or -inf, result 0) with fewer instructions: no upper clamp, and the rounding to an
-// integer as in exp_tab_core; the scaling keeps results below the normal range.
-LANTERN_HD double exp_tab_nonpos(double d, const double* tab) {
-    const double INV_STEP = 184.6649652337873;
-    const double STEP_HI = 0x1.62e42fee00000p-8;
-    const double STEP_LO = 0x1.a39ef35793c76p-40;
-    const double MAGIC = 6755399441055744.0;               // 1.5 * 2^52
-#if defined(__HIP_DEVICE_COMPILE__)
-    double c;                                               // fmax would quiet its operands first
-    asm("v_max_f64 %0, %1, %2" : "=v"(c) : "v"(d), "s"(-1000.0));
-    d = c;
-#else
-    d = fmax(d, -1000.0);
-#endif
-    const double t = __builtin_fma(d, INV_STEP, MAGIC);
-    unsigned long long tb;
-    __builtin_memcpy(&tb, &t, 8);
-    const int mi = (int)(unsigned)tb;
-    const double m = t - MAGIC;
-    double r = __builtin_fma(-m, STEP_HI, d);
-    r = __builtin_fma(-m, STEP_LO, r);
-    const int j = mi & 127;
-    const double hi = tab[2 * j], lo = tab[2 * j + 1];
-    const double p = exp_poly5(r);
-    const double res = hi + __builtin_fma(hi, p, lo);
-    return ldexp(res, mi >> 7);
-}
-
-// exp_tab for arguments known to lie in [-700, 700], with fewer instructions: the rounding to an
-// integer is one fused multiply-add onto 1.5 * 2^52 (the integer then sits in the low word of
-// the sum), and the scaling by 2^n is an integer addition to the exponent field (the result
-// stays a normal number on this range).  Same reduction, table and polynomial as exp_tab: the
-// same value.  The caller clamps; outside the range the result is meaningless.
-// tab_bytes: the table as bytes (on the device an LDS address: placed at offset 0 of the
-// workgroup's LDS, the lookup's address is the masked integer itself).
-LANTERN_HD double exp_tab_core(double d, const unsigned char* tab_bytes) {
-    const double INV_STEP = 184.6649652337873;
-    const double STEP_HI = 0x1.62e42fee00000p-8;
-    const double STEP_LO = 0x1.a39ef35793c76p-40;
-    const double MAGIC = 6755399441055744.0;               // 1.5 * 2^52
-    const double t = __builtin_fma(d, INV_STEP, MAGIC);
-    unsigned long long tb;
-    __builtin_memcpy(&tb, &t, 8);
-    const unsigned mi = (unsigned)tb;                       // low word: the rounded integer, two's complement
-    const double m = t - MAGIC;
-    double r = __builtin_fma(-m, STEP_HI, d);
-    r = __builtin_fma(-m, STEP_LO, r);
-    const double* entry = reinterpret_cast<const double*>(tab_bytes + ((mi & 127u) << 4));
-    const double hi = entry[0], lo = entry[1];
-    const double p = exp_poly5(r);
-    const double res = hi + __builtin_fma(hi, p, lo);
-    unsigned long long rb;
-    __builtin_memcpy(&rb, &res, 8);
-    // n = mi >> 7 (arithmetic) into the exponent field: bits 52.. of the double, 20.. of its high word
-    const unsigned hi_word = (unsigned)(rb >> 32) + ((mi & ~127u) << 13);
-    rb = ((unsigned long long)hi_word << 32) | (unsigned)rb;
-    double out;
-    __builtin_memcpy(&out, &rb, 8);
-    return out;
-}
-
-// The form that the fp64 pass over a rejected row uses: 16 instructions a value.  Terms are counted in steps of
+// The form that the fp64 pass over a rejected row uses: 15 instructions a value, the clamp and the conversion of its logit
+// and the table's lookup among them.  Terms are counted in steps of
 // ln2/256 from a whole number of steps K common to the row: e^l 2^(-K/256), with the logit l taken as it is (no
 // subtraction of a reference: K only scales the terms).
 //   l = m ln2/256 + r with m = rint(l 256/ln2), |r| <= ln2/512: one fused multiply-add onto 1.5 2^52 - K leaves
@@ -161,8 +101,9 @@ LANTERN_HD double exp_tab_core(double d, const unsigned char* tab_bytes) {
 //   cover the fifth-order term (error below 6e-18); the table (EXP_FINE) holds 2^(j/256) as hi (1 + rest), so the
 //   remainder goes in with the polynomial, and its hi comes without the j 2^44 that (m - K) 2^44 puts back with the
 //   exponent: one addition to the high word, and the value is one fused multiply-add.
-// Error: half an ulp of that last step and below 0.05 ulp of the rest, for |l| <= 5000 and results in the normal
-// range; the caller clamps.  start: EXP_UNITS_START - K.  tab_bytes: the table, 16-byte aligned; on the device an object
+// Error: half an ulp of that last step and below 0.05 ulp of the rest, for |l| <= 5600 (|m| < 2^21) and results in the
+// normal range; the caller clamps: rows with a reference beyond 4096 in magnitude are not evaluated here, and no logit is
+// taken more than 1100 below it.  start: EXP_UNITS_START - K.  tab_bytes: the table, 16-byte aligned; on the device an object
 // of its own in LDS, whose place is known when the kernel is compiled: the lookup's address is then two instructions and
 // a constant of the load, with no base to add.
 constexpr double EXP_UNITS_START = 6755399441055744.0;       // 1.5 * 2^52

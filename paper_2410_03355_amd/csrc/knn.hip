@@ -1007,15 +1007,15 @@ __global__ __launch_bounds__(NT) void knn_pack(const CT* cb, const float* norms,
     }
 }
 
-// One wavefront per row: a value with between rank and rank + slack of the row's S <= 64 * NS keys
+// One wavefront per row: a value with between rank and rank + slack of the row's S <= 64 * NS = 4096 keys
 // to the sample at or below it (bisection over the integer range of the keys, each step one
 // count) becomes the row's threshold (as the value that the filtering contraction compares); the row's list length is
 // cleared.  For samples beyond what knn_thresholds holds.
 // (At most four wavefronts per SIMD are aimed at: with more as its goal the compiler's scheduler
-// keeps the register count down by waiting for each of the 64 loads of the largest variant in turn.)
-template <int NS>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, NS > 32 ? 4 : 8))) void knn_sample_rank(const float* skeys, int S, int rows, int rank, int slack,
+// keeps the register count down by waiting for each of the 64 loads in turn.)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 4))) void knn_sample_rank(const float* skeys, int S, int rows, int rank, int slack,
                                                       const float* norms, int r0, int metric, float* thr, int* counts) {
+    constexpr int NS = 64;
     const int lane = threadIdx.x & (WAVE - 1);
     const int row = blockIdx.x * NW + (threadIdx.x >> 6);
     if (row >= rows) return;   // whole wavefronts leave; no workgroup barrier below
@@ -1980,7 +1980,7 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
         if (plan.S > THRESHOLDS_MAX_S) {
             hipLaunchKernelGGL((knn_sample_keys<CT>), dim3((plan.S + 127) / 128, (rows + 127) / 128), dim3(NT), 0, stream,
                                packed, spacked, norms, snorms, a.V, plan.S, steps, r0, rows, a.metric, skeys);
-            hipLaunchKernelGGL((knn_sample_rank<64>), dim3((rows + NW - 1) / NW), dim3(NT), 0, stream, skeys, plan.S, rows,
+            hipLaunchKernelGGL(knn_sample_rank, dim3((rows + NW - 1) / NW), dim3(NT), 0, stream, skeys, plan.S, rows,
                                plan.rank, plan.slack, norms, r0, a.metric, least, fo.counts);
             return;
         }

@@ -126,10 +126,6 @@ struct Lane<float> {
         const uint32_t w = e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
         return __uint_as_float(w);
     }
-    // the vector without its first two elements (the freed places read -inf)
-    __device__ static __forceinline__ uint4 drop2(const uint4& v) {
-        return make_uint4(v.z, v.w, NEG_INF_WORD, NEG_INF_WORD);
-    }
     __device__ static __forceinline__ float lds(const unsigned char* row, int x) {
         return reinterpret_cast<const float*>(row)[x];
     }
@@ -149,9 +145,6 @@ struct Lane<uint16_t> {  // bfloat16 storage
         const int wi = e >> 1;
         const uint32_t w = wi == 0 ? v.x : wi == 1 ? v.y : wi == 2 ? v.z : v.w;
         return __uint_as_float((e & 1) ? (w & 0xFFFF0000u) : (w << 16));
-    }
-    __device__ static __forceinline__ uint4 drop2(const uint4& v) {
-        return make_uint4(v.y, v.z, v.w, NEG_INF_WORD);
     }
     __device__ static __forceinline__ float lds(const unsigned char* row, int x) {
         return __uint_as_float(static_cast<uint32_t>(reinterpret_cast<const uint16_t*>(row)[x]) << 16);
