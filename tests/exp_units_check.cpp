@@ -33,6 +33,23 @@ int main() {
     const bool ends = exp_units_any(0.0, start, tab) == 1.0 && exp_units_any(-1100.0, start, tab) == 0.0 &&
                       exp_units_any(-5000.0, EXP_UNITS_START + 1400000.0, tab) == 0.0 &&
                       std::fabs(exp_units_any(-720.0, start, tab) / std::exp(-720.0) - 1.0) < 1e-10;
+    // the form that may leave the normal range, down to 1100 below references of up to 4096 in magnitude
+    std::uniform_real_distribution<double> d_low(-1100.0, 45.0);
+    double worst_any = 0.0, worst_any_below = 0.0;
+    for (int i = 0; i < 400000; ++i) {
+        const float ref = (float)(i % 4 == 0 ? -4096.0 : i % 4 == 1 ? 4096.0 : ref_any(rng));
+        const float l = (float)(ref + d_low(rng));
+        const double K = std::rint((double)ref * EXP_UNITS_INV);
+        const double v = exp_units_any((double)l, EXP_UNITS_START - K, tab);
+        const __float128 exact = expq((__float128)l - (__float128)K * M_LN2q / 256), err = fabsq((__float128)v - exact);
+        if (exact > 0x1p-1021) {
+            int e;
+            std::frexp(v, &e);
+            worst_any = std::fmax(worst_any, (double)(err / (__float128)std::ldexp(1.0, e - 53)));
+        } else {
+            worst_any_below = std::fmax(worst_any_below, (double)(err / (__float128)std::ldexp(1.0, -1074)));
+        }
+    }
     // e^d, d <= 0, from the table laid out whole: rounding error where the result is normal, otherwise in units of the
     // smallest number; arguments of any size (what the tree walk subtracts from a maximum near the largest float)
     static uint64_t whole[2 * EXP_FINE_N];
@@ -61,6 +78,7 @@ int main() {
         for (float l : {(float)top, -3.4028234e38f, -(float)INFINITY})
             wrong += exp_units_nonpos((double)l - (double)(float)top, wtab) !=
                      (l == (float)top || (double)l - (double)(float)top > -700.0 ? std::exp((double)l - (double)(float)top) : 0.0);
-    std::printf("%.6f %ld %d %.6f %.6f %ld\n", worst, differ, ends ? 1 : 0, worst_nonpos, worst_below, wrong);
+    std::printf("%.6f %ld %d %.6f %.6f %ld %.6f %.6f\n", worst, differ, ends ? 1 : 0, worst_nonpos, worst_below, wrong, worst_any,
+                worst_any_below);
     return 0;
 }

@@ -26,7 +26,14 @@ def test_exp_units_within_one_rounding(figures):
 def test_exp_units_nonpos(figures):
     """The same where the result is a normal number; below, where it is rounded once more, a little over half a unit of
     the smallest number.  Differences from a maximum of any size: what lies far below it is nothing."""
-    worst, below, wrong = figures[3:]
+    worst, below, wrong = figures[3:6]
     assert worst <= 0.55
     assert below <= 1.0
     assert wrong == 0
+
+
+def test_exp_units_any_far_from_zero(figures):
+    """Logits down to 1100 below a reference of 4096 in magnitude: the same bounds."""
+    worst, below = figures[6:]
+    assert worst <= 0.55
+    assert below <= 1.0
