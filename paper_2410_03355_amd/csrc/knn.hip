@@ -2009,7 +2009,7 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
         // selection is bound by the latency of its many short phases, so its throughput is the number
         // of workgroups a compute unit holds at once, and that number is set by this LDS footprint
         // (12 bytes a slot).
-        const int want_slots = (a.k - 1) + 8 + (a.k - 1) / 128;
+        const int want_slots = candidate_slots(a.k);
 #define LANTERN_LAUNCH_SELECT_VECS(NKV, CAPV, TNTV, LISTV, VECSV)                                           \
         hipLaunchKernelGGL((knn_select<CT, NKV, CAPV, TNTV, LISTV, VECSV>), dim3(rows), dim3(TNTV),         \
                            (CAPV) <= 1024 ? own_code_bytes(a.d, key_vecs) : 0, stream, cb,          \
@@ -2026,7 +2026,7 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
             thresholds(r0, rows);
             filter(r0, rows);
             static_assert(LIST_THREADS == NT, "threads per row of the selection from lists");
-            const int pairs = list_pairs(plan.tokens ? 1024 : want_slots, plan.cap);   // 64 < want_slots <= 1024
+            const int pairs = plan_pairs(plan, a.k);   // 64 < want_slots <= 1024
 #define LANTERN_LAUNCH_RANK(NPV)                                                                                         \
             do {                                                                                                         \
                 auto* kernel = a.metric == 0 ? (vecs == 1   ? &knn_rank_list<CT, NPV, 1, 0>                              \

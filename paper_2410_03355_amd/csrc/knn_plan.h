@@ -57,6 +57,9 @@ struct FilterPlan {
     int cap;    // slots of a row's candidate list: 1024, 2048, 3072 or 4096
 };
 
+// Candidates wanted of a row: its k - 1 others and a few more, so that the proof that none is missing passes.
+inline int candidate_slots(int k) { return (k - 1) + 8 + (k - 1) / 128; }
+
 constexpr int FILTER_STAGE = 8192;   // hits of a tile that are staged at once
 
 inline double normal_density(double z) { return exp(-0.5 * z * z) * 0.39894228040143267794; }
@@ -73,8 +76,7 @@ inline double normal_upper_quantile(double share) {
 inline FilterPlan filter_plan(int V, int d, int k, int cb_dtype) {
     FilterPlan P = {false, false, false, 0, 0, 0, 0};
     const bool vec = cb_dtype == 1 ? (d % 8) == 0 : (d % 4) == 0;   // what the matrix-core kernels need
-    const int need = k - 1;
-    const int want = need + 8 + need / 128;
+    const int want = candidate_slots(k);
     // 64 candidates or fewer: the lists would be several times longer than what the selection wants
     if (!vec || V < 4096 || want <= 64 || want > 1024) return P;
     int S = V / 8;
@@ -128,5 +130,7 @@ inline int list_pairs(int candidate_slots, int cap) {
     const int pairs = (cap + LIST_THREADS * 4 - 1) / (LIST_THREADS * 4) * 4;
     return pairs < least ? least : pairs;
 }
+// What a plan's selection holds per thread: lists of tokens have 1024 candidate slots whatever is wanted of them.
+inline int plan_pairs(const FilterPlan& plan, int k) { return list_pairs(plan.tokens ? 1024 : candidate_slots(k), plan.cap); }
 
 }  // namespace lantern
