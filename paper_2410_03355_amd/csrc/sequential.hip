@@ -31,7 +31,7 @@
 // total variation keeps out of scratch memory: setting that up is 1 to 3 us of every walk (64 trees none of which draws,
 // V = 8192 fp32: 43.6 -> 39.7 us the step) and the spilled terms more (V = 16384 fp32, 64 trees: 163 -> 148 us).
 // The exponentials (two rows of them per group, on one compute unit: 6 of a plain draw's 21 us) are those of the one-pass
-// evaluation, 18 instructions each with the subtraction of the maximum, and what is the same in all lanes is kept
+// evaluation, 17 instructions each with the subtraction of the maximum, and what is the same in all lanes is kept
 // in scalar registers: V = 16384 bf16, 64 trees, 90 -> 83 us the walk, 26.6 -> 23.9 the plain draw.
 // Second half of the plain step (PLAIN): its first wavefront walks the tree over the decisions as every other walk
 // does (tree_walk.h), then the workgroup evaluates the one candidate whose draw is wanted.  V = 16384 bf16, 1 / 64
