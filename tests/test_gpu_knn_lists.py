@@ -25,17 +25,23 @@ def _clusters(V, d, size, spread, seed):
     return (np.repeat(centre, size, axis=0)[:V] + spread * rng.standard_normal((V, d))).astype(np.float32)
 
 
-@pytest.mark.parametrize("V,d,k,size,spread,dtype,metric", [
-    (8192, 8, 1000, 1400, 1e-3, torch.float32, "l2"),        # a cluster is one bucket of the list's range
-    (8192, 8, 1000, 1400, 1e-3, torch.float32, "cosine"),
-    (9000, 16, 900, 1100, 0.02, torch.bfloat16, "l2"),
-    (8192, 8, 100, 700, 1e-3, torch.float32, "l2"),
-    (12288, 16, 100, 300, 0.01, torch.float32, "l2"),        # codes of four vectors
-    (6000, 24, 500, 800, 1e-3, torch.float32, "l2"),         # lists with keys
+# most: rows that may be left to the all-pairs pass.  None where distances within a cluster are well above the error of the
+# approximate keys, about 1e-6 of the codes' norms; any where they are not.
+@pytest.mark.parametrize("V,d,k,size,spread,dtype,metric,most", [
+    (8192, 8, 1000, 1400, 1e-3, torch.float32, "l2", 0),        # a cluster is one bucket of the list's range
+    (8192, 8, 1000, 1150, 1e-3, torch.float32, "l2", 0),        # and holds more than the selection: it is divided again
+    (8192, 8, 1000, 1150, 0.03, torch.bfloat16, "l2", 0),
+    (8192, 8, 1000, 1400, 1e-3, torch.float32, "cosine", 8192),
+    (9000, 16, 900, 1100, 0.02, torch.bfloat16, "l2", 0),
+    (8192, 8, 100, 700, 1e-3, torch.float32, "l2", 8192),
+    (8192, 8, 100, 700, 1e-2, torch.float32, "l2", 0),
+    (12288, 16, 100, 300, 0.01, torch.float32, "l2", 0),        # codes of four vectors
+    (6000, 24, 500, 800, 1e-3, torch.float32, "l2", 6000),      # lists with keys
+    (6000, 24, 500, 800, 0.1, torch.float32, "l2", 0),
 ])
-def test_clustered_codes(oracle_mod, lantern_gpu, V, d, k, size, spread, dtype, metric):
+def test_clustered_codes(oracle_mod, lantern_gpu, V, d, k, size, spread, dtype, metric, most):
     cb = torch.from_numpy(_clusters(V, d, size, spread, V + d + k)).to(dtype)
-    got = _table(lantern_gpu, cb, k, metric, V)
+    got = _table(lantern_gpu, cb, k, metric, most)
     want = oracle_mod.build_knn(cb.float().numpy(), k, metric=metric, threads=16)
     np.testing.assert_array_equal(got, want)
 
@@ -51,12 +57,23 @@ def test_small_and_large_codes(oracle_mod, lantern_gpu, V, d, k, dtype, scale):
     np.testing.assert_array_equal(got[rows[0]:rows[1]], want)
 
 
+def _reach(cb, code, ranks):
+    """Rows that have `code` within their first `ranks` tokens, themselves among them."""
+    c = cb.double().cuda()
+    closer = torch.cat([(((row[:, None, :] - c[None]) ** 2).sum(2) < ((row - c[code]) ** 2).sum(1)[:, None]).sum(1)
+                        for row in c.split(256)])
+    return int((closer < ranks).sum())
+
+
+# A run of equal codes that does not fit leaves the rows whose table or list reaches it to the all-pairs pass: lists are about
+# 300 tokens long for k = 70.
 @pytest.mark.parametrize("k", [70, 1000])
 def test_more_equal_codes_than_the_selection_holds(oracle_mod, lantern_gpu, k):
     rng = np.random.default_rng(k)
     cb = rng.standard_normal((8192, 8)).astype(np.float32)
-    cb[rng.permutation(8192)[:1200]] = cb[17]
-    got = _table(lantern_gpu, torch.from_numpy(cb), k, "l2", 8192)
+    equal = rng.permutation(8192)[:1200]
+    cb[equal] = cb[17]
+    got = _table(lantern_gpu, torch.from_numpy(cb), k, "l2", _reach(torch.from_numpy(cb), equal[0], max(k, 512)))
     np.testing.assert_array_equal(got, oracle_mod.build_knn(cb, k, threads=16))
 
 
@@ -66,7 +83,7 @@ def test_longer_lists_than_their_room(oracle_mod, lantern_gpu, dtype):
     cb = torch.randn(8192, 8, generator=torch.Generator().manual_seed(9))
     cb[1000:7000] = cb[1000]
     cb = cb.to(dtype)
-    got = _table(lantern_gpu, cb, 70, "l2", 8192)
+    got = _table(lantern_gpu, cb, 70, "l2", _reach(cb, 1000, 512))
     np.testing.assert_array_equal(got, oracle_mod.build_knn(cb.float().numpy(), 70, threads=16))
 
 
