@@ -755,7 +755,7 @@ __global__ __launch_bounds__(NT, 4) void knn_filter_list(const uint4* packed, co
     __shared__ FilterShared<FORM> sh;
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1);
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // its tiles' places in scalar registers: the cosine key spills otherwise
     const int nct = (V + 128 * TT - 1) / (128 * TT), nrt = (rows + 127) / 128;
     const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
     const int ti = (q / nct) * 8 + xcd;

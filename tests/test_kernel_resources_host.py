@@ -106,3 +106,11 @@ def test_exponential_tables_are_objects_of_their_own(kernels):
     for name in os.listdir(csrc):
         with open(os.path.join(csrc, name)) as f:
             assert "address_space(3)" not in f.read(), name
+
+
+def test_filtering_contraction_keeps_out_of_scratch(kernels):
+    """Every form of it (key, list, tokens to a tile): setting up scratch memory alone is felt in launches of this length."""
+    filters = {name: r for name, r in kernels.items() if "knn_filter_list" in name}
+    assert len(filters) == 12
+    for name, r in filters.items():
+        assert r[:2] == (0, 0), name
