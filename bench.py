@@ -35,17 +35,17 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 # (FETCH_SIZE scaled by the factor a plain 256 MiB copy gives in the same run).  Counters cannot be
 # read from inside this process, so the figure is a record of that run: it is reported only while the
 # library still has the version it was measured at, and with the file it comes from.
-_FETCH_SCALE = 262144.0 / 131091.8   # what FETCH_SIZE read for a 256 MiB copy in the same run
+_FETCH_SCALE = 262144.0 / 131096.2   # what FETCH_SIZE read for a 256 MiB copy in the same run
 MEASURED_TRAFFIC = {
     # (workload, variant, mode): (bytes per launch, library version, source)
-    ("stress", "plain", "sample"): ((130993.8 * _FETCH_SCALE + 240.2) * 1024, 240,
-                                    "profiles/verify_fast_stress_plain.md (FETCH_SIZE, WRITE_SIZE; version 240)"),
-    ("stress", "reject", "sample"): ((165169.3 * _FETCH_SCALE + 284.6) * 1024, 240,
-                                     "profiles/verify_fast_stress_plain.md (reject mix; version 240)"),
-    ("wide_latent", "plain", "sample"): ((124426.1 * _FETCH_SCALE + 240.4) * 1024, 240,
-                                         "profiles/verify_fast_stress_plain.md (wide_latent; version 240)"),
-    ("stress", "plain", "greedy"): ((69188.6 * _FETCH_SCALE + 240.0) * 1024, 240,
-                                    "profiles/greedy_fast_stress_plain.md (version 240)"),
+    ("stress", "plain", "sample"): ((130993.5 * _FETCH_SCALE + 240.2) * 1024, 241,
+                                    "profiles/verify_fast_stress_plain.md (FETCH_SIZE, WRITE_SIZE; version 241)"),
+    ("stress", "reject", "sample"): ((165291.7 * _FETCH_SCALE + 285.7) * 1024, 241,
+                                     "profiles/verify_fast_stress_plain.md (reject mix; version 241)"),
+    ("wide_latent", "plain", "sample"): ((124432.1 * _FETCH_SCALE + 240.6) * 1024, 241,
+                                         "profiles/verify_fast_stress_plain.md (wide_latent; version 241)"),
+    ("stress", "plain", "greedy"): ((69189.1 * _FETCH_SCALE + 240.0) * 1024, 241,
+                                    "profiles/greedy_fast_stress_plain.md (version 241)"),
 }
 
 
@@ -56,12 +56,12 @@ MEASURED_TRAFFIC = {
 # 2048 and 1024 tokens itself; its product is not counted among the contractions.
 MEASURED_KNN_SPLIT = {
     # workload: ({kernel: us per build}, extra contraction flop, library version, source)
-    "stress": ({"thresholds": 34.7, "filter_contraction": 107.4, "selection": 170.9, "exact_check": 4.2,
-                "operands_and_norms": 8.1}, 0.0, 240,
-               "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 240)"),
-    "wide_latent": ({"thresholds": 21.9, "filter_contraction": 72.4, "selection": 72.5, "exact_check": 4.1,
-                     "operands_and_norms": 10.6}, 0.0, 240,
-                    "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 240)"),
+    "stress": ({"thresholds": 34.8, "filter_contraction": 105.2, "selection": 171.7, "exact_check": 4.1,
+                "operands_and_norms": 8.3}, 0.0, 241,
+               "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 241)"),
+    "wide_latent": ({"thresholds": 22.0, "filter_contraction": 71.7, "selection": 72.8, "exact_check": 4.1,
+                     "operands_and_norms": 11.7}, 0.0, 241,
+                    "profiles/knn_build_stress_and_wide_latent.md (kernel trace; version 241)"),
 }
 
 

@@ -409,6 +409,6 @@ const char* lantern_status_string(int status) {
     }
 }
 
-int lantern_version(void) { return 240; }
+int lantern_version(void) { return 241; }
 
 }  // extern "C"

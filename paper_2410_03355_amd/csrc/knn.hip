@@ -743,8 +743,8 @@ struct FilterShared {
 // the masks' bits, so several column tiles share one reservation; with keys, whose registers cannot be numbered at run
 // time, by going over all 32 values, and the tile is one.
 // V = 16384, d = 8 fp32, k = 1000: 193 us with hits written by the lanes that found them, 189 staged with their keys,
-// 126 staged as tokens, 108 with 512 tokens to a tile and masks of shifted-in signs.  V = 8192, d = 256 bf16,
-// k = 100 (keys kept; bound by the operand loads): 78 -> 73.
+// 126 staged as tokens, 108 with 512 tokens to a tile and masks of shifted-in signs, 105 with the reservation on its way meanwhile.  V = 8192,
+// d = 256 bf16, k = 100 (keys kept; bound by the operand loads): 78 -> 72.
 typedef uint32_t tokens4 __attribute__((ext_vector_type(4), aligned(4)));
 template <typename CT, int METRIC, int FORM, int TT>
 __global__ __launch_bounds__(NT, 4) void knn_filter_list(const uint4* packed, const float* fold, const float* norms, int V,
@@ -1660,7 +1660,7 @@ __global__ __launch_bounds__(TNT, NK >= 64 ? 4 : !LIST ? 8 : NK == 32 ? 5 : (CAP
 // the LDS holds (many nearly equal keys), the keys below that bucket are set aside and the bucket itself is divided
 // again, until they fit or its keys are equal; then the places come from a histogram of their own.
 // Every token not on the list has a value below the row's threshold, which is what the proof uses.
-// V = 16384, d = 8, k = 1000 (lists of 1624 tokens, 16384 rows): 175 us, and 182 for the selection from pairs, whose
+// V = 16384, d = 8, k = 1000 (lists of 1672 tokens, 16384 rows): 172 us, and 182 for the selection from pairs, whose
 // lists take the filtering contraction 80 us longer.
 template <typename CT, int NP, int VECS, int METRIC>
 __global__ __launch_bounds__(LIST_THREADS, 4) void knn_rank_list(const CT* cb, int V, int d, int k, int r0,

@@ -32,10 +32,11 @@
 // V = 8192 fp32: 43.6 -> 39.7 us the step) and the spilled terms more (V = 16384 fp32, 64 trees: 163 -> 148 us).
 // The exponentials (two rows of them per group, on one compute unit: 6 of a plain draw's 21 us) are those of the one-pass
 // evaluation, 17 instructions each with the subtraction of the maximum, and what is the same in all lanes is kept
-// in scalar registers: V = 16384 bf16, 64 trees, 90 -> 83 us the walk, 26.6 -> 23.9 the plain draw.
+// in scalar registers: V = 16384 bf16, 64 trees, 90 -> 83 us the walk, 26.6 -> 23.9 the plain draw; with the table an LDS object whose
+// place the compiler knows 87 -> 80 and 23.6 -> 22.2.
 // Second half of the plain step (PLAIN): its first wavefront walks the tree over the decisions as every other walk
 // does (tree_walk.h), then the workgroup evaluates the one candidate whose draw is wanted.  V = 16384 bf16, 1 / 64
-// trees that draw: 21 / 24 us, without a draw 4 us (24 / 28 with the exponentials before); 27 / 31 and 10 us with the search for children among the passes.
+// trees that draw: 20 / 22 us, without a draw 4 us (24 / 28 with the exponentials before); 27 / 31 and 10 us with the search for children among the passes.
 // Vocabularies that do not fit in LDS keep both vectors in the workspace.
 #include <hip/hip_runtime.h>
 #include <limits.h>
