@@ -283,6 +283,8 @@ struct KeySum {
     }
 };
 constexpr int VEC_MAX_D = 1024;   // own code in LDS: 8 KiB
+// How the exact keys of knn_select's candidates read their codes: element by element, as whole vectors (above), or either.
+enum KeyForm { KEYS_ELEMENTS, KEYS_VECTORS, KEYS_EITHER };
 template <typename CT, int METRIC, int U>
 __device__ __forceinline__ double exact_key_vec(const CT* cb, int vecs, const double* own, int j, double norm2) {
     constexpr int EPV = KeySum<CT, METRIC>::EPV;
@@ -1369,10 +1371,11 @@ __device__ __forceinline__ void for_keys(int npt, F body) {
 // list that was cut at its capacity, is longer than the registers hold (the proof takes every listed
 // token for seen), or is shorter than the selection wants, flags the row.
 //
-// VECS false: the codes are no whole vectors at aligned addresses (vecs is 0).  A kernel of its own for the smallest vocabularies
-// only, whose selection is a few microseconds: V = 1024, d = 9, k = 700 36.6 us the build with both forms of the
-// exact keys in one kernel, 34.7 without; from V = 2000 on there is no difference.
-template <typename CT, int NK, int CAP, int TNT, bool LIST, bool VECS>
+// KEYS: how the candidates' exact keys read their codes.  Both forms in one kernel cost registers, and short codes gain nothing by vectors: so
+// selections from whole rows are kernels of one form each (which one: row_vecs at the launch).  Builds before exact keys by vectors /
+// with both forms in every kernel / now: V = 8192, d = 8 fp32, k = 30, cosine 201.5 / 204.7 / 201.5 us; V = 4000, d = 8 bf16, k = 300
+// 77.7 / 80.0 / 78.1; V = 1024, d = 9, k = 700 34.9 / 36.6 / 34.7.
+template <typename CT, int NK, int CAP, int TNT, bool LIST, int KEYS>
 __global__ __launch_bounds__(TNT, NK >= 64 ? 4 : !LIST ? 8 : NK == 32 ? 5 : (CAP > 256 || NK == 24) ? 6 : 8) void knn_select(const CT* cb, int V, int d, int k, int metric, int r0,
                                                  const float* dist, FilterOut list, float err_rel, float err_abs,
                                                  float err_norm, const float* norms, const float* nmax,
@@ -1382,7 +1385,7 @@ __global__ __launch_bounds__(TNT, NK >= 64 ? 4 : !LIST ? 8 : NK == 32 ? 5 : (CAP
     using Shared = SelectShared<CAP, TNT>;
     __shared__ Shared sh;
     extern __shared__ __align__(16) double own[];   // vecs > 0: the row's own code
-    const int vecs = VECS ? vecs_or_0 : 0;
+    const int vecs = KEYS == KEYS_ELEMENTS ? 0 : vecs_or_0;
     const int row = blockIdx.x;
     const int i = r0 + row;
     const int tid = threadIdx.x;
@@ -1472,7 +1475,7 @@ __global__ __launch_bounds__(TNT, NK >= 64 ? 4 : !LIST ? 8 : NK == 32 ? 5 : (CAP
         }
     }
 
-    if (CAP <= 1024 && vecs) own_code<CT>(cb + (int64_t)i * d, d, own, tid, TNT);
+    if (CAP <= 1024 && (KEYS == KEYS_VECTORS || vecs)) own_code<CT>(cb + (int64_t)i * d, d, own, tid, TNT);
     // range of the keys
     for (int w = tid; w < Shared::BUCKETS / 2; w += TNT) sh.hist[w] = 0u;
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
@@ -1587,13 +1590,13 @@ __global__ __launch_bounds__(TNT, NK >= 64 ? 4 : !LIST ? 8 : NK == 32 ? 5 : (CAP
         double ck[CPT];
         int ct[CPT], at[CPT];
         float fmin_ = INFINITY, fmax_ = neg_inf_f();
-        const double norm2 = vecs && metric != 0 ? own_norm2(own, d) : 0.0;
+        const double norm2 = (KEYS == KEYS_VECTORS || vecs) && metric != 0 ? own_norm2(own, d) : 0.0;
 #pragma unroll
         for (int e = 0; e < CPT; ++e) {
             const int c = e * TNT + tid;
             if (c < count) {
                 ct[e] = sh.idx[c];
-                ck[e] = vecs == 0 ? exact_key<CT>(cb, d, i, ct[e], metric, vec4)
+                ck[e] = vecs == 0 && KEYS != KEYS_VECTORS ? exact_key<CT>(cb, d, i, ct[e], metric, vec4)
                         : metric == 0 ? exact_key_vec<CT, 0, 4>(cb, vecs, own, ct[e], 0.0)
                                       : exact_key_vec<CT, 1, 4>(cb, vecs, own, ct[e], norm2);
                 fmin_ = fminf(fmin_, (float)ck[e]);
@@ -1958,6 +1961,14 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
     }
     const int vecs = mfma ? a.d * (int)sizeof(CT) / 16 : 0;   // rows of whole vectors at aligned addresses
     const int key_vecs = a.d <= VEC_MAX_D ? vecs : 0;
+    // The exact keys of a selection from whole rows read codes of up to 32 bytes by elements where 256 slots do and a thread holds 32
+    // keys or more (with fewer there is no difference), of 64 bytes as well unless many cosine keys each take the own code's norm.
+    // Vectors / elements, fp32: V = 8192, k = 30, cosine, d = 8 204.5 / 201.6 us, d = 16 219.3 / 216.7; V = 4000, d = 16, k = 200, l2 82.3 /
+    // 82.1, cosine 96.9 / 106.7; V = 4000, d = 32, k = 200, l2 94.5 / 95.4.
+    const int want_slots = candidate_slots(a.k);
+    auto row_vecs = [&](int keys, int slots) {
+        return key_vecs > (slots > 256 || keys == 8 ? 0 : a.metric == 0 || want_slots <= 128 ? 4 : 2);
+    };
     auto filter = [&](int r0, int rows) {
         const int nrt = (rows + 127) / 128;
 #define LANTERN_LAUNCH_FILTER(METRICV, FORMV, TTV)                                                                       \
@@ -2009,18 +2020,21 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
         // selection is bound by the latency of its many short phases, so its throughput is the number
         // of workgroups a compute unit holds at once, and that number is set by this LDS footprint
         // (12 bytes a slot).
-        const int want_slots = candidate_slots(a.k);
-#define LANTERN_LAUNCH_SELECT_VECS(NKV, CAPV, TNTV, LISTV, VECSV)                                           \
-        hipLaunchKernelGGL((knn_select<CT, NKV, CAPV, TNTV, LISTV, VECSV>), dim3(rows), dim3(TNTV),         \
-                           (CAPV) <= 1024 ? own_code_bytes(a.d, key_vecs) : 0, stream, cb,          \
+#define LANTERN_LAUNCH_SELECT_KEYS(NKV, CAPV, TNTV, LISTV, KEYSV, VECSV)                                    \
+        hipLaunchKernelGGL((knn_select<CT, NKV, CAPV, TNTV, LISTV, KEYSV>), dim3(rows), dim3(TNTV),         \
+                           own_code_bytes(a.d, VECSV), stream, cb,                                          \
                            a.V, a.d, a.k, a.metric, r0, dist, LISTV ? fo : no_list, err_rel, err_abs,       \
-                           err_norm, nsel, nmax, doubt, a.out, flags + r0, (CAPV) <= 1024 ? key_vecs : 0)
-#define LANTERN_LAUNCH_SELECT(NKV, CAPV, TNTV, LISTV)                                                       \
+                           err_norm, nsel, nmax, doubt, a.out, flags + r0, VECSV)
+        // whole rows of keys; beyond 1024 candidates their exact keys are taken by elements
+#define LANTERN_LAUNCH_SELECT_ROWS(NKV, CAPV, TNTV)                                                         \
         do {                                                                                                \
-            constexpr bool OWN = !LISTV && NKV == 8 && CAPV <= 1024;                                        \
-            if (OWN && key_vecs == 0) LANTERN_LAUNCH_SELECT_VECS(NKV, CAPV, TNTV, LISTV, !OWN);             \
-            else LANTERN_LAUNCH_SELECT_VECS(NKV, CAPV, TNTV, LISTV, true);                                  \
+            /* of 1024 slots a kernel of both forms spills less than one of vectors alone, but for these two */ \
+            constexpr bool BOTH = (CAPV) == 1024 && (sizeof(CT) == 2 ? NKV != 32 : NKV != 8);               \
+            constexpr int BY_VECTORS = (CAPV) > 1024 ? KEYS_ELEMENTS : BOTH ? KEYS_EITHER : KEYS_VECTORS;   \
+            if ((CAPV) > 1024 || !row_vecs(NKV, CAPV)) LANTERN_LAUNCH_SELECT_KEYS(NKV, CAPV, TNTV, false, KEYS_ELEMENTS, 0); \
+            else LANTERN_LAUNCH_SELECT_KEYS(NKV, CAPV, TNTV, false, BY_VECTORS, key_vecs);                  \
         } while (0)
+#define LANTERN_LAUNCH_SELECT_LIST(NKV, CAPV, TNTV) LANTERN_LAUNCH_SELECT_KEYS(NKV, CAPV, TNTV, true, KEYS_EITHER, key_vecs)
         if (plan.use) {
             // thresholds from the sample, then the contraction that keeps what lies below them
             thresholds(r0, rows);
@@ -2046,13 +2060,13 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
             } else if (want_slots <= 256) {
                 // two wavefronts a row: its candidates would leave some of four without any
                 static_assert(LIST_THREADS == 2 * NARROW_THREADS, "twice the pairs per thread");
-                if (pairs == 4) LANTERN_LAUNCH_SELECT(8, 256, NARROW_THREADS, true);
-                else if (pairs == 8) LANTERN_LAUNCH_SELECT(16, 256, NARROW_THREADS, true);
-                else if (pairs == 12) LANTERN_LAUNCH_SELECT(24, 256, NARROW_THREADS, true);
-                else LANTERN_LAUNCH_SELECT(32, 256, NARROW_THREADS, true);
-            } else if (pairs == 8) LANTERN_LAUNCH_SELECT(8, 1024, NT, true);
-            else if (pairs == 12) LANTERN_LAUNCH_SELECT(12, 1024, NT, true);
-            else LANTERN_LAUNCH_SELECT(16, 1024, NT, true);
+                if (pairs == 4) LANTERN_LAUNCH_SELECT_LIST(8, 256, NARROW_THREADS);
+                else if (pairs == 8) LANTERN_LAUNCH_SELECT_LIST(16, 256, NARROW_THREADS);
+                else if (pairs == 12) LANTERN_LAUNCH_SELECT_LIST(24, 256, NARROW_THREADS);
+                else LANTERN_LAUNCH_SELECT_LIST(32, 256, NARROW_THREADS);
+            } else if (pairs == 8) LANTERN_LAUNCH_SELECT_LIST(8, 1024, NT);
+            else if (pairs == 12) LANTERN_LAUNCH_SELECT_LIST(12, 1024, NT);
+            else LANTERN_LAUNCH_SELECT_LIST(16, 1024, NT);
         } else {
             if (mfma)
                 hipLaunchKernelGGL((knn_dist_mfma<CT>), dim3((a.V + 127) / 128, (rows + 127) / 128), dim3(NT), 0, stream,
@@ -2062,10 +2076,10 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
                                    cb, a.V, a.d, r0, a.metric, dist, doubt);
 #define LANTERN_LAUNCH_SELECT_NK(NKV, TNTV)                                                                 \
             do {                                                                                            \
-                if (want_slots <= 256) LANTERN_LAUNCH_SELECT(NKV, 256, TNTV, false);                        \
-                else if (want_slots <= 1024) LANTERN_LAUNCH_SELECT(NKV, 1024, TNTV, false);                 \
-                else if (want_slots <= 2048) LANTERN_LAUNCH_SELECT(NKV, 2048, TNTV, false);                 \
-                else LANTERN_LAUNCH_SELECT(NKV, CAND_CAP, TNTV, false);                                     \
+                if (want_slots <= 256) LANTERN_LAUNCH_SELECT_ROWS(NKV, 256, TNTV);                        \
+                else if (want_slots <= 1024) LANTERN_LAUNCH_SELECT_ROWS(NKV, 1024, TNTV);                 \
+                else if (want_slots <= 2048) LANTERN_LAUNCH_SELECT_ROWS(NKV, 2048, TNTV);                 \
+                else LANTERN_LAUNCH_SELECT_ROWS(NKV, CAND_CAP, TNTV);                                     \
             } while (0)
             // threads per row and keys per thread: up to 64 keys per thread in registers; vocabularies
             // beyond 64 x 256 tokens take 512 threads per row (32 keys per thread on 512 threads measured
@@ -2077,8 +2091,9 @@ static hipError_t build_typed(const KnnArgs& a, const KnnLayout& L, hipStream_t 
             else LANTERN_LAUNCH_SELECT_NK(0, NT);
 #undef LANTERN_LAUNCH_SELECT_NK
         }
-#undef LANTERN_LAUNCH_SELECT
-#undef LANTERN_LAUNCH_SELECT_VECS
+#undef LANTERN_LAUNCH_SELECT_ROWS
+#undef LANTERN_LAUNCH_SELECT_LIST
+#undef LANTERN_LAUNCH_SELECT_KEYS
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

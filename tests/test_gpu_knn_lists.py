@@ -117,6 +117,10 @@ def test_codes_that_are_no_numbers(oracle_mod, lantern_gpu, V, d, k, metric):
     (6001, 20, 150, torch.float32), (4500, 120, 700, torch.bfloat16), (8192, 16, 1000, torch.float32),   # lists with keys
     (2000, 12, 60, torch.float32), (1500, 88, 400, torch.bfloat16), (300, 1028, 50, torch.float32),      # whole rows
     (20000, 8, 100, torch.float32), (33000, 8, 230, torch.bfloat16),                                     # larger samples
+    (1000, 9, 100, torch.float32), (4000, 8, 30, torch.float32), (4000, 16, 100, torch.bfloat16),        # whole rows by elements,
+    (9000, 8, 30, torch.bfloat16), (20000, 8, 30, torch.float32), (34000, 8, 20, torch.bfloat16),        # of any length
+    (2000, 16, 200, torch.float32), (2000, 24, 30, torch.bfloat16), (4000, 8, 300, torch.bfloat16),      # by vectors: 64 bytes and many cosine
+    (4000, 16, 300, torch.float32), (9000, 32, 30, torch.bfloat16), (20000, 24, 40, torch.float32),      # keys, 48 bytes, more than 256 slots
 ])
 def test_forms_of_the_exact_keys(oracle_mod, lantern_gpu, V, d, k, dtype, metric):
     g = torch.Generator().manual_seed(V + d)

@@ -76,13 +76,14 @@ def test_smallest_full_rows_leave_room_for_five_wavefronts(kernels):
     assert kernels[name][0] == 0 and kernels[name][2] <= 96
 
 
-def test_selection_of_small_tables_by_elements(kernels):
-    """The selection from whole rows of up to 2048 keys whose codes are read element by element (last template argument)
-    holds nothing of the vectors' way: fewer registers, no scratch."""
+def test_selections_from_whole_rows_by_elements(kernels):
+    """Whole rows of any number of keys have a selection that reads codes element by element (last template argument) and holds
+    nothing of the vectors' way: fewer registers, no scratch."""
     for code in "ft":
-        for slots, most in ((256, 48), (1024, 62)):
-            name, = [n for n in kernels if re.search(rf"knn_selectI{code}Li8ELi{slots}ELi256ELb0ELb0EE", n)]
-            assert kernels[name][0] == 0 and kernels[name][2] <= most, name
+        for keys, threads, most in ((0, 256, (48, 62)), (8, 256, (48, 62)), (32, 256, (64, 64)), (64, 256, (128, 128)), (64, 512, (128, 128))):
+            for slots, limit in zip((256, 1024), most):
+                name, = [n for n in kernels if re.search(rf"knn_selectI{code}Li{keys}ELi{slots}ELi{threads}ELb0ELi0EE", n)]
+                assert kernels[name][0] == 0 and kernels[name][2] <= limit, name
 
 
 def test_rows_arrive_without_scratch_memory(objects):
